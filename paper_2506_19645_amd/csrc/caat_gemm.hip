@@ -10,10 +10,10 @@ namespace caat {
 // workgroup on every 64 (or, for wide outputs, 128) weight rows replace the big tile; their stages are 64 k deep so
 // that a weight row is fetched 128 contiguous bytes at a time (64-byte pieces of rows that lie kilobytes apart cost
 // about a fifth of the HBM rate), 4 stages, two workgroups per CU.
-typedef TileCfg<256, 256, 2, 4, 2, 2, true, 64> CfgBig;
-typedef TileCfg<128, 128, 2, 2, 2, 2, false, 64> CfgMid;   // problems with too few 256 x 256 tiles to fill the chip
-typedef TileCfg<64, 64, 2, 2, 4, 2, false, 64> CfgSkinny;
-typedef TileCfg<64, 128, 2, 2, 4, 2, false, 64> CfgSkinnyWide;
+typedef TileCfg<256, 256, 2, 4, 2, true> CfgBig;
+typedef TileCfg<128, 128, 2, 2, 2, false> CfgMid;   // problems with too few 256 x 256 tiles to fill the chip
+typedef TileCfg<64, 64, 2, 2, 4, false> CfgSkinny;
+typedef TileCfg<64, 128, 2, 2, 4, false> CfgSkinnyWide;
 typedef CfgSkinnyWide CfgSkinnySwi;
 
 // every (layout, epilogue) pair that exists, for one block-sized tile shape

@@ -1,4 +1,4 @@
-// Grouped bf16 shard GEMM kernel template for gfx950 (CDNA4): MFMA 32x32x16 bf16, fp32 accumulation.
+// Grouped bf16 shard GEMM kernel template for gfx950 (CDNA4): MFMA 16x16x32 bf16, fp32 accumulation.
 //
 // One launch covers all T emulated tensor-parallel ranks (group index g).  It implements the two contractions
 // of Eq. A3 (column-parallel X_m A_m with the activation fused, row-parallel Y_m B_m with the private-column
@@ -8,54 +8,71 @@
 // stages of both operand tiles live in LDS and every operand goes global -> LDS directly (buffer_load ... lds, no
 // register staging), NSTAGE-1 stages ahead of the MFMAs, so a global / L2 round trip is hidden.
 //   * operand contiguous along K in memory (NT's a and b, NN's a): stage = [rows][BKS k], fragment reads are
-//     ds_read_b128 (32 consecutive rows x one 16-byte chunk);
+//     ds_read_b128 (16 consecutive rows x four 16-byte chunks);
 //   * operand contiguous along its row index in memory (NN's b, TN's a and b): stage = [BKS k][rows], the memory
 //     layout as it is, and the MFMA fragments (8 consecutive k of one row per lane) are gathered by the LDS
 //     transpose read ds_read_b64_tr_b16 (16 lanes fetch 4 k-rows x 16 rows and lane j receives row j's 4 k).
 // 16-byte chunks are XOR-swizzled (applied on the global side of the copy) so that both kinds of reads are
 // bank-conflict free.  Rows / k outside the matrix get an out-of-range buffer offset and arrive as zeros, so
-// the main loop has no branch.  MFMA fragments are double buffered over the 16-wide k sub-steps of a stage.
+// the main loop has no branch on them.
 //
 // The accumulator is computed transposed (operands swapped in the MFMA) so that each lane ends up with 4
-// consecutive columns of one row of C; in the epilogue every wave passes its sub-tile, 32 rows at a time, through a
-// private LDS scratch and stores row segments of 16 bytes per lane (no workgroup barrier).  With PERSIST a workgroup
-// walks several tiles, the first NSTAGE-1 stages of the next tile are already in flight during the epilogue, and
-// only half of its waves issue copies (NLOAD below), so that the other half's stores can drain under the next tile.
-// Decode-sized tiles (BM <= 64) may cover fewer output columns than the MFMA tile is wide (bn_out).
+// consecutive columns of one row of C; the epilogue gathers 8 of them per lane with cross-lane swaps and stores 16
+// bytes per lane straight from registers.  With PERSIST a workgroup walks several tiles, whose stages form one stream of
+// copies: the first stages of the next tile are in flight while a tile is finished and stored, and the next main loop
+// starts without a barrier.  Only half of the waves issue copies (NLOAD below), so that the other half's stores can
+// drain under the next tile.  Decode-sized tiles (BM <= 64) may cover fewer output columns than the MFMA tile is wide
+// (bn_out).
+//
+// What bounds the block-sized tiles: on N(0,1) operands the chip's power, then the operand copies and the epilogue.  A
+// loop of MFMAs on registers alone sustains 1.55 - 1.79 PFLOP/s with 32x32x16 and 1.98 - 2.03 with 16x16x32 (2.49 / 2.45
+// on zeros, where both run at full clock), hence the shape.  h = 2048, T = 4, ffn 8192, 8192 tokens, forward GELU /
+// row-parallel / GELU' / dX / dA: 263 / 247 / 281 / 243 / 213 us with 32x32x16, an epilogue through LDS and a barrier
+// between tiles, 250 / 235 / 271 / 227 / 204 us as it is; 7B SwiGLU (T = 8, 4096 tokens) 670 / 403 / 414 / 608 / 621
+// to 626 / 379 / 391 / 557 / 603 us.  Without any epilogue (results dropped) the same launches take 194 / 205 / 220 /
+// 203 / 193 us.
 #pragma once
 #include <type_traits>
 #include "caat_internal.h"
 
 namespace caat {
 
+// The lane number as a value the optimiser knows nothing about: what is derived from it inside the tile loop stays there.
+// Otherwise per-lane offsets of the copies and of the epilogue are computed once in front of the loop over the tiles
+// and, the registers being taken, kept in scratch memory, whose reloads wait for every copy and store in flight.
+__device__ __forceinline__ int fresh_lane() {
+  int lane = threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));
+  return lane;
+}
+
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef short short4_t __attribute__((ext_vector_type(4)));
 typedef short short8_t __attribute__((ext_vector_type(8)));
 
-static constexpr int BKS = 32;                // default k extent of one LDS stage
 static constexpr unsigned OOB = 0x80000000u;  // buffer offset that is always out of range -> load returns 0
 static constexpr int DMA_SHIFT = 3072;        // operand windows start this many bytes early (see dma16_group's offsets)
 
-template <int BM_, int BN_, int WM_, int WN_, int NSTAGE_ = 4, int SCHED_ = 2, bool PERSIST_ = true, int BKS_ = 32>
+// LDS pointers with a type (address space 3): reads through them are single ds_read instructions with immediate offsets
+typedef __attribute__((address_space(3))) const char* lds_c_t;
+typedef __attribute__((address_space(3))) const uint4* lds_u4_t;
+typedef __attribute__((address_space(3))) short4_t* lds_s4_t;
+
+template <int BM_, int BN_, int WM_, int WN_, int NSTAGE_ = 2, bool PERSIST_ = true, int BKS_ = 64>
 struct TileCfg {
   static constexpr int BKS = BKS_;              // k extent of one LDS stage (multiple of 32; K-contiguous operands only if > 32)
   // PERSIST: one workgroup per CU walks several tiles and fetches the next tile's first stages under the epilogue
   static constexpr bool PERSIST = PERSIST_;
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, NSTAGE = NSTAGE_;
-  static constexpr int SCHED = SCHED_;  // 0: compiler's order, 1: fences between sub-steps, 2: + LDS reads spread 1:1 between
-                                        // the MFMAs, 3: + all LDS reads of a sub-step issued ahead of its MFMAs
   static constexpr int THREADS = 64 * WM * WN;
   static constexpr int NWAVES = WM * WN;
   static constexpr int WTM = BM / WM, WTN = BN / WN;  // wave tile
-  static constexpr int TM = WTM / 32, TN = WTN / 32;  // 32x32 MFMA tiles per wave
+  static constexpr int TM = WTM / 16, TN = WTN / 16;  // 16x16 MFMA tiles per wave
   static constexpr int STAGE_CHUNKS = (BM + BN) * (BKS / 8);  // uint4 per LDS stage
   static constexpr int SMEM_CHUNKS = NSTAGE * STAGE_CHUNKS;
   static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be a multiple of 32x32");
-  // epilogue scratch: every wave parks 32 rows x its WTN columns of bf16 at a time, at the tail of the LDS buffer
-  static constexpr int SCRATCH_BYTES = NWAVES * 32 * WTN * 2;
-  static_assert(SCRATCH_BYTES <= SMEM_CHUNKS * 16, "epilogue scratch must fit");
-  static_assert(!PERSIST || SCRATCH_BYTES <= STAGE_CHUNKS * 16, "persistent tiles keep NSTAGE-1 stages free of the scratch");
+  static_assert(!PERSIST || NSTAGE == 2, "the persistent loop counts on two slots");
   static_assert(SMEM_CHUNKS * 16 <= 160 * 1024, "LDS capacity");
   // workgroups that fit on one compute unit: LDS (160 KB) and at most 8 waves (2 per SIMD, 256 registers each)
   static constexpr int WGS_PER_CU = ((160 * 1024) / (SMEM_CHUNKS * 16)) < (8 / NWAVES) ? ((160 * 1024) / (SMEM_CHUNKS * 16))
@@ -64,11 +81,11 @@ struct TileCfg {
 };
 
 // ---- operand contiguous along K: stage [ROWS][BKS k], row = BKS*2 bytes = CPR chunks of 16 bytes; 16 chunks make
-// up the 64 LDS banks, so chunk c of row r sits at c ^ ((r >> SWZ_SHIFT) & (CPR-1)) (for 64-byte rows: c ^ ((r>>2)&3)):
+// up the 64 LDS banks, so chunk c of row r sits at c ^ swz(r) (128-byte rows: (r>>1)&7, 64-byte rows: 0, 2, 3, 1 for (r>>2)&3):
 // 16 consecutive rows then read the same logical chunk from 16 different bank groups.
 // One wave instruction fills 64/CPR rows (64 lanes x 16 B, lane order).  `origin` points at the tile's first row;
 // rowmap(rr) gives the row of tile row rr RELATIVE to the origin, or -1 if that row does not exist.
-template <int ROWS, int NWAVES, int BKS_ = 32, bool GROUPED = true>
+template <int ROWS, int NWAVES, int BKS_ = 64, bool GROUPED = true>
 struct KContigOperand {
   static constexpr int CPR = BKS_ / 8;           // chunks per row: 4, 8 or 16
   static constexpr int RPI = 64 / CPR;           // rows per copy instruction
@@ -85,7 +102,10 @@ struct KContigOperand {
   static_assert(NI % GRP == 0, "whole groups of copies");
   static_assert(CPR == 4 || CPR == 8 || CPR == 16, "stage depth must be 32, 64 or 128");
   static_assert(ROWS % (RPI * NWAVES) == 0, "rows must divide over the waves");
-  static __device__ __forceinline__ int swz(int row) { return (row >> SWZ_SHIFT) & (CPR - 1); }
+  static __device__ __forceinline__ int swz(int row) {
+    const int g = (row >> SWZ_SHIFT) & (CPR - 1);
+    return CPR == 4 ? (((g & 1) << 1) ^ ((g >> 1) * 3)) : g;
+  }
   const bf16_t* origin;
   unsigned voff[NI];
   int wave;
@@ -94,7 +114,7 @@ struct KContigOperand {
   template <class RowMap>
   __device__ __forceinline__ void init(const bf16_t* origin_, long long ld, RowMap rowmap) {
     origin = origin_;
-    const int lane = threadIdx.x & 63;
+    const int lane = fresh_lane();
     wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 #pragma unroll
     for (int it = 0; it < NI; ++it) {
@@ -126,18 +146,28 @@ struct KContigOperand {
       dma16_group<STREAM, GRP>(rs, v, tile + group_of(wave, gi * GRP) * 64);
     }
   }
-  // fragment for MFMA rows row0 .. row0+31, k sub-step ks (16 wide): lane (row0 + lane%32, k = 16 ks + 8 (lane/32) ..+7)
-  static __device__ __forceinline__ bf16x8_t frag(const uint4* tile, int row0, int ks, int lane) {
-    const int row = row0 + (lane & 31);
-    const int c = ks * 2 + (lane >> 5);
-    return __builtin_bit_cast(bf16x8_t, tile[row * CPR + (c ^ swz(row))]);
-  }
+  // Fragments of a wave whose sub-tile starts at tile row row0 (a multiple of 16): MFMA tile i, k sub-step ks (32 wide):
+  // lane (row row0 + 16 i + lane%16, k = 32 ks + 8 (lane/16) ..+7).  The swizzle has a period of 16 rows, so a lane's
+  // address is one of two (ks) plus 16 i rows, a constant in the instruction.
+  struct Reader {
+    lds_c_t p[BKS_ / 32];
+    __device__ __forceinline__ void init(const uint4* tile, int row0, int lane) {
+      const int r = lane & 15;
+#pragma unroll
+      for (int ks = 0; ks < BKS_ / 32; ++ks)
+        p[ks] = (lds_c_t)tile + ((row0 + r) * CPR + ((ks * 4 + (lane >> 4)) ^ swz(r))) * 16;
+    }
+    __device__ __forceinline__ bf16x8_t frag(int stage_bytes, int i, int ks) const {
+      return __builtin_bit_cast(bf16x8_t, *(lds_u4_t)(p[ks] + stage_bytes + i * 16 * CPR * 16));
+    }
+  };
 };
 
 // ---- operand contiguous along its row index ([K][rows] in memory): stage [BKS k][ROWS] as in memory, k-row =
-// ROWS*2 bytes; chunk c of k-row k sits at c ^ ((k&3)<<2).  One wave instruction fills 512/ROWS k-rows.
+// ROWS*2 bytes; chunk c of k-row k sits at c ^ (((k&3)<<2) | (((k>>3)&1)<<1)): the transpose read of 32 lanes (two groups of
+// 4 k-rows, 8 apart, 32 bytes of each) then touches every bank once.  One wave instruction fills 512/ROWS k-rows.
 // `origin` points at (k = 0, first row of the tile); rows_valid = rows of the tile that exist (multiple of 8).
-template <int ROWS, int NWAVES, int BKS_ = 32, bool GROUPED = true>
+template <int ROWS, int NWAVES, int BKS_ = 64, bool GROUPED = true>
 struct RowContigOperand {
   static constexpr int CPR = ROWS / 8;       // chunks per k-row
   static constexpr int KPI = 64 / CPR;       // k-rows per copy instruction
@@ -157,14 +187,14 @@ struct RowContigOperand {
   __device__ __forceinline__ void init(const bf16_t* origin_, long long ld_, RowMap rowmap) {
     origin = origin_;
     ld = ld_;
-    const int lane = threadIdx.x & 63;
+    const int lane = fresh_lane();
     wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     klocal = lane / CPR;
     const int phys = lane % CPR;
 #pragma unroll
     for (int it = 0; it < NI; ++it) {
       const int k = group_of(wave, it) * KPI + klocal;
-      const int c = phys ^ ((k & 3) << 2);
+      const int c = phys ^ swz(k);
       const long long r = rowmap(c * 8);  // 8 consecutive rows share validity (dims % 8 == 0)
       voff[it] = (r >= 0) ? (unsigned)(((long long)k * ld_ + r) * 2 + DMA_SHIFT - (it % GRP) * 1024) : OOB;
     }
@@ -188,21 +218,29 @@ struct RowContigOperand {
       dma16_group<STREAM, GRP>(rs, v, tile + group_of(wave, gi * GRP) * 64);
     }
   }
-  // same fragment as KContigOperand::frag, gathered by two transpose reads of 4 k each
-  static __device__ __forceinline__ bf16x8_t frag(const uint4* tile, int row0, int ks, int lane) {
-    const int i16 = lane & 15;
-    const int m = row0 + ((lane >> 4) & 1) * 16 + (i16 & 3) * 4;  // the 4 rows this lane's 8 bytes cover
-    const int kq = i16 >> 2;                                      // which of the 4 k-rows this lane fetches
-    const int kb = ks * 16 + (lane >> 5) * 8;
-    const char* base = reinterpret_cast<const char*>(tile);
-    const int coff = (((m >> 3) ^ (kq << 2)) << 4) + ((m & 7) << 1);  // (k & 3) == kq for both reads
-    const short4_t v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (__attribute__((address_space(3))) short4_t*)(base + (kb + kq) * (ROWS * 2) + coff));
-    const short4_t v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (__attribute__((address_space(3))) short4_t*)(base + (kb + 4 + kq) * (ROWS * 2) + coff));
-    const short8_t v = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-    return __builtin_bit_cast(bf16x8_t, v);
-  }
+  static __device__ __forceinline__ int swz(int k) { return ((k & 3) << 2) | (((k >> 3) & 1) << 1); }
+  // The same fragments as KContigOperand::Reader, each gathered by two transpose reads of 4 k.  A lane fetches 8 bytes
+  // (rows 4 (lane%4) ..+3 of the 16) of k-row 32 ks + 8 (lane/16) + (lane%16)/4 and of the k-row 4 further on; both have
+  // the same swizzle.  TT = MFMA tiles of the wave: the tile index moves the chunk inside the swizzle, so there is an
+  // address per tile (up to eight: 8 tiles are one swizzle period); ks is a constant in the instruction.
+  struct Reader {
+    lds_c_t p[8];
+    __device__ __forceinline__ void init(const uint4* tile, int row0, int lane) {
+      const int i16 = lane & 15, k = (lane >> 4) * 8 + (i16 >> 2);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int m = row0 + i * 16 + (i16 & 3) * 4;
+        p[i] = (lds_c_t)tile + k * (ROWS * 2) + ((((m >> 3) ^ swz(k)) << 4) + ((m & 7) << 1));
+      }
+    }
+    __device__ __forceinline__ bf16x8_t frag(int stage_bytes, int i, int ks) const {
+      const lds_c_t q = p[i] + stage_bytes + ks * 32 * (ROWS * 2);
+      const short4_t v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_t)q);
+      const short4_t v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_t)(q + 4 * (ROWS * 2)));
+      const short8_t v = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+      return __builtin_bit_cast(bf16x8_t, v);
+    }
+  };
 };
 
 template <bool ROWCONTIG, int ROWS, int NWAVES, int BKS_, bool GROUPED>
@@ -219,7 +257,7 @@ __device__ __forceinline__ long long b_tile_row(int rr, int n0, int bn_out, int 
   if constexpr (SWI) {
     const int w = rr / CFG::WTN, rw = rr - w * CFG::WTN;
     const int j = rw >> 5, c = rw & 31;
-    const int col = (w * (CFG::TN / 2) + (j >> 1)) * 32 + c;  // output column relative to n0
+    const int col = (w * (CFG::WTN / 64) + (j >> 1)) * 32 + c;  // output column relative to n0
     if (col >= bn_out || n0 + col >= half) return -1;
     return (long long)col + ((j & 1) ? half : 0);
   } else {
@@ -228,34 +266,13 @@ __device__ __forceinline__ long long b_tile_row(int rr, int n0, int bn_out, int 
   }
 }
 
-template <int TM, int TN>
-struct Frags {
-  bf16x8_t a[TM], b[TN];
-};
-
-// Instruction-order request for one k sub-step (between two scheduling fences): after every MFMA place this
-// MFMA's share of the NR LDS reads and NV global->LDS copies.
-template <int I, int NM, int NR, int NV>
-struct Pipe {
-  static __device__ __forceinline__ void run() {
-    if constexpr (I < NM) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      constexpr int r = (NR * (I + 1)) / NM - (NR * I) / NM;
-      constexpr int v = (NV * (I + 1)) / NM - (NV * I) / NM;
-      if constexpr (r > 0) __builtin_amdgcn_sched_group_barrier(0x100, r, 0);
-      if constexpr (v > 0) __builtin_amdgcn_sched_group_barrier(0x020, v, 0);
-      Pipe<I + 1, NM, NR, NV>::run();
-    }
-  }
-};
-
 template <class CFG, bool AT, bool BT, int EPI>
 __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kernel(const GemmParams p) {
   constexpr int BM = CFG::BM, BN = CFG::BN, NSTAGE = CFG::NSTAGE;
   constexpr int TM = CFG::TM, TN = CFG::TN, WTM = CFG::WTM, WTN = CFG::WTN;
   constexpr bool SWI = (EPI == EPI_SWIGLU_FWD);
   constexpr int BN_OUT = SWI ? BN / 2 : BN;  // output columns covered by one tile
-  static_assert(!SWI || TN % 2 == 0, "SwiGLU pairing needs an even number of N tiles per wave");
+  static_assert(!SWI || WTN % 64 == 0, "SwiGLU pairing needs 32 gate and 32 up columns per wave");
 
   __shared__ uint4 smem[CFG::SMEM_CHUNKS];
 
@@ -264,8 +281,6 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / CFG::WN;
   const int wn = wave - wm * CFG::WN;
-  const int frow = lane & 31;  // accumulator row within a 32-row MFMA tile
-  const int fk = lane >> 5;    // which half of the tile's columns / k this lane holds
 
   // ---- tiles of this workgroup.  Tile ids are cut into 8 contiguous ranges, one per XCD (workgroup b runs on XCD
   // b % 8), so that the workgroups sharing an L2 work on neighbouring tiles; inside a range the workgroups of the XCD
@@ -290,7 +305,7 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
   }
 
   constexpr int BKS = CFG::BKS;         // this instantiation's stage depth (hides the namespace default)
-  constexpr int NSUB = BKS / 16;        // 16-wide k sub-steps (one MFMA deep) per stage
+  constexpr int NSUB = BKS / 32;        // 32-wide k sub-steps (one MFMA deep) per stage
   // Waves that issue the global -> LDS copies.  A wave's copies and its epilogue stores complete in issue order on one
   // counter, so a wave that copies has to let its stores drain before it can wait for the next tile's second stage,
   // and the stores of all compute units come as one chip-wide burst (the workgroups run in lockstep) that takes
@@ -304,11 +319,8 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
   typedef typename OperandSel<BT, BN, NLOAD, BKS, (BM > 64)>::type OpB;
   OpA la;
   OpB lb;
-  int g = 0, m0 = 0, n0 = 0;
-  int ik0 = 0, ikg = 0;  // k position and K-group of the next stage to be copied
-  auto setup_tile = [&](int id) {
-    ik0 = 0;
-    ikg = 0;
+  // rank g, first row m0 and first column n0 of a tile
+  auto tile_coords = [&](int id, int& g, int& m0, int& n0) {
     g = id / tiles;
     const int t = id - g * tiles;
     constexpr int GROUP = 8;
@@ -319,6 +331,10 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
     const int r = t - grp * width;
     m0 = (first + r % gsize) * BM;
     n0 = (r / gsize) * bn_out;
+  };
+  auto setup_copies = [&](int id) {   // la, lb onto tile id
+    int g, m0, n0;
+    tile_coords(id, g, m0, n0);
     const bf16_t* ag = p.a + (long long)g * p.stride_a;
     const bf16_t* bg = p.b + (long long)g * p.stride_b;
     const int mrem = p.M - m0;
@@ -340,147 +356,160 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
   constexpr bool KCAT = (EPI == EPI_SHARED_BCAST);
   const int K = p.K;
   const int kcat = KCAT ? (p.kcat > 1 ? p.kcat : 1) : 1;
-  const int nk = ((K + BKS - 1) / BKS) * kcat;
+  const int nkg = (K + BKS - 1) / BKS;   // stages of one K-group
+  const int nk = nkg * kcat;             // stages of a tile
   constexpr int A_CHUNKS = BM * (BKS / 8);
+  constexpr int STAGE_BYTES = CFG::STAGE_CHUNKS * 16;
+  constexpr int NV = OpA::N_VMEM + OpB::N_VMEM;  // copies of a loading wave per stage
   // decode-sized tiles (at most 64 token rows per rank: one tile row) read every weight row exactly once
   constexpr bool B_STREAM = (BM <= 64);
-  auto stage_a = [&](int s) -> uint4* { return smem + (s % NSTAGE) * CFG::STAGE_CHUNKS; };
-  // stages are issued in order; past the end every offset is out of range: zeros land in a slot nobody reads
-  auto issue_stage = [&](int s) {
-    if (!loader) return;
-    uint4* As = stage_a(s);
-    if constexpr (KCAT) {
-      const int kk = ikg < kcat ? K : 0;
-      la.issue(ik0, kk, As, (long long)ikg * p.kstride_a);
-      lb.template issue<B_STREAM>(ik0, kk, As + A_CHUNKS, (long long)ikg * p.kstride_b);
-      ik0 += BKS;
-      if (ik0 >= K) {
-        ik0 = 0;
-        ++ikg;
+
+  // ---- the loading side.  The stages of all tiles of this workgroup form one stream; issue_one copies the next one
+  // into the next slot, and steps on to the next tile behind a tile's last stage: the first stages of a tile are on
+  // their way while the tile before is still computed and stored.
+  int lpid = pid;          // tile of the next copy
+  int lstage = 0;          // its stage
+  int lslot = 0;           // slot it goes to
+  bool lmore = pid < pid_end;
+  auto issue_one = [&]() {
+    if (!lmore) return;
+    if (loader) {
+      uint4* slot = smem + lslot * CFG::STAGE_CHUNKS;
+      if constexpr (KCAT) {
+        const int kg = lstage / nkg, k0 = (lstage - kg * nkg) * BKS;
+        la.issue(k0, K, slot, (long long)kg * p.kstride_a);
+        lb.template issue<B_STREAM>(k0, K, slot + A_CHUNKS, (long long)kg * p.kstride_b);
+      } else {
+        la.issue(lstage * BKS, K, slot, 0);
+        lb.template issue<B_STREAM>(lstage * BKS, K, slot + A_CHUNKS, 0);
       }
-    } else {
-      la.issue(s * BKS, K, As, 0);
-      lb.template issue<B_STREAM>(s * BKS, K, As + A_CHUNKS, 0);
+    }
+    lslot = lslot + 1 == NSTAGE ? 0 : lslot + 1;
+    if (++lstage == nk) {
+      lstage = 0;
+      lpid += pid_step;
+      lmore = CFG::PERSIST && lpid < pid_end;
+      if (lmore && loader) setup_copies(lpid);
     }
   };
 
-  constexpr int SCHED = CFG::SCHED;
-  constexpr int NM = TM * TN;
-  constexpr int NR = TM * OpA::READS_PER_FRAG + TN * OpB::READS_PER_FRAG;
-  constexpr int NV = OpA::N_VMEM + OpB::N_VMEM;  // copies per wave per stage
-  auto fence = [&]() {
-    if constexpr (SCHED >= 1) __builtin_amdgcn_sched_barrier(0);
-  };
+  constexpr int TMH = TM / 2;                    // MFMA tile rows of half a wave tile
+  static_assert(TM % 2 == 0 && NSUB % 2 == 0, "the main loop takes a wave's tile rows in two halves, two sets of columns");
+  auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
+  typename OpA::Reader ra;
+  typename OpB::Reader rb;
+  ra.init(smem, wm * WTM, lane);
+  rb.init(smem + A_CHUNKS, wn * WTN, lane);
 
+  constexpr int NS = WTN / 32;                   // 32-column groups of a wave's sub-tile
   // epilogue stores per wave and tile (known at compile time except for the broadcast epilogue's loop over ranks)
   constexpr int EPI_STORES =
       (EPI == EPI_SHARED_BCAST)
           ? 1000
-          : TM * (32 * (SWI ? WTN / 16 : WTN / 8) / 64) *
-                (EPI == EPI_SWIGLU_FWD ? 3 : ((EPI == EPI_GELU_FWD || EPI == EPI_SWIGLU_BWD) ? 2 : 1));
-  bool first_tile = true;
+          : TM * (SWI ? NS / 2 : NS) * (EPI == EPI_SWIGLU_FWD ? 3 : ((EPI == EPI_GELU_FWD || EPI == EPI_SWIGLU_BWD) ? 2 : 1));
 
   if (pid >= pid_end) return;
-  setup_tile(pid);
+  if (loader) setup_copies(pid);
 #pragma unroll
-  for (int s = 0; s < NSTAGE - 1; ++s) issue_stage(s);
+  for (int q = 0; q < NSTAGE; ++q) issue_one();
+  // copies complete in order: with at most the NSTAGE-1 newer stages outstanding, the first one has landed
+  if (loader) {
+    if (lmore) wait_vmcnt<(NSTAGE - 1) * NV>();
+    else wait_vmcnt<0>();
+  }
+  __syncthreads();
+  int cur = 0;                       // LDS offset of the stage being computed
+  bool behind_stores = false;        // this wave's stores of the tile before stand behind this tile's second stage
 
   while (true) {
-    f32x16_t acc[TM][TN];
+    f32x4_t acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+        for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.0f;
 
-    auto load_frags = [&](int s, int ks, Frags<TM, TN>& f) {
-      const uint4* As = stage_a(s);
-      const uint4* Bs = As + A_CHUNKS;
+    // ---- main loop.  A wave's MFMAs of a k sub-step run in two halves of its tile rows: half 0 computes on aq[0] while
+    // the fragments of half 1 are read into aq[1], half 1 computes on aq[1] while aq[0] and the other set of bq are
+    // filled for the next sub-step.  In the last sub-step of a stage nothing of the stage is left to read after half 0:
+    // there all waves meet, the next stage has landed, and the next copies go into the slot just freed (one barrier per
+    // stage, NSTAGE-1 whole stages of lead for a copy).  One MFMA per step with its share of the reads right behind it:
+    // a wave issues in order, and the fences keep the steps in order.
+    bf16x8_t aq[2][TMH], bq[2][TN];
 #pragma unroll
-      for (int i = 0; i < TM; ++i) f.a[i] = OpA::frag(As, wm * WTM + i * 32, ks, lane);
+    for (int j = 0; j < TN; ++j) bq[0][j] = rb.frag(cur, j, 0);
 #pragma unroll
-      for (int j = 0; j < TN; ++j) f.b[j] = OpB::frag(Bs, wn * WTN + j * 32, ks, lane);
-    };
-    auto mfma_all = [&](const Frags<TM, TN>& f) {
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          // operands swapped: the accumulator holds C^T, i.e. lane = row of C, registers = columns of C
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.b[j], f.a[i], acc[i][j], 0, 0, 0);
-    };
-
-    // copies complete in order: with at most the two newest stages outstanding, stage 0 has landed.  After a
-    // previous tile, the wave's newest vector-memory instructions are that tile's epilogue stores (a fixed number,
-    // all issued after this tile's first copies): they may stay in flight under the first stage's MFMAs.  The
-    // barrier also separates the previous tile's epilogue scratch from the copies that will reuse its LDS slot.
-    if (loader) {
-      if (first_tile || EPI_STORES + (NSTAGE - 2) * NV > 63)
-        wait_vmcnt<(NSTAGE - 2) * NV>();
-      else
-        wait_vmcnt<(EPI_STORES + (NSTAGE - 2) * NV > 63) ? 0 : EPI_STORES + (NSTAGE - 2) * NV>();
-    }
-    first_tile = false;
-    __syncthreads();
-    // fragments are double buffered over the NSUB 16-wide k sub-steps of a stage (NSUB is even)
-    Frags<TM, TN> fr[2];
-    load_frags(0, 0, fr[0]);
+    for (int i = 0; i < TMH; ++i) aq[0][i] = ra.frag(cur, i, 0);
     fence();
-
-    for (int kt = 0; kt < nk; ++kt) {
-      // the slot of stage kt-1 is free (everyone passed the barrier below in the previous iteration)
-      issue_stage(kt + NSTAGE - 1);
+    auto stage = [&](int kt, auto last_c) {
+      constexpr bool LAST = decltype(last_c)::value;
+      const int nxt = cur + STAGE_BYTES == NSTAGE * STAGE_BYTES ? 0 : cur + STAGE_BYTES;
 #pragma unroll
       for (int ss = 0; ss < NSUB; ++ss) {
-        if (ss + 1 < NSUB) {
-          load_frags(kt, ss + 1, fr[(ss + 1) & 1]);
-        } else {
-          // last sub-step: stage kt+1 must have landed (the two newest stages may still be in flight) and be visible
-          if (loader) wait_vmcnt<(NSTAGE - 2) * NV>();
+        constexpr int NM = TMH * TN;
+        const bool tail = ss + 1 == NSUB;
+#pragma unroll
+        for (int m = 0; m < NM; ++m) {   // half 0; reads: half 1's rows of the same sub-step
+          const int i = m / TN, j = m % TN;
+          // operands swapped: the accumulator holds C^T, i.e. lane = row of C, registers = columns of C
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bq[ss & 1][j], aq[0][i], acc[i][j], 0, 0, 0);
+#pragma unroll
+          for (int r = m * TMH / NM; r < (m + 1) * TMH / NM; ++r) aq[1][r] = ra.frag(cur, TMH + r, ss);
+          fence();
+        }
+        if (tail) {
+          if (loader) {
+            // the next stage has landed: newer are NSTAGE-2 stages and, in a tile's first stage, the stores of the tile
+            // before (a fixed number, issued after this tile's second stage), which may stay in flight
+            if (EPI_STORES <= 63 && behind_stores) wait_vmcnt<EPI_STORES <= 63 ? EPI_STORES : 0>();
+            else if (lmore) wait_vmcnt<(NSTAGE - 2) * NV>();
+            else wait_vmcnt<0>();
+            behind_stores = false;
+          }
           __syncthreads();
           fence();
-          load_frags(kt + 1, 0, fr[0]);
+          issue_one();
         }
-        mfma_all(fr[ss & 1]);
-        if constexpr (SCHED == 2) Pipe<0, NM, NR, 0>::run();
-        if constexpr (SCHED == 3) {
-          __builtin_amdgcn_sched_group_barrier(0x100, NR, 0);
-          __builtin_amdgcn_sched_group_barrier(0x008, NM, 0);
-        }
-        fence();
-      }
-    }
-    // the zero-filled stages past K still target LDS: let them land, and let every wave finish its fragment reads,
-    // before the buffers are reused
-    if (loader) wait_vmcnt<0>();
-    __syncthreads();
-
-    // ---- the finished tile's coordinates; then start on the next tile's data before the epilogue
-    const int eg = g, em0 = m0, en0 = n0;
-    const int next = pid + pid_step;
-    const bool has_next = CFG::PERSIST && next < pid_end;
-    if (has_next) {
-      setup_tile(next);
 #pragma unroll
-      for (int s = 0; s < NSTAGE - 1; ++s) issue_stage(s);  // slots 0 .. NSTAGE-2; the scratch below is in the last slot
-    }
+        for (int m = 0; m < NM; ++m) {   // half 1; reads: half 0's rows and all columns of the next sub-step
+          const int i = m / TN, j = m % TN;
+          acc[TMH + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bq[ss & 1][j], aq[1][i], acc[TMH + i][j], 0, 0, 0);
+          if (!(LAST && tail)) {
+            constexpr int NR = TMH + TN;
+#pragma unroll
+            for (int r = m * NR / NM; r < (m + 1) * NR / NM; ++r) {
+              if (r < TN) bq[(ss + 1) & 1][r] = rb.frag(tail ? nxt : cur, r, tail ? 0 : ss + 1);
+              else aq[0][r - TN] = ra.frag(tail ? nxt : cur, r - TN, tail ? 0 : ss + 1);
+            }
+          }
+          fence();
+        }
+      }
+      cur = nxt;
+    };
+#pragma clang loop unroll(disable)
+    for (int kt = 0; kt + 1 < nk; ++kt) stage(kt, std::false_type{});
+    stage(nk - 1, std::true_type{});
 
-    // ---- epilogue.  Each lane holds C[row = lane%32][col = 8*q + 4*(lane/32) + 0..3] of every 32x32 tile in
-    // acc[..][4q..4q+3].  Stored as they are, these 8-byte pieces would scatter over 32 rows per instruction; so each
-    // wave rounds 32 rows x WTN columns to bf16 into its own LDS scratch (chunk index XOR-swizzled by the row) and
-    // reads them back row-wise: 16 bytes per lane, consecutive lanes = consecutive columns.  The fused element-wise
-    // work (activation, its derivative, the private half of the partial channel-reduce + residual) happens there.
+    // ---- epilogue.  Each lane holds C[row = lane%16][col = 4*(lane/16) + 0..3] of every 16x16 tile.  Stored as they
+    // are, these 8-byte pieces would leave as 32-byte runs; so two neighbouring tiles exchange pieces between the
+    // 16-lane groups (v_permlane16_swap: odd groups of the first against even groups of the second), after which a lane
+    // holds 8 consecutive columns of its row and the four lanes of a row 64 contiguous bytes, without a trip through
+    // LDS.  Where the wave has 64 output columns, lanes 8 apart exchange once more (DPP rotation by 8): an instruction
+    // then writes whole 128-byte lines of 8 rows (half lines with the non-temporal hint cost the data-gradient GEMM of
+    // the 7B shape 5 %: 590 against 559 us).  The fused element-wise work (activation, its derivative, the private half of the partial channel-reduce +
+    // residual) happens on these vectors.
     //
     // Every global access of the epilogue is a raw buffer load / store whose offset is replaced by an out-of-range
     // one where the row or column does not exist (the load then returns zero, the store is dropped): the code has no
-    // branch, so the number of vector-memory instructions per tile is fixed (the wait at the top of the next tile
-    // counts on it) and the compiler's own waits for the prefetched second operand stay exact (vmcnt(n), not
-    // vmcnt(0), which would also wait for the stores and the prefetch issued just before).
-    constexpr int CHW = WTN / 8;  // 16-byte chunks per scratch row
-    char* scratch = reinterpret_cast<char*>(smem) + (CFG::SMEM_CHUNKS * 16 - CFG::SCRATCH_BYTES) + wave * (32 * WTN * 2);
-    const uint4* scr4 = reinterpret_cast<const uint4*>(scratch);
-    auto staged = [&](int row, int c) -> uint4 { return scr4[row * CHW + (c ^ (row & (CHW - 1)))]; };
+    // branch, so the number of vector-memory instructions per tile is fixed (the wait in the next tile's first stage
+    // counts on it) and the compiler's own waits for the prefetched second operand stay exact.
+    int eg, em0, en0;
+    tile_coords(pid, eg, em0, en0);
+    const int elane = fresh_lane();
+    const int eq = elane >> 4;
+    const int ecol0 = (eq & 1) * 16 + (eq >> 1) * 8;   // the lane's 8 columns of a 32-column group
     auto unpack = [](const uint4& v, float* f) {
       f[0] = lo_bf(v.x); f[1] = hi_bf(v.x); f[2] = lo_bf(v.y); f[3] = hi_bf(v.y);
       f[4] = lo_bf(v.z); f[5] = hi_bf(v.z); f[6] = lo_bf(v.w); f[7] = hi_bf(v.w);
@@ -488,27 +517,47 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
     auto pack = [](const float* f) -> uint4 {
       return make_uint4(pack2bf(f[0], f[1]), pack2bf(f[2], f[3]), pack2bf(f[4], f[5]), pack2bf(f[6], f[7]));
     };
-    constexpr int OCW = SWI ? CHW / 2 : CHW;      // 16-byte chunks per output row of the wave
-    constexpr int STEPS = 32 * OCW / 64;          // vectors per lane per 32-row slab
-    static_assert(STEPS >= 1, "a slab must give every lane at least one vector");
+    // the lane's 8 columns of 32-column group s, row 16 i + lane%16, rounded to bf16
+    auto rounded = [&](int i, int s) -> uint4 {
+      const f32x4_t x = acc[i][2 * s], y = acc[i][2 * s + 1];
+      const auto lo = __builtin_amdgcn_permlane16_swap(pack2bf(x[0], x[1]), pack2bf(y[0], y[1]), false, false);
+      const auto hi = __builtin_amdgcn_permlane16_swap(pack2bf(x[2], x[3]), pack2bf(y[2], y[3]), false, false);
+      return make_uint4(lo[0], hi[0], lo[1], hi[1]);
+    };
+    // Output vectors per lane and 16 rows (SwiGLU: group 2s gate, 2s+1 up).  LINES: two vectors, whole lines of 8 rows
+    // each: vector v belongs to row 16 i + 8 v + lane%8 and to column group (lane/8)%2.
+    constexpr int NO = SWI ? NS / 2 : NS;
+    constexpr bool LINES = !SWI && NS == 2;
+    auto vectors = [&](int i, uint4* v) {
+#pragma unroll
+      for (int st = 0; st < NO; ++st) v[st] = rounded(i, st);
+      if constexpr (LINES) {
+        auto swap8 = [](unsigned& a, unsigned& b) {   // lanes 8-15 of a against lanes 0-7 of b, in every 16 lanes
+          const unsigned a0 = a, b0 = b;
+          a = (unsigned)__builtin_amdgcn_update_dpp((int)a0, (int)b0, 0x128, 0xF, 0xC, false);
+          b = (unsigned)__builtin_amdgcn_update_dpp((int)b0, (int)a0, 0x128, 0xF, 0x3, false);
+        };
+        swap8(v[0].x, v[1].x);
+        swap8(v[0].y, v[1].y);
+        swap8(v[0].z, v[1].z);
+        swap8(v[0].w, v[1].w);
+      }
+    };
     constexpr bool HAS_AUX = (EPI == EPI_ROWPAR || EPI == EPI_GELU_BWD || EPI == EPI_SWIGLU_BWD);
     constexpr int AUXV = (EPI == EPI_SWIGLU_BWD) ? 2 : 1;
     const int wrow0 = em0 + wm * WTM;             // first row of the wave's sub-tile
     const int wcol0 = en0 + wn * (SWI ? WTN / 2 : WTN);  // first output column of the wave's sub-tile
     const int ncols = SWI ? p.half : p.N;
-    // buffer windows start at the wave's first row, so that offsets stay small: (row in slab) * ld + column, in
-    // bytes; the slab's 32 * i rows go into the scalar offset
+    // buffer windows start at the wave's first row, so that offsets stay small: row in the sub-tile * ld + column, in bytes
     const rsrc_t rc = make_rsrc_t(p.c + (long long)eg * p.stride_c + (long long)wrow0 * p.ldc);
     const rsrc_t rc2 = make_rsrc_t((EPI == EPI_GELU_FWD || SWI) ? p.c2 + (long long)eg * p.stride_c2 + (long long)wrow0 * p.ldc2 : p.c);
     const rsrc_t raux = make_rsrc_t(HAS_AUX ? p.aux + (long long)eg * p.stride_aux + (long long)wrow0 * p.ldaux : p.c);
-    int erow[STEPS], ecol[STEPS];                 // slab row and output column of the lane's vector in step st
-    unsigned voff_c[STEPS], voff_c2[STEPS], voff_aux[STEPS];
+    int erow[NO], ecol[NO];                       // row (of 16) and first output column of the lane's vector st
+    unsigned voff_c[NO], voff_c2[NO], voff_aux[NO];
 #pragma unroll
-    for (int st = 0; st < STEPS; ++st) {
-      const int idx = st * 64 + lane;
-      erow[st] = idx / OCW;
-      const int oc = idx - erow[st] * OCW;
-      ecol[st] = wcol0 + oc * 8;
+    for (int st = 0; st < NO; ++st) {
+      erow[st] = LINES ? (elane & 7) + 8 * st : elane & 15;
+      ecol[st] = wcol0 + (LINES ? (elane >> 3) & 1 : st) * 32 + ecol0;
       const bool colok = ecol[st] < ncols && ecol[st] - en0 < bn_out;
       voff_c[st] = colok ? (unsigned)((erow[st] * p.ldc + ecol[st]) * 2) : OOB;
       voff_c2[st] = colok ? (unsigned)((erow[st] * p.ldc2 + ecol[st]) * 2) : OOB;
@@ -516,19 +565,17 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
       const bool auxok = colok && (EPI != EPI_ROWPAR || ecol[st] + 7 >= p.hs);
       voff_aux[st] = auxok ? (unsigned)((erow[st] * p.ldaux + ecol[st]) * 2) : OOB;
     }
-    auto rows_left = [&](int i) { return p.M - wrow0 - i * 32; };
-    // epilogues that read a second tensor (residual, saved pre-activations) fetch it AUXD 32-row slabs ahead: a slab's
-    // conversion, LDS round trip and stores take less time than one trip to memory.  The residual epilogue, light on
-    // registers, fetches all of the wave's slabs at once; the activation-derivative epilogues (whose NN main loop
-    // already needs nearly every register) measured faster with two.
-    constexpr int AUXD = !HAS_AUX ? 1 : (TM < 2 ? 1 : (EPI == EPI_ROWPAR && STEPS * 4 * TM <= 64 ? TM : 2));
-    u32x4_t auxbuf[AUXD][HAS_AUX ? STEPS * AUXV : 1];
+    auto row_ok = [&](int i, int st) { return i * 16 + erow[st] < p.M - wrow0; };
+    // epilogues that read a second tensor (residual, saved pre-activations) fetch it AUXD 16-row slabs ahead: a slab's
+    // conversion and stores take less time than one trip to memory.  The residual epilogue, light on registers, fetches
+    // all of the wave's slabs at once.
+    constexpr int AUXD = !HAS_AUX ? 1 : (EPI == EPI_ROWPAR ? TM : (TM < 4 ? TM : 4));
+    u32x4_t auxbuf[AUXD][HAS_AUX ? NO * AUXV : 1];
     auto aux_fetch = [&](int i, u32x4_t* buf) {
-      const int rl = rows_left(i);
-      const int so = i * 32 * (int)p.ldaux * 2;
+      const int so = i * 16 * (int)p.ldaux * 2;
 #pragma unroll
-      for (int st = 0; st < STEPS; ++st) {
-        const unsigned vo = erow[st] < rl ? voff_aux[st] : OOB;
+      for (int st = 0; st < NO; ++st) {
+        const unsigned vo = row_ok(i, st) ? voff_aux[st] : OOB;
         // read once by this tile only: non-temporal hint (cache policy bit 1)
         buf[st * AUXV] = __builtin_amdgcn_raw_buffer_load_b128(raux, vo, so, 2);
         if constexpr (AUXV == 2) buf[st * AUXV + 1] = __builtin_amdgcn_raw_buffer_load_b128(raux, vo, so + p.half * 2, 2);
@@ -567,30 +614,20 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
       }
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
+        uint4 vec[NS];
+        if constexpr (SWI) {
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
+          for (int q = 0; q < NS; ++q) vec[q] = rounded(i, q);
+        } else {
+          vectors(i, vec);
+        }
+        const int so_c = i * 16 * (int)p.ldc * 2, so_c2 = i * 16 * (int)p.ldc2 * 2;
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int c = j * 4 + q;
-            uint2 w;
-            w.x = pack2bf(acc[i][j][q * 4 + 0], acc[i][j][q * 4 + 1]);
-            w.y = pack2bf(acc[i][j][q * 4 + 2], acc[i][j][q * 4 + 3]);
-            *reinterpret_cast<uint2*>(scratch + ((frow * CHW + (c ^ (frow & (CHW - 1)))) * 16 + fk * 8)) = w;
-          }
-        // the wave reads back what its other lanes wrote: LDS executes a wave's operations in order; the compiler
-        // must not reorder across this point either
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        const int rl = rows_left(i);
-        const int so_c = i * 32 * (int)p.ldc * 2;
-#pragma unroll
-        for (int st = 0; st < STEPS; ++st) {
-          const bool rowok = erow[st] < rl;
+        for (int st = 0; st < NO; ++st) {
+          const bool rowok = row_ok(i, st);
           const unsigned vo = voff_c[st];
           if constexpr (SWI) {
-            // scratch columns: [gate 32 | up 32] pairs; output chunk oc -> gate chunk (oc/4)*8 + oc%4, up chunk = +4
-            const int oc = (st * 64 + lane) - erow[st] * OCW;
-            const int gc = (oc >> 2) * 8 + (oc & 3);
-            const uint4 gw = staged(erow[st], gc), uw = staged(erow[st], gc + 4);
+            const uint4 gw = vec[2 * st], uw = vec[2 * st + 1];
             float gt[8], up[8], y[8];
             unpack(gw, gt);
             unpack(uw, up);
@@ -598,10 +635,9 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
             for (int e = 0; e < 8; ++e) y[e] = gt[e] * sigmoid_f(gt[e]) * up[e];
             put_late(rc, gw, rowok, vo, so_c);
             put_late(rc, uw, rowok, vo, so_c + p.half * 2);
-            put(rc2, pack(y), rowok, voff_c2[st], i * 32 * (int)p.ldc2 * 2);
+            put(rc2, pack(y), rowok, voff_c2[st], so_c2);
           } else {
-            const int c = (st * 64 + lane) - erow[st] * CHW;
-            const uint4 raw = staged(erow[st], c);
+            const uint4 raw = vec[st];
             if constexpr (EPI == EPI_PLAIN) {
               if (p.late_c) put_late(rc, raw, rowok, vo, so_c);
               else put(rc, raw, rowok, vo, so_c);
@@ -612,7 +648,7 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
 #pragma unroll
               for (int e = 0; e < 8; ++e) y[e] = gelu_f(v[e]);
               put_late(rc, raw, rowok, vo, so_c);
-              put(rc2, pack(y), rowok, voff_c2[st], i * 32 * (int)p.ldc2 * 2);
+              put(rc2, pack(y), rowok, voff_c2[st], so_c2);
             } else if constexpr (EPI == EPI_ROWPAR && SH) {
               put(rc, raw, rowok, vo, so_c);  // a tile of shared channels only: this rank's partial sums as they are
             } else if constexpr (EPI == EPI_ROWPAR) {
@@ -633,9 +669,9 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
               for (int m = 0; m < p.bcast; ++m) {
                 const rsrc_t rr = make_rsrc_t(p.aux + (long long)m * p.stride_aux + (long long)wrow0 * p.ldaux);
                 const rsrc_t rw = make_rsrc_t(p.c + (long long)m * p.stride_c + (long long)wrow0 * p.ldc);
-                const unsigned va = (rowok && ecol[st] < ncols) ? (unsigned)((erow[st] * p.ldaux + ecol[st]) * 2) : OOB;
+                const unsigned va = rowok ? voff_aux[st] : OOB;
                 float r[8], o[8];
-                unpack(to_u4(__builtin_amdgcn_raw_buffer_load_b128(rr, va, i * 32 * (int)p.ldaux * 2, 0)), r);
+                unpack(to_u4(__builtin_amdgcn_raw_buffer_load_b128(rr, va, i * 16 * (int)p.ldaux * 2, 0)), r);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) o[e] = v[e] + r[e];
                 put(rw, pack(o), rowok, vo, so_c);
@@ -663,7 +699,6 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
             }
           }
         }
-        asm volatile("" ::: "memory");  // keep the next 32 rows' scratch writes behind these reads
         if constexpr (HAS_AUX && !SH) {
           if (i + AUXD < TM) aux_fetch(i + AUXD, auxbuf[i % AUXD]);  // this slab's registers are free again
         }
@@ -676,8 +711,9 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
     } else {
       slabs(std::integral_constant<int, 0>{});
     }
-    if (!has_next) break;
-    pid = next;
+    pid += pid_step;
+    if (!CFG::PERSIST || pid >= pid_end) break;
+    behind_stores = true;
   }
 }
 

@@ -1,0 +1,33 @@
+"""Shard GEMM on small integers: every product and sum is exact in fp32 and the result is an integer of at most 8 bits
+(|sum| <= 256) or is rounded once to bf16, so the GPU bits must equal the correctly rounded integer result -- at the
+edges of the tiles, of the k stages and of the walk over several tiles per workgroup."""
+import numpy as np
+import pytest
+
+from paper_2506_19645_amd import binding as B
+from paper_2506_19645_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+# (G, M, N, K): below / at / past one tile in each dimension; 1, 2 and 3 stages of k with and without a remainder;
+# more tiles than compute units with stage counts 1, 2, 3 (the stream of copies runs on from tile to tile)
+SHAPES = [(1, 8, 8, 8), (2, 256, 256, 64), (1, 264, 248, 72), (1, 520, 776, 200), (3, 296, 520, 136), (1, 24, 136, 320),
+          (5, 2048, 2048, 64), (5, 2040, 1928, 128), (5, 2008, 2056, 184)]
+
+
+@pytest.mark.parametrize("G,M,N,K", SHAPES)
+@pytest.mark.parametrize("layout", [B.GEMM_NT, B.GEMM_NN, B.GEMM_TN])
+def test_gemm_small_integers_bit_exact(layout, G, M, N, K):
+    import torch
+    rng = np.random.default_rng(M * 7 + N * 3 + K + layout)
+    a = rng.integers(-2, 3, size=(G, M, K)).astype(np.float32)
+    b = rng.integers(-2, 3, size=(G, N, K)).astype(np.float32)
+    want = I.f32_to_bf16_bits(np.matmul(a, b.transpose(0, 2, 1)))        # |sum| < 2^24: exact in fp32
+    at = a.transpose(0, 2, 1) if layout == B.GEMM_TN else a
+    bt = b if layout == B.GEMM_NT else b.transpose(0, 2, 1)
+    da, db = B.to_device(I.f32_to_bf16_bits(at)), B.to_device(I.f32_to_bf16_bits(bt))
+    out = torch.full((G, M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    B.gemm_bf16(da, db, out, layout, G, M, N, K, M if layout == B.GEMM_TN else K, K if layout == B.GEMM_NT else N, N,
+                M * K, N * K, M * N)
+    torch.cuda.synchronize()
+    assert np.array_equal(B.to_host_bits(out), want)
