@@ -5,16 +5,12 @@
 namespace caat {
 
 // Tile choices: 256 x 256 tiles with 8 waves (2 x 4) and 2 LDS stages of 64 k for the block-sized GEMMs of every
-// layout (with 4 stages of 32 k an operand that is contiguous along K was fetched in 64-byte pieces of rows that lie
-// kilobytes apart, which cost the NT GEMMs 12 %; 64-k stages fetch whole 128-byte lines).  For decode (at most 64 token rows per rank) the GEMM is a weight stream, so small tiles that put a
-// workgroup on every 64 (or, for wide outputs, 128) weight rows replace the big tile; their stages are 64 k deep so
-// that a weight row is fetched 128 contiguous bytes at a time (64-byte pieces of rows that lie kilobytes apart cost
-// about a fifth of the HBM rate), 4 stages, two workgroups per CU.
+// layout (stages of 32 k fetch an operand that is contiguous along K in 64-byte pieces of rows that lie kilobytes apart
+// and meet at twice as many barriers: with five of them and the two halves of a line copied back to back, NT 241 us
+// against 210, TN 210 against 203).  64 x 128 tiles, 4 stages, for small batches whose weights fill the chip.
 typedef TileCfg<256, 256, 2, 4, 2, true> CfgBig;
 typedef TileCfg<128, 128, 2, 2, 2, false> CfgMid;   // problems with too few 256 x 256 tiles to fill the chip
-typedef TileCfg<64, 64, 2, 2, 4, false> CfgSkinny;
-typedef TileCfg<64, 128, 2, 2, 4, false> CfgSkinnyWide;
-typedef CfgSkinnyWide CfgSkinnySwi;
+typedef TileCfg<64, 128, 2, 2, 4, false> CfgSkinny;
 
 // every (layout, epilogue) pair that exists, for one block-sized tile shape
 template <class CFG>
@@ -54,32 +50,24 @@ static int compute_units() {
   return n_cu;
 }
 
-// Decode (at most 64 token rows per rank): the launch streams N weight rows per rank, and what a compute unit can have
-// in flight is bounded, so its time is set by the bytes it has to pull: per tile the weight rows the tile covers (from
-// HBM) plus the 64 activation rows every tile re-reads (from L2, at about a third of the latency: counted as 20 rows),
-// times the tiles a compute unit gets.  Among the widths a tile may cover (multiples of 8 up to the MFMA tile's), take
-// the one that minimises this, the widest on a tie.  Example: 8 ranks x 1536 rows in tiles of 64 are 192 tiles (a
-// quarter of the chip idle), in tiles of 48 they are 256.
-struct DecodeTile {
-  bool wide;   // 64 x 128 tile (CfgSkinnyWide) instead of 64 x 64; SwiGLU always takes its own 64 x 128 tile
-  int bn_out;  // output columns one tile covers
-};
-static DecodeTile choose_decode_tile(int G, int N, int epilogue) {
-  DecodeTile t;
-  t.wide = (N >= 2048) && (epilogue == EPI_PLAIN || epilogue == EPI_ROWPAR || epilogue == EPI_SHARED_BCAST);
-  const int full = epilogue == EPI_SWIGLU_FWD ? CfgSkinnySwi::BN / 2 : (t.wide ? CfgSkinnyWide::BN : CfgSkinny::BN);
+// Output columns a 64 x 128 tile covers (a multiple of 8 up to the tile's width): what a compute unit can have in flight
+// is bounded, so the time is set by the bytes it has to pull, per tile the weight rows it covers (from HBM) plus the 64
+// activation rows every tile re-reads (from L2, at about a third of the latency: counted as 20 rows), times the tiles a
+// compute unit gets.  The width that minimises this, the widest on a tie.
+static int choose_skinny_width(int G, int N, int epilogue) {
+  const int full = epilogue == EPI_SWIGLU_FWD ? CfgSkinny::BN / 2 : CfgSkinny::BN;
   const int n_cu = compute_units();
-  t.bn_out = full;
+  int width = full;
   long long best = -1;
   for (int bn = full; bn >= 16; bn -= 8) {
     const long long tiles = (long long)((N + bn - 1) / bn) * G;
     const long long cost = ((tiles + n_cu - 1) / n_cu) * ((epilogue == EPI_SWIGLU_FWD ? 2 : 1) * bn + 20);
     if (best < 0 || cost < best) {
       best = cost;
-      t.bn_out = bn;
+      width = bn;
     }
   }
-  return t;
+  return width;
 }
 
 hipError_t launch_gemm(const GemmParams& p, int layout, int epilogue, hipStream_t s) {
@@ -91,24 +79,24 @@ hipError_t launch_gemm(const GemmParams& p, int layout, int epilogue, hipStream_
   const long long ldmax = std::max(std::max(p.ldc, p.ldc2), p.ldaux);
   if ((256 * ldmax + 2 * (long long)p.half + (long long)p.N) * 2 >= 0x7FFFFFFFLL) return hipErrorInvalidValue;
   const int n_cu = compute_units();
-  if (layout == 0 && p.M <= 64) {
-    const DecodeTile t = choose_decode_tile(p.G, p.N, epilogue);
-    GemmParams q = p;
-    q.bn_out = t.bn_out;
-    if (t.wide) {
+  if (layout == 0 && p.M <= 128 && epilogue != EPI_SHARED_BCAST) {
+    // Few token rows: the weights are what has to be read.  The streaming kernel, except where 17 rows or more meet so
+    // many weight rows that 128 of them fall to every compute unit: there the 64 x 128 tile (the 128 x 128 one from 65
+    // rows on) reads the token rows half as often.  Measured (us, streaming kernel / tile kernel): 32768 rows of 1376 k,
+    // 16 token rows 20.6 / 22.1, 32: 23.7 / 22.4, 64: 28.6 / 24.3, 128: 46 / 30; 57344 rows of 8192 k, 64 token rows
+    // 177 / 172, 128: 278 / 213; 12288 rows of 4096 k, 64 token rows 22.9 / 26.1, 128: 31.5 / 60.8.
+    const long long wrows = (long long)p.G * p.N * (epilogue == EPI_SWIGLU_FWD ? 2 : 1);
+    if (p.M <= 16 || wrows < 128LL * n_cu) return launch_gemm_stream(p, epilogue, n_cu, s);
+    if (p.M <= 64) {
+      GemmParams q = p;
+      q.bn_out = choose_skinny_width(p.G, p.N, epilogue);
       switch (epilogue) {
-        case EPI_PLAIN: return launch_one<CfgSkinnyWide, false, false, EPI_PLAIN>(q, s);
-        case EPI_ROWPAR: return launch_one<CfgSkinnyWide, false, false, EPI_ROWPAR>(q, s);
-        default: return launch_one<CfgSkinnyWide, false, false, EPI_SHARED_BCAST>(q, s);
+        case EPI_PLAIN: return launch_one<CfgSkinny, false, false, EPI_PLAIN>(q, s);
+        case EPI_GELU_FWD: return launch_one<CfgSkinny, false, false, EPI_GELU_FWD>(q, s);
+        case EPI_SWIGLU_FWD: return launch_one<CfgSkinny, false, false, EPI_SWIGLU_FWD>(q, s);
+        case EPI_ROWPAR: return launch_one<CfgSkinny, false, false, EPI_ROWPAR>(q, s);
+        default: return hipErrorInvalidValue;
       }
-    }
-    switch (epilogue) {
-      case EPI_PLAIN: return launch_one<CfgSkinny, false, false, EPI_PLAIN>(q, s);
-      case EPI_GELU_FWD: return launch_one<CfgSkinny, false, false, EPI_GELU_FWD>(q, s);
-      case EPI_SWIGLU_FWD: return launch_one<CfgSkinnySwi, false, false, EPI_SWIGLU_FWD>(q, s);
-      case EPI_ROWPAR: return launch_one<CfgSkinny, false, false, EPI_ROWPAR>(q, s);
-      case EPI_SHARED_BCAST: return launch_one<CfgSkinny, false, false, EPI_SHARED_BCAST>(q, s);
-      default: return hipErrorInvalidValue;
     }
   }
   // 256 x 256 tiles (one workgroup per CU) unless they would leave much of the chip idle: then 128 x 128 tiles, two

@@ -200,6 +200,8 @@ struct GemmParams {
 
 // layout: 0 NT, 1 NN, 2 TN (see caat_gemm_layout).  Returns hipError_t of the launch.
 hipError_t launch_gemm(const GemmParams& p, int layout, int epilogue, hipStream_t s);
+// NT, at most 128 token rows, EPI_PLAIN / EPI_GELU_FWD / EPI_SWIGLU_FWD / EPI_ROWPAR (launch_gemm decides when)
+hipError_t launch_gemm_stream(const GemmParams& p, int epilogue, int n_cu, hipStream_t s);
 
 // ---------------------------------------------------------------- streaming kernels
 hipError_t launch_partial_sync(const bf16_t* y, const bf16_t* resid, bf16_t* out, int T, long long tokens, int h,

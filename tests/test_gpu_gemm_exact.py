@@ -31,3 +31,23 @@ def test_gemm_small_integers_bit_exact(layout, G, M, N, K):
                 M * K, N * K, M * N)
     torch.cuda.synchronize()
     assert np.array_equal(B.to_host_bits(out), want)
+
+
+# few token rows: one, around 16-row tiles, past 64 and up to the streaming kernel's limit; short and ragged contractions;
+# shards whose widths leave a remainder in every tile width; the last two have so many weight rows that more than 16
+# token rows take the tile kernel
+@pytest.mark.parametrize("G,N,K", [(2, 8, 8), (8, 1376, 512), (3, 520, 72), (2, 1288, 2048), (1, 40, 4104), (4, 8192, 136),
+                                   (16, 2056, 200)])
+def test_gemm_few_rows_small_integers_bit_exact(G, N, K):
+    import torch
+    rng = np.random.default_rng(N + K)
+    b = rng.integers(-2, 3, size=(G, N, K)).astype(np.float32)
+    db = B.to_device(I.f32_to_bf16_bits(b))
+    for M in (1, 2, 15, 16, 17, 32, 33, 48, 63, 64, 65, 80, 97, 128, 129):
+        a = rng.integers(-2, 3, size=(G, M, K)).astype(np.float32)
+        want = I.f32_to_bf16_bits(np.matmul(a, b.transpose(0, 2, 1)))
+        da = B.to_device(I.f32_to_bf16_bits(a))
+        out = torch.full((G, M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+        B.gemm_bf16(da, db, out, B.GEMM_NT, G, M, N, K, K, K, N, M * K, N * K, M * N)
+        torch.cuda.synchronize()
+        assert np.array_equal(B.to_host_bits(out), want), M
