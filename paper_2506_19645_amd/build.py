@@ -9,7 +9,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libcaat.so")
-SOURCES = ["caat_api.hip", "caat_gemm.hip", "caat_gemm_stream.hip", "caat_stream.hip", "caat_attn.hip"]
+SOURCES = ["caat_api.hip", "caat_gemm.hip", "caat_gemm_stream.hip", "caat_stream.hip", "caat_attn.hip", "caat_decode_attn.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
          "-packed-fp32-ops", "-Wall", "-Wno-unused-function"]

@@ -137,6 +137,8 @@ int layout_of(const caat_desc* d, caat_ws_layout* L) {
     take(T * n * 2 * fr * 2, &L->off_P, &L->bytes_P);
     take(T * n * fr * 2, &L->off_Y, &L->bytes_Y);
     take(T * n * 4, &L->off_rstd, &L->bytes_rstd);
+    if (d->kind == CAAT_ATTN_DECODE && d->kv_len >= 0)   // partial results of the attention over ranges of keys
+      take(decode_attn_scratch_bytes((long long)T * n, d->n_heads / d->T, kv_heads_of(d) / d->T, d->kv_len + 1), &L->off_scratch, &L->bytes_scratch);
   } else {
     return CAAT_EUNSUPPORTED;
   }
@@ -422,7 +424,8 @@ int layer_fwd(const caat_desc* d, const caat_ws_layout& L, const void* const* we
     // decode: the attention kernel rotates q and the new k itself, appends k, v to the caches and attends to
     // kv_len cached keys plus the new one
     CAAT_STEP("decode_attn", launch_decode_attn(QKV, (bf16_t*)kv_k, (bf16_t*)kv_v, H, T * n, (int)hpr, (int)kvpr,
-                                                d->head_dim, d->kv_cap, d->kv_len + 1, d->rope_base, s))
+                                                d->head_dim, d->kv_cap, d->kv_len + 1, d->rope_base,
+                                                L.bytes_scratch ? ws + L.off_scratch : nullptr, s))
   }
   // the reduce after o_proj and the RMSNorm in front of the MLP run as one launch where the fused kernel takes the
   // shape: for decode-sized batches both are start-up latency, for prompts the fused kernel does not read the

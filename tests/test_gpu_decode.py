@@ -98,3 +98,23 @@ def test_decode_layer_outputs_alone_with_a_tiny_residual(separate):
     hs = hs_of(cfg)
     for m in range(1, cfg.T):
         assert np.array_equal(got["R2_bits"][m, :, :hs], got["R2_bits"][0, :, :hs])
+
+
+@pytest.mark.parametrize("T,b,heads,kv_heads,L", [
+    (2, 1, 4, 0, 15),        # one block of 16 keys, the new key its last row
+    (2, 1, 4, 0, 16),        # the new key opens a block
+    (2, 3, 8, 2, 1023),      # few sequences, long cache: many ranges of keys, four query heads per key / value head
+    (1, 1, 2, 1, 2050),      # two query heads, 64 ranges at most
+    (2, 2, 34, 2, 333),      # 17 query heads per key / value head: a second workgroup for the last one
+    (4, 9, 8, 4, 767),       # more workgroups, fewer ranges
+])
+def test_decode_attention_over_ranges_of_keys(T, b, heads, kv_heads, L):
+    cfg = _cfg(T, b, heads, T * 64, L, 0.5, kv_heads)
+    d = make_inputs(cfg, seed=37, weight_std=0.05 if cfg.h < 4096 else 0.02)
+    got = run_decode(cfg, d)
+    ref = oracle_decode(cfg, d)
+    assert_close(got["H"], ref["H"], "H", tol=1e-2)     # q, k, v and H are each rounded to bf16 once: 4 x 2^-9 at most
+    assert_close(bits_to_f64(got["Kc_bits"][:, :, :, L]), ref["k_new"], "k_new")
+    assert_close(bits_to_f64(got["Vc_bits"][:, :, :, L]), ref["v_new"], "v_new")
+    assert np.array_equal(got["Kc_bits"][:, :, :, :L], d["Kc"][:, :, :, :L])
+    assert np.array_equal(got["Vc_bits"][:, :, :, :L], d["Vc"][:, :, :, :L])
