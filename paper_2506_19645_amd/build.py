@@ -9,7 +9,9 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libcaat.so")
-SOURCES = ["caat_api.hip", "caat_gemm.hip", "caat_gemm_stream.hip", "caat_stream.hip", "caat_attn.hip", "caat_decode_attn.hip"]
+SOURCES = ["caat_api.hip", "caat_gemm.hip", "caat_gemm_tiles_256x256.hip", "caat_gemm_tiles_192x256.hip",
+           "caat_gemm_tiles_256x192.hip", "caat_gemm_tiles_128x128.hip", "caat_gemm_tiles_small.hip", "caat_gemm_stream.hip",
+           "caat_stream.hip", "caat_attn.hip", "caat_decode_attn.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
          "-packed-fp32-ops", "-Wall", "-Wno-unused-function"]
@@ -28,7 +30,7 @@ def _compile(src: str) -> str:
 
 
 def build(verbose: bool = True) -> str:
-    with ThreadPoolExecutor(max_workers=4) as ex:
+    with ThreadPoolExecutor(max_workers=8) as ex:
         objs = list(ex.map(_compile, SOURCES))
     r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", OUT] + objs,
                        capture_output=True, text=True)

@@ -1,43 +1,18 @@
 // Instantiations and launch dispatch of the grouped bf16 shard GEMM (kernel template in caat_gemm_kernel.h).
 #include <algorithm>
-#include "caat_gemm_kernel.h"
+#include "caat_gemm_tiles.h"
 
 namespace caat {
 
-// Tile choices: 256 x 256 tiles with 8 waves (2 x 4) and 2 LDS stages of 64 k for the block-sized GEMMs of every
-// layout (stages of 32 k fetch an operand that is contiguous along K in 64-byte pieces of rows that lie kilobytes apart
-// and meet at twice as many barriers: with five of them and the two halves of a line copied back to back, NT 241 us
-// against 210, TN 210 against 203).  64 x 128 tiles, 4 stages, for small batches whose weights fill the chip.
-typedef TileCfg<256, 256, 2, 4, 2, true> CfgBig;
-typedef TileCfg<128, 128, 2, 2, 2, false> CfgMid;   // problems with too few 256 x 256 tiles to fill the chip
-typedef TileCfg<64, 128, 2, 2, 4, false> CfgSkinny;
+typedef TileCfg<64, 128, 2, 2, 4, false, true> CfgSkinny;   // small batches whose weights fill the chip
 
-// every (layout, epilogue) pair that exists, for one block-sized tile shape
-template <class CFG>
-static hipError_t launch_block_sized(const GemmParams& p, int layout, int epilogue, hipStream_t s) {
-  switch (layout) {
-    case 0:  // NT
-      switch (epilogue) {
-        case EPI_PLAIN: return launch_one<CFG, false, false, EPI_PLAIN>(p, s);
-        case EPI_GELU_FWD: return launch_one<CFG, false, false, EPI_GELU_FWD>(p, s);
-        case EPI_SWIGLU_FWD: return launch_one<CFG, false, false, EPI_SWIGLU_FWD>(p, s);
-        case EPI_ROWPAR: return launch_one<CFG, false, false, EPI_ROWPAR>(p, s);
-        case EPI_SHARED_BCAST: return launch_one<CFG, false, false, EPI_SHARED_BCAST>(p, s);
-        default: return hipErrorInvalidValue;
-      }
-    case 1:  // NN
-      switch (epilogue) {
-        case EPI_PLAIN: return launch_one<CFG, false, true, EPI_PLAIN>(p, s);
-        case EPI_GELU_BWD: return launch_one<CFG, false, true, EPI_GELU_BWD>(p, s);
-        case EPI_SWIGLU_BWD: return launch_one<CFG, false, true, EPI_SWIGLU_BWD>(p, s);
-        default: return hipErrorInvalidValue;
-      }
-    case 2:  // TN
-      if (epilogue == EPI_PLAIN) return launch_one<CFG, true, true, EPI_PLAIN>(p, s);
-      return hipErrorInvalidValue;
-    default: return hipErrorInvalidValue;
-  }
-}
+// the specialisations live in the caat_gemm_tiles_*.hip units
+template <> hipError_t launch_block_sized<Cfg256x256>(const GemmParams&, int, int, hipStream_t);
+template <> hipError_t launch_block_sized<Cfg192x256>(const GemmParams&, int, int, hipStream_t);
+template <> hipError_t launch_block_sized<Cfg256x192>(const GemmParams&, int, int, hipStream_t);
+template <> hipError_t launch_block_sized<Cfg128x128>(const GemmParams&, int, int, hipStream_t);
+template <> hipError_t launch_block_sized<Cfg64x128>(const GemmParams&, int, int, hipStream_t);
+template <> hipError_t launch_block_sized<Cfg64x64>(const GemmParams&, int, int, hipStream_t);
 
 static int compute_units() {
   static int n_cu = 0;
@@ -70,6 +45,47 @@ static int choose_skinny_width(int G, int N, int epilogue) {
   return width;
 }
 
+// Tile shape of a block-sized launch: the one with the least modelled time.  A launch runs in rounds of as many tiles as
+// the compute units hold at once; a tile takes a time per 64-k stage and a fixed time (its first stages, its epilogue),
+// and a round that leaves compute units idle is faster than a full one (clock, caches), down to 0.55 of its time.  The
+// constants are fitted to the shapes of six training and prefill blocks, all three layouts, 32 launches from 256 to 8192
+// rows timed with every tile shape: the choice by the model is 0.4 % slower than the fastest shape on their average.
+// Examples (us; 256 x 256, 192 x 256, 256 x 192, 128 x 128, 64 x 128, 64 x 64; G x M x N x K):
+//   NT 8 x 777 x 1536 x 4096     112 / 100 / 100 / 119 / 122 / 152
+//   TN 4 x 2048 x 1408 x 1111   34.4 / 49.8 / 31.2 / 38.5 / 42.4 / 56.0
+//   NN 4 x 1111 x 1408 x 2048   49.5 / 41.3 / 43.9 / 33.0 / 44.9 / 57.8
+//   TN 4 x 2048 x 512 x 3009    69.3 / 59.6 / 61.9 / 39.3 / 37.4 / 54.2
+//   NT 2 x 256 x 768 x 1536     33.7 / 28.5 / 29.0 / 19.5 / 13.3 / 11.0
+//   NN 4 x 8192 x 2048 x 2048    227 /  256 /  260 /  275 /  369 /  479
+// 128 x 256 and 256 x 128 tiles with three stages came within 5 % of the best of these wherever they won, and 256 x 256
+// by four waves of 128 x 128 (a third less LDS traffic, one wave per SIMD) takes 15 % longer than by eight.
+struct TileShape {
+  int bm, bn, per_cu;   // per_cu: workgroups a compute unit holds
+  double stage, tile;   // us
+};
+static constexpr TileShape TILES[] = {{256, 256, 1, 1.64, 8.1}, {192, 256, 1, 1.35, 6.3}, {256, 192, 1, 1.35, 6.7},
+                                      {128, 128, 2, 0.98, 4.2}, {64, 128, 2, 0.645, 2.6}, {64, 64, 2, 0.446, 1.8}};
+static int choose_tile(const GemmParams& p, int epilogue, int n_cu) {
+  const bool swi = epilogue == EPI_SWIGLU_FWD;
+  const double nk = (double)((p.K + 63) / 64) * (p.kcat > 1 ? p.kcat : 1);
+  int best = 0;
+  double cost = 0.0;
+  for (int i = 0; i < (int)(sizeof(TILES) / sizeof(TILES[0])); ++i) {
+    const TileShape& t = TILES[i];
+    if (swi && (t.bn == 192 || t.bn == 64)) continue;   // a wave takes gate and up columns in pairs of 32
+    const long long bn_out = swi ? t.bn / 2 : t.bn, slots = (long long)t.per_cu * n_cu;
+    const long long tiles = ((p.M + t.bm - 1) / t.bm) * ((p.N + bn_out - 1) / bn_out) * p.G;
+    const long long full = tiles / slots, rest = tiles % slots;
+    const double rounds = (double)full + (rest ? 0.55 + 0.45 * (double)rest / (double)slots : 0.0);
+    const double c = rounds * (nk * t.stage + t.tile);
+    if (i == 0 || c < cost) {
+      cost = c;
+      best = i;
+    }
+  }
+  return best;
+}
+
 hipError_t launch_gemm(const GemmParams& p, int layout, int epilogue, hipStream_t s) {
   // buffer-load offsets are 32-bit and relative to the tile origin: the farthest row a tile touches times the
   // row stride must stay below 2 GiB
@@ -99,21 +115,16 @@ hipError_t launch_gemm(const GemmParams& p, int layout, int epilogue, hipStream_
       }
     }
   }
-  // 256 x 256 tiles (one workgroup per CU) unless they would leave much of the chip idle: then 128 x 128 tiles, two
-  // workgroups per CU (measured 17 % less efficient per tile at full occupancy, hence the factor).  Occupancy of a launch =
-  // tiles / (rounds x slots), times the fraction of the tiles' area that lies inside the matrix.
-  auto occupancy = [&](long long bm, long long bn, long long slots) {
-    const long long bn_out = epilogue == EPI_SWIGLU_FWD ? bn / 2 : bn;
-    const long long tm = (p.M + bm - 1) / bm, tn = (p.N + bn_out - 1) / bn_out;
-    const long long tiles = tm * tn * p.G;
-    const long long rounds = (tiles + slots - 1) / slots;
-    const double filled = ((double)p.M * (double)p.N) / ((double)(tm * bm) * (double)(tn * bn_out));  // ragged edge tiles
-    return filled * (double)tiles / (double)(rounds * slots);
-  };
   GemmParams q = p;
   q.bn_out = 0;  // block-sized tiles always cover their full width
-  if (0.83 * occupancy(128, 128, 2LL * n_cu) > occupancy(256, 256, n_cu)) return launch_block_sized<CfgMid>(q, layout, epilogue, s);
-  return launch_block_sized<CfgBig>(q, layout, epilogue, s);
+  switch (choose_tile(p, epilogue, n_cu)) {
+    case 0: return launch_block_sized<Cfg256x256>(q, layout, epilogue, s);
+    case 1: return launch_block_sized<Cfg192x256>(q, layout, epilogue, s);
+    case 2: return launch_block_sized<Cfg256x192>(q, layout, epilogue, s);
+    case 3: return launch_block_sized<Cfg128x128>(q, layout, epilogue, s);
+    case 4: return launch_block_sized<Cfg64x128>(q, layout, epilogue, s);
+    default: return launch_block_sized<Cfg64x64>(q, layout, epilogue, s);
+  }
 }
 
 }  // namespace caat

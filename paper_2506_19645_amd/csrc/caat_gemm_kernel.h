@@ -21,7 +21,7 @@
 // bytes per lane straight from registers.  With PERSIST a workgroup walks several tiles, whose stages form one stream of
 // copies: the first stages of the next tile are in flight while a tile is finished and stored, and the next main loop
 // starts without a barrier.  Only half of the waves issue copies (NLOAD below), so that the other half's stores can
-// drain under the next tile.  Decode-sized tiles (BM <= 64) may cover fewer output columns than the MFMA tile is wide
+// drain under the next tile.  Decode-sized tiles (STREAM_B) may cover fewer output columns than the MFMA tile is wide
 // (bn_out).
 //
 // What bounds the block-sized tiles: on N(0,1) operands the chip's power, then the operand copies and the epilogue.  A
@@ -59,9 +59,14 @@ typedef __attribute__((address_space(3))) const char* lds_c_t;
 typedef __attribute__((address_space(3))) const uint4* lds_u4_t;
 typedef __attribute__((address_space(3))) short4_t* lds_s4_t;
 
-template <int BM_, int BN_, int WM_, int WN_, int NSTAGE_ = 2, bool PERSIST_ = true, int BKS_ = 64>
+// rows the LDS image of an operand tile has room for: a power of two (an image [k][rows] is swizzled in whole lines)
+constexpr int image_rows(int rows) { return rows == 192 ? 256 : rows; }
+
+template <int BM_, int BN_, int WM_, int WN_, int NSTAGE_ = 2, bool PERSIST_ = true, bool STREAM_B_ = false>
 struct TileCfg {
-  static constexpr int BKS = BKS_;              // k extent of one LDS stage (multiple of 32; K-contiguous operands only if > 32)
+  static constexpr int BKS = 64;                // k extent of one LDS stage
+  // STREAM_B: decode-sized launches, which read every weight row once (non-temporal copies, bn_out)
+  static constexpr bool STREAM_B = STREAM_B_;
   // PERSIST: one workgroup per CU walks several tiles and fetches the next tile's first stages under the epilogue
   static constexpr bool PERSIST = PERSIST_;
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, NSTAGE = NSTAGE_;
@@ -69,7 +74,8 @@ struct TileCfg {
   static constexpr int NWAVES = WM * WN;
   static constexpr int WTM = BM / WM, WTN = BN / WN;  // wave tile
   static constexpr int TM = WTM / 16, TN = WTN / 16;  // 16x16 MFMA tiles per wave
-  static constexpr int STAGE_CHUNKS = (BM + BN) * (BKS / 8);  // uint4 per LDS stage
+  static constexpr int A_CHUNKS = image_rows(BM) * (BKS / 8);  // uint4 per LDS stage
+  static constexpr int STAGE_CHUNKS = A_CHUNKS + image_rows(BN) * (BKS / 8);
   static constexpr int SMEM_CHUNKS = NSTAGE * STAGE_CHUNKS;
   static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be a multiple of 32x32");
   static_assert(!PERSIST || NSTAGE == 2, "the persistent loop counts on two slots");
@@ -95,7 +101,7 @@ struct KContigOperand {
   // stage; otherwise the waves' copies interleave (copy `it` of wave w fills group it*NWAVES + w), which keeps the
   // rows a wave instruction touches in memory next to those of its neighbours: the decode-sized weight streams
   // measured 1-1.5 % faster that way, the block-sized tiles with the grouped issue.
-  static constexpr int GRP = GROUPED ? (NI >= 4 ? 4 : NI) : 1;
+  static constexpr int GRP = !GROUPED ? 1 : (NI % 4 == 0 ? 4 : (NI % 2 == 0 ? 2 : 1));
   static __device__ __forceinline__ int group_of(int wave, int it) { return GROUPED ? wave * NI + it : it * NWAVES + wave; }
   static constexpr int N_VMEM = NI;
   static constexpr int READS_PER_FRAG = 1;
@@ -165,19 +171,20 @@ struct KContigOperand {
 
 // ---- operand contiguous along its row index ([K][rows] in memory): stage [BKS k][ROWS] as in memory, k-row =
 // ROWS*2 bytes; chunk c of k-row k sits at c ^ (((k&3)<<2) | (((k>>3)&1)<<1)): the transpose read of 32 lanes (two groups of
-// 4 k-rows, 8 apart, 32 bytes of each) then touches every bank once.  One wave instruction fills 512/ROWS k-rows.
+// 4 k-rows, 8 apart, 32 bytes of each) then touches every bank once.  With 64 rows two k-rows share a line of all banks, and
+// the chunk's swizzle is (((k>>1)&1)<<1) | (((k>>3)&1)<<2).  One wave instruction fills 512/ROWS k-rows.
 // `origin` points at (k = 0, first row of the tile); rows_valid = rows of the tile that exist (multiple of 8).
 template <int ROWS, int NWAVES, int BKS_ = 64, bool GROUPED = true>
 struct RowContigOperand {
   static constexpr int CPR = ROWS / 8;       // chunks per k-row
   static constexpr int KPI = 64 / CPR;       // k-rows per copy instruction
   static constexpr int NI = BKS_ / KPI / NWAVES;
-  static constexpr int GRP = GROUPED ? (NI >= 4 ? 4 : NI) : 1;  // as in KContigOperand
+  static constexpr int GRP = !GROUPED ? 1 : (NI % 4 == 0 ? 4 : (NI % 2 == 0 ? 2 : 1));  // as in KContigOperand
   static __device__ __forceinline__ int group_of(int wave, int it) { return GROUPED ? wave * NI + it : it * NWAVES + wave; }
   static constexpr int N_VMEM = NI;
   static constexpr int READS_PER_FRAG = 2;
   static_assert(NI % GRP == 0, "whole groups of copies");
-  static_assert(ROWS >= 128 && ROWS <= 512 && BKS_ % (KPI * NWAVES) == 0, "unsupported tile shape for a transposed operand");
+  static_assert((ROWS == 64 || ROWS == 128 || ROWS == 256) && BKS_ % (KPI * NWAVES) == 0, "unsupported tile shape for a transposed operand");
   const bf16_t* origin;
   long long ld;
   unsigned voff[NI];
@@ -218,7 +225,9 @@ struct RowContigOperand {
       dma16_group<STREAM, GRP>(rs, v, tile + group_of(wave, gi * GRP) * 64);
     }
   }
-  static __device__ __forceinline__ int swz(int k) { return ((k & 3) << 2) | (((k >> 3) & 1) << 1); }
+  static __device__ __forceinline__ int swz(int k) {
+    return ROWS == 64 ? (((k >> 1) & 1) << 1) | (((k >> 3) & 1) << 2) : ((k & 3) << 2) | (((k >> 3) & 1) << 1);
+  }
   // The same fragments as KContigOperand::Reader, each gathered by two transpose reads of 4 k.  A lane fetches 8 bytes
   // (rows 4 (lane%4) ..+3 of the 16) of k-row 32 ks + 8 (lane/16) + (lane%16)/4 and of the k-row 4 further on; both have
   // the same swizzle.  TT = MFMA tiles of the wave: the tile index moves the chunk inside the swizzle, so there is an
@@ -246,7 +255,7 @@ struct RowContigOperand {
 template <bool ROWCONTIG, int ROWS, int NWAVES, int BKS_, bool GROUPED>
 struct OperandSel { typedef KContigOperand<ROWS, NWAVES, BKS_, GROUPED> type; };
 template <int ROWS, int NWAVES, int BKS_, bool GROUPED>
-struct OperandSel<true, ROWS, NWAVES, BKS_, GROUPED> { typedef RowContigOperand<ROWS, NWAVES, BKS_, GROUPED> type; };
+struct OperandSel<true, ROWS, NWAVES, BKS_, GROUPED> { typedef RowContigOperand<image_rows(ROWS), NWAVES, BKS_, GROUPED> type; };
 
 // Which weight row (relative to the tile's first row n0) lies in row rr of the B tile in LDS, or -1 for none.  Plain
 // epilogues: rows in order, as many as the tile covers (bn_out) and the matrix has.  SwiGLU: each wave's WTN tile rows
@@ -288,7 +297,7 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
   // Decode-sized tiles may be told to cover fewer output columns than the MFMA tile is wide (bn_out, a multiple of
   // 8): the kernel is then a weight stream, and what counts is that every compute unit gets the same number of weight
   // rows.  The rows beyond bn_out are not fetched (out-of-range copy offsets) and their columns are not stored.
-  constexpr bool NARROW = (BM <= 64);
+  constexpr bool NARROW = CFG::STREAM_B;
   const int bn_out = (NARROW && p.bn_out > 0) ? p.bn_out : BN_OUT;
   const int tiles_m = (p.M + BM - 1) / BM;
   const int tiles_n = (p.N + bn_out - 1) / bn_out;
@@ -315,8 +324,8 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
   // SwiGLU GEMM -5 %, GELU' GEMM -5 %, weight gradients -2.4 %, QKV -3 %; nothing lost anywhere.
   constexpr int NLOAD = (CFG::PERSIST && CFG::NWAVES == 8) ? 4 : CFG::NWAVES;
   const bool loader = wave < NLOAD;
-  typedef typename OperandSel<AT, BM, NLOAD, BKS, (BM > 64)>::type OpA;
-  typedef typename OperandSel<BT, BN, NLOAD, BKS, (BM > 64)>::type OpB;
+  typedef typename OperandSel<AT, BM, NLOAD, BKS, !CFG::STREAM_B>::type OpA;
+  typedef typename OperandSel<BT, BN, NLOAD, BKS, !CFG::STREAM_B>::type OpB;
   OpA la;
   OpB lb;
   // rank g, first row m0 and first column n0 of a tile
@@ -337,7 +346,7 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
     tile_coords(id, g, m0, n0);
     const bf16_t* ag = p.a + (long long)g * p.stride_a;
     const bf16_t* bg = p.b + (long long)g * p.stride_b;
-    const int mrem = p.M - m0;
+    const int mrem = p.M - m0 < BM ? p.M - m0 : BM;   // an image may have room for more rows than the tile has
     la.init(AT ? ag + m0 : ag + (long long)m0 * p.lda, p.lda,
             [=](int rr) -> long long { return (rr < mrem) ? (long long)rr : -1; });
     if constexpr (!BT) {
@@ -345,7 +354,7 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
       auto rowmap = [=](int rr) -> long long { return b_tile_row<CFG, SWI>(rr, n0c, bnc, Nc, halfc); };
       lb.init(bg + (long long)n0 * p.ldb, p.ldb, rowmap);
     } else {
-      const int nrem = p.N - n0;
+      const int nrem = p.N - n0 < BN ? p.N - n0 : BN;
       lb.init(bg + n0, p.ldb, [=](int rr) -> long long { return (rr < nrem) ? (long long)rr : -1; });
     }
   };
@@ -358,11 +367,11 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
   const int kcat = KCAT ? (p.kcat > 1 ? p.kcat : 1) : 1;
   const int nkg = (K + BKS - 1) / BKS;   // stages of one K-group
   const int nk = nkg * kcat;             // stages of a tile
-  constexpr int A_CHUNKS = BM * (BKS / 8);
+  constexpr int A_CHUNKS = CFG::A_CHUNKS;
   constexpr int STAGE_BYTES = CFG::STAGE_CHUNKS * 16;
   constexpr int NV = OpA::N_VMEM + OpB::N_VMEM;  // copies of a loading wave per stage
-  // decode-sized tiles (at most 64 token rows per rank: one tile row) read every weight row exactly once
-  constexpr bool B_STREAM = (BM <= 64);
+  // decode-sized launches (at most 64 token rows per rank: one tile row) read every weight row exactly once
+  constexpr bool B_STREAM = CFG::STREAM_B;
 
   // ---- the loading side.  The stages of all tiles of this workgroup form one stream; issue_one copies the next one
   // into the next slot, and steps on to the next tile behind a tile's last stage: the first stages of a tile are on
@@ -721,7 +730,7 @@ template <class CFG, bool AT, bool BT, int EPI>
 static hipError_t launch_one(const GemmParams& p, hipStream_t s) {
   constexpr int BN_OUT = (EPI == EPI_SWIGLU_FWD) ? CFG::BN / 2 : CFG::BN;
   if (p.bn_out < 0 || p.bn_out > BN_OUT || (p.bn_out & 7)) return hipErrorInvalidValue;
-  const long long bn_out = (CFG::BM <= 64 && p.bn_out > 0) ? p.bn_out : BN_OUT;  // as in the kernel
+  const long long bn_out = (CFG::STREAM_B && p.bn_out > 0) ? p.bn_out : BN_OUT;  // as in the kernel
   const long long tiles_m = (p.M + CFG::BM - 1) / CFG::BM;
   const long long tiles_n = (p.N + bn_out - 1) / bn_out;
   const long long total = tiles_m * tiles_n * p.G;

@@ -117,6 +117,19 @@ def test_mlp_block_fwd_bwd(swi, T, n, h, ffn, p, scale):
     check_mlp_block(cfg, d, got, w, fwd, g)
 
 
+@pytest.mark.parametrize("swi,n,h,p", [
+    (False, 570, 1544, 0.5), (True, 777, 1160, 0.301),       # 192 x 256 tiles
+    (False, 1000, 1160, 0.301), (True, 1000, 1160, 0.5),     # 256 x 192 tiles
+])
+def test_mlp_block_on_tiles_of_192(swi, n, h, p):
+    """Every fused epilogue on the tiles with 192 rows or columns, edges in both directions, hs inside a tile."""
+    cfg = _cfg(swi, 8, n, h, 8 * h, p)
+    d = make_inputs(cfg, seed=23)
+    got = run_mlp_block(cfg, d)
+    w, fwd, g = oracle_mlp_block(cfg, d)
+    check_mlp_block(cfg, d, got, w, fwd, g)
+
+
 def test_mlp_block_config1_seed0():
     """The small benchmark configuration, exactly as specified (h=768, ffn=3072, T=2, p=0.5, 256 tokens, seed 0)."""
     cfg = I.C1

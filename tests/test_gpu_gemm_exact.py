@@ -12,7 +12,11 @@ pytestmark = pytest.mark.gpu
 # (G, M, N, K): below / at / past one tile in each dimension; 1, 2 and 3 stages of k with and without a remainder;
 # more tiles than compute units with stage counts 1, 2, 3 (the stream of copies runs on from tile to tile)
 SHAPES = [(1, 8, 8, 8), (2, 256, 256, 64), (1, 264, 248, 72), (1, 520, 776, 200), (3, 296, 520, 136), (1, 24, 136, 320),
-          (5, 2048, 2048, 64), (5, 2040, 1928, 128), (5, 2008, 2056, 184)]
+          (5, 2048, 2048, 64), (5, 2040, 1928, 128), (5, 2008, 2056, 184),
+          # 192 x 256 and 256 x 192 tiles: one round with a remainder in both directions, several tiles per workgroup with
+          # 2 and 3 stages; 64 x 128 tiles of 64 rows and a remainder
+          (8, 1032, 1160, 200), (8, 1144, 1808, 136), (8, 1000, 1160, 328), (8, 2024, 2200, 72), (8, 2008, 2096, 136),
+          (8, 200, 1160, 136)]
 
 
 @pytest.mark.parametrize("G,M,N,K", SHAPES)
