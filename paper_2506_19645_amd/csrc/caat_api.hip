@@ -4,6 +4,7 @@
 #include "caat_tools.h"
 #include "caat_internal.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <vector>
@@ -67,6 +68,15 @@ long long qkv_width(const caat_desc* d) {
   return (long long)(d->n_heads / d->T + 2 * (kv_heads_of(d) / d->T)) * d->head_dim;
 }
 
+// the reduce is taken inside the row-parallel GEMM (see rowpar_pcr), and the scratch that takes for contraction lengths
+// k1 and k2 per rank
+bool sums_in_gemm(const caat_desc* d) { return d->reduce_in_gemm && d->hs % 8 == 0 && d->tokens > 64; }
+size_t shared_scratch(const caat_desc* d, long long k1, long long k2) {
+  if (!sums_in_gemm(d) || d->hs == 0) return 0;
+  return std::max(gemm_shared_scratch_bytes((int)d->tokens, d->hs, (int)k1, d->T),
+                  gemm_shared_scratch_bytes((int)d->tokens, d->hs, (int)k2, d->T));
+}
+
 int validate_desc(const caat_desc* d) {
   if (!d) return CAAT_EINVAL;
   if (d->kind < CAAT_MLP_GELU || d->kind > CAAT_LAYER_PREFILL) return CAAT_EINVAL;
@@ -115,7 +125,8 @@ int layout_of(const caat_desc* d, caat_ws_layout* L) {
     take(T * n * 4, &L->off_rstd, &L->bytes_rstd);
     take(T * n * h * 2, &L->off_dZt, &L->bytes_dZt);
     take(T * n * pw * 2, &L->off_dP, &L->bytes_dP);
-    take(norm_bwd_workspace_bytes(d->T, d->tokens, d->h), &L->off_scratch, &L->bytes_scratch);
+    take(std::max(norm_bwd_workspace_bytes(d->T, d->tokens, d->h), shared_scratch(d, (long long)fr, (long long)fr)),
+         &L->off_scratch, &L->bytes_scratch);
   } else if (d->kind == CAAT_ATTN) {
     const size_t hd = (size_t)(d->n_heads / d->T) * d->head_dim, qw = (size_t)qkv_width(d);
     take(T * n * qw * 2, &L->off_Q, &L->bytes_Q);
@@ -126,7 +137,8 @@ int layout_of(const caat_desc* d, caat_ws_layout* L) {
     take(T * n * h * 2, &L->off_dZt, &L->bytes_dZt);
     take(T * n * hd * 2, &L->off_dH, &L->bytes_dH);
     take(T * n * qw * 2, &L->off_dP, &L->bytes_dP);
-    take(norm_bwd_workspace_bytes(d->T, d->tokens, d->h), &L->off_scratch, &L->bytes_scratch);
+    take(std::max(norm_bwd_workspace_bytes(d->T, d->tokens, d->h), shared_scratch(d, (long long)hd, (long long)hd)),
+         &L->off_scratch, &L->bytes_scratch);
   } else if (is_layer(d->kind)) {
     const size_t hd = (size_t)(d->n_heads / d->T) * d->head_dim, fr = d->ffn / d->T;
     take(T * n * h * 2, &L->off_X1, &L->bytes_X1);
@@ -137,8 +149,10 @@ int layout_of(const caat_desc* d, caat_ws_layout* L) {
     take(T * n * 2 * fr * 2, &L->off_P, &L->bytes_P);
     take(T * n * fr * 2, &L->off_Y, &L->bytes_Y);
     take(T * n * 4, &L->off_rstd, &L->bytes_rstd);
+    size_t scratch = shared_scratch(d, (long long)hd, (long long)fr);
     if (d->kind == CAAT_ATTN_DECODE && d->kv_len >= 0)   // partial results of the attention over ranges of keys
-      take(decode_attn_scratch_bytes((long long)T * n, d->n_heads / d->T, kv_heads_of(d) / d->T, d->kv_len + 1), &L->off_scratch, &L->bytes_scratch);
+      scratch = std::max(scratch, decode_attn_scratch_bytes((long long)T * n, d->n_heads / d->T, kv_heads_of(d) / d->T, d->kv_len + 1));
+    if (scratch > 0) take(scratch, &L->off_scratch, &L->bytes_scratch);
   } else {
     return CAAT_EUNSUPPORTED;
   }
@@ -163,17 +177,17 @@ bool fuse_norm_bwd_reduce(const caat_desc* d) {
 // shared ones, then the reduce kernel over the T partials (the stand-in for the tensor-parallel collective).
 // reduce_in_gemm (single-device serving with logical ranks, Sec. 3.2: the reduce becomes a local summation): the
 // private channels come from a grouped GEMM over columns hs..h-1, the shared channels from ONE GEMM whose contraction
-// index runs over all T ranks' inputs and weight rows, so the sum over ranks is taken in the accumulator and no partial
-// sum ever reaches memory.
+// index runs over all T ranks' inputs and weight rows, so the sum over ranks is taken in the accumulator (for a prompt
+// too short to fill the chip that way: in one accumulator per group of ranks, added up by a second kernel).
 int rowpar_pcr(const caat_desc* d, const bf16_t* a, long long kdim, const bf16_t* w, const bf16_t* resid, bf16_t* out,
-               hipStream_t s, bool leave_reduce_to_caller = false) {
+               void* scratch, hipStream_t s, bool leave_reduce_to_caller = false) {
   const long long T = d->T, n = d->tokens, h = d->h;
   const int hs = d->hs;
   hipError_t e = hipSuccess;
   GemmParams q;
   // (Not for skinny problems: with at most 64 token rows per rank the GEMM is a weight stream whose only parallelism
   // is the number of tiles, and folding the ranks into the contraction would leave hs/64 workgroups for 256 CUs.)
-  if (d->reduce_in_gemm && hs % 8 == 0 && n > 64) {
+  if (sums_in_gemm(d)) {
     // residual stream layouts: [T,n,h] (shared columns in every rank's rows), or de-duplicated: [n,hs] once, then the
     // private columns [T,n,h-hs]
     const bool dd = dedup_on(d);
@@ -203,7 +217,7 @@ int rowpar_pcr(const caat_desc* d, const bf16_t* a, long long kdim, const bf16_t
       q.G = 1; q.M = (int)n; q.N = hs; q.K = (int)kdim; q.kcat = (int)T; q.bcast = dd ? 1 : (int)T;
       {
         ProfScope ps(s, "gemm_nt_shared_kcat");
-        e = launch_gemm(q, 0, EPI_SHARED_BCAST, s);
+        e = launch_gemm_shared(q, scratch, s);
       }
       if (e != hipSuccess) return CAAT_EHIP;
     }
@@ -274,7 +288,7 @@ int attn_block_fwd(const caat_desc* d, const caat_ws_layout& L, const void* cons
   if (e != hipSuccess) return CAAT_EHIP;
   const bool fuse = fuse_reduce_norm(d);
   {
-    const int st = rowpar_pcr(d, H, hd, (const bf16_t*)wo, (const bf16_t*)r, (bf16_t*)r_out, s, fuse);
+    const int st = rowpar_pcr(d, H, hd, (const bf16_t*)wo, (const bf16_t*)r, (bf16_t*)r_out, ws + L.off_scratch, s, fuse);
     if (st != CAAT_OK) return st;
   }
   if (fuse) {
@@ -405,6 +419,7 @@ int layer_fwd(const caat_desc* d, const caat_ws_layout& L, const void* const* we
   bf16_t* P = (bf16_t*)(ws + L.off_P);
   bf16_t* Y = (bf16_t*)(ws + L.off_Y);
   float* rstd = (float*)(ws + L.off_rstd);
+  void* scratch = L.bytes_scratch ? ws + L.off_scratch : nullptr;
   hipError_t e;
   GemmParams q;
 #define CAAT_STEP(name, call) { ProfScope ps(s, name); e = (call); } if (e != hipSuccess) return CAAT_EHIP;
@@ -425,14 +440,14 @@ int layer_fwd(const caat_desc* d, const caat_ws_layout& L, const void* const* we
     // kv_len cached keys plus the new one
     CAAT_STEP("decode_attn", launch_decode_attn(QKV, (bf16_t*)kv_k, (bf16_t*)kv_v, H, T * n, (int)hpr, (int)kvpr,
                                                 d->head_dim, d->kv_cap, d->kv_len + 1, d->rope_base,
-                                                L.bytes_scratch ? ws + L.off_scratch : nullptr, s))
+                                                scratch, s))
   }
   // the reduce after o_proj and the RMSNorm in front of the MLP run as one launch where the fused kernel takes the
   // shape: for decode-sized batches both are start-up latency, for prompts the fused kernel does not read the
   // reduced shared channels back from memory (measured 1.28 ms instead of 0.61 + 0.78 ms on 16 prompts of 2048)
   const bool fuse_mid = fuse_reduce_norm(d);
   {
-    const int st = rowpar_pcr(d, H, hd, (const bf16_t*)wo, (const bf16_t*)r, R1, s, fuse_mid);
+    const int st = rowpar_pcr(d, H, hd, (const bf16_t*)wo, (const bf16_t*)r, R1, scratch, s, fuse_mid);
     if (st != CAAT_OK) return st;
   }
   if (fuse_mid) {
@@ -450,7 +465,7 @@ int layer_fwd(const caat_desc* d, const caat_ws_layout& L, const void* const* we
   q.G = (int)T; q.M = (int)n; q.N = (int)fr; q.K = (int)h; q.half = (int)fr;
   CAAT_STEP("gemm_nt_swiglu_fwd", launch_gemm(q, 0, EPI_SWIGLU_FWD, s))
   {
-    const int st = rowpar_pcr(d, Y, fr, (const bf16_t*)wb, R1, (bf16_t*)r_out, s);
+    const int st = rowpar_pcr(d, Y, fr, (const bf16_t*)wb, R1, (bf16_t*)r_out, scratch, s);
     if (st != CAAT_OK) return st;
   }
 #undef CAAT_STEP
@@ -675,7 +690,7 @@ int caat_block_fwd(const caat_desc* d, const void* const* weights, const void* x
   // the reduce as a kernel of its own) the shared half of the reduce, the residual add and the norm are one launch
   const bool fuse = fuse_reduce_norm(d);
   {
-    const int st2 = rowpar_pcr(d, Y, fr, (const bf16_t*)w1, (const bf16_t*)r, (bf16_t*)r_out, s, fuse);
+    const int st2 = rowpar_pcr(d, Y, fr, (const bf16_t*)w1, (const bf16_t*)r, (bf16_t*)r_out, ws + L.off_scratch, s, fuse);
     if (st2 != CAAT_OK) return st2;
   }
   if (fuse) {

@@ -65,7 +65,7 @@ struct TileShape {
 };
 static constexpr TileShape TILES[] = {{256, 256, 1, 1.64, 8.1}, {192, 256, 1, 1.35, 6.3}, {256, 192, 1, 1.35, 6.7},
                                       {128, 128, 2, 0.98, 4.2}, {64, 128, 2, 0.645, 2.6}, {64, 64, 2, 0.446, 1.8}};
-static int choose_tile(const GemmParams& p, int epilogue, int n_cu) {
+static int choose_tile(const GemmParams& p, int epilogue, int n_cu, double* us = nullptr) {
   const bool swi = epilogue == EPI_SWIGLU_FWD;
   const double nk = (double)((p.K + 63) / 64) * (p.kcat > 1 ? p.kcat : 1);
   int best = 0;
@@ -83,6 +83,7 @@ static int choose_tile(const GemmParams& p, int epilogue, int n_cu) {
       best = i;
     }
   }
+  if (us) *us = cost;
   return best;
 }
 
@@ -93,9 +94,10 @@ hipError_t launch_gemm(const GemmParams& p, int layout, int epilogue, hipStream_
   if (far_rows * p.lda * 2 >= 0x7FFFF000LL || far_rows * p.ldb * 2 >= 0x7FFFF000LL) return hipErrorInvalidValue;
   // the epilogue's buffer offsets are relative to a wave's first row: up to 256 rows of any output / second operand
   const long long ldmax = std::max(std::max(p.ldc, p.ldc2), p.ldaux);
-  if ((256 * ldmax + 2 * (long long)p.half + (long long)p.N) * 2 >= 0x7FFFFFFFLL) return hipErrorInvalidValue;
+  const long long elem = epilogue == EPI_PARTIAL ? 4 : 2;
+  if ((256 * ldmax + 2 * (long long)p.half + (long long)p.N) * elem >= 0x7FFFFFFFLL) return hipErrorInvalidValue;
   const int n_cu = compute_units();
-  if (layout == 0 && p.M <= 128 && epilogue != EPI_SHARED_BCAST) {
+  if (layout == 0 && p.M <= 128 && epilogue != EPI_SHARED_BCAST && epilogue != EPI_PARTIAL) {
     // Few token rows: the weights are what has to be read.  The streaming kernel, except where 17 rows or more meet so
     // many weight rows that 128 of them fall to every compute unit: there the 64 x 128 tile (the 128 x 128 one from 65
     // rows on) reads the token rows half as often.  Measured (us, streaming kernel / tile kernel): 32768 rows of 1376 k,
@@ -125,6 +127,61 @@ hipError_t launch_gemm(const GemmParams& p, int layout, int epilogue, hipStream_
     case 4: return launch_block_sized<Cfg64x128>(q, layout, epilogue, s);
     default: return launch_block_sized<Cfg64x64>(q, layout, epilogue, s);
   }
+}
+
+// The shared channels of all ranks as one product with a contraction kcat times as long: few tiles, each a long chain.
+// A prompt of some hundred tokens leaves most of the chip idle, so the ranks are cut into groups that are summed in
+// parallel into fp32 buffers, and a second kernel adds the groups up in ascending order.  The number of groups is the one
+// with the least modelled time, the model of the tile choice (on the 256 compute units of the chip, so that the workspace
+// does not depend on the device that is current) times 1.4 for weights that come from HBM and not, as where the model was
+// fitted, from the memory-side cache, plus the merge: a launch and the fp32 sums at 7 TB/s.  Measured for 777 tokens, 2048
+// shared channels, 8 ranks (us, 1 / 2 / 4 / 8 groups): 512 k per rank 39 / 37 / 36 / 40, 1376 k 121 / 94 / 69 / 66.
+int gemm_shared_groups(int M, int N, int K, int kcat) {
+  GemmParams q = {};
+  q.M = M;
+  q.N = N;
+  q.K = K;
+  int best = 1;
+  double cost = 0.0;
+  for (int g = 1; g <= kcat; g *= 2) {
+    if (kcat % g != 0) break;
+    q.G = g;
+    q.kcat = kcat / g;
+    double us = 0.0;
+    choose_tile(q, EPI_PARTIAL, 256, &us);
+    us *= 1.4;
+    if (g > 1) us += 3.4 + (double)g * M * N * 4.0 / 7e6;
+    if (g == 1 || us < cost) {
+      cost = us;
+      best = g;
+    }
+  }
+  return best;
+}
+
+size_t gemm_shared_scratch_bytes(int M, int N, int K, int kcat) {
+  const int groups = gemm_shared_groups(M, N, K, kcat);
+  return groups == 1 ? 0 : (size_t)groups * (size_t)M * (size_t)N * sizeof(float);
+}
+
+hipError_t launch_gemm_shared(const GemmParams& p, void* scratch, hipStream_t s) {
+  const int groups = gemm_shared_groups(p.M, p.N, p.K, p.kcat);
+  if (groups == 1) return launch_gemm(p, 0, EPI_SHARED_BCAST, s);
+  if (scratch == nullptr) return hipErrorInvalidValue;
+  GemmParams q = p;
+  q.G = groups;
+  q.kcat = p.kcat / groups;
+  q.stride_a = p.kstride_a * q.kcat;
+  q.stride_b = p.kstride_b * q.kcat;
+  q.c = reinterpret_cast<bf16_t*>(scratch);
+  q.ldc = p.N;
+  q.stride_c = (long long)p.M * p.N;
+  q.aux = nullptr;
+  q.ldaux = 0;
+  const hipError_t e = launch_gemm(q, 0, EPI_PARTIAL, s);
+  if (e != hipSuccess) return e;
+  return launch_shared_merge(reinterpret_cast<const float*>(scratch), groups, p.aux, p.c, p.M, p.N, p.ldaux, p.ldc, p.stride_aux,
+                             p.stride_c, p.bcast, s);
 }
 
 }  // namespace caat

@@ -359,10 +359,10 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
     }
   };
 
-  // With the broadcast epilogue the contraction index runs over kcat buffers of K each (operand g' of both a and b lies
+  // With the broadcast and the partial-sum epilogue the contraction index runs over kcat buffers of K each (operand g' of both a and b lies
   // kstride elements after operand g'-1): that is how the sum over ranks of Eq. A3's shared channels is taken inside
   // the accumulator.  Every other instantiation keeps the single-buffer code (no per-stage bookkeeping).
-  constexpr bool KCAT = (EPI == EPI_SHARED_BCAST);
+  constexpr bool KCAT = (EPI == EPI_SHARED_BCAST || EPI == EPI_PARTIAL);
   const int K = p.K;
   const int kcat = KCAT ? (p.kcat > 1 ? p.kcat : 1) : 1;
   const int nkg = (K + BKS - 1) / BKS;   // stages of one K-group
@@ -377,7 +377,8 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
   // into the next slot, and steps on to the next tile behind a tile's last stage: the first stages of a tile are on
   // their way while the tile before is still computed and stored.
   int lpid = pid;          // tile of the next copy
-  int lstage = 0;          // its stage
+  int lstage = 0;          // its stage (inside its K-group)
+  int lkg = 0;             // its K-group
   int lslot = 0;           // slot it goes to
   bool lmore = pid < pid_end;
   auto issue_one = [&]() {
@@ -385,17 +386,18 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
     if (loader) {
       uint4* slot = smem + lslot * CFG::STAGE_CHUNKS;
       if constexpr (KCAT) {
-        const int kg = lstage / nkg, k0 = (lstage - kg * nkg) * BKS;
-        la.issue(k0, K, slot, (long long)kg * p.kstride_a);
-        lb.template issue<B_STREAM>(k0, K, slot + A_CHUNKS, (long long)kg * p.kstride_b);
+        la.issue(lstage * BKS, K, slot, (long long)lkg * p.kstride_a);
+        lb.template issue<B_STREAM>(lstage * BKS, K, slot + A_CHUNKS, (long long)lkg * p.kstride_b);
       } else {
         la.issue(lstage * BKS, K, slot, 0);
         lb.template issue<B_STREAM>(lstage * BKS, K, slot + A_CHUNKS, 0);
       }
     }
     lslot = lslot + 1 == NSTAGE ? 0 : lslot + 1;
-    if (++lstage == nk) {
+    if (++lstage == nkg) {
       lstage = 0;
+      if (KCAT && ++lkg < kcat) return;
+      lkg = 0;
       lpid += pid_step;
       lmore = CFG::PERSIST && lpid < pid_end;
       if (lmore && loader) setup_copies(lpid);
@@ -415,7 +417,7 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
   constexpr int EPI_STORES =
       (EPI == EPI_SHARED_BCAST)
           ? 1000
-          : TM * (SWI ? NS / 2 : NS) * (EPI == EPI_SWIGLU_FWD ? 3 : ((EPI == EPI_GELU_FWD || EPI == EPI_SWIGLU_BWD) ? 2 : 1));
+          : EPI == EPI_PARTIAL ? TM * TN : TM * (SWI ? NS / 2 : NS) * (EPI == EPI_SWIGLU_FWD ? 3 : ((EPI == EPI_GELU_FWD || EPI == EPI_SWIGLU_BWD) ? 2 : 1));
 
   if (pid >= pid_end) return;
   if (loader) setup_copies(pid);
@@ -713,7 +715,22 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
         }
       }
     };
-    if constexpr (EPI == EPI_ROWPAR) {
+    if constexpr (EPI == EPI_PARTIAL) {
+      // fp32 sums as they are: 16 bytes per lane, 64 contiguous bytes per row and MFMA tile.  The merge reads them next.
+      float* cf = reinterpret_cast<float*>(p.c) + (long long)eg * p.stride_c + (long long)wrow0 * p.ldc;
+      const rsrc_t rf = make_rsrc_t(cf);
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        const int row = i * 16 + (elane & 15);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          const int col = wcol0 + j * 16 + 4 * eq;
+          const bool ok = row < p.M - wrow0 && col < ncols && col - en0 < bn_out;
+          const uint4 w = __builtin_bit_cast(uint4, acc[i][j]);
+          put(rf, w, ok, (unsigned)((row * p.ldc + col) * 4), 0);
+        }
+      }
+    } else if constexpr (EPI == EPI_ROWPAR) {
       if (en0 + bn_out <= p.hs) slabs(std::integral_constant<int, 1>{});
       else if (en0 >= p.hs) slabs(std::integral_constant<int, 2>{});
       else slabs(std::integral_constant<int, 0>{});

@@ -36,6 +36,7 @@ static hipError_t launch_block_sized_impl(const GemmParams& p, int layout, int e
           else return hipErrorInvalidValue;
         case EPI_ROWPAR: return launch_one<CFG, false, false, EPI_ROWPAR>(p, s);
         case EPI_SHARED_BCAST: return launch_one<CFG, false, false, EPI_SHARED_BCAST>(p, s);
+        case EPI_PARTIAL: return launch_one<CFG, false, false, EPI_PARTIAL>(p, s);
         default: return hipErrorInvalidValue;
       }
     case 1:  // NN

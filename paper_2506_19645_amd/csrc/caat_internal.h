@@ -175,7 +175,8 @@ enum GemmEpilogue {
   EPI_ROWPAR = 3,      // col < hs: c = acc (partial sum);  col >= hs: c = scale*acc + resid
   EPI_GELU_BWD = 4,    // c = acc * gelu'(aux)
   EPI_SWIGLU_BWD = 5,  // c[:, col] = acc*up*silu'(gate), c[:, half+col] = acc*silu(gate); aux = [gate|up]
-  EPI_SHARED_BCAST = 6 // for m in [0, bcast): c[m] = round_bf16(acc) + aux[m]   (c, aux advance by stride_c / stride_aux)
+  EPI_SHARED_BCAST = 6, // for m in [0, bcast): c[m] = round_bf16(acc) + aux[m]   (c, aux advance by stride_c / stride_aux)
+  EPI_PARTIAL = 7      // c as fp32 = acc: partial sums over a part of the contraction (launch_gemm_shared)
 };
 
 struct GemmParams {
@@ -200,6 +201,14 @@ struct GemmParams {
 
 // layout: 0 NT, 1 NN, 2 TN (see caat_gemm_layout).  Returns hipError_t of the launch.
 hipError_t launch_gemm(const GemmParams& p, int layout, int epilogue, hipStream_t s);
+// EPI_SHARED_BCAST (NT, kcat ranks in the contraction), directly or as sums over groups of ranks that a second kernel adds
+// up: gemm_shared_groups() groups (1 = directly) with fp32 scratch of gemm_shared_scratch_bytes() (may be null when 0).
+int gemm_shared_groups(int M, int N, int K, int kcat);
+size_t gemm_shared_scratch_bytes(int M, int N, int K, int kcat);
+hipError_t launch_gemm_shared(const GemmParams& p, void* scratch, hipStream_t s);
+// the second kernel: for m in [0, bcast): out[m] = round_bf16(sum over groups of part) + resid[m]; part [groups][M][N] fp32
+hipError_t launch_shared_merge(const float* part, int groups, const bf16_t* resid, bf16_t* out, long long M, int N, long long ldr,
+                               long long ldo, long long stride_r, long long stride_o, int bcast, hipStream_t s);
 // NT, at most 128 token rows, EPI_PLAIN / EPI_GELU_FWD / EPI_SWIGLU_FWD / EPI_ROWPAR (launch_gemm decides when)
 hipError_t launch_gemm_stream(const GemmParams& p, int epilogue, int n_cu, hipStream_t s);
 

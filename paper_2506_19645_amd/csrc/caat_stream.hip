@@ -193,6 +193,47 @@ hipError_t launch_partial_sync_shared_from(const bf16_t* src, bf16_t* dst, int T
 }
 
 // ---------------------------------------------------------------------------------------------------------
+// Shared channels summed over groups of ranks by the GEMM (fp32, [groups][M][N]): the groups in ascending order, one rounding
+// to bf16, then each output copy with its residual -- what the GEMM's broadcast epilogue does with its accumulator.  One
+// thread per 8 columns; the partial sums were just written (plain loads), the residual is read once.
+__global__ __launch_bounds__(256) void shared_merge_kernel(const float* __restrict__ part, int groups, const bf16_t* resid,
+                                                           bf16_t* out, long long M, int N, long long ldr, long long ldo,
+                                                           long long stride_r, long long stride_o, int bcast) {
+  const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
+  const int nvec = N >> 3;
+  if (idx >= M * nvec) return;
+  const long long i = idx / nvec;
+  const int col = (int)(idx - i * nvec) * 8;
+  float sum[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  const float* src = part + i * N + col;
+#pragma unroll 4
+  for (int g = 0; g < groups; ++g) {
+    const float4 a = *reinterpret_cast<const float4*>(src + g * (M * N)), b = *reinterpret_cast<const float4*>(src + g * (M * N) + 4);
+    sum[0] += a.x; sum[1] += a.y; sum[2] += a.z; sum[3] += a.w;
+    sum[4] += b.x; sum[5] += b.y; sum[6] += b.z; sum[7] += b.w;
+  }
+  float v[8];
+  unpack8(pack8(sum), v);
+#pragma unroll 4
+  for (int m = 0; m < bcast; ++m) {
+    float r[8], o[8];
+    unpack8(ld_stream(resid + m * stride_r + i * ldr + col), r);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = v[e] + r[e];
+    *reinterpret_cast<uint4*>(out + m * stride_o + i * ldo + col) = pack8(o);
+  }
+}
+
+hipError_t launch_shared_merge(const float* part, int groups, const bf16_t* resid, bf16_t* out, long long M, int N, long long ldr,
+                               long long ldo, long long stride_r, long long stride_o, int bcast, hipStream_t s) {
+  const long long blocks = (M * (N / 8) + 255) / 256;
+  if (N % 8 != 0 || blocks <= 0 || blocks > 0x7FFFFFFFLL) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(shared_merge_kernel, dim3((unsigned)blocks), dim3(256), 0, s, part, groups, resid, out, M, N, ldr, ldo,
+                     stride_r, stride_o, bcast);
+  return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------------------------------------
 // Norm forward: one wavefront per row, the row stays in registers (VPL 16-byte vectors per lane), statistics
 // by wave reduction in fp32 (two passes over registers: mean, then centred second moment).
 // Split source (xs != null): the first hs_split channels of every rank's row are stored once, xs [tokens, hs_split]

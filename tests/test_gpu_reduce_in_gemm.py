@@ -24,6 +24,8 @@ pytestmark = pytest.mark.gpu
     (2, 129, 256, 1024, 1.0, 1.0),              # p = 1: only the shared GEMM runs
     (2, 129, 256, 1024, 0.0, 1.0),              # p = 0: only the private GEMM runs
     (8, 300, 1024, 8 * 136, 0.5, 1.0),          # T = 8, 136 columns per rank (4 stages + tail of 8)
+    (6, 200, 784, 6 * 1032, 0.5, 1.0),          # long contractions, few tiles: sums over groups of ranks, two groups of three
+    (8, 131, 1568, 8 * 1032, 0.25, 1.0),        # ... and groups of a single rank, a ragged last tile in both directions
 ])
 def test_mlp_block_reduce_in_gemm(swi, T, n, h, ffn, p, scale):
     cfg = mlp_cfg(swi, T, n, h, ffn, p, scale)
@@ -68,6 +70,19 @@ def test_prefill_layer_reduce_in_gemm():
         assert np.array_equal(got["R2_bits"][m, :, :hs_of(cfg)], got["R2_bits"][0, :, :hs_of(cfg)])
 
 
+def test_prefill_layer_reduce_over_groups_of_ranks():
+    """A prompt whose shared GEMM is cut into groups of ranks (both projections need scratch for their fp32 sums)."""
+    from paper_2506_19645_amd import binding as B
+    cfg = pre_cfg(4, 1, 130, 8, 4 * 1032, 0.5)
+    assert B.workspace_layout(B.make_desc(cfg, reduce_in_gemm=True)).bytes_scratch > 0
+    d = make_inputs(cfg, seed=57, weight_std=0.05)
+    got = run_prefill(cfg, d, reduce_in_gemm=True)
+    w, ref = oracle_prefill(cfg, d)
+    check_prefill(cfg, d, got, ref)
+    for m in range(1, cfg.T):
+        assert np.array_equal(got["R2_bits"][m, :, :hs_of(cfg)], got["R2_bits"][0, :, :hs_of(cfg)])
+
+
 # ---------------------------------------------------------------------------------------------------------
 # De-duplicated residual stream: the shared channels are stored once ([n, hs]) instead of T identical copies.
 def _run_mlp_dedup(cfg, d):
@@ -92,6 +107,7 @@ def _run_mlp_dedup(cfg, d):
     (False, 2, 129, 256, 1024, 0.5),
     (True, 4, 515, 512, 4 * 520, 0.25),
     (True, 3, 300, 256, 3 * 344, 1.0),      # everything shared: the private block is empty
+    (True, 8, 131, 1568, 8 * 1032, 0.25),   # sums over groups of ranks
     (False, 2, 200, 256, 1024, 0.0),        # nothing shared: the layout is the ordinary one
 ])
 def test_mlp_block_dedup_shared_layout(swi, T, n, h, ffn, p):
