@@ -97,7 +97,9 @@ def test_partial_sync_empty():
 # ------------------------------------------------------------------------------------------ fused reduce + norm
 @pytest.mark.parametrize("layernorm", [False, True])
 @pytest.mark.parametrize("T,n,h,hs", [(2, 37, 40, 8), (4, 9, 2048, 1024), (8, 5, 4096, 2048), (8, 3, 8192, 4096),
-                                        (16, 6, 4096, 2048), (16, 4, 264, 264), (4, 3, 520, 512)])
+                                        (16, 6, 4096, 2048), (16, 4, 264, 264), (4, 3, 520, 512),
+                                        # a thread per column group up to 256 tokens: past 512 and 1024 threads' columns
+                                        (4, 3, 2056, 1032), (2, 5, 4104, 3000), (4, 2, 8184, 8184), (2, 257, 2056, 1024)])
 def test_partial_sync_norm_fwd_integer_bit_exact(layernorm, T, n, h, hs):
     """The one-launch reduce + residual + norm: with small-integer partial sums and residuals every sum is exact, so
     the shared channels of R' must carry exactly the oracle's bits on every rank and the private channels must keep
@@ -146,7 +148,8 @@ def test_partial_sync_norm_fwd_shapes_not_taken():
 
 # ------------------------------------------------------------------------------------------ norms
 @pytest.mark.parametrize("layernorm", [True, False])
-@pytest.mark.parametrize("T,n,h", [(2, 33, 64), (2, 256, 768), (3, 70, 520), (4, 65, 2048), (2, 40, 4096), (1, 9, 8192)])
+@pytest.mark.parametrize("T,n,h", [(2, 33, 64), (2, 256, 768), (3, 70, 520), (4, 65, 2048), (2, 40, 4096), (1, 9, 8192),
+                                   (3, 70, 1032), (4, 256, 2056), (1, 1025, 2056), (2, 4, 4104)])
 def test_norm_fwd_bwd(layernorm, T, n, h):
     torch = _torch()
     kind = O.LAYERNORM if layernorm else O.RMSNORM

@@ -108,6 +108,7 @@ def _run_mlp_dedup(cfg, d):
     (True, 4, 515, 512, 4 * 520, 0.25),
     (True, 3, 300, 256, 3 * 344, 1.0),      # everything shared: the private block is empty
     (True, 8, 131, 1568, 8 * 1032, 0.25),   # sums over groups of ranks
+    (True, 4, 131, 2048, 4 * 264, 0.25),    # a workgroup per row in the norm
     (False, 2, 200, 256, 1024, 0.0),        # nothing shared: the layout is the ordinary one
 ])
 def test_mlp_block_dedup_shared_layout(swi, T, n, h, ffn, p):
