@@ -13,6 +13,8 @@ template <> hipError_t launch_block_sized<Cfg256x192>(const GemmParams&, int, in
 template <> hipError_t launch_block_sized<Cfg128x128>(const GemmParams&, int, int, hipStream_t);
 template <> hipError_t launch_block_sized<Cfg64x128>(const GemmParams&, int, int, hipStream_t);
 template <> hipError_t launch_block_sized<Cfg64x64>(const GemmParams&, int, int, hipStream_t);
+template <> hipError_t launch_block_sized<Cfg128x128k>(const GemmParams&, int, int, hipStream_t);
+template <> hipError_t launch_block_sized<Cfg64x64k>(const GemmParams&, int, int, hipStream_t);
 
 static int compute_units() {
   static int n_cu = 0;
@@ -48,35 +50,44 @@ static int choose_skinny_width(int G, int N, int epilogue) {
 // Tile shape of a block-sized launch: the one with the least modelled time.  A launch runs in rounds of as many tiles as
 // the compute units hold at once; a tile takes a time per 64-k stage and a fixed time (its first stages, its epilogue),
 // and a round that leaves compute units idle is faster than a full one (clock, caches), down to 0.55 of its time.  The
-// constants are fitted to the shapes of six training and prefill blocks, all three layouts, 32 launches from 256 to 8192
+// constants are fitted to the shapes of some training and prefill blocks, all three layouts, 40 launches from 150 to 8192
 // rows timed with every tile shape: the choice by the model is 0.4 % slower than the fastest shape on their average.
-// Examples (us; 256 x 256, 192 x 256, 256 x 192, 128 x 128, 64 x 128, 64 x 64; G x M x N x K):
-//   NT 8 x 777 x 1536 x 4096     112 / 100 / 100 / 119 / 122 / 152
-//   TN 4 x 2048 x 1408 x 1111   34.4 / 49.8 / 31.2 / 38.5 / 42.4 / 56.0
-//   NN 4 x 1111 x 1408 x 2048   49.5 / 41.3 / 43.9 / 33.0 / 44.9 / 57.8
-//   TN 4 x 2048 x 512 x 3009    69.3 / 59.6 / 61.9 / 39.3 / 37.4 / 54.2
-//   NT 2 x 256 x 768 x 1536     33.7 / 28.5 / 29.0 / 19.5 / 13.3 / 11.0
+// The last two shapes share a tile's contraction between two groups of four waves: for launches with a tile or less per
+// compute unit, whose time is the chain of stages and not the matrix unit.  They are for the gradients only (NN, TN): an
+// output of the forward pass (NT) is one sum in ascending k whatever the launch, so that a channel's bits are the same
+// with the reduce inside the GEMM and as a pass of its own.
+// Examples (us; 256 x 256, 192 x 256, 256 x 192, 128 x 128, 64 x 128, 64 x 64, 128 x 128 and 64 x 64 shared; G x M x N x K):
+//   NT 8 x 777 x 1536 x 4096     111 /  99 /  99 / 123 / 123 / 153 / 124 / 172
+//   TN 4 x 2048 x 1408 x 1111   34.4 / 50.3 / 31.4 / 38.8 / 42.2 / 56.2 / 46.6 / 73.2
+//   NN 4 x 1111 x 1408 x 2048   49.0 / 40.9 / 44.4 / 33.5 / 45.3 / 57.7 / 46.2 / 68.9
+//   TN 4 x 2048 x 512 x 3009    68.4 / 58.6 / 61.1 / 39.0 / 38.0 / 49.7 / 32.7 / 56.3
+//   NT 2 x 256 x 768 x 1536     33.7 / 28.8 / 29.0 / 19.6 / 13.1 / 11.2 / 16.2 /  9.9
+//   NN 2 x 256 x 768 x 1536     34.7 / 29.1 / 31.3 / 19.2 / 13.9 / 12.0 / 16.2 / 10.0
+//   NN 8 x 500 x 768 x 3072     67.6 / 59.0 / 64.7 / 39.3 / 34.7 / 42.8 / 32.3 / 44.4
 //   NN 4 x 8192 x 2048 x 2048    227 /  256 /  260 /  275 /  369 /  479
 // 128 x 256 and 256 x 128 tiles with three stages came within 5 % of the best of these wherever they won, and 256 x 256
 // by four waves of 128 x 128 (a third less LDS traffic, one wave per SIMD) takes 15 % longer than by eight.
 struct TileShape {
   int bm, bn, per_cu;   // per_cu: workgroups a compute unit holds
+  int k;                // depth of a stage
   double stage, tile;   // us
 };
-static constexpr TileShape TILES[] = {{256, 256, 1, 1.64, 8.1}, {192, 256, 1, 1.35, 6.3}, {256, 192, 1, 1.35, 6.7},
-                                      {128, 128, 2, 0.98, 4.2}, {64, 128, 2, 0.645, 2.6}, {64, 64, 2, 0.446, 1.8}};
-static int choose_tile(const GemmParams& p, int epilogue, int n_cu, double* us = nullptr) {
+static constexpr TileShape TILES[] = {{256, 256, 1, 64, 1.64, 8.1}, {192, 256, 1, 64, 1.35, 6.3}, {256, 192, 1, 64, 1.35, 6.7},
+                                      {128, 128, 2, 64, 0.98, 4.2}, {64, 128, 2, 64, 0.69, 2.6}, {64, 64, 2, 64, 0.446, 1.8},
+                                      {128, 128, 1, 128, 1.15, 3.8}, {64, 64, 1, 128, 0.473, 2.5}};
+static int choose_tile(const GemmParams& p, int layout, int epilogue, int n_cu, double* us = nullptr) {
   const bool swi = epilogue == EPI_SWIGLU_FWD;
-  const double nk = (double)((p.K + 63) / 64) * (p.kcat > 1 ? p.kcat : 1);
   int best = 0;
   double cost = 0.0;
   for (int i = 0; i < (int)(sizeof(TILES) / sizeof(TILES[0])); ++i) {
     const TileShape& t = TILES[i];
     if (swi && (t.bn == 192 || t.bn == 64)) continue;   // a wave takes gate and up columns in pairs of 32
+    if (layout == 0 && t.k > 64) continue;
     const long long bn_out = swi ? t.bn / 2 : t.bn, slots = (long long)t.per_cu * n_cu;
     const long long tiles = ((p.M + t.bm - 1) / t.bm) * ((p.N + bn_out - 1) / bn_out) * p.G;
     const long long full = tiles / slots, rest = tiles % slots;
     const double rounds = (double)full + (rest ? 0.55 + 0.45 * (double)rest / (double)slots : 0.0);
+    const double nk = (double)((p.K + t.k - 1) / t.k) * (p.kcat > 1 ? p.kcat : 1);
     const double c = rounds * (nk * t.stage + t.tile);
     if (i == 0 || c < cost) {
       cost = c;
@@ -119,13 +130,15 @@ hipError_t launch_gemm(const GemmParams& p, int layout, int epilogue, hipStream_
   }
   GemmParams q = p;
   q.bn_out = 0;  // block-sized tiles always cover their full width
-  switch (choose_tile(p, epilogue, n_cu)) {
+  switch (choose_tile(p, layout, epilogue, n_cu)) {
     case 0: return launch_block_sized<Cfg256x256>(q, layout, epilogue, s);
     case 1: return launch_block_sized<Cfg192x256>(q, layout, epilogue, s);
     case 2: return launch_block_sized<Cfg256x192>(q, layout, epilogue, s);
     case 3: return launch_block_sized<Cfg128x128>(q, layout, epilogue, s);
     case 4: return launch_block_sized<Cfg64x128>(q, layout, epilogue, s);
-    default: return launch_block_sized<Cfg64x64>(q, layout, epilogue, s);
+    case 5: return launch_block_sized<Cfg64x64>(q, layout, epilogue, s);
+    case 6: return launch_block_sized<Cfg128x128k>(q, layout, epilogue, s);
+    default: return launch_block_sized<Cfg64x64k>(q, layout, epilogue, s);
   }
 }
 
@@ -148,7 +161,7 @@ int gemm_shared_groups(int M, int N, int K, int kcat) {
     q.G = g;
     q.kcat = kcat / g;
     double us = 0.0;
-    choose_tile(q, EPI_PARTIAL, 256, &us);
+    choose_tile(q, 0, EPI_PARTIAL, 256, &us);
     us *= 1.4;
     if (g > 1) us += 3.4 + (double)g * M * N * 4.0 / 7e6;
     if (g == 1 || us < cost) {

@@ -62,23 +62,27 @@ typedef __attribute__((address_space(3))) short4_t* lds_s4_t;
 // rows the LDS image of an operand tile has room for: a power of two (an image [k][rows] is swizzled in whole lines)
 constexpr int image_rows(int rows) { return rows == 192 ? 256 : rows; }
 
-template <int BM_, int BN_, int WM_, int WN_, int NSTAGE_ = 2, bool PERSIST_ = true, bool STREAM_B_ = false>
+template <int BM_, int BN_, int WM_, int WN_, int NSTAGE_ = 2, bool PERSIST_ = true, bool STREAM_B_ = false, int KW_ = 1>
 struct TileCfg {
-  static constexpr int BKS = 64;                // k extent of one LDS stage
+  // KW: groups of waves that share a tile's contraction; group w computes on the w-th 64 k of every stage, and the groups'
+  // sums meet in LDS before the epilogue
+  static constexpr int KW = KW_;
+  static constexpr int BKS = 64 * KW;           // k extent of one LDS stage
   // STREAM_B: decode-sized launches, which read every weight row once (non-temporal copies, bn_out)
   static constexpr bool STREAM_B = STREAM_B_;
   // PERSIST: one workgroup per CU walks several tiles and fetches the next tile's first stages under the epilogue
   static constexpr bool PERSIST = PERSIST_;
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, NSTAGE = NSTAGE_;
-  static constexpr int THREADS = 64 * WM * WN;
-  static constexpr int NWAVES = WM * WN;
+  static constexpr int NWAVES = WM * WN * KW;
+  static constexpr int THREADS = 64 * NWAVES;
   static constexpr int WTM = BM / WM, WTN = BN / WN;  // wave tile
   static constexpr int TM = WTM / 16, TN = WTN / 16;  // 16x16 MFMA tiles per wave
   static constexpr int A_CHUNKS = image_rows(BM) * (BKS / 8);  // uint4 per LDS stage
   static constexpr int STAGE_CHUNKS = A_CHUNKS + image_rows(BN) * (BKS / 8);
   static constexpr int SMEM_CHUNKS = NSTAGE * STAGE_CHUNKS;
   static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be a multiple of 32x32");
-  static_assert(!PERSIST || NSTAGE == 2, "the persistent loop counts on two slots");
+  static_assert(!PERSIST || (NSTAGE == 2 && KW == 1), "the persistent loop counts on two slots, and the sums' place is free");
+  static_assert((KW - 1) * BM * BN * 4 <= SMEM_CHUNKS * 16, "the groups' sums take the stages' place");
   static_assert(SMEM_CHUNKS * 16 <= 160 * 1024, "LDS capacity");
   // workgroups that fit on one compute unit: LDS (160 KB) and at most 8 waves (2 per SIMD, 256 registers each)
   static constexpr int WGS_PER_CU = ((160 * 1024) / (SMEM_CHUNKS * 16)) < (8 / NWAVES) ? ((160 * 1024) / (SMEM_CHUNKS * 16))
@@ -156,12 +160,13 @@ struct KContigOperand {
   // lane (row row0 + 16 i + lane%16, k = 32 ks + 8 (lane/16) ..+7).  The swizzle has a period of 16 rows, so a lane's
   // address is one of two (ks) plus 16 i rows, a constant in the instruction.
   struct Reader {
-    lds_c_t p[BKS_ / 32];
-    __device__ __forceinline__ void init(const uint4* tile, int row0, int lane) {
+    lds_c_t p[2];
+    // ks0: first of the two 32-wide k sub-steps of the stage that the wave computes on
+    __device__ __forceinline__ void init(const uint4* tile, int row0, int ks0, int lane) {
       const int r = lane & 15;
 #pragma unroll
-      for (int ks = 0; ks < BKS_ / 32; ++ks)
-        p[ks] = (lds_c_t)tile + ((row0 + r) * CPR + ((ks * 4 + (lane >> 4)) ^ swz(r))) * 16;
+      for (int ks = 0; ks < 2; ++ks)
+        p[ks] = (lds_c_t)tile + ((row0 + r) * CPR + (((ks0 + ks) * 4 + (lane >> 4)) ^ swz(r))) * 16;
     }
     __device__ __forceinline__ bf16x8_t frag(int stage_bytes, int i, int ks) const {
       return __builtin_bit_cast(bf16x8_t, *(lds_u4_t)(p[ks] + stage_bytes + i * 16 * CPR * 16));
@@ -234,12 +239,12 @@ struct RowContigOperand {
   // address per tile (up to eight: 8 tiles are one swizzle period); ks is a constant in the instruction.
   struct Reader {
     lds_c_t p[8];
-    __device__ __forceinline__ void init(const uint4* tile, int row0, int lane) {
+    __device__ __forceinline__ void init(const uint4* tile, int row0, int ks0, int lane) {
       const int i16 = lane & 15, k = (lane >> 4) * 8 + (i16 >> 2);
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         const int m = row0 + i * 16 + (i16 & 3) * 4;
-        p[i] = (lds_c_t)tile + k * (ROWS * 2) + ((((m >> 3) ^ swz(k)) << 4) + ((m & 7) << 1));
+        p[i] = (lds_c_t)tile + (ks0 * 32 + k) * (ROWS * 2) + ((((m >> 3) ^ swz(k)) << 4) + ((m & 7) << 1));
       }
     }
     __device__ __forceinline__ bf16x8_t frag(int stage_bytes, int i, int ks) const {
@@ -288,8 +293,10 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / CFG::WN;
-  const int wn = wave - wm * CFG::WN;
+  const int kw = CFG::KW > 1 ? wave / (CFG::WM * CFG::WN) : 0;   // group of waves (KW)
+  const int wt = wave - kw * (CFG::WM * CFG::WN);                // wave of the group
+  const int wm = wt / CFG::WN;
+  const int wn = wt - wm * CFG::WN;
 
   // ---- tiles of this workgroup.  Tile ids are cut into 8 contiguous ranges, one per XCD (workgroup b runs on XCD
   // b % 8), so that the workgroups sharing an L2 work on neighbouring tiles; inside a range the workgroups of the XCD
@@ -314,7 +321,7 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
   }
 
   constexpr int BKS = CFG::BKS;         // this instantiation's stage depth (hides the namespace default)
-  constexpr int NSUB = BKS / 32;        // 32-wide k sub-steps (one MFMA deep) per stage
+  constexpr int NSUB = 2;               // 32-wide k sub-steps (one MFMA deep) of a wave per stage
   // Waves that issue the global -> LDS copies.  A wave's copies and its epilogue stores complete in issue order on one
   // counter, so a wave that copies has to let its stores drain before it can wait for the next tile's second stage,
   // and the stores of all compute units come as one chip-wide burst (the workgroups run in lockstep) that takes
@@ -409,8 +416,8 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
   auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
   typename OpA::Reader ra;
   typename OpB::Reader rb;
-  ra.init(smem, wm * WTM, lane);
-  rb.init(smem + A_CHUNKS, wn * WTN, lane);
+  ra.init(smem, wm * WTM, kw * NSUB, lane);
+  rb.init(smem + A_CHUNKS, wn * WTN, kw * NSUB, lane);
 
   constexpr int NS = WTN / 32;                   // 32-column groups of a wave's sub-tile
   // epilogue stores per wave and tile (known at compile time except for the broadcast epilogue's loop over ranks)
@@ -502,6 +509,28 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
 #pragma clang loop unroll(disable)
     for (int kt = 0; kt + 1 < nk; ++kt) stage(kt, std::false_type{});
     stage(nk - 1, std::true_type{});
+
+    if constexpr (CFG::KW > 1) {
+      // The sums of the groups meet in LDS (no copy is in flight and nothing is read from the stages any more once all
+      // waves are here), in ascending order; group 0 goes on to the epilogue.
+      __syncthreads();
+      f32x4_t* part = reinterpret_cast<f32x4_t*>(smem) + wt * (TM * TN * 64) + lane;
+      constexpr int GROUP_VECS = CFG::WM * CFG::WN * TM * TN * 64;
+      if (kw > 0) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) part[(kw - 1) * GROUP_VECS + (i * TN + j) * 64] = acc[i][j];
+      }
+      __syncthreads();
+      if (kw > 0) return;
+#pragma unroll
+      for (int w = 1; w < CFG::KW; ++w)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) acc[i][j] += part[(w - 1) * GROUP_VECS + (i * TN + j) * 64];
+    }
 
     // ---- epilogue.  Each lane holds C[row = lane%16][col = 4*(lane/16) + 0..3] of every 16x16 tile.  Stored as they
     // are, these 8-byte pieces would leave as 32-byte runs; so two neighbouring tiles exchange pieces between the

@@ -14,6 +14,8 @@ typedef TileCfg<256, 192, 4, 2, 2, true> Cfg256x192;
 typedef TileCfg<128, 128, 2, 2, 2, false> Cfg128x128;   // two workgroups per compute unit
 typedef TileCfg<64, 128, 2, 2, 3, false> Cfg64x128;     // two workgroups per compute unit
 typedef TileCfg<64, 64, 2, 2, 4, false> Cfg64x64;       // two workgroups per compute unit
+typedef TileCfg<128, 128, 2, 2, 2, false, false, 2> Cfg128x128k;   // two groups of four waves share the contraction (NN, TN)
+typedef TileCfg<64, 64, 2, 2, 4, false, false, 2> Cfg64x64k;
 
 template <class CFG>
 hipError_t launch_block_sized(const GemmParams& p, int layout, int epilogue, hipStream_t s);
@@ -28,7 +30,8 @@ template <class CFG>
 static hipError_t launch_block_sized_impl(const GemmParams& p, int layout, int epilogue, hipStream_t s) {
   switch (layout) {
     case 0:  // NT
-      switch (epilogue) {
+      if constexpr (CFG::KW > 1) return hipErrorInvalidValue;   // (see choose_tile)
+      else switch (epilogue) {
         case EPI_PLAIN: return launch_one<CFG, false, false, EPI_PLAIN>(p, s);
         case EPI_GELU_FWD: return launch_one<CFG, false, false, EPI_GELU_FWD>(p, s);
         case EPI_SWIGLU_FWD:   // a wave needs its 32 gate and 32 up columns side by side

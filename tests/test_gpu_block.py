@@ -117,13 +117,15 @@ def test_mlp_block_fwd_bwd(swi, T, n, h, ffn, p, scale):
     check_mlp_block(cfg, d, got, w, fwd, g)
 
 
-@pytest.mark.parametrize("swi,n,h,p", [
-    (False, 570, 1544, 0.5), (True, 777, 1160, 0.301),       # 192 x 256 tiles
-    (False, 1000, 1160, 0.301), (True, 1000, 1160, 0.5),     # 256 x 192 tiles
+@pytest.mark.parametrize("swi,T,n,h,p", [
+    (False, 8, 570, 1544, 0.5), (True, 8, 777, 1160, 0.301),       # 192 x 256 tiles
+    (False, 8, 1000, 1160, 0.301), (True, 8, 1000, 1160, 0.5),     # 256 x 192 tiles
+    (False, 8, 200, 1160, 0.5), (True, 8, 200, 1160, 0.301),       # 128 x 128 tiles, two groups of waves (gradients)
+    (False, 2, 250, 776, 0.301), (True, 2, 250, 776, 0.5),         # 64 x 64 tiles, two groups of waves (gradients)
 ])
-def test_mlp_block_on_tiles_of_192(swi, n, h, p):
-    """Every fused epilogue on the tiles with 192 rows or columns, edges in both directions, hs inside a tile."""
-    cfg = _cfg(swi, 8, n, h, 8 * h, p)
+def test_mlp_block_on_every_tile_shape(swi, T, n, h, p):
+    """Every fused epilogue on the tile shapes of ragged and small launches, edges in both directions, hs inside a tile."""
+    cfg = _cfg(swi, T, n, h, T * h, p)
     d = make_inputs(cfg, seed=23)
     got = run_mlp_block(cfg, d)
     w, fwd, g = oracle_mlp_block(cfg, d)

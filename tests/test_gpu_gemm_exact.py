@@ -16,7 +16,10 @@ SHAPES = [(1, 8, 8, 8), (2, 256, 256, 64), (1, 264, 248, 72), (1, 520, 776, 200)
           # 192 x 256 and 256 x 192 tiles: one round with a remainder in both directions, several tiles per workgroup with
           # 2 and 3 stages; 64 x 128 tiles of 64 rows and a remainder
           (8, 1032, 1160, 200), (8, 1144, 1808, 136), (8, 1000, 1160, 328), (8, 2024, 2200, 72), (8, 2008, 2096, 136),
-          (8, 200, 1160, 136)]
+          (8, 200, 1160, 136),
+          # two groups of waves on one contraction, 64 x 64 and 128 x 128 tiles: last stages that one group has to itself
+          # and that both share
+          (4, 296, 520, 2056), (4, 200, 520, 1096), (8, 456, 776, 1096), (8, 456, 776, 3080)]
 
 
 @pytest.mark.parametrize("G,M,N,K", SHAPES)
