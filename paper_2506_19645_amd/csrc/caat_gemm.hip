@@ -84,10 +84,10 @@ static int choose_tile(const GemmParams& p, int layout, int epilogue, int n_cu, 
     if (swi && (t.bn == 192 || t.bn == 64)) continue;   // a wave takes gate and up columns in pairs of 32
     if (layout == 0 && t.k > 64) continue;
     const long long bn_out = swi ? t.bn / 2 : t.bn, slots = (long long)t.per_cu * n_cu;
-    const long long tiles = ((p.M + t.bm - 1) / t.bm) * ((p.N + bn_out - 1) / bn_out) * p.G;
+    const long long tiles = (((long long)p.M + t.bm - 1) / t.bm) * ((p.N + bn_out - 1) / bn_out) * p.G;
     const long long full = tiles / slots, rest = tiles % slots;
     const double rounds = (double)full + (rest ? 0.55 + 0.45 * (double)rest / (double)slots : 0.0);
-    const double nk = (double)((p.K + t.k - 1) / t.k) * (p.kcat > 1 ? p.kcat : 1);
+    const double nk = (double)(((long long)p.K + t.k - 1) / t.k) * (p.kcat > 1 ? p.kcat : 1);
     const double c = rounds * (nk * t.stage + t.tile);
     if (i == 0 || c < cost) {
       cost = c;

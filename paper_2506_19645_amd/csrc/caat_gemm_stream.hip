@@ -51,9 +51,10 @@ static hipError_t stream_swiglu(const GemmParams& p, int mt, int rt, hipStream_t
 hipError_t launch_gemm_stream(const GemmParams& p, int epilogue, int n_cu, hipStream_t s) {
   const bool swi = epilogue == EPI_SWIGLU_FWD;
   const int m16 = (p.M + 15) / 16, tiles_m = (m16 + 3) / 4, mt = (m16 + tiles_m - 1) / tiles_m;
-  // a wave should have more than one chunk of k: with fewer than 12 chunks of 64 two waves share a workgroup's contraction
-  // (K = 512, 1 token row, 33 MB: 8.4 us with two waves, 10.4 with four)
-  const bool short_k = (p.K + 63) / 64 < 12;
+  // a wave should have some chunks of k: with fewer than 18 chunks of 64 two waves share a workgroup's contraction (us, two
+  // waves / four: K = 512, 1 token row, 33 MB 8.4 / 10.4; K = 1024, 16 rows, 134 MB 25.0 / 26.9; K = 1376, 1 row, 90 MB
+  // 21.5 / 19.0)
+  const bool short_k = (p.K + 63) / 64 < 18;
   // A launch takes as long as the compute unit with the most rows to read: the weight rows of a tile plus its token
   // rows (from L2, at about a third of the cost), times the tiles a compute unit gets.
   static const int plain_rt[4][4] = {{2, 3, 4, 0}, {2, 3, 4, 0}, {2, 3, 6, 0}, {2, 3, 4, 6}};

@@ -226,6 +226,10 @@ bool sync_norm_takes(int T, long long tokens, int h, int hs);
 hipError_t launch_sync_norm(bf16_t* io, const bf16_t* resid, const bf16_t* gamma, const bf16_t* beta, bf16_t* xout,
                             float* mean, float* rstd, int norm, int T, long long tokens, int h, int hs, float eps,
                             hipStream_t s);
+// the same for a few tokens, RMSNorm, from a buffer of its own into R' and xout (sync_norm_rank_takes)
+bool sync_norm_rank_takes(int T, long long tokens, int h, int hs);
+hipError_t launch_sync_norm_rank(const bf16_t* part, const bf16_t* resid, const bf16_t* gamma, bf16_t* out, bf16_t* xout,
+                                 float* rstd, int T, long long tokens, int h, int hs, float eps, hipStream_t s);
 size_t norm_bwd_workspace_bytes(int T, long long tokens, int h);
 hipError_t launch_norm_bwd(const bf16_t* dy, const bf16_t* dres, const bf16_t* x, const bf16_t* gamma,
                            const float* mean, const float* rstd, bf16_t* g_out, bf16_t* g_scaled, float* dgamma,

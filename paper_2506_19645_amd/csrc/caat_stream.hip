@@ -314,7 +314,7 @@ __global__ __launch_bounds__(256) void norm_fwd_kernel(const bf16_t* __restrict_
 // The same for a few rows (decode steps, short prompts): a workgroup per row, a thread per 16-byte vector, so that a row is
 // one trip to memory and the rows spread over the chip.  What bounds it is that trip and the launch, not bytes; gamma and
 // beta are fetched with the row and not behind its statistics.  Wave per row / workgroup per row, RMSNorm: 512 rows of 4096
-// 7.3 / 5.6 us, 128 rows of 8192 9.4 / 5.2, 8 rows of 4096 4.1 / 4.6.
+// 7.3 / 5.6 us, 128 rows of 8192 9.4 / 5.2, 8 rows of 4096 4.1 - 4.8 / 4.6.
 template <int NG, bool LN>
 __global__ __launch_bounds__(256) void norm_fwd_row_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ gamma,
                                                            const bf16_t* __restrict__ beta, bf16_t* __restrict__ y,
@@ -392,9 +392,8 @@ __global__ __launch_bounds__(256) void norm_fwd_row_kernel(const bf16_t* __restr
   }
 }
 
-// rows for which a workgroup takes one row: up to four per compute unit, which all run at once, from one row per 32 compute
-// units on (fewer are a single trip to memory either way, and a wave needs no barrier for its statistics)
-static constexpr long long NORM_ROW_MIN = 9, NORM_ROW_MAX = 1024;
+// rows up to which a workgroup takes one row: four per compute unit, which all run at once
+static constexpr long long NORM_ROW_MAX = 1024;
 
 template <int VPL>
 static hipError_t norm_fwd_dispatch(const bf16_t* x, const bf16_t* gamma, const bf16_t* beta, bf16_t* y, float* mean,
@@ -430,7 +429,7 @@ hipError_t launch_norm_fwd(const bf16_t* x, const bf16_t* gamma, const bf16_t* b
     xs = x;
     x = x + tokens * dedup_hs;
   }
-  if (rows >= NORM_ROW_MIN && rows <= NORM_ROW_MAX && h > 1024 && h <= 8192) {
+  if (rows > 0 && rows <= NORM_ROW_MAX && h > 1024 && h <= 8192) {
 #define CAAT_NORM_ROW(NG_) \
   if (norm == 0) hipLaunchKernelGGL((norm_fwd_row_kernel<NG_, true>), dim3((unsigned)rows), dim3(256), 0, s, x, gamma, beta, y, mean, rstd, h, eps, xs, dedup_hs, tokens); \
   else hipLaunchKernelGGL((norm_fwd_row_kernel<NG_, false>), dim3((unsigned)rows), dim3(256), 0, s, x, gamma, beta, y, mean, rstd, h, eps, xs, dedup_hs, tokens)
@@ -676,6 +675,111 @@ hipError_t launch_sync_norm(bf16_t* io, const bf16_t* resid, const bf16_t* gamma
 #undef CAAT_SN_WIDE
 #undef CAAT_SN_T
 #undef CAAT_SN
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// Reduce + residual + RMSNorm of a decode step, not in place: a workgroup per (token, rank).  With one workgroup per token
+// a step of 16 tokens pulls 450 KB through each of 16 compute units, and that is what bounds it; here every workgroup reads the T partial vectors of
+// the shared channels itself (from L2, T times in all) and otherwise only its own rank's row.  Sums and roundings as in
+// sync_norm_kernel.  T = 8 (us, workgroup per token / per token and rank): 1 token of 4096 7.0 / 4.6, 16 of 8192 9.0 / 5.6,
+// 64 of 4096 9.2 / 7.6.
+template <int TT, int NG>
+__global__ __launch_bounds__(256) void sync_norm_rank_kernel(const bf16_t* __restrict__ part, const bf16_t* __restrict__ resid,
+                                                             const bf16_t* __restrict__ gamma, bf16_t* __restrict__ out,
+                                                             bf16_t* __restrict__ xout, float* __restrict__ rstd, long long n,
+                                                             int h, int hs, float eps) {
+  __shared__ float red[4];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const long long i = blockIdx.x / TT;                   // token
+  const int m = (int)(blockIdx.x - i * TT);              // rank
+  const long long plane = n * (long long)h;
+  const int nvec = h >> 3;
+  uint4 pv[NG][TT], rv[NG], gw[NG];
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+    const int vi = g * 256 + tid;
+    rv[g] = gw[g] = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+    for (int k = 0; k < TT; ++k) pv[g][k] = make_uint4(0u, 0u, 0u, 0u);
+    if (vi < nvec) {
+      const long long off = i * h + vi * 8;
+      gw[g] = *reinterpret_cast<const uint4*>(gamma + vi * 8);
+      if (vi * 8 < hs) {
+#pragma unroll
+        for (int k = 0; k < TT; ++k) pv[g][k] = *reinterpret_cast<const uint4*>(part + k * plane + off);
+        rv[g] = *reinterpret_cast<const uint4*>(resid + m * plane + off);
+      } else {
+        rv[g] = *reinterpret_cast<const uint4*>(part + m * plane + off);   // private: final since the GEMM epilogue
+      }
+    }
+  }
+  float ss = 0.0f;
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+    const int vi = g * 256 + tid;
+    if (vi * 8 < hs) {                                   // hs is a multiple of 8 and at most h
+      float sum[8] = {0, 0, 0, 0, 0, 0, 0, 0}, r[8];
+#pragma unroll
+      for (int k = 0; k < TT; ++k) {
+        float f[8];
+        unpack8(pv[g][k], f);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) sum[e] += f[e];
+      }
+      unpack8(rv[g], r);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) sum[e] += r[e];
+      rv[g] = pack8(sum);
+    }
+    float f[8];
+    unpack8(rv[g], f);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ss += f[e] * f[e];
+  }
+  ss = wave_sum(ss);
+  if (lane == 0) red[wave] = ss;
+  __syncthreads();
+  const float rs = rsqrtf((((red[0] + red[1]) + red[2]) + red[3]) * (1.0f / (float)h) + eps);
+  if (tid == 0) rstd[m * n + i] = rs;
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+    const int vi = g * 256 + tid;
+    if (vi < nvec) {
+      const long long off = m * plane + i * h + vi * 8;
+      float f[8], gm[8], o[8];
+      unpack8(rv[g], f);
+      unpack8(gw[g], gm);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) o[e] = f[e] * rs * gm[e];
+      *reinterpret_cast<uint4*>(out + off) = rv[g];
+      *reinterpret_cast<uint4*>(xout + off) = pack8(o);
+    }
+  }
+}
+
+// up to four workgroups per compute unit, which all run at once; beyond that the T reads of the partial sums cost more than
+// the spreading gains
+bool sync_norm_rank_takes(int T, long long tokens, int h, int hs) {
+  return sync_norm_takes(T, tokens, h, hs) && (T == 2 || T == 4 || T == 8) && h > 1024 && tokens * T <= 1024;
+}
+
+// part [T,n,h]: partial sums on the shared channels, final values on the private ones; out = R', xout = RMSNorm(R')
+hipError_t launch_sync_norm_rank(const bf16_t* part, const bf16_t* resid, const bf16_t* gamma, bf16_t* out, bf16_t* xout,
+                                 float* rstd, int T, long long tokens, int h, int hs, float eps, hipStream_t s) {
+  if (!sync_norm_rank_takes(T, tokens, h, hs)) return hipErrorInvalidValue;
+#define CAAT_SNR(TT_, NG_) hipLaunchKernelGGL((sync_norm_rank_kernel<TT_, NG_>), dim3((unsigned)(tokens * T)), dim3(256), 0, s, part, resid, gamma, out, xout, rstd, tokens, h, hs, eps)
+#define CAAT_SNR_T(TT_) \
+  if (h <= 2048) CAAT_SNR(TT_, 1); \
+  else if (h <= 4096) CAAT_SNR(TT_, 2); \
+  else CAAT_SNR(TT_, 4)
+  switch (T) {
+    case 2: CAAT_SNR_T(2); break;
+    case 4: CAAT_SNR_T(4); break;
+    default: CAAT_SNR_T(8); break;
+  }
+#undef CAAT_SNR_T
+#undef CAAT_SNR
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------------------------------------

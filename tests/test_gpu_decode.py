@@ -58,6 +58,9 @@ def oracle_decode(cfg, d):
     (4, 7, 4, 4 * 128, 61, 0.5, 0, 2.0),      # private channel scaling sqrt(T) (Sec. 4) in both halves of the layer
     (2, 5, 4, 2 * 256, 40, 0.0, 0, 2.0 ** 0.5),   # the same at p = 0: every channel private and scaled
     (16, 3, 32, 16 * 128, 70, 0.5, 0, 1.0),   # tensor-parallel degree 16 (Sec. 5's largest): 32 heads, 2 per rank
+    (4, 3, 12, 4 * 128, 40, 0.5, 0, 1.0),     # reduce + norm per token and rank: one column group per thread (h = 1536), ...
+    (2, 5, 20, 2 * 256, 30, 0.25, 0, 1.0),    # ... two (2560, the second one ragged), ...
+    (8, 2, 40, 8 * 128, 20, 0.4, 8, 1.0),     # ... and four (5120), hs = 2048
     (16, 2, 32, 16 * 136, 20, 0.3, 0, 4.0),   # T = 16, hs not a multiple of 8 (two-kernel route), scaling sqrt(T)
 ])
 def test_decode_layer(T, b, heads, ffn, L, p, kv_heads, scale):
