@@ -89,7 +89,9 @@ typedef struct caat_desc {
                            pass sums them (the in-HBM stand-in for the tensor-parallel collective).  1: single-device
                            serving with logical ranks (Sec. 3.2, the reduce becomes a local summation): the shared
                            channels come from one GEMM whose contraction runs over all T ranks, so the sum is taken in
-                           the accumulator, no partial sum reaches memory and no reduce pass runs.  Needs hs % 8 == 0
+                           the accumulator, no bf16 partial sum reaches memory and no reduce pass runs (batches too small
+                           to fill the chip that way are summed in groups of ranks, fp32, in the workspace, which is
+                           larger for it).  Needs hs % 8 == 0
                            and more than 64 tokens (otherwise the default path is taken: a decode-sized GEMM has too few
                            tiles once the ranks are folded into the contraction).  Same result up to the rounding of the partials. */
   int dedup_shared;     /* forward only, needs reduce_in_gemm = 1, hs % 8 == 0, more than 64 tokens, not the decode kind
