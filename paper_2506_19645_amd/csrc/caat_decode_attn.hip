@@ -14,6 +14,7 @@
 // batch 32, 32 / 8 heads, 4000 keys 314 -> 85; batch 100, 16 heads, 300 keys 47 -> 47.  Two waves, or blocks of 32 keys,
 // or three and four slots per wave were up to 8 % slower at batch 64 or up to 40 % on short caches.
 #include <math.h>
+#include <type_traits>
 #include "caat_internal.h"
 
 namespace caat {
@@ -162,70 +163,106 @@ __global__ __launch_bounds__(64 * DNW) void decode_attn_kernel(const bf16_t* __r
 #pragma unroll
   for (int dt = 0; dt < 8; ++dt) acc[dt] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
   float m = -INFINITY, l = 0.0f;                 // l: this lane's keys only
-  int slot = 0;
-  for (int b = b0 + wave; b < b1; b += DNW) {
-    wait_vmcnt<(DNS - 1) * DNI>();               // this block has landed; the next ones may be in flight
-    uint4* ks = mine + slot * (DNI * 64);
-    uint4* vs = ks + 4 * 64;
-    if (ROPE && b == nb - 1 && g == 0) {         // the token's own key and value take their row of the last block
-      const int r = (nkeys - 1) & (DKB - 1);
-      ks[r * 16 + (r16 ^ dk_swz(r))] = knew;
-      vs[r * 16 + (r16 ^ dv_swz(r))] = vnew;
+  auto sweep = [&](auto fp32_c) {                // the wave's blocks; the first DNS copies are under way
+    int slot = 0;
+    for (int b = b0 + wave; b < b1; b += DNW) {
+      wait_vmcnt<(DNS - 1) * DNI>();             // this block has landed; the next ones may be in flight
+      uint4* ks = mine + slot * (DNI * 64);
+      uint4* vs = ks + 4 * 64;
+      if (ROPE && b == nb - 1 && g == 0) {       // the token's own key and value take their row of the last block
+        const int r = (nkeys - 1) & (DKB - 1);
+        ks[r * 16 + (r16 ^ dk_swz(r))] = knew;
+        vs[r * 16 + (r16 ^ dv_swz(r))] = vnew;
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      bf16x8_t kf[4];
+      short4_t vf[8];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) kf[t] = __builtin_bit_cast(bf16x8_t, ks[r16 * 16 + ((t * 4 + g) ^ dk_swz(r16))]);
+      const int vr = 4 * g + (r16 >> 2);         // the keys of this lane's scores are 4 g .. 4 g + 3
+      const lds_c_t va = (lds_c_t)vs + vr * 256 + (r16 & 1) * 8;
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt)
+        vf[dt] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_t)(va + (((dt * 2 + ((r16 & 3) >> 1)) ^ dv_swz(vr)) << 4)));
+#pragma unroll
+      for (int t = 0; t < 4; ++t) asm volatile("" : "+v"(kf[t]));
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt) asm volatile("" : "+v"(vf[dt]));
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the fragments are in registers before the slot is filled again
+      copy(b + DNS * DNW, slot);
+      f32x4_t sc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int t = 0; t < 4; ++t) sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[t], qf[t], sc, 0, 0, 0);
+      // scores of query head r16 and keys 16 b + 4 g + r
+      float p[4], mx = -INFINITY;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        p[i] = sc[i] * scale_log2;
+        if (b * DKB + 4 * g + i >= nkeys) p[i] = -INFINITY;
+        mx = fmaxf(mx, p[i]);
+      }
+      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      const float m_new = fmaxf(m, mx);          // every block holds a key below nkeys: -inf only if all its scores are
+      const float alpha = exp2f(m - m_new);      // 0 in the first block
+      float sum = 0.0f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        p[i] = exp2f(p[i] - m_new);
+        sum += p[i];
+      }
+      l = l * alpha + sum;
+      m = m_new;
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[dt][r] *= alpha;
+      if constexpr (decltype(fp32_c)::value) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)              // step i of the product: the keys 4 g + i, g = 0 .. 3
+#pragma unroll
+          for (int dt = 0; dt < 8; ++dt)
+            acc[dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(bf2f((bf16_t)vf[dt][i]), p[i], acc[dt], 0, 0, 0);
+      } else {
+        unsigned hi[2], mid[2], lo[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          hi[i] = pack2bf(p[2 * i], p[2 * i + 1]);
+          const float a = p[2 * i] - lo_bf(hi[i]), c = p[2 * i + 1] - hi_bf(hi[i]);   // exact, as is the next difference
+          mid[i] = pack2bf(a, c);
+          lo[i] = pack2bf(a - lo_bf(mid[i]), c - hi_bf(mid[i]));
+        }
+        const bf16x8_t ph = __builtin_bit_cast(bf16x8_t, make_uint4(hi[0], hi[1], mid[0], mid[1]));
+        const short4_t pl = __builtin_bit_cast(short4_t, make_uint2(lo[0], lo[1]));
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt) {           // one product takes the first two parts against the values twice
+          const uint2 v = __builtin_bit_cast(uint2, vf[dt]);
+          const bf16x8_t v2 = __builtin_bit_cast(bf16x8_t, make_uint4(v.x, v.y, v.x, v.y));
+          acc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v2, ph, acc[dt], 0, 0, 0);
+        }
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt) acc[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vf[dt], pl, acc[dt], 0, 0, 0);
+      }
+      slot = slot + 1 == DNS ? 0 : slot + 1;
     }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    bf16x8_t kf[4];
-    short4_t vf[8];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) kf[t] = __builtin_bit_cast(bf16x8_t, ks[r16 * 16 + ((t * 4 + g) ^ dk_swz(r16))]);
-    const int vr = 4 * g + (r16 >> 2);           // the keys of this lane's scores are 4 g .. 4 g + 3
-    const lds_c_t va = (lds_c_t)vs + vr * 256 + (r16 & 1) * 8;
-#pragma unroll
-    for (int dt = 0; dt < 8; ++dt)
-      vf[dt] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_t)(va + (((dt * 2 + ((r16 & 3) >> 1)) ^ dv_swz(vr)) << 4)));
-#pragma unroll
-    for (int t = 0; t < 4; ++t) asm volatile("" : "+v"(kf[t]));
-#pragma unroll
-    for (int dt = 0; dt < 8; ++dt) asm volatile("" : "+v"(vf[dt]));
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the fragments are in registers before the slot is filled again
-    copy(b + DNS * DNW, slot);
-    f32x4_t sc = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int t = 0; t < 4; ++t) sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[t], qf[t], sc, 0, 0, 0);
-    // scores of query head r16 and keys 16 b + 4 g + r
-    float p[4], mx = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      p[i] = sc[i] * scale_log2;
-      if (b * DKB + 4 * g + i >= nkeys) p[i] = -INFINITY;
-      mx = fmaxf(mx, p[i]);
-    }
-    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float m_new = fmaxf(m, mx);            // finite: every block holds a key below nkeys
-    const float alpha = exp2f(m - m_new);        // 0 in the first block
-    float sum = 0.0f;
-    unsigned hi[2], lo[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const float a = exp2f(p[2 * i] - m_new), c = exp2f(p[2 * i + 1] - m_new);
-      sum += a + c;
-      hi[i] = pack2bf(a, c);
-      lo[i] = pack2bf(a - lo_bf(hi[i]), c - hi_bf(hi[i]));
-    }
-    l = l * alpha + sum;
-    m = m_new;
-    const short4_t ph = __builtin_bit_cast(short4_t, make_uint2(hi[0], hi[1]));
-    const short4_t pl = __builtin_bit_cast(short4_t, make_uint2(lo[0], lo[1]));
-#pragma unroll
-    for (int dt = 0; dt < 8; ++dt) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc[dt][r] *= alpha;
-      acc[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vf[dt], ph, acc[dt], 0, 0, 0);
-      acc[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vf[dt], pl, acc[dt], 0, 0, 0);
-    }
-    slot = slot + 1 == DNS ? 0 : slot + 1;
-  }
+  };
+  sweep(std::false_type{});
   wait_vmcnt<0>();                               // the copies past the end write zeros: let them land
+  bool odd = false;
+#pragma unroll
+  for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) odd |= !(fabsf(acc[dt][r]) < INFINITY);
+  if (__any(odd)) {
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) acc[dt] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    m = -INFINITY;
+    l = 0.0f;
+#pragma unroll
+    for (int i = 0; i < DNS; ++i) copy(b0 + wave + i * DNW, i);
+    sweep(std::true_type{});
+    wait_vmcnt<0>();
+  }
   if (ROPE && qt == 0 && split == splits - 1 && wave == 0 && g == 0) {   // one 16-lane group writes the new rows of the caches
     const long long dst = ((long long)u * cap + (nkeys - 1)) * DHD + r16 * 8;
     st_stream(kc + dst, knew);

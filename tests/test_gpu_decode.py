@@ -121,3 +121,47 @@ def test_decode_attention_over_ranges_of_keys(T, b, heads, kv_heads, L):
     assert_close(bits_to_f64(got["Vc_bits"][:, :, :, L]), ref["v_new"], "v_new")
     assert np.array_equal(got["Kc_bits"][:, :, :, :L], d["Kc"][:, :, :, :L])
     assert np.array_equal(got["Vc_bits"][:, :, :, :L], d["Vc"][:, :, :, :L])
+
+
+@pytest.mark.parametrize("kv_heads,L", [(0, 37), (2, 1023)])
+def test_decode_attention_infinite_values(kv_heads, L):
+    """An infinite element of a cached value makes that output element infinite for the query heads that attend to it
+    (every probability here is positive) and touches nothing else."""
+    cfg = _cfg(2, 3, 8, 2 * 256, L, 0.5, kv_heads)
+    d = make_inputs(cfg, seed=41, weight_std=0.05)
+    shape = (cfg.T, cfg.batch, cfg.n_heads // cfg.T, 128)
+    want = run_decode(cfg, d)["H"].reshape(shape)
+    grp = cfg.n_heads // cfg.kv_heads
+    for m, sq, hd, key, dim, bits in ((0, 0, 0, 3, 5, 0x7F80), (1, 2, 0, L - 1, 127, 0xFF80), (0, 1, 0, 20, 64, 0x7F80)):
+        d["Vc"][m, sq, hd, key, dim] = bits
+        want[m, sq, hd * grp:(hd + 1) * grp, dim] = np.inf if bits == 0x7F80 else -np.inf
+    # the infinities spread over the rest of the layer, so only the heads' outputs are compared
+    assert np.array_equal(run_decode(cfg, d)["H"].reshape(shape), want)
+
+
+def test_decode_attention_probabilities_keep_fp32():
+    """Per sequence: a key with probability weight w < 1 and value 1, and two keys of weight 1 whose values are minus the
+    first two bf16 parts of w, so that the output is what is left of w below them, at most 2^-18."""
+    L, n = 3, 8
+    kappa = np.unique(I.bf16_bits_to_f32(I.f32_to_bf16_bits(np.linspace(-7.0, -0.1, 4001).astype(np.float32))))
+    w = np.exp(kappa.astype(np.float64) / np.sqrt(128.0))
+    rnd = lambda x: bits_to_f64(I.f32_to_bf16_bits(x.astype(np.float32)))
+    hi = rnd(w)
+    lo = rnd(w - hi)
+    rest = w - hi - lo
+    pick = np.argsort(-np.abs(rest))[:n]
+    cfg = _cfg(1, n, 1, 64, L, 0.0)
+    d = make_inputs(cfg, seed=43)
+    d["R"][:] = 0x3F80                     # ones: their RMSNorm rounds to one
+    d["gamma_attn"][:] = 0x3F80
+    for name in ("Wqkv", "Kc", "Vc"):
+        d[name][:] = 0
+    d["Wqkv"][0, 63, 0] = 0x3F80           # q = 1 in dimension 63, whose angle at position 3 is 3.5e-4: cos rounds to 1
+    for sq, c in enumerate(pick):
+        d["Kc"][0, sq, 0, 0, 63] = I.f32_to_bf16_bits(kappa[c:c + 1])[0]
+        d["Vc"][0, sq, 0, :3, 0] = I.f32_to_bf16_bits(np.array([1.0, -hi[c], -lo[c]], dtype=np.float32))
+    got = run_decode(cfg, d)["H"][0, :, 0]
+    want = rest[pick] / (3.0 + w[pick])    # the token's own key has weight 1 too and a value of zero
+    # fp32: the score, its exponential and the sum are each off by at most about 2^-24; the output is rounded to bf16
+    assert np.abs(got - want).max() <= 4 * 2.0 ** -24 / 3.0 + np.abs(want).max() * 2.0 ** -8
+    assert np.abs(want).min() >= 2.0 ** -21
