@@ -90,9 +90,8 @@ typedef struct caat_desc {
                            serving with logical ranks (Sec. 3.2, the reduce becomes a local summation): the shared
                            channels come from one GEMM whose contraction runs over all T ranks, so the sum is taken in
                            the accumulator, no bf16 partial sum reaches memory and no reduce pass runs (batches too small
-                           to fill the chip that way are summed in groups of ranks, fp32, in the workspace, which is
-                           larger for it).  Needs hs % 8 == 0
-                           and more than 64 tokens (otherwise the default path is taken: a decode-sized GEMM has too few
+                           to fill the chip that way are summed in groups of ranks, fp32, in the workspace).  Needs
+                           hs % 8 == 0 and more than 64 tokens (otherwise the default path is taken: a decode-sized GEMM has too few
                            tiles once the ranks are folded into the contraction).  Same result up to the rounding of the partials. */
   int dedup_shared;     /* forward only, needs reduce_in_gemm = 1, hs % 8 == 0, more than 64 tokens, not the decode kind
                            (CAAT_EUNSUPPORTED otherwise).  1: the residual-stream tensors r and r_out (and the layer
@@ -143,7 +142,11 @@ int caat_shared_channels(int h, double p);
 const char* caat_status_string(int status);
 
 /* Workspace (bytes) that caat_block_fwd / caat_block_bwd need for `d` (host pointer).  0 on an invalid
- * descriptor.  caat_workspace_layout fills `out` (host pointer) and returns a caat_status. */
+ * descriptor.  caat_workspace_layout fills `out` (host pointer) and returns a caat_status.
+ * The size never falls when tokens (batch) grows, and a decode step's does not depend on kv_len or kv_cap: one workspace,
+ * sized for the largest batch, serves every step.  The scratch at the end of a layer kind's workspace (off_scratch) may
+ * also be missing in part or whole: such a call splits its work less and is slower where it would have used it, and its
+ * sums may round differently; CAAT_EWORKSPACE is returned below off_scratch bytes. */
 size_t caat_workspace_bytes(const caat_desc* d);
 int caat_workspace_layout(const caat_desc* d, caat_ws_layout* out);
 

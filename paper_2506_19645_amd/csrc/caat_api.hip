@@ -68,14 +68,8 @@ long long qkv_width(const caat_desc* d) {
   return (long long)(d->n_heads / d->T + 2 * (kv_heads_of(d) / d->T)) * d->head_dim;
 }
 
-// the reduce is taken inside the row-parallel GEMM (see rowpar_pcr), and the scratch that takes for contraction lengths
-// k1 and k2 per rank
+// the reduce is taken inside the row-parallel GEMM (see rowpar_pcr)
 bool sums_in_gemm(const caat_desc* d) { return d->reduce_in_gemm && d->hs % 8 == 0 && d->tokens > 64; }
-size_t shared_scratch(const caat_desc* d, long long k1, long long k2) {
-  if (!sums_in_gemm(d) || d->hs == 0) return 0;
-  return std::max(gemm_shared_scratch_bytes((int)d->tokens, d->hs, (int)k1, d->T),
-                  gemm_shared_scratch_bytes((int)d->tokens, d->hs, (int)k2, d->T));
-}
 
 // The reduce over ranks, the residual add and the norm run as one kernel where its shape is taken and the caller has
 // not asked for the reduce as a kernel of its own; the folded-into-the-GEMM serving modes have no reduce pass at all.
@@ -84,8 +78,22 @@ bool fuse_reduce_norm(const caat_desc* d) {
 }
 
 // decode steps: that kernel with a workgroup per (token, rank); the GEMM's output then has a buffer of its own in the scratch
-bool spread_reduce_norm(const caat_desc* d) {
-  return d->kind == CAAT_ATTN_DECODE && fuse_reduce_norm(d) && sync_norm_rank_takes(d->T, d->tokens, d->h, d->hs);
+bool spread_reduce_norm(const caat_desc* d, size_t scratch_bytes) {
+  return d->kind == CAAT_ATTN_DECODE && fuse_reduce_norm(d) && sync_norm_rank_takes(d->T, d->tokens, d->h, d->hs) &&
+         sync_norm_rank_bytes(d->T, d->tokens, d->h) <= scratch_bytes;
+}
+
+// Scratch of the layer kinds, used in turn: a decode step's partial attention results over ranges of keys, the o_proj output
+// of spread_reduce_norm, the sums over groups of ranks of rowpar_pcr.  It lies behind everything else, a call runs with any
+// part of it (some launches then split less), and it never falls when the number of tokens grows; a decode step's depends
+// on nothing that changes from step to step either.  So a program that sizes its workspace once, for its largest batch, is
+// never refused.
+size_t layer_scratch(const caat_desc* d) {
+  size_t bytes = sums_in_gemm(d) ? gemm_shared_scratch_bytes((int)d->tokens, d->hs, d->T) : 0;
+  if (d->kind == CAAT_ATTN_DECODE)
+    bytes = std::max({bytes, sync_norm_rank_bytes(d->T, d->tokens, d->h),
+                      decode_attn_scratch_bytes((long long)d->T * d->tokens, d->n_heads / d->T, kv_heads_of(d) / d->T)});
+  return bytes;
 }
 
 int validate_desc(const caat_desc* d) {
@@ -136,8 +144,7 @@ int layout_of(const caat_desc* d, caat_ws_layout* L) {
     take(T * n * 4, &L->off_rstd, &L->bytes_rstd);
     take(T * n * h * 2, &L->off_dZt, &L->bytes_dZt);
     take(T * n * pw * 2, &L->off_dP, &L->bytes_dP);
-    take(std::max(norm_bwd_workspace_bytes(d->T, d->tokens, d->h), shared_scratch(d, (long long)fr, (long long)fr)),
-         &L->off_scratch, &L->bytes_scratch);
+    take(norm_bwd_workspace_bytes(d->T, d->tokens, d->h), &L->off_scratch, &L->bytes_scratch);
   } else if (d->kind == CAAT_ATTN) {
     const size_t hd = (size_t)(d->n_heads / d->T) * d->head_dim, qw = (size_t)qkv_width(d);
     take(T * n * qw * 2, &L->off_Q, &L->bytes_Q);
@@ -148,8 +155,7 @@ int layout_of(const caat_desc* d, caat_ws_layout* L) {
     take(T * n * h * 2, &L->off_dZt, &L->bytes_dZt);
     take(T * n * hd * 2, &L->off_dH, &L->bytes_dH);
     take(T * n * qw * 2, &L->off_dP, &L->bytes_dP);
-    take(std::max(norm_bwd_workspace_bytes(d->T, d->tokens, d->h), shared_scratch(d, (long long)hd, (long long)hd)),
-         &L->off_scratch, &L->bytes_scratch);
+    take(norm_bwd_workspace_bytes(d->T, d->tokens, d->h), &L->off_scratch, &L->bytes_scratch);
   } else if (is_layer(d->kind)) {
     const size_t hd = (size_t)(d->n_heads / d->T) * d->head_dim, fr = d->ffn / d->T;
     take(T * n * h * 2, &L->off_X1, &L->bytes_X1);
@@ -160,10 +166,7 @@ int layout_of(const caat_desc* d, caat_ws_layout* L) {
     take(T * n * 2 * fr * 2, &L->off_P, &L->bytes_P);
     take(T * n * fr * 2, &L->off_Y, &L->bytes_Y);
     take(T * n * 4, &L->off_rstd, &L->bytes_rstd);
-    size_t scratch = shared_scratch(d, (long long)hd, (long long)fr);
-    if (d->kind == CAAT_ATTN_DECODE && d->kv_len >= 0)   // partial results of the attention over ranges of keys
-      scratch = std::max(scratch, decode_attn_scratch_bytes((long long)T * n, d->n_heads / d->T, kv_heads_of(d) / d->T, d->kv_len + 1));
-    if (spread_reduce_norm(d)) scratch = std::max(scratch, T * n * h * 2);
+    const size_t scratch = layer_scratch(d);
     if (scratch > 0) take(scratch, &L->off_scratch, &L->bytes_scratch);
   } else {
     return CAAT_EUNSUPPORTED;
@@ -186,7 +189,7 @@ bool fuse_norm_bwd_reduce(const caat_desc* d) {
 // index runs over all T ranks' inputs and weight rows, so the sum over ranks is taken in the accumulator (for a prompt
 // too short to fill the chip that way: in one accumulator per group of ranks, added up by a second kernel).
 int rowpar_pcr(const caat_desc* d, const bf16_t* a, long long kdim, const bf16_t* w, const bf16_t* resid, bf16_t* out,
-               void* scratch, hipStream_t s, bool leave_reduce_to_caller = false) {
+               void* scratch, size_t scratch_bytes, hipStream_t s, bool leave_reduce_to_caller = false) {
   const long long T = d->T, n = d->tokens, h = d->h;
   const int hs = d->hs;
   hipError_t e = hipSuccess;
@@ -223,7 +226,7 @@ int rowpar_pcr(const caat_desc* d, const bf16_t* a, long long kdim, const bf16_t
       q.G = 1; q.M = (int)n; q.N = hs; q.K = (int)kdim; q.kcat = (int)T; q.bcast = dd ? 1 : (int)T;
       {
         ProfScope ps(s, "gemm_nt_shared_kcat");
-        e = launch_gemm_shared(q, scratch, s);
+        e = launch_gemm_shared(q, scratch, scratch_bytes, s);
       }
       if (e != hipSuccess) return CAAT_EHIP;
     }
@@ -294,7 +297,8 @@ int attn_block_fwd(const caat_desc* d, const caat_ws_layout& L, const void* cons
   if (e != hipSuccess) return CAAT_EHIP;
   const bool fuse = fuse_reduce_norm(d);
   {
-    const int st = rowpar_pcr(d, H, hd, (const bf16_t*)wo, (const bf16_t*)r, (bf16_t*)r_out, ws + L.off_scratch, s, fuse);
+    const int st = rowpar_pcr(d, H, hd, (const bf16_t*)wo, (const bf16_t*)r, (bf16_t*)r_out, ws + L.off_dZt,
+                              L.total_bytes - L.off_dZt, s, fuse);   // the gradients' buffers are free
     if (st != CAAT_OK) return st;
   }
   if (fuse) {
@@ -411,7 +415,7 @@ int layer_fwd(const caat_desc* d, const caat_ws_layout& L, const void* const* we
   if (misaligned(g_attn) || misaligned(wqkv) || misaligned(wo) || misaligned(g_mlp) || misaligned(wgu) || misaligned(wb) ||
       misaligned(r) || misaligned(r_out) || misaligned(kv_k) || misaligned(kv_v) || misaligned(workspace))
     return CAAT_EALIGN;
-  if (ws_bytes < L.total_bytes) return CAAT_EWORKSPACE;
+  if (ws_bytes < (L.bytes_scratch ? L.off_scratch : L.total_bytes)) return CAAT_EWORKSPACE;   // see layer_scratch
   if (d->tokens == 0) return CAAT_OK;
   hipStream_t s = (hipStream_t)hip_stream;
   char* ws = (char*)workspace;
@@ -426,6 +430,7 @@ int layer_fwd(const caat_desc* d, const caat_ws_layout& L, const void* const* we
   bf16_t* Y = (bf16_t*)(ws + L.off_Y);
   float* rstd = (float*)(ws + L.off_rstd);
   void* scratch = L.bytes_scratch ? ws + L.off_scratch : nullptr;
+  const size_t scratch_bytes = scratch ? std::min(L.bytes_scratch, ws_bytes - L.off_scratch) : 0;
   hipError_t e;
   GemmParams q;
 #define CAAT_STEP(name, call) { ProfScope ps(s, name); e = (call); } if (e != hipSuccess) return CAAT_EHIP;
@@ -446,14 +451,15 @@ int layer_fwd(const caat_desc* d, const caat_ws_layout& L, const void* const* we
     // kv_len cached keys plus the new one
     CAAT_STEP("decode_attn", launch_decode_attn(QKV, (bf16_t*)kv_k, (bf16_t*)kv_v, H, T * n, (int)hpr, (int)kvpr,
                                                 d->head_dim, d->kv_cap, d->kv_len + 1, d->rope_base,
-                                                scratch, s))
+                                                scratch, scratch_bytes, s))
   }
   // the reduce after o_proj and the RMSNorm in front of the MLP run as one launch where the fused kernel takes the
   // shape: for decode-sized batches both are start-up latency, for prompts the fused kernel does not read the
   // reduced shared channels back from memory (measured 1.28 ms instead of 0.61 + 0.78 ms on 16 prompts of 2048)
-  const bool fuse_mid = fuse_reduce_norm(d), spread = spread_reduce_norm(d);
+  const bool fuse_mid = fuse_reduce_norm(d), spread = spread_reduce_norm(d, scratch_bytes);
   {
-    const int st = rowpar_pcr(d, H, hd, (const bf16_t*)wo, (const bf16_t*)r, spread ? (bf16_t*)scratch : R1, scratch, s, fuse_mid);
+    const int st = rowpar_pcr(d, H, hd, (const bf16_t*)wo, (const bf16_t*)r, spread ? (bf16_t*)scratch : R1, scratch,
+                              scratch_bytes, s, fuse_mid);
     if (st != CAAT_OK) return st;
   }
   if (spread) {
@@ -474,7 +480,7 @@ int layer_fwd(const caat_desc* d, const caat_ws_layout& L, const void* const* we
   q.G = (int)T; q.M = (int)n; q.N = (int)fr; q.K = (int)h; q.half = (int)fr;
   CAAT_STEP("gemm_nt_swiglu_fwd", launch_gemm(q, 0, EPI_SWIGLU_FWD, s))
   {
-    const int st = rowpar_pcr(d, Y, fr, (const bf16_t*)wb, R1, (bf16_t*)r_out, scratch, s);
+    const int st = rowpar_pcr(d, Y, fr, (const bf16_t*)wb, R1, (bf16_t*)r_out, scratch, scratch_bytes, s);
     if (st != CAAT_OK) return st;
   }
 #undef CAAT_STEP
@@ -699,7 +705,8 @@ int caat_block_fwd(const caat_desc* d, const void* const* weights, const void* x
   // the reduce as a kernel of its own) the shared half of the reduce, the residual add and the norm are one launch
   const bool fuse = fuse_reduce_norm(d);
   {
-    const int st2 = rowpar_pcr(d, Y, fr, (const bf16_t*)w1, (const bf16_t*)r, (bf16_t*)r_out, ws + L.off_scratch, s, fuse);
+    const int st2 = rowpar_pcr(d, Y, fr, (const bf16_t*)w1, (const bf16_t*)r, (bf16_t*)r_out, ws + L.off_dZt,
+                               L.total_bytes - L.off_dZt, s, fuse);   // the gradients' buffers are free
     if (st2 != CAAT_OK) return st2;
   }
   if (fuse) {

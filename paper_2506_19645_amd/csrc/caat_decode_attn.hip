@@ -14,6 +14,7 @@
 // batch 32, 32 / 8 heads, 4000 keys 314 -> 85; batch 100, 16 heads, 300 keys 47 -> 47.  Two waves, or blocks of 32 keys,
 // or three and four slots per wave were up to 8 % slower at batch 64 or up to 40 % on short caches.
 #include <math.h>
+#include <algorithm>
 #include <type_traits>
 #include "caat_internal.h"
 
@@ -308,6 +309,7 @@ __global__ __launch_bounds__(64 * DNW) void decode_attn_kernel(const bf16_t* __r
 
 // the ranges of keys of one query head: their weights, then the sums in ascending order
 static constexpr int DMAX_SPLITS = 64;
+static constexpr long long DMAX_WGS = 1024;      // workgroups of a launch with more than one range: two rounds
 __global__ __launch_bounds__(128) void decode_merge_kernel(const float* __restrict__ part, bf16_t* __restrict__ out, int splits) {
   __shared__ float s_f[DMAX_SPLITS];
   const int d = threadIdx.x, lane = d & 63;
@@ -337,11 +339,12 @@ __global__ __launch_bounds__(128) void decode_merge_kernel(const float* __restri
 // Number of key ranges per (sequence, key / value head).  512 workgroups run at a time (two per compute unit) and together
 // take about 830 blocks per microsecond (6.8 TB/s), one by itself at most about 3 (four waves, two blocks each per trip
 // to memory); starting and finishing costs a workgroup about 3 us and the second kernel a launch about 4.5.
-static int decode_splits(long long units, long long nkeys) {
+// `most`: as many as the scratch holds.
+static int decode_splits(long long units, long long nkeys, long long most) {
   const long long nb = (nkeys + DKB - 1) / DKB;
   int best = 1;
   double cost = 0.0;
-  for (int s = 1; s <= DMAX_SPLITS && (s == 1 || nb / s >= DNW); ++s) {
+  for (int s = 1; s <= DMAX_SPLITS && (s == 1 || (s <= most && nb / s >= DNW && units * s <= DMAX_WGS)); ++s) {
     const long long wgs = units * s;
     const double rate = wgs < 277 ? 3.0 : 830.0 / (double)(wgs < 512 ? wgs : 512);   // blocks per us and workgroup
     const double c = (double)((wgs + 511) / 512) * ((double)((nb + s - 1) / s) / rate + 3.0) + (s > 1 ? 4.5 : 0.0);
@@ -353,10 +356,12 @@ static int decode_splits(long long units, long long nkeys) {
   return best;
 }
 
-size_t decode_attn_scratch_bytes(long long n_seq, int hpr, int kvpr, long long nkeys) {
-  const int grp = hpr / kvpr;
-  const int splits = decode_splits(n_seq * kvpr * ((grp + 15) / 16), nkeys);
-  return splits == 1 ? 0 : (size_t)(n_seq * hpr) * splits * (DHD + 4) * sizeof(float);
+// What any number of keys can take: it neither depends on it, so that one scratch serves a sequence as it grows, nor falls
+// with the number of sequences.
+size_t decode_attn_scratch_bytes(long long n_seq, int hpr, int kvpr) {
+  const long long grp = hpr / kvpr, qtiles = (grp + 15) / 16, heads = (grp + qtiles - 1) / qtiles;
+  const long long rows = std::min(n_seq * hpr * DMAX_SPLITS, DMAX_WGS * heads);   // heads: of one workgroup, at most
+  return (size_t)rows * (DHD + 4) * sizeof(float);
 }
 
 // out [n_seq, hpr*128] = softmax(q K^T / sqrt(d)) V over keys 0 .. nkeys-1 of caches [n_seq][kvpr][cap][128].
@@ -364,13 +369,15 @@ size_t decode_attn_scratch_bytes(long long n_seq, int hpr, int kvpr, long long n
 // uses the new key / value from registers and stores them at cache row nkeys - 1 (no RoPE + append launch needed).
 // rope_base = 0: q is rotated already and all nkeys keys are in the caches.
 hipError_t launch_decode_attn(const bf16_t* qkv, bf16_t* kc, bf16_t* vc, bf16_t* out, long long n_seq, int hpr,
-                              int kvpr, int d, long long cap, long long nkeys, float rope_base, void* scratch, hipStream_t s) {
+                              int kvpr, int d, long long cap, long long nkeys, float rope_base, void* scratch, size_t scratch_bytes,
+                              hipStream_t s) {
   if (d != DHD || kvpr < 1 || hpr % kvpr != 0 || nkeys < 1 || nkeys > cap || cap * 256 >= 0x7FFFFFFFLL)
     return hipErrorInvalidValue;
   if (n_seq * hpr == 0) return hipSuccess;
   const long long units = n_seq * kvpr * ((hpr / kvpr + 15) / 16);
-  const int splits = decode_splits(units, nkeys);
-  if (units * splits > 0x7FFFFFFFLL || n_seq * hpr > 0x7FFFFFFFLL || (splits > 1 && scratch == nullptr)) return hipErrorInvalidValue;
+  const long long row = (DHD + 4) * (long long)sizeof(float);
+  const int splits = decode_splits(units, nkeys, scratch ? (long long)scratch_bytes / (n_seq * hpr * row) : 1);
+  if (units * splits > 0x7FFFFFFFLL || n_seq * hpr > 0x7FFFFFFFLL) return hipErrorInvalidValue;
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)d);
   const dim3 grid((unsigned)(units * splits)), wg(64 * DNW);
   float* part = reinterpret_cast<float*>(scratch);

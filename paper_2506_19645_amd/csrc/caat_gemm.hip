@@ -149,7 +149,8 @@ hipError_t launch_gemm(const GemmParams& p, int layout, int epilogue, hipStream_
 // does not depend on the device that is current) times 1.4 for weights that come from HBM and not, as where the model was
 // fitted, from the memory-side cache, plus the merge: a launch and the fp32 sums at 7 TB/s.  Measured for 777 tokens, 2048
 // shared channels, 8 ranks (us, 1 / 2 / 4 / 8 groups): 512 k per rank 39 / 37 / 36 / 40, 1376 k 121 / 94 / 69 / 66.
-int gemm_shared_groups(int M, int N, int K, int kcat) {
+// `scratch_bytes`: what there is for the groups' sums.
+static int gemm_shared_groups(int M, int N, int K, int kcat, size_t scratch_bytes) {
   GemmParams q = {};
   q.M = M;
   q.N = N;
@@ -157,7 +158,7 @@ int gemm_shared_groups(int M, int N, int K, int kcat) {
   int best = 1;
   double cost = 0.0;
   for (int g = 1; g <= kcat; g *= 2) {
-    if (kcat % g != 0) break;
+    if (kcat % g != 0 || (g > 1 && (size_t)g * M * N * sizeof(float) > scratch_bytes)) break;
     q.G = g;
     q.kcat = kcat / g;
     double us = 0.0;
@@ -172,15 +173,15 @@ int gemm_shared_groups(int M, int N, int K, int kcat) {
   return best;
 }
 
-size_t gemm_shared_scratch_bytes(int M, int N, int K, int kcat) {
-  const int groups = gemm_shared_groups(M, N, K, kcat);
-  return groups == 1 ? 0 : (size_t)groups * (size_t)M * (size_t)N * sizeof(float);
+// As many groups as there are ranks, up to 128 MiB: does not fall when M grows, so that the scratch of the largest batch serves
+// the smaller ones too.  By the model the limit costs nothing up to 8 ranks of K = 3584.
+size_t gemm_shared_scratch_bytes(int M, int N, int kcat) {
+  return kcat > 1 ? std::min((size_t)kcat * M * N * sizeof(float), (size_t)128 << 20) : 0;
 }
 
-hipError_t launch_gemm_shared(const GemmParams& p, void* scratch, hipStream_t s) {
-  const int groups = gemm_shared_groups(p.M, p.N, p.K, p.kcat);
+hipError_t launch_gemm_shared(const GemmParams& p, void* scratch, size_t scratch_bytes, hipStream_t s) {
+  const int groups = gemm_shared_groups(p.M, p.N, p.K, p.kcat, scratch ? scratch_bytes : 0);
   if (groups == 1) return launch_gemm(p, 0, EPI_SHARED_BCAST, s);
-  if (scratch == nullptr) return hipErrorInvalidValue;
   GemmParams q = p;
   q.G = groups;
   q.kcat = p.kcat / groups;

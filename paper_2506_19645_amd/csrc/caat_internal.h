@@ -201,11 +201,10 @@ struct GemmParams {
 
 // layout: 0 NT, 1 NN, 2 TN (see caat_gemm_layout).  Returns hipError_t of the launch.
 hipError_t launch_gemm(const GemmParams& p, int layout, int epilogue, hipStream_t s);
-// EPI_SHARED_BCAST (NT, kcat ranks in the contraction), directly or as sums over groups of ranks that a second kernel adds
-// up: gemm_shared_groups() groups (1 = directly) with fp32 scratch of gemm_shared_scratch_bytes() (may be null when 0).
-int gemm_shared_groups(int M, int N, int K, int kcat);
-size_t gemm_shared_scratch_bytes(int M, int N, int K, int kcat);
-hipError_t launch_gemm_shared(const GemmParams& p, void* scratch, hipStream_t s);
+// EPI_SHARED_BCAST (NT, kcat ranks in the contraction), directly or as fp32 sums over groups of ranks that a second kernel
+// adds up.  scratch: gemm_shared_scratch_bytes() bytes; with less, or none, there are fewer groups
+size_t gemm_shared_scratch_bytes(int M, int N, int kcat);
+hipError_t launch_gemm_shared(const GemmParams& p, void* scratch, size_t scratch_bytes, hipStream_t s);
 // the second kernel: for m in [0, bcast): out[m] = round_bf16(sum over groups of part) + resid[m]; part [groups][M][N] fp32
 hipError_t launch_shared_merge(const float* part, int groups, const bf16_t* resid, bf16_t* out, long long M, int N, long long ldr,
                                long long ldo, long long stride_r, long long stride_o, int bcast, hipStream_t s);
@@ -228,6 +227,7 @@ hipError_t launch_sync_norm(bf16_t* io, const bf16_t* resid, const bf16_t* gamma
                             hipStream_t s);
 // the same for a few tokens, RMSNorm, from a buffer of its own into R' and xout (sync_norm_rank_takes)
 bool sync_norm_rank_takes(int T, long long tokens, int h, int hs);
+size_t sync_norm_rank_bytes(int T, long long tokens, int h);   // that buffer: never less for more tokens, for any hs
 hipError_t launch_sync_norm_rank(const bf16_t* part, const bf16_t* resid, const bf16_t* gamma, bf16_t* out, bf16_t* xout,
                                  float* rstd, int T, long long tokens, int h, int hs, float eps, hipStream_t s);
 size_t norm_bwd_workspace_bytes(int T, long long tokens, int h);
@@ -260,9 +260,10 @@ hipError_t launch_flash_fwd(const bf16_t* qkv, bf16_t* out, float* stats, long l
                             int d, hipStream_t s);
 hipError_t launch_flash_bwd(const bf16_t* qkv, const bf16_t* out, const bf16_t* dout, float* stats, bf16_t* dqkv,
                             long long n_seq, int seq, int heads, int kv_heads, int d, hipStream_t s);
-// scratch: decode_attn_scratch_bytes() bytes (may be null when that is 0)
-size_t decode_attn_scratch_bytes(long long n_seq, int hpr, int kvpr, long long nkeys);
+// scratch: decode_attn_scratch_bytes() bytes; with less, or none, the keys are taken in fewer ranges
+size_t decode_attn_scratch_bytes(long long n_seq, int hpr, int kvpr);
 hipError_t launch_decode_attn(const bf16_t* qkv, bf16_t* kc, bf16_t* vc, bf16_t* out, long long n_seq, int hpr, int kvpr,
-                              int d, long long cap, long long nkeys, float rope_base, void* scratch, hipStream_t s);
+                              int d, long long cap, long long nkeys, float rope_base, void* scratch, size_t scratch_bytes,
+                              hipStream_t s);
 
 }  // namespace caat

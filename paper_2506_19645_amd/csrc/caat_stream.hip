@@ -1,6 +1,7 @@
 // HBM-bound streaming kernels of the partial-sync block (gfx950): the partial channel-reduce of Eq. A3/A5 with
 // the residual add of Sec. 4, and the per-rank LayerNorm / RMSNorm forward and backward (Sec. 4, Fig. 2b).
 // All of them move 16-byte vectors (8 bf16), keep arithmetic in fp32 and round once.
+#include <algorithm>
 #include "caat_internal.h"
 
 namespace caat {
@@ -759,8 +760,13 @@ __global__ __launch_bounds__(256) void sync_norm_rank_kernel(const bf16_t* __res
 
 // up to four workgroups per compute unit, which all run at once; beyond that the T reads of the partial sums cost more than
 // the spreading gains
+static constexpr long long SYNC_NORM_RANK_MAX = 1024;
+static bool sync_norm_rank_ever(int T, int h) { return (T == 2 || T == 4 || T == 8) && h > 1024; }
 bool sync_norm_rank_takes(int T, long long tokens, int h, int hs) {
-  return sync_norm_takes(T, tokens, h, hs) && (T == 2 || T == 4 || T == 8) && h > 1024 && tokens * T <= 1024;
+  return sync_norm_takes(T, tokens, h, hs) && sync_norm_rank_ever(T, h) && tokens * T <= SYNC_NORM_RANK_MAX;
+}
+size_t sync_norm_rank_bytes(int T, long long tokens, int h) {
+  return sync_norm_rank_ever(T, h) ? (size_t)std::min(tokens * T, SYNC_NORM_RANK_MAX) * (size_t)h * 2 : 0;
 }
 
 // part [T,n,h]: partial sums on the shared channels, final values on the private ones; out = R', xout = RMSNorm(R')

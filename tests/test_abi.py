@@ -126,3 +126,33 @@ def test_descriptor_validation_of_the_attention_and_serving_fields():
     pre = I.C6
     assert B.workspace_bytes(B.make_desc(pre)) > 0
     assert B.workspace_bytes(B.make_desc(pre, kv_cap=pre.seq - 1)) > 0       # capacity is checked at the call, not here
+
+
+def test_one_workspace_serves_every_step_and_smaller_batches():
+    """Workspace sizes: a decode step's does not depend on the cache's length, nor any kind's layout in front of the scratch
+    on the way the reduce runs; no kind's falls when the number of tokens grows."""
+    base = I.BlockConfig("w", I.KIND_DECODE, I.NORM_RMSNORM, h=4096, T=8, p=0.5, batch=1, seq=1, ffn=11008, n_heads=32, head_dim=128)
+    for cfg in (base, base.with_(h=8192, n_heads=64, n_kv_heads=8, ffn=28672), base.with_(T=2, h=1024, n_heads=8, ffn=2816),
+                base.with_(T=1), base.with_(T=2, n_heads=34, n_kv_heads=2, h=34 * 128)):
+        at = lambda kv_len, kv_cap=70000: B.workspace_bytes(B.make_desc(cfg.with_(kv_len=kv_len), kv_cap=kv_cap))
+        assert {at(k) for k in list(range(0, 4200, 7)) + [65535]} == {at(0, 1)}
+        for kw in ({"hs": 0}, {"hs": 13}, {"separate_reduce": True}):
+            assert B.workspace_bytes(B.make_desc(cfg, **kw)) == at(0)
+    kinds = [(I.KIND_DECODE, dict(batch=1), {}), (I.KIND_DECODE, dict(batch=1), dict(reduce_in_gemm=True)),
+             (I.KIND_PREFILL, dict(seq=1), dict(reduce_in_gemm=True)), (I.KIND_PREFILL, dict(seq=1), {}),
+             (I.KIND_ATTN, dict(seq=1), dict(reduce_in_gemm=True)), (I.KIND_MLP_SWIGLU, dict(seq=1), dict(reduce_in_gemm=True))]
+    for T, h in ((8, 4096), (2, 8192), (4, 1024)):
+        for kind, size, kw in kinds:
+            cfg = base.with_(kind=kind, T=T, h=h, n_heads=h // 128)
+            key = next(iter(size))
+            last = 0
+            for n in list(range(1, 1300, 3)) + [2047, 2048, 2049, 4096, 5000, 32768]:
+                L = B.workspace_layout(B.make_desc(cfg.with_(**{key: n}), **kw))
+                assert L.total_bytes >= last
+                last = L.total_bytes
+    # the ways to run the reduce need the same workspace in front of a layer kind's scratch, and the same one of the others
+    for kind in (I.KIND_MLP_GELU, I.KIND_ATTN):
+        cfg = base.with_(kind=kind, seq=777)
+        assert B.workspace_bytes(B.make_desc(cfg, reduce_in_gemm=True)) == B.workspace_bytes(B.make_desc(cfg))
+    cfg = base.with_(kind=I.KIND_PREFILL, seq=777)
+    assert B.workspace_layout(B.make_desc(cfg, reduce_in_gemm=True)).off_scratch == B.workspace_bytes(B.make_desc(cfg))

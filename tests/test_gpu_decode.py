@@ -10,7 +10,7 @@ from tests.util import assert_close, bits_to_f64, make_inputs, hs_of
 pytestmark = pytest.mark.gpu
 
 
-def run_decode(cfg, d, reduce_in_gemm=False, separate_reduce=False):
+def run_decode(cfg, d, reduce_in_gemm=False, separate_reduce=False, ws=None):
     import torch
     desc = B.make_desc(cfg, reduce_in_gemm=reduce_in_gemm, separate_reduce=separate_reduce)
     T, b, h, hd = cfg.T, cfg.batch, cfg.h, cfg.hd_r
@@ -19,7 +19,8 @@ def run_decode(cfg, d, reduce_in_gemm=False, separate_reduce=False):
     r = B.to_device(d["R"])
     kc, vc = B.to_device(d["Kc"]), B.to_device(d["Vc"])
     r_out = torch.empty_like(r)
-    ws = torch.zeros(B.workspace_bytes(desc), dtype=torch.uint8, device="cuda")
+    if ws is None:
+        ws = torch.zeros(B.workspace_bytes(desc), dtype=torch.uint8, device="cuda")
     B.block_fwd(desc, weights, None, r, r_out, None, ws, kv_k=kc, kv_v=vc)
     torch.cuda.synchronize()
     L = B.workspace_layout(desc)
@@ -165,3 +166,30 @@ def test_decode_attention_probabilities_keep_fp32():
     # fp32: the score, its exponential and the sum are each off by at most about 2^-24; the output is rounded to bf16
     assert np.abs(got - want).max() <= 4 * 2.0 ** -24 / 3.0 + np.abs(want).max() * 2.0 ** -8
     assert np.abs(want).min() >= 2.0 ** -21
+
+
+@pytest.mark.parametrize("scratch", ["whole", "two ranges of keys", "one range", "none"])
+def test_decode_steps_on_one_workspace(scratch):
+    """A workspace sized at the first step serves every length of the cache, through several numbers of key ranges, and
+    smaller batches; one that ends anywhere in the scratch is good for the same results, with fewer ranges and the
+    reduce + norm in place.  Nothing is written behind it."""
+    import torch
+    first = _cfg(4, 2, 12, 4 * 128, 0, 0.5)
+    L = B.workspace_layout(B.make_desc(first))
+    row = 4 * 2 * 3 * (128 + 4) * 4            # partial results of one range for all query heads
+    spread = 4 * 2 * first.h * 2               # the o_proj output of the reduce + norm per (token, rank)
+    assert row < spread < 2 * row < L.bytes_scratch
+    size = {"whole": L.total_bytes, "two ranges of keys": L.off_scratch + 2 * row, "one range": L.off_scratch + row,
+            "none": L.off_scratch}[scratch]
+    guarded = torch.full((size + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+    for batch, length in ((2, 0), (2, 15), (2, 140), (2, 700), (1, 700), (2, 1600), (2, 2500)):
+        cfg = _cfg(4, batch, 12, 4 * 128, length, 0.5)
+        d = make_inputs(cfg, seed=47, weight_std=0.05)
+        got = run_decode(cfg, d, ws=guarded[:size])
+        ref = oracle_decode(cfg, d)
+        for name in ("X1", "H", "R1", "X2", "R2"):
+            assert_close(got[name], ref[name], name)
+        assert bool((guarded[size:] == 0xA5).all())
+    with pytest.raises(B.CaatError) as e:
+        run_decode(first, make_inputs(first, seed=47), ws=guarded[:L.off_scratch - 1])
+    assert e.value.status == B.EWORKSPACE

@@ -16,7 +16,8 @@ def layer_weights(d):
             B.to_device(np.concatenate([d["Wg"], d["Wu"]], axis=1)), B.to_device(d["B"])]
 
 
-def run_prefill(cfg, d, kv_cap=None, keep=("X1", "H", "R1", "X2"), reduce_in_gemm=False, separate_reduce=False):
+def run_prefill(cfg, d, kv_cap=None, keep=("X1", "H", "R1", "X2"), reduce_in_gemm=False, separate_reduce=False,
+                ws=None):
     import torch
     desc = B.make_desc(cfg, kv_cap=kv_cap, reduce_in_gemm=reduce_in_gemm, separate_reduce=separate_reduce)
     T, n, h, hd, hpr = cfg.T, cfg.tokens, cfg.h, cfg.hd_r, cfg.kv_heads // cfg.T     # hpr: key / value heads per rank
@@ -26,7 +27,8 @@ def run_prefill(cfg, d, kv_cap=None, keep=("X1", "H", "R1", "X2"), reduce_in_gem
     kc = torch.zeros((T, cfg.batch, hpr, cap, cfg.head_dim), dtype=torch.bfloat16, device="cuda")
     vc = torch.zeros_like(kc)
     r_out = torch.empty_like(r)
-    ws = torch.zeros(B.workspace_bytes(desc), dtype=torch.uint8, device="cuda")
+    if ws is None:
+        ws = torch.zeros(B.workspace_bytes(desc), dtype=torch.uint8, device="cuda")
     B.block_fwd(desc, weights, None, r, r_out, None, ws, kv_k=kc, kv_v=vc)
     torch.cuda.synchronize()
     L = B.workspace_layout(desc)

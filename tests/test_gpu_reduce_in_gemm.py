@@ -70,13 +70,21 @@ def test_prefill_layer_reduce_in_gemm():
         assert np.array_equal(got["R2_bits"][m, :, :hs_of(cfg)], got["R2_bits"][0, :, :hs_of(cfg)])
 
 
-def test_prefill_layer_reduce_over_groups_of_ranks():
-    """A prompt whose shared GEMM is cut into groups of ranks (both projections need scratch for their fp32 sums)."""
+@pytest.mark.parametrize("groups", [4, 2, 1])
+def test_prefill_layer_reduce_over_groups_of_ranks(groups):
+    """A prompt whose shared GEMM is cut into groups of ranks, as many as the workspace has scratch for; nothing is written
+    behind it."""
+    import torch
     from paper_2506_19645_amd import binding as B
     cfg = pre_cfg(4, 1, 130, 8, 4 * 1032, 0.5)
-    assert B.workspace_layout(B.make_desc(cfg, reduce_in_gemm=True)).bytes_scratch > 0
+    L = B.workspace_layout(B.make_desc(cfg, reduce_in_gemm=True))
+    one = 130 * hs_of(cfg) * 4                 # fp32 sums of one group
+    assert 4 * one <= L.bytes_scratch < 5 * one
+    size = L.off_scratch + (groups * one if groups > 1 else 0)
+    guarded = torch.full((size + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
     d = make_inputs(cfg, seed=57, weight_std=0.05)
-    got = run_prefill(cfg, d, reduce_in_gemm=True)
+    got = run_prefill(cfg, d, reduce_in_gemm=True, ws=guarded[:size])
+    assert bool((guarded[size:] == 0xA5).all())
     w, ref = oracle_prefill(cfg, d)
     check_prefill(cfg, d, got, ref)
     for m in range(1, cfg.T):
