@@ -46,7 +46,8 @@ class caat_ws_layout(C.Structure):
 EXPORTS = ["caat_shared_channels", "caat_status_string", "caat_workspace_bytes", "caat_workspace_layout",
            "caat_partial_sync", "caat_norm_fwd", "caat_partial_sync_norm_fwd", "caat_norm_bwd_workspace_bytes",
            "caat_norm_bwd", "caat_norm_bwd_static", "caat_gemm_bf16", "caat_block_fwd", "caat_block_bwd"]
-TOOL_EXPORTS = ["caat_profile_enable", "caat_profile_reset", "caat_profile_count", "caat_profile_get", "caat_hbm_probe"]
+TOOL_EXPORTS = ["caat_profile_enable", "caat_profile_reset", "caat_profile_count", "caat_profile_get", "caat_hbm_probe",
+                "caat_gemm_route"]
 
 _lib = None
 
@@ -96,6 +97,8 @@ def lib() -> C.CDLL:
         L.caat_profile_get.restype = i
         L.caat_hbm_probe.argtypes = [vp, vp, C.c_size_t, i, vp]
         L.caat_hbm_probe.restype = i
+        L.caat_gemm_route.argtypes = [i, i, i, ll, ll, ll, i, ll]
+        L.caat_gemm_route.restype = i
         _lib = L
     return _lib
 
@@ -264,6 +267,10 @@ def block_bwd(desc: caat_desc, weights: Sequence, x, r_out, workspace, dx_out, d
 
 def hbm_probe(src, dst, nbytes: int, mode: int, stream=None) -> None:
     _check(lib().caat_hbm_probe(_ptr(src), _ptr(dst), nbytes, mode, _stream(stream)), "caat_hbm_probe")
+
+
+def gemm_route(layout: int, epilogue: int, G: int, M: int, N: int, K: int, ranks: int = 1, shard_cols: int = 0) -> int:
+    return lib().caat_gemm_route(layout, epilogue, G, M, N, K, ranks, shard_cols)
 
 
 def profile_enable(on: bool) -> None:

@@ -531,6 +531,17 @@ int caat_hbm_probe(const void* src, void* dst, size_t bytes, int mode, void* hip
   return hip_status(launch_hbm_probe(src, dst, bytes, mode, (hipStream_t)hip_stream));
 }
 
+int caat_gemm_route(int layout, int epilogue, int G, long long M, long long N, long long K, int ranks, long long shard_cols) {
+  constexpr long long MAX = 0x7FFFFFFFLL;
+  if (layout < CAAT_GEMM_NT || layout > CAAT_GEMM_TN || epilogue < EPI_PLAIN || epilogue > EPI_PARTIAL || G < 1 || ranks < 1 || M < 1 ||
+      N < 1 || K < 1 || M > MAX || N > MAX || K > MAX || shard_cols < 0 || shard_cols > MAX)
+    return -1;
+  GemmParams p;
+  std::memset(&p, 0, sizeof(p));
+  p.G = G; p.M = (int)M; p.N = (int)N; p.K = (int)K; p.kcat = ranks; p.n_route = (int)shard_cols;
+  return gemm_route(p, layout, epilogue);
+}
+
 int caat_profile_enable(int on) {
   g_prof_on = on != 0;
   return CAAT_OK;

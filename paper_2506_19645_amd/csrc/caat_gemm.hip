@@ -53,9 +53,9 @@ static int choose_skinny_width(int G, int N, int epilogue) {
 // constants are fitted to the shapes of some training and prefill blocks, all three layouts, 40 launches from 150 to 8192
 // rows timed with every tile shape: the choice by the model is 0.4 % slower than the fastest shape on their average.
 // The last two shapes share a tile's contraction between two groups of four waves: for launches with a tile or less per
-// compute unit, whose time is the chain of stages and not the matrix unit.  They are for the gradients only (NN, TN): an
-// output of the forward pass (NT) is one sum in ascending k whatever the launch, so that a channel's bits are the same
-// with the reduce inside the GEMM and as a pass of its own.
+// compute unit, whose time is the chain of stages and not the matrix unit.  They are for the gradients only (NN, TN): a
+// tile of the forward pass (NT) is one sum in ascending k whatever its shape, so that a channel's bits are the same with
+// the reduce inside the GEMM and as a pass of its own (for 65 to 128 rows see gemm_route).
 // Examples (us; 256 x 256, 192 x 256, 256 x 192, 128 x 128, 64 x 128, 64 x 64, 128 x 128 and 64 x 64 shared; G x M x N x K):
 //   NT 8 x 777 x 1536 x 4096     111 /  99 /  99 / 123 / 123 / 153 / 124 / 172
 //   TN 4 x 2048 x 1408 x 1111   34.4 / 50.3 / 31.4 / 38.8 / 42.2 / 56.2 / 46.6 / 73.2
@@ -98,6 +98,41 @@ static int choose_tile(const GemmParams& p, int layout, int epilogue, int n_cu, 
   return best;
 }
 
+// Few token rows (NT): the weights are what has to be read.  The streaming kernel reads them best, except where many token
+// rows meet many weight rows: every workgroup reads all of its token rows, so there a tile kernel takes over (the 64 x 128
+// one up to 64 token rows).  Streaming / tile kernel, us, weights from HBM:
+//   17 - 48   below 128 weight rows per compute unit.  32 token rows: 24576 of 2048 k 20.4 / 23.3, 28672 of 8192 79 / 91, 32768
+//             of 1376 23.3 / 23.1, of 512 12.2 / 10.0; 48 token rows: 24576 of 2048 23.4 / 23.8, 28672 of 8192 90 / 93, 32768 of
+//             1376 29.5 / 23.9; above the line at best 8 % faster (49152 of 2048), below it at worst 22 % slower (27648 of 5120)
+//   49 - 64   below 96.  64 token rows: 16384 of 3072 22.7 / 23.9, 22016 of 4096 38.0 / 38.6, 20480 of 1728 19.4 / 16.6, 24576 of
+//             2048 25.0 / 23.9, 27648 of 5120 68 / 54, 32768 of 1376 29.5 / 24.5
+//   65 - 128  while one round of workgroups covers the launch, or two of the widest a long contraction.  96 token rows, one
+//             round: 6144 of 4096 17.1 / 24.2, 12288 of 4096 28.4 / 36.8; two of the widest: 20480 of 1728 28.9 / 27.7, 24576 of
+//             2048 33.9 / 33.2, 22016 of 4096 56.8 / 57.8 (in a layer 61.0 / 63.2); other: 8192 of 5504 35.7 / 33.6, 16384 of
+//             1376 25.7 / 20.8, 28672 of 4096 75.7 / 62.3, 32768 of 512 23.7 / 12.8, but 18432 of 6144 76 / 88
+enum { ROUTE_FEW_ROWS = 8, ROUTE_STREAM = 16 };
+static int choose_route(const GemmParams& p, int layout, int epilogue, int n_cu) {
+  if (layout == 0 && p.M <= 128 && epilogue != EPI_SHARED_BCAST && epilogue != EPI_PARTIAL) {
+    GemmParams q = p;
+    if (p.n_route > 0) q.N = p.n_route;
+    const long long wrows = (long long)q.G * q.N * (epilogue == EPI_SWIGLU_FWD ? 2 : 1);
+    const StreamTile t = choose_stream_tile(q, epilogue, n_cu);
+    bool stream = true;
+    if (p.M > 64) stream = t.tiles <= n_cu || (t.tiles <= 2LL * n_cu && t.rt == 6 && p.K >= 4096);
+    else if (p.M > 16) stream = wrows < (p.M <= 48 ? 128LL : 96LL) * n_cu;
+    if (stream) return ROUTE_STREAM;
+    if (p.M <= 64) return ROUTE_FEW_ROWS;
+  }
+  return choose_tile(p, layout, epilogue, n_cu);
+}
+
+int gemm_route(const GemmParams& p, int layout, int epilogue) {
+  const int route = choose_route(p, layout, epilogue, compute_units());
+  if (route != ROUTE_STREAM) return route;
+  const StreamTile t = choose_stream_tile(p, epilogue, compute_units());
+  return t.mt * 16 + t.rt + (t.two_waves ? 128 : 0);
+}
+
 hipError_t launch_gemm(const GemmParams& p, int layout, int epilogue, hipStream_t s) {
   // buffer-load offsets are 32-bit and relative to the tile origin: the farthest row a tile touches times the
   // row stride must stay below 2 GiB
@@ -108,29 +143,9 @@ hipError_t launch_gemm(const GemmParams& p, int layout, int epilogue, hipStream_
   const long long elem = epilogue == EPI_PARTIAL ? 4 : 2;
   if ((256 * ldmax + 2 * (long long)p.half + (long long)p.N) * elem >= 0x7FFFFFFFLL) return hipErrorInvalidValue;
   const int n_cu = compute_units();
-  if (layout == 0 && p.M <= 128 && epilogue != EPI_SHARED_BCAST && epilogue != EPI_PARTIAL) {
-    // Few token rows: the weights are what has to be read.  The streaming kernel, except where 17 rows or more meet so
-    // many weight rows that 128 of them fall to every compute unit: there the 64 x 128 tile (the 128 x 128 one from 65
-    // rows on) reads the token rows half as often.  Measured (us, streaming kernel / tile kernel): 32768 rows of 1376 k,
-    // 16 token rows 20.6 / 22.1, 32: 23.7 / 22.4, 64: 28.6 / 24.3, 128: 46 / 30; 57344 rows of 8192 k, 64 token rows
-    // 177 / 172, 128: 278 / 213; 12288 rows of 4096 k, 64 token rows 22.9 / 26.1, 128: 31.5 / 60.8.
-    const long long wrows = (long long)p.G * p.N * (epilogue == EPI_SWIGLU_FWD ? 2 : 1);
-    if (p.M <= 16 || wrows < 128LL * n_cu) return launch_gemm_stream(p, epilogue, n_cu, s);
-    if (p.M <= 64) {
-      GemmParams q = p;
-      q.bn_out = choose_skinny_width(p.G, p.N, epilogue);
-      switch (epilogue) {
-        case EPI_PLAIN: return launch_one<CfgSkinny, false, false, EPI_PLAIN>(q, s);
-        case EPI_GELU_FWD: return launch_one<CfgSkinny, false, false, EPI_GELU_FWD>(q, s);
-        case EPI_SWIGLU_FWD: return launch_one<CfgSkinny, false, false, EPI_SWIGLU_FWD>(q, s);
-        case EPI_ROWPAR: return launch_one<CfgSkinny, false, false, EPI_ROWPAR>(q, s);
-        default: return hipErrorInvalidValue;
-      }
-    }
-  }
   GemmParams q = p;
   q.bn_out = 0;  // block-sized tiles always cover their full width
-  switch (choose_tile(p, layout, epilogue, n_cu)) {
+  switch (choose_route(p, layout, epilogue, n_cu)) {
     case 0: return launch_block_sized<Cfg256x256>(q, layout, epilogue, s);
     case 1: return launch_block_sized<Cfg192x256>(q, layout, epilogue, s);
     case 2: return launch_block_sized<Cfg256x192>(q, layout, epilogue, s);
@@ -138,7 +153,17 @@ hipError_t launch_gemm(const GemmParams& p, int layout, int epilogue, hipStream_
     case 4: return launch_block_sized<Cfg64x128>(q, layout, epilogue, s);
     case 5: return launch_block_sized<Cfg64x64>(q, layout, epilogue, s);
     case 6: return launch_block_sized<Cfg128x128k>(q, layout, epilogue, s);
-    default: return launch_block_sized<Cfg64x64k>(q, layout, epilogue, s);
+    case 7: return launch_block_sized<Cfg64x64k>(q, layout, epilogue, s);
+    case ROUTE_STREAM: return launch_gemm_stream(p, epilogue, n_cu, s);
+    default: break;
+  }
+  q.bn_out = choose_skinny_width(p.G, p.N, epilogue);
+  switch (epilogue) {
+    case EPI_PLAIN: return launch_one<CfgSkinny, false, false, EPI_PLAIN>(q, s);
+    case EPI_GELU_FWD: return launch_one<CfgSkinny, false, false, EPI_GELU_FWD>(q, s);
+    case EPI_SWIGLU_FWD: return launch_one<CfgSkinny, false, false, EPI_SWIGLU_FWD>(q, s);
+    case EPI_ROWPAR: return launch_one<CfgSkinny, false, false, EPI_ROWPAR>(q, s);
+    default: return hipErrorInvalidValue;
   }
 }
 

@@ -14,11 +14,11 @@ static hipError_t stream_launch(const GemmParams& p, hipStream_t s) {
 // Widths a workgroup may cover: RT tiles of 16 weight rows per MT tiles of 16 token rows, with the LDS that gives every
 // wave two slots or more and, for few token rows, two or three workgroups per compute unit.
 template <int EPI>
-static hipError_t stream_plain(const GemmParams& p, int mt, int rt, bool short_k, hipStream_t s) {
-  switch (mt * 8 + rt) {
-    case 8 + 2: return short_k ? stream_launch<1, 2, 2, 24, EPI>(p, s) : stream_launch<1, 2, 4, 48, EPI>(p, s);
+static hipError_t stream_plain(const GemmParams& p, const StreamTile& t, hipStream_t s) {
+  switch (t.mt * 8 + t.rt) {
+    case 8 + 2: return t.two_waves ? stream_launch<1, 2, 2, 24, EPI>(p, s) : stream_launch<1, 2, 4, 48, EPI>(p, s);
     case 8 + 3: return stream_launch<1, 3, 4, 64, EPI>(p, s);
-    case 8 + 4: return short_k ? stream_launch<1, 4, 2, 40, EPI>(p, s) : stream_launch<1, 4, 4, 80, EPI>(p, s);
+    case 8 + 4: return t.two_waves ? stream_launch<1, 4, 2, 40, EPI>(p, s) : stream_launch<1, 4, 4, 80, EPI>(p, s);
     case 16 + 2: return stream_launch<2, 2, 4, 64, EPI>(p, s);
     case 16 + 3: return stream_launch<2, 3, 4, 80, EPI>(p, s);
     case 16 + 4: return stream_launch<2, 4, 4, 96, EPI>(p, s);
@@ -32,8 +32,8 @@ static hipError_t stream_plain(const GemmParams& p, int mt, int rt, bool short_k
     default: return hipErrorInvalidValue;
   }
 }
-static hipError_t stream_swiglu(const GemmParams& p, int mt, int rt, hipStream_t s) {
-  switch (mt * 8 + rt) {
+static hipError_t stream_swiglu(const GemmParams& p, const StreamTile& t, hipStream_t s) {
+  switch (t.mt * 8 + t.rt) {
     case 8 + 2: return stream_launch<1, 2, 4, 48, EPI_SWIGLU_FWD>(p, s);
     case 16 + 2: return stream_launch<2, 2, 4, 64, EPI_SWIGLU_FWD>(p, s);
     case 16 + 4: return stream_launch<2, 4, 4, 96, EPI_SWIGLU_FWD>(p, s);
@@ -48,40 +48,45 @@ static hipError_t stream_swiglu(const GemmParams& p, int mt, int rt, hipStream_t
   }
 }
 
-hipError_t launch_gemm_stream(const GemmParams& p, int epilogue, int n_cu, hipStream_t s) {
+StreamTile choose_stream_tile(const GemmParams& p, int epilogue, int n_cu) {
   const bool swi = epilogue == EPI_SWIGLU_FWD;
   const int m16 = (p.M + 15) / 16, tiles_m = (m16 + 3) / 4, mt = (m16 + tiles_m - 1) / tiles_m;
   // a wave should have some chunks of k: with fewer than 18 chunks of 64 two waves share a workgroup's contraction (us, two
   // waves / four: K = 512, 1 token row, 33 MB 8.4 / 10.4; K = 1024, 16 rows, 134 MB 25.0 / 26.9; K = 1376, 1 row, 90 MB
   // 21.5 / 19.0)
-  const bool short_k = (p.K + 63) / 64 < 18;
+  StreamTile t = {mt, 0, 0, !swi && mt == 1 && (p.K + 63) / 64 < 18, 0};
   // A launch takes as long as the compute unit with the most rows to read: the weight rows of a tile plus its token
   // rows (from L2, at about a third of the cost), times the tiles a compute unit gets.
   static const int plain_rt[4][4] = {{2, 3, 4, 0}, {2, 3, 4, 0}, {2, 3, 6, 0}, {2, 3, 4, 6}};
   static const int swiglu_rt[4][4] = {{2, 0, 0, 0}, {2, 4, 6, 0}, {2, 4, 6, 0}, {2, 4, 6, 0}};
-  int best_rt = 0, best_bn = 0;
   double best = 0.0;
   for (int i = 0; i < 4; ++i) {
     const int rt = swi ? swiglu_rt[mt - 1][i] : plain_rt[mt - 1][i];
-    if (rt == 0 || (short_k && mt == 1 && rt == 3)) continue;
+    if (rt == 0 || (t.two_waves && rt == 3)) continue;
     const int full = (swi ? rt / 2 : rt) * 16;
     for (int bn = full; bn > full - 16; bn -= 8) {
-      const long long tiles = (long long)tiles_m * ((p.N + bn - 1) / bn) * p.G;
+      const long long tiles = (long long)tiles_m * (((long long)p.N + bn - 1) / bn) * p.G;
       const double cost = (double)((tiles + n_cu - 1) / n_cu) * ((swi ? 2 : 1) * bn + 0.3 * 16 * mt);
-      if (best_rt == 0 || cost < best) {
+      if (t.rt == 0 || cost < best) {
         best = cost;
-        best_rt = rt;
-        best_bn = bn;
+        t.rt = rt;
+        t.bn = bn;
+        t.tiles = tiles;
       }
     }
   }
+  return t;
+}
+
+hipError_t launch_gemm_stream(const GemmParams& p, int epilogue, int n_cu, hipStream_t s) {
+  const StreamTile t = choose_stream_tile(p, epilogue, n_cu);
   GemmParams q = p;
-  q.bn_out = best_bn;
+  q.bn_out = t.bn;
   switch (epilogue) {
-    case EPI_PLAIN: return stream_plain<EPI_PLAIN>(q, mt, best_rt, short_k, s);
-    case EPI_GELU_FWD: return stream_plain<EPI_GELU_FWD>(q, mt, best_rt, short_k, s);
-    case EPI_ROWPAR: return stream_plain<EPI_ROWPAR>(q, mt, best_rt, short_k, s);
-    case EPI_SWIGLU_FWD: return stream_swiglu(q, mt, best_rt, s);
+    case EPI_PLAIN: return stream_plain<EPI_PLAIN>(q, t, s);
+    case EPI_GELU_FWD: return stream_plain<EPI_GELU_FWD>(q, t, s);
+    case EPI_ROWPAR: return stream_plain<EPI_ROWPAR>(q, t, s);
+    case EPI_SWIGLU_FWD: return stream_swiglu(q, t, s);
     default: return hipErrorInvalidValue;
   }
 }

@@ -197,6 +197,7 @@ struct GemmParams {
   int bcast;           // EPI_SHARED_BCAST: number of output copies (ranks)
   int late_c;          // EPI_PLAIN: c is not read again soon (weight / input gradients): store it with the non-temporal hint
   int bn_out;          // decode-sized tiles: output columns one tile covers (0 = the tile's full width); set by launch_gemm
+  int n_route;         // EPI_ROWPAR on a part of a shard's columns: the columns of the whole shard (0 = N); see gemm_route
 };
 
 // layout: 0 NT, 1 NN, 2 TN (see caat_gemm_layout).  Returns hipError_t of the launch.
@@ -208,7 +209,17 @@ hipError_t launch_gemm_shared(const GemmParams& p, void* scratch, size_t scratch
 // the second kernel: for m in [0, bcast): out[m] = round_bf16(sum over groups of part) + resid[m]; part [groups][M][N] fp32
 hipError_t launch_shared_merge(const float* part, int groups, const bf16_t* resid, bf16_t* out, long long M, int N, long long ldr,
                                long long ldo, long long stride_r, long long stride_o, int bcast, hipStream_t s);
-// NT, at most 128 token rows, EPI_PLAIN / EPI_GELU_FWD / EPI_SWIGLU_FWD / EPI_ROWPAR (launch_gemm decides when)
+// The kernel that launch_gemm takes: a tile shape 0 .. 7, 8 the tile for few token rows, from 16 on the streaming kernel,
+// 16 mt + rt (+ 128 where two waves share a contraction; see StreamTile)
+int gemm_route(const GemmParams& p, int layout, int epilogue);
+// NT, at most 128 token rows, EPI_PLAIN / EPI_GELU_FWD / EPI_SWIGLU_FWD / EPI_ROWPAR (gemm_route decides when)
+struct StreamTile {
+  int mt, rt;        // 16 mt token rows x 16 rt weight rows per workgroup
+  int bn;            // output columns it covers
+  bool two_waves;    // that share the contraction, instead of four
+  long long tiles;
+};
+StreamTile choose_stream_tile(const GemmParams& p, int epilogue, int n_cu);
 hipError_t launch_gemm_stream(const GemmParams& p, int epilogue, int n_cu, hipStream_t s);
 
 // ---------------------------------------------------------------- streaming kernels
