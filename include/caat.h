@@ -23,6 +23,9 @@
  *  - Device pointers must be 16-byte aligned; h, ffn/T and (n_heads/T)*head_dim must be multiples
  *    of 8.  hs may be any integer in [0, h].
  *  - Calls that overlap in time must not share output or workspace buffers.
+ *  - The same call on the same inputs gives the same bits.  The order in which an fp32 sum is taken follows from the sizes
+ *    of the call (tokens, keys in the cache, widths) and, for the layer kinds, from the scratch they are given: a token's
+ *    result may differ in its last bit between batches of different size.
  */
 #ifndef CAAT_H
 #define CAAT_H

@@ -211,6 +211,7 @@ int rowpar_pcr(const caat_desc* d, const bf16_t* a, long long kdim, const bf16_t
       q.aux = resid_p; q.ldaux = ldp; q.stride_aux = n * ldp;
       q.G = (int)T; q.M = (int)n; q.N = (int)(h - hs); q.K = (int)kdim;
       q.hs = 0; q.scale = d->private_scale;
+      q.n_route = (int)h;   // the kernel, and so the order of the sums, as without reduce_in_gemm
       {
         ProfScope ps(s, "gemm_nt_rowpar_private");
         e = launch_gemm(q, 0, EPI_ROWPAR, s);

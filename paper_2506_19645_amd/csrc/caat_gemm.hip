@@ -110,6 +110,8 @@ static int choose_tile(const GemmParams& p, int layout, int epilogue, int n_cu, 
 //             round: 6144 of 4096 17.1 / 24.2, 12288 of 4096 28.4 / 36.8; two of the widest: 20480 of 1728 28.9 / 27.7, 24576 of
 //             2048 33.9 / 33.2, 22016 of 4096 56.8 / 57.8 (in a layer 61.0 / 63.2); other: 8192 of 5504 35.7 / 33.6, 16384 of
 //             1376 25.7 / 20.8, 28672 of 4096 75.7 / 62.3, 32768 of 512 23.7 / 12.8, but 18432 of 6144 76 / 88
+// The streaming kernel adds up sums of several waves, the tiles are one sum.  So a row-parallel GEMM on the private columns
+// of a shard alone (reduce_in_gemm, more than 64 rows) goes by the columns of the whole shard, as without reduce_in_gemm.
 enum { ROUTE_FEW_ROWS = 8, ROUTE_STREAM = 16 };
 static int choose_route(const GemmParams& p, int layout, int epilogue, int n_cu) {
   if (layout == 0 && p.M <= 128 && epilogue != EPI_SHARED_BCAST && epilogue != EPI_PARTIAL) {

@@ -26,6 +26,9 @@ pytestmark = pytest.mark.gpu
     (8, 300, 1024, 8 * 136, 0.5, 1.0),          # T = 8, 136 columns per rank (4 stages + tail of 8)
     (6, 200, 784, 6 * 1032, 0.5, 1.0),          # long contractions, few tiles: sums over groups of ranks, two groups of three
     (8, 131, 1568, 8 * 1032, 0.25, 1.0),        # ... and groups of a single rank, a ragged last tile in both directions
+    # few rows of a wide shard: tiles for all of its columns, a kernel with several sums per output for the private ones alone
+    (8, 65, 2048, 8 * 264, 0.5, 1.0), (8, 100, 2048, 8 * 264, 0.75, 1.0), (8, 128, 4096, 8 * 264, 0.5, 1.0),
+    (2, 100, 2048, 2 * 1032, 0.5, 1.0),         # ... that kernel for both
 ])
 def test_mlp_block_reduce_in_gemm(swi, T, n, h, ffn, p, scale):
     cfg = mlp_cfg(swi, T, n, h, ffn, p, scale)
