@@ -85,7 +85,7 @@ typedef struct caat_desc {
   float eps;            /* norm epsilon */
   float private_scale;  /* factor applied to private channels (Sec. 4 private channel scaling,
                            sqrt(T) in the paper); 1.0f switches it off */
-  float rope_base;      /* RoPE base (10000) */
+  float rope_base;      /* RoPE base (10000); attention and layer kinds: > 0, else CAAT_EINVAL from the forward / backward call */
   int n_kv_heads;       /* grouped-query attention: key / value heads over all ranks; 0 = n_heads (multi-head).
                            n_heads % n_kv_heads == 0 and n_kv_heads % T == 0 (each rank owns whole groups) */
   int reduce_in_gemm;   /* forward only.  0: every rank's partial sum on the shared channels is written out and a reduce

@@ -259,6 +259,7 @@ int attn_block_fwd(const caat_desc* d, const caat_ws_layout& L, const void* cons
                    void* r_out, void* x_out, void* workspace, size_t ws_bytes, void* hip_stream) {
   const void* wqkv = weights[0]; const void* wo = weights[1]; const void* gamma = weights[2]; const void* beta = weights[3];
   if (!wqkv || !wo || !gamma || (d->norm == CAAT_LAYERNORM && !beta)) return CAAT_EINVAL;
+  if (!(d->rope_base > 0.0f)) return CAAT_EINVAL;
   if (d->head_dim != 128) return CAAT_EUNSUPPORTED;
   if (misaligned(wqkv) || misaligned(wo) || misaligned(gamma) || (beta && misaligned(beta)) || misaligned(x) ||
       misaligned(r) || misaligned(r_out) || misaligned(x_out) || misaligned(workspace))
@@ -323,6 +324,7 @@ int attn_block_bwd(const caat_desc* d, const caat_ws_layout& L, const void* cons
   const void* wqkv = weights[0]; const void* wo = weights[1]; const void* gamma = weights[2];
   void* dwqkv = dweights[0]; void* dwo = dweights[1];
   if (!wqkv || !wo || !gamma || !dwqkv || !dwo || (d->norm == CAAT_LAYERNORM && !dbeta)) return CAAT_EINVAL;
+  if (!(d->rope_base > 0.0f)) return CAAT_EINVAL;
   if (d->head_dim != 128) return CAAT_EUNSUPPORTED;
   if (misaligned(wqkv) || misaligned(wo) || misaligned(gamma) || misaligned(dwqkv) || misaligned(dwo) || misaligned(x) ||
       misaligned(r_out) || misaligned(workspace) || misaligned(dx_out) || misaligned(dr_out) || misaligned(dx) ||
@@ -406,6 +408,7 @@ int layer_fwd(const caat_desc* d, const caat_ws_layout& L, const void* const* we
   const void* g_attn = weights[0]; const void* wqkv = weights[1]; const void* wo = weights[2];
   const void* g_mlp = weights[3]; const void* wgu = weights[4]; const void* wb = weights[5];
   if (!g_attn || !wqkv || !wo || !g_mlp || !wgu || !wb) return CAAT_EINVAL;
+  if (!(d->rope_base > 0.0f)) return CAAT_EINVAL;
   if (d->norm != CAAT_RMSNORM || d->head_dim != 128) return CAAT_EUNSUPPORTED;
   if (prefill) {
     if (d->kv_len != 0 || d->kv_cap < d->seq) return CAAT_ESHAPE;     // the prompt starts an empty cache

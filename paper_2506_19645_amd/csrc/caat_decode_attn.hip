@@ -37,10 +37,9 @@ static constexpr int DNI = 8;                    // 1 KB copies per block: 4 of 
 __device__ __forceinline__ int dk_swz(int row) { return row & 15; }
 __device__ __forceinline__ int dv_swz(int row) { return (row & 7) << 1; }
 
-// ROPE: qkv holds the UN-rotated projections of the token at position nkeys - 1; q and the new k are rotated here
-// (rounded to bf16 as the RoPE kernels store them), the new k and v take part from registers and are written to cache
-// row nkeys - 1, which nobody reads in this launch.  Otherwise q is rotated already and all nkeys keys are cached.
-template <bool ROPE>
+// qkv holds the UN-rotated projections of the token at position nkeys - 1; q and the new k are rotated here (rounded to
+// bf16 as the RoPE kernels store them), the new k and v take part from registers and are written to cache row nkeys - 1,
+// which nobody reads in this launch.
 __global__ __launch_bounds__(64 * DNW) void decode_attn_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ kc,
                                                                bf16_t* __restrict__ vc, bf16_t* __restrict__ out,
                                                                float* __restrict__ part, int hpr, int kvpr, long long cap,
@@ -65,7 +64,7 @@ __global__ __launch_bounds__(64 * DNW) void decode_attn_kernel(const bf16_t* __r
   const int head0 = kvh * grp + qt * 16;         // the first, inside the rank
   const bf16_t* kbase = kc + (long long)u * cap * DHD;
   const bf16_t* vbase = vc + (long long)u * cap * DHD;
-  const int ncache = ROPE ? nkeys - 1 : nkeys;   // keys that come from the caches
+  const int ncache = nkeys - 1;                  // keys that come from the caches
   const int nb = (nkeys + DKB - 1) / DKB;        // blocks; the new key sits in the last one
   const int b0 = (int)((long long)nb * split / splits), b1 = (int)((long long)nb * (split + 1) / splits);
 
@@ -90,13 +89,13 @@ __global__ __launch_bounds__(64 * DNW) void decode_attn_kernel(const bf16_t* __r
     const int hd = wave * 4 + g;
     static_assert(DNW == 4, "four query heads per wave");
     dma16(make_rsrc(row + (long long)head0 * DHD), hd < nq ? (unsigned)(hd * 256 + r16 * 16) : 0x80000000u, s_q + wave * 64);
-    if (ROPE && wave == 0 && lane < 32)
+    if (wave == 0 && lane < 32)
       dma16(make_rsrc(row + (long long)(hpr + kvh) * DHD), (unsigned)(g * kvpr * 256 + r16 * 16), s_q + 16 * 16);
   }
   // ... then the first keys are on their way while q is prepared
 #pragma unroll
   for (int i = 0; i < DNS; ++i) copy(b0 + wave + i * DNW, i);
-  if (ROPE && tid < 64) {
+  if (tid < 64) {
     // angle j of the position, j = 0 .. 63, once per workgroup (the same expressions as the RoPE kernels)
     const float inv = exp2f(-2.0f * (float)tid / 128.0f * log2_base);
     float sn, cs;
@@ -112,49 +111,47 @@ __global__ __launch_bounds__(64 * DNW) void decode_attn_kernel(const bf16_t* __r
     uint4 qw[4];
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) qw[ks] = s_q[r16 * 16 + ks * 4 + g];   // heads past nq were filled with zeros
-    if constexpr (ROPE) {
-      const uint4 kw = s_q[16 * 16 + r16];
-      vnew = s_q[17 * 16 + r16];
-      // q: the pairs (j, j + 64) of a lane's 8 dims are its slices ks and ks + 2
+    const uint4 kw = s_q[16 * 16 + r16];
+    vnew = s_q[17 * 16 + r16];
+    // q: the pairs (j, j + 64) of a lane's 8 dims are its slices ks and ks + 2
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        const unsigned x1[4] = {qw[ks].x, qw[ks].y, qw[ks].z, qw[ks].w}, x2[4] = {qw[ks + 2].x, qw[ks + 2].y, qw[ks + 2].z, qw[ks + 2].w};
-        unsigned y1[4], y2[4];
+    for (int ks = 0; ks < 2; ++ks) {
+      const unsigned x1[4] = {qw[ks].x, qw[ks].y, qw[ks].z, qw[ks].w}, x2[4] = {qw[ks + 2].x, qw[ks + 2].y, qw[ks + 2].z, qw[ks + 2].w};
+      unsigned y1[4], y2[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          float a[2], b[2];
+      for (int i = 0; i < 4; ++i) {
+        float a[2], b[2];
 #pragma unroll
-          for (int e = 0; e < 2; ++e) {
-            const float cs = s_cs[ks * 32 + g * 8 + i * 2 + e], sn = s_sn[ks * 32 + g * 8 + i * 2 + e];
-            const float p = e ? hi_bf(x1[i]) : lo_bf(x1[i]), q = e ? hi_bf(x2[i]) : lo_bf(x2[i]);
-            a[e] = p * cs - q * sn;
-            b[e] = q * cs + p * sn;
-          }
-          y1[i] = pack2bf(a[0], a[1]);
-          y2[i] = pack2bf(b[0], b[1]);
+        for (int e = 0; e < 2; ++e) {
+          const float cs = s_cs[ks * 32 + g * 8 + i * 2 + e], sn = s_sn[ks * 32 + g * 8 + i * 2 + e];
+          const float p = e ? hi_bf(x1[i]) : lo_bf(x1[i]), q = e ? hi_bf(x2[i]) : lo_bf(x2[i]);
+          a[e] = p * cs - q * sn;
+          b[e] = q * cs + p * sn;
         }
-        qw[ks] = make_uint4(y1[0], y1[1], y1[2], y1[3]);
-        qw[ks + 2] = make_uint4(y2[0], y2[1], y2[2], y2[3]);
+        y1[i] = pack2bf(a[0], a[1]);
+        y2[i] = pack2bf(b[0], b[1]);
       }
-      // the new key: lane r16 holds dims 8 r16 .. + 7, its pair is 8 lanes away
-      {
-        const unsigned own[4] = {kw.x, kw.y, kw.z, kw.w};
-        unsigned res[4];
+      qw[ks] = make_uint4(y1[0], y1[1], y1[2], y1[3]);
+      qw[ks + 2] = make_uint4(y2[0], y2[1], y2[2], y2[3]);
+    }
+    // the new key: lane r16 holds dims 8 r16 .. + 7, its pair is 8 lanes away
+    {
+      const unsigned own[4] = {kw.x, kw.y, kw.z, kw.w};
+      unsigned res[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const unsigned oth = (unsigned)__shfl_xor((int)own[i], 8, 64);
-          float y[2];
+      for (int i = 0; i < 4; ++i) {
+        const unsigned oth = (unsigned)__shfl_xor((int)own[i], 8, 64);
+        float y[2];
 #pragma unroll
-          for (int e = 0; e < 2; ++e) {
-            const int j = (r16 & 7) * 8 + i * 2 + e;
-            const float a = e ? hi_bf(own[i]) : lo_bf(own[i]), b = e ? hi_bf(oth) : lo_bf(oth);
-            const float cs = s_cs[j], sn = s_sn[j];
-            y[e] = r16 < 8 ? a * cs - b * sn : a * cs + b * sn;
-          }
-          res[i] = pack2bf(y[0], y[1]);
+        for (int e = 0; e < 2; ++e) {
+          const int j = (r16 & 7) * 8 + i * 2 + e;
+          const float a = e ? hi_bf(own[i]) : lo_bf(own[i]), b = e ? hi_bf(oth) : lo_bf(oth);
+          const float cs = s_cs[j], sn = s_sn[j];
+          y[e] = r16 < 8 ? a * cs - b * sn : a * cs + b * sn;
         }
-        knew = make_uint4(res[0], res[1], res[2], res[3]);
+        res[i] = pack2bf(y[0], y[1]);
       }
+      knew = make_uint4(res[0], res[1], res[2], res[3]);
     }
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) qf[ks] = __builtin_bit_cast(bf16x8_t, qw[ks]);
@@ -170,7 +167,7 @@ __global__ __launch_bounds__(64 * DNW) void decode_attn_kernel(const bf16_t* __r
       wait_vmcnt<(DNS - 1) * DNI>();             // this block has landed; the next ones may be in flight
       uint4* ks = mine + slot * (DNI * 64);
       uint4* vs = ks + 4 * 64;
-      if (ROPE && b == nb - 1 && g == 0) {       // the token's own key and value take their row of the last block
+      if (b == nb - 1 && g == 0) {               // the token's own key and value take their row of the last block
         const int r = (nkeys - 1) & (DKB - 1);
         ks[r * 16 + (r16 ^ dk_swz(r))] = knew;
         vs[r * 16 + (r16 ^ dv_swz(r))] = vnew;
@@ -264,7 +261,7 @@ __global__ __launch_bounds__(64 * DNW) void decode_attn_kernel(const bf16_t* __r
     sweep(std::true_type{});
     wait_vmcnt<0>();
   }
-  if (ROPE && qt == 0 && split == splits - 1 && wave == 0 && g == 0) {   // one 16-lane group writes the new rows of the caches
+  if (qt == 0 && split == splits - 1 && wave == 0 && g == 0) {   // one 16-lane group writes the new rows of the caches
     const long long dst = ((long long)u * cap + (nkeys - 1)) * DHD + r16 * 8;
     st_stream(kc + dst, knew);
     st_stream(vc + dst, vnew);
@@ -365,13 +362,11 @@ size_t decode_attn_scratch_bytes(long long n_seq, int hpr, int kvpr) {
 }
 
 // out [n_seq, hpr*128] = softmax(q K^T / sqrt(d)) V over keys 0 .. nkeys-1 of caches [n_seq][kvpr][cap][128].
-// rope_base > 0: qkv holds the un-rotated projections of the token at position nkeys - 1; the kernel rotates q and k,
-// uses the new key / value from registers and stores them at cache row nkeys - 1 (no RoPE + append launch needed).
-// rope_base = 0: q is rotated already and all nkeys keys are in the caches.
+// qkv as above; rope_base > 0.
 hipError_t launch_decode_attn(const bf16_t* qkv, bf16_t* kc, bf16_t* vc, bf16_t* out, long long n_seq, int hpr,
                               int kvpr, int d, long long cap, long long nkeys, float rope_base, void* scratch, size_t scratch_bytes,
                               hipStream_t s) {
-  if (d != DHD || kvpr < 1 || hpr % kvpr != 0 || nkeys < 1 || nkeys > cap || cap * 256 >= 0x7FFFFFFFLL)
+  if (d != DHD || kvpr < 1 || hpr % kvpr != 0 || nkeys < 1 || nkeys > cap || cap * 256 >= 0x7FFFFFFFLL || !(rope_base > 0.0f))
     return hipErrorInvalidValue;
   if (n_seq * hpr == 0) return hipSuccess;
   const long long units = n_seq * kvpr * ((hpr / kvpr + 15) / 16);
@@ -381,12 +376,8 @@ hipError_t launch_decode_attn(const bf16_t* qkv, bf16_t* kc, bf16_t* vc, bf16_t*
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)d);
   const dim3 grid((unsigned)(units * splits)), wg(64 * DNW);
   float* part = reinterpret_cast<float*>(scratch);
-  if (rope_base > 0.0f)
-    hipLaunchKernelGGL(decode_attn_kernel<true>, grid, wg, 0, s, qkv, kc, vc, out, part, hpr, kvpr, cap, (int)nkeys, scale_log2,
-                       log2f(rope_base), splits);
-  else
-    hipLaunchKernelGGL(decode_attn_kernel<false>, grid, wg, 0, s, qkv, kc, vc, out, part, hpr, kvpr, cap, (int)nkeys, scale_log2,
-                       0.0f, splits);
+  hipLaunchKernelGGL(decode_attn_kernel, grid, wg, 0, s, qkv, kc, vc, out, part, hpr, kvpr, cap, (int)nkeys, scale_log2,
+                     log2f(rope_base), splits);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || splits == 1) return e;
   hipLaunchKernelGGL(decode_merge_kernel, dim3((unsigned)(n_seq * hpr)), dim3(128), 0, s, part, out, splits);

@@ -156,3 +156,29 @@ def test_one_workspace_serves_every_step_and_smaller_batches():
         assert B.workspace_bytes(B.make_desc(cfg, reduce_in_gemm=True)) == B.workspace_bytes(B.make_desc(cfg))
     cfg = base.with_(kind=I.KIND_PREFILL, seq=777)
     assert B.workspace_layout(B.make_desc(cfg, reduce_in_gemm=True)).off_scratch == B.workspace_bytes(B.make_desc(cfg))
+
+
+def test_attention_kinds_refuse_a_rope_base_that_is_none():
+    """Base 0 or below, or NaN: refused by the forward and the backward call; sizes can still be asked for, and the MLP kinds
+    do not read it."""
+    class Workspace:      # stands in for a device buffer: the call ends before anything is read
+        is_cuda = True
+        def __init__(self, n): self.n = n
+        def numel(self): return self.n
+        def element_size(self): return 1
+        def is_contiguous(self): return True
+        def data_ptr(self): return 0x1000
+    fake = 0x1000
+    attn = I.BlockConfig("a", I.KIND_ATTN, I.NORM_RMSNORM, h=1024, T=2, p=0.5, batch=1, seq=256, n_heads=8, head_dim=128)
+    for base in (0.0, -1.0, float("nan")):
+        for cfg in (attn, attn.with_(kind=I.KIND_DECODE, seq=1, ffn=512), attn.with_(kind=I.KIND_PREFILL, ffn=512)):
+            d = B.make_desc(cfg)
+            size = B.workspace_bytes(d)
+            d.rope_base = base
+            assert B.workspace_bytes(d) == size
+            w = [fake] * 6
+            assert B.block_fwd(d, w, fake, fake, fake, fake, Workspace(size), kv_k=fake, kv_v=fake, stream=0, check=False) == B.EINVAL
+        d = B.make_desc(attn)
+        d.rope_base = base
+        assert B.block_bwd(d, [fake] * 4, fake, fake, Workspace(size), fake, fake, fake, fake, [fake, fake], fake, None, stream=0,
+                           check=False) == B.EINVAL
