@@ -4,9 +4,9 @@
 // of Eq. A3 (column-parallel X_m A_m with the activation fused, row-parallel Y_m B_m with the private-column
 // half of the partial channel-reduce + residual fused) and their data / weight gradients.
 //
-// Tiling: a workgroup owns a BM x BN tile of C and walks K in stages of BKS (64 in every tile shape in use).  NSTAGE
-// stages of both operand tiles live in LDS and every operand goes global -> LDS directly (buffer_load ... lds, no
-// register staging), NSTAGE-1 stages ahead of the MFMAs, so a global / L2 round trip is hidden.
+// Tiling: a workgroup owns a BM x BN tile of C and walks K in stages of BKS (64, or 128 where two groups of waves share a
+// tile's contraction).  NSTAGE stages of both operand tiles live in LDS and every operand goes global -> LDS directly
+// (buffer_load ... lds, no register staging), NSTAGE-1 stages ahead of the MFMAs, so a global / L2 round trip is hidden.
 //   * operand contiguous along K in memory (NT's a and b, NN's a): stage = [rows][BKS k], fragment reads are
 //     ds_read_b128 (16 consecutive rows x four 16-byte chunks);
 //   * operand contiguous along its row index in memory (NN's b, TN's a and b): stage = [BKS k][rows], the memory
@@ -91,15 +91,15 @@ struct TileCfg {
 };
 
 // ---- operand contiguous along K: stage [ROWS][BKS k], row = BKS*2 bytes = CPR chunks of 16 bytes; 16 chunks make
-// up the 64 LDS banks, so chunk c of row r sits at c ^ swz(r) (128-byte rows: (r>>1)&7, 64-byte rows: 0, 2, 3, 1 for (r>>2)&3):
+// up the 64 LDS banks, so chunk c of row r sits at c ^ swz(r) (128-byte rows: (r>>1)&7, 256-byte rows: r&15):
 // 16 consecutive rows then read the same logical chunk from 16 different bank groups.
 // One wave instruction fills 64/CPR rows (64 lanes x 16 B, lane order).  `origin` points at the tile's first row;
 // rowmap(rr) gives the row of tile row rr RELATIVE to the origin, or -1 if that row does not exist.
 template <int ROWS, int NWAVES, int BKS_ = 64, bool GROUPED = true>
 struct KContigOperand {
-  static constexpr int CPR = BKS_ / 8;           // chunks per row: 4, 8 or 16
+  static constexpr int CPR = BKS_ / 8;           // chunks per row: 8 or 16
   static constexpr int RPI = 64 / CPR;           // rows per copy instruction
-  static constexpr int SWZ_SHIFT = CPR == 4 ? 2 : (CPR == 8 ? 1 : 0);
+  static constexpr int SWZ_SHIFT = CPR == 8 ? 1 : 0;
   static constexpr int NI = ROWS / RPI / NWAVES;  // copy instructions per wave per stage
   // copies that share one LDS base (see dma16_group).  GROUPED: a wave's NI copies fill consecutive 1 KB groups of the
   // stage; otherwise the waves' copies interleave (copy `it` of wave w fills group it*NWAVES + w), which keeps the
@@ -110,16 +110,13 @@ struct KContigOperand {
   static constexpr int N_VMEM = NI;
   static constexpr int READS_PER_FRAG = 1;
   static_assert(NI % GRP == 0, "whole groups of copies");
-  static_assert(CPR == 4 || CPR == 8 || CPR == 16, "stage depth must be 32, 64 or 128");
+  static_assert(CPR == 8 || CPR == 16, "stage depth must be 64 or 128");
   static_assert(ROWS % (RPI * NWAVES) == 0, "rows must divide over the waves");
-  static __device__ __forceinline__ int swz(int row) {
-    const int g = (row >> SWZ_SHIFT) & (CPR - 1);
-    return CPR == 4 ? (((g & 1) << 1) ^ ((g >> 1) * 3)) : g;
-  }
+  static __device__ __forceinline__ int swz(int row) { return (row >> SWZ_SHIFT) & (CPR - 1); }
   const bf16_t* origin;
   unsigned voff[NI];
   int wave;
-  int kc[NI];  // logical chunk this lane fetches in copy instruction `it` (the same for all `it` when RPI == 16)
+  int kc[NI];  // logical chunk this lane fetches in copy instruction `it`
 
   template <class RowMap>
   __device__ __forceinline__ void init(const bf16_t* origin_, long long ld, RowMap rowmap) {
@@ -129,10 +126,9 @@ struct KContigOperand {
 #pragma unroll
     for (int it = 0; it < NI; ++it) {
       // a wave's NI copies fill consecutive groups of RPI rows (1 KB of LDS each).  Physical slot lane % CPR of row
-      // (wave*NI + it)*RPI + lane / CPR holds logical chunk slot ^ swz(row); the swizzle has a period of 16 rows, so
-      // with 16 rows per instruction it does not depend on `it`
+      // (wave*NI + it)*RPI + lane / CPR holds logical chunk slot ^ swz(row)
       const int row = group_of(wave, it) * RPI + lane / CPR;
-      kc[it] = (lane & (CPR - 1)) ^ swz(RPI == 16 ? lane / CPR : row);
+      kc[it] = (lane & (CPR - 1)) ^ swz(row);
       const long long r = rowmap(row);
       // memory-side offsets are relative to a base DMA_SHIFT bytes in front of the operand, less the immediate offset
       // the copy carries as member it % GRP of its group (dma16_group)
@@ -152,7 +148,7 @@ struct KContigOperand {
     for (int gi = 0; gi < NI / GRP; ++gi) {
       unsigned v[GRP];
 #pragma unroll
-      for (int j = 0; j < GRP; ++j) v[j] = (k0 + kc[RPI == 16 ? 0 : gi * GRP + j] * 8) < K ? voff[gi * GRP + j] : OOB;
+      for (int j = 0; j < GRP; ++j) v[j] = (k0 + kc[gi * GRP + j] * 8) < K ? voff[gi * GRP + j] : OOB;
       dma16_group<STREAM, GRP>(rs, v, tile + group_of(wave, gi * GRP) * 64);
     }
   }

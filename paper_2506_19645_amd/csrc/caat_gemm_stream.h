@@ -8,7 +8,7 @@
 // Measured, 7B shapes at T = 8 (us, tile kernel -> this one; 1 / 16 / 64 token rows):
 //   q|k|v     100 MB  26.4 -> 17.8   26.0 -> 18.2   26.1 -> 22.9
 //   gate|up   180 MB  40.0 -> 30.1   41.0 -> 31.1   46.0 -> 37.3
-//   down       90 MB  21.4 -> 17.9   22.1 -> 20.6   (24.3, 28.6: see launch_gemm)
+//   down       90 MB  21.4 -> 17.9   22.1 -> 20.6   (24.3, 28.6: see choose_route)
 #pragma once
 #include "caat_internal.h"
 
