@@ -537,7 +537,7 @@ int caat_hbm_probe(const void* src, void* dst, size_t bytes, int mode, void* hip
 
 int caat_gemm_route(int layout, int epilogue, int G, long long M, long long N, long long K, int ranks, long long shard_cols) {
   constexpr long long MAX = 0x7FFFFFFFLL;
-  if (layout < CAAT_GEMM_NT || layout > CAAT_GEMM_TN || epilogue < EPI_PLAIN || epilogue > EPI_PARTIAL || G < 1 || ranks < 1 || M < 1 ||
+  if (layout < CAAT_GEMM_NT || layout > CAAT_GEMM_TN || epilogue < EPI_PLAIN || epilogue > EPI_SHARED_BCAST || G < 1 || ranks < 1 || M < 1 ||
       N < 1 || K < 1 || M > MAX || N > MAX || K > MAX || shard_cols < 0 || shard_cols > MAX)
     return -1;
   GemmParams p;

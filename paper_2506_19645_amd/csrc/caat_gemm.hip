@@ -55,7 +55,7 @@ static int choose_skinny_width(int G, int N, int epilogue) {
 // The last two shapes share a tile's contraction between two groups of four waves: for launches with a tile or less per
 // compute unit, whose time is the chain of stages and not the matrix unit.  They are for the gradients only (NN, TN): a
 // tile of the forward pass (NT) is one sum in ascending k whatever its shape, so that a channel's bits are the same with
-// the reduce inside the GEMM and as a pass of its own (for 65 to 128 rows see gemm_route).
+// the reduce inside the GEMM and as a pass of its own (for 65 to 128 rows see choose_route).
 // Examples (us; 256 x 256, 192 x 256, 256 x 192, 128 x 128, 64 x 128, 64 x 64, 128 x 128 and 64 x 64 shared; G x M x N x K):
 //   NT 8 x 777 x 1536 x 4096     111 /  99 /  99 / 123 / 123 / 153 / 124 / 172
 //   TN 4 x 2048 x 1408 x 1111   34.4 / 50.3 / 31.4 / 38.8 / 42.2 / 56.2 / 46.6 / 73.2
@@ -126,13 +126,6 @@ static int choose_route(const GemmParams& p, int layout, int epilogue, int n_cu)
     if (p.M <= 64) return ROUTE_FEW_ROWS;
   }
   return choose_tile(p, layout, epilogue, n_cu);
-}
-
-int gemm_route(const GemmParams& p, int layout, int epilogue) {
-  const int route = choose_route(p, layout, epilogue, compute_units());
-  if (route != ROUTE_STREAM) return route;
-  const StreamTile t = choose_stream_tile(p, epilogue, compute_units());
-  return t.mt * 16 + t.rt + (t.two_waves ? 128 : 0);
 }
 
 hipError_t launch_gemm(const GemmParams& p, int layout, int epilogue, hipStream_t s) {
@@ -223,6 +216,21 @@ hipError_t launch_gemm_shared(const GemmParams& p, void* scratch, size_t scratch
   if (e != hipSuccess) return e;
   return launch_shared_merge(reinterpret_cast<const float*>(scratch), groups, p.aux, p.c, p.M, p.N, p.ldaux, p.ldc, p.stride_aux,
                              p.stride_c, p.bcast, s);
+}
+
+int gemm_route(const GemmParams& p, int layout, int epilogue) {
+  GemmParams q = p;
+  int groups = 1;
+  if (epilogue == EPI_SHARED_BCAST) {
+    groups = gemm_shared_groups(p.M, p.N, p.K, p.kcat, gemm_shared_scratch_bytes(p.M, p.N, p.kcat));
+    q.G = groups;
+    q.kcat = p.kcat / groups;
+    if (groups > 1) epilogue = EPI_PARTIAL;
+  }
+  const int n_cu = compute_units(), route = choose_route(q, layout, epilogue, n_cu);
+  if (route != ROUTE_STREAM) return groups > 1 ? 256 * groups + route : route;
+  const StreamTile t = choose_stream_tile(q, epilogue, n_cu);
+  return t.mt * 16 + t.rt + (t.two_waves ? 128 : 0);
 }
 
 }  // namespace caat

@@ -210,7 +210,8 @@ hipError_t launch_gemm_shared(const GemmParams& p, void* scratch, size_t scratch
 hipError_t launch_shared_merge(const float* part, int groups, const bf16_t* resid, bf16_t* out, long long M, int N, long long ldr,
                                long long ldo, long long stride_r, long long stride_o, int bcast, hipStream_t s);
 // The kernel that launch_gemm takes: a tile shape 0 .. 7, 8 the tile for few token rows, from 16 on the streaming kernel,
-// 16 mt + rt (+ 128 where two waves share a contraction; see StreamTile)
+// 16 mt + rt (+ 128 where two waves share a contraction; see StreamTile).  EPI_SHARED_BCAST: what launch_gemm_shared takes
+// with all the scratch it can use, 256 groups + the tile where it cuts the ranks into groups
 int gemm_route(const GemmParams& p, int layout, int epilogue);
 // NT, at most 128 token rows, EPI_PLAIN / EPI_GELU_FWD / EPI_SWIGLU_FWD / EPI_ROWPAR (gemm_route decides when)
 struct StreamTile {

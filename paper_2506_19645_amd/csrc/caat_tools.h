@@ -41,11 +41,12 @@ int caat_hbm_probe(const void* src, void* dst, size_t bytes, int mode, void* hip
 /*
  * Which kernel a shard GEMM of these sizes runs on (host only, nothing is launched), for tests that mean to reach every
  * kernel and for traces.  layout: caat_gemm_layout; epilogue: 0 plain, 1 GELU, 2 SwiGLU, 3 row-parallel, 4 GELU', 5
- * SwiGLU', 6 shared channels of `ranks` ranks in one contraction, 7 fp32 sums over groups of `ranks` ranks; shard_cols: for
- * 3, the columns of the whole shard where N is a part of them (0 = N).  Returns
+ * SwiGLU', 6 the shared channels of `ranks` ranks (G = 1); shard_cols: for 3, the columns of the whole shard where N is a
+ * part of them (0 = N).  Returns
  *   0 .. 7   tile of 256 x 256, 192 x 256, 256 x 192, 128 x 128, 64 x 128, 64 x 64, and 128 x 128, 64 x 64 by two wave groups
  *   8        the tile for few token rows that meet many weight rows
  *   16 mt + rt (+ 128)   the weight-streaming kernel, 16 mt token rows x 16 rt weight rows per workgroup (128: of two waves)
+ *   256 g + tile         6 only: fp32 sums over g groups of ranks on that tile, then a kernel that adds them up
  * or -1 for arguments out of range.
  */
 int caat_gemm_route(int layout, int epilogue, int G, long long M, long long N, long long K, int ranks, long long shard_cols);

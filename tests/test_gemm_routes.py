@@ -26,3 +26,50 @@ def test_private_columns_alone_take_the_kernel_of_the_whole_shard():
             whole = B.gemm_route(B.GEMM_NT, ROWPAR, G, M, h, K) >= 16
             for part in range(8, h, 8):
                 assert (B.gemm_route(B.GEMM_NT, ROWPAR, G, M, part, K, 1, h) >= 16) == whole
+
+
+# ---------------------------------------------------------------- what the GPU tests reach
+GELU_BWD, SWIGLU_BWD, SHARED = 4, 5, 6
+
+
+def _route(layout, epilogue, *sizes):
+    r = B.gemm_route(layout, epilogue, *sizes)
+    return layout, epilogue, r if r < 256 else 256 + r % 256      # the number of groups of ranks does not matter
+
+
+def _mlp_gemms(swi, T, n, h, fr, hs, reduce_in_gemm):
+    """The GEMM launches of an MLP block, forward and backward."""
+    pw = 2 * fr if swi else fr
+    out = [(B.GEMM_NT, SWIGLU if swi else GELU, T, n, fr, h)]
+    if reduce_in_gemm and n > 64 and hs % 8 == 0:
+        out += [(B.GEMM_NT, ROWPAR, T, n, h - hs, fr, 1, h)] * (hs < h) + [(B.GEMM_NT, SHARED, 1, n, hs, fr, T)] * (hs > 0)
+    else:
+        out.append((B.GEMM_NT, ROWPAR, T, n, h, fr))
+    return out + [(B.GEMM_NN, SWIGLU_BWD if swi else GELU_BWD, T, n, fr, h), (B.GEMM_TN, PLAIN, T, h, fr, n),
+                  (B.GEMM_NN, PLAIN, T, n, h, pw), (B.GEMM_TN, PLAIN, T, pw, h, n)]
+
+
+def _reachable():
+    rows = (1, 16, 17, 33, 48, 49, 65, 100, 128, 136, 200, 456, 777, 1000, 1300, 2048)
+    cols = (8, 72, 136, 520, 1032, 1160, 1544, 2056, 3080, 4104, 6152)
+    depths = (8, 72, 264, 1032, 1160, 3080)
+    for G in (1, 2, 4, 8, 16):
+        for M in rows:
+            for N in cols:
+                for K in depths:
+                    yield from ((B.GEMM_NT, e, G, M, N, K) for e in (PLAIN, GELU, SWIGLU, ROWPAR))
+                    yield from ((B.GEMM_NN, e, G, M, N, K) for e in (PLAIN, GELU_BWD, SWIGLU_BWD))
+                    if M % 8 == 0:
+                        yield B.GEMM_TN, PLAIN, G, M, N, K
+                    if M > 64 and G > 1:
+                        yield B.GEMM_NT, SHARED, 1, M, N, K, G
+
+
+def test_gpu_tests_reach_every_gemm_kernel():
+    from tests import test_gpu_gemm_exact as exact
+    from tests import test_gpu_gemm_kernels as blocks
+    covered = {_route(*g) for b in blocks.BLOCKS for g in _mlp_gemms(*b)}
+    covered |= {_route(layout, PLAIN, *s) for s in exact.SHAPES for layout in (B.GEMM_NT, B.GEMM_NN, B.GEMM_TN)}
+    covered |= {_route(B.GEMM_NT, PLAIN, G, M, N, K) for G, N, K in exact.FEW_ROWS for M in exact.FEW_ROWS_M}
+    missing = {_route(*g) for g in _reachable()} - covered
+    assert not missing, sorted(missing)

@@ -19,7 +19,9 @@ SHAPES = [(1, 8, 8, 8), (2, 256, 256, 64), (1, 264, 248, 72), (1, 520, 776, 200)
           (8, 200, 1160, 136),
           # two groups of waves on one contraction, 64 x 64 and 128 x 128 tiles: last stages that one group has to itself
           # and that both share
-          (4, 296, 520, 2056), (4, 200, 520, 1096), (8, 456, 776, 1096), (8, 456, 776, 3080)]
+          (4, 296, 520, 2056), (4, 200, 520, 1096), (8, 456, 776, 1096), (8, 456, 776, 3080),
+          # 256 x 256 tiles of 200 rows
+          (8, 200, 6152, 72)]
 
 
 @pytest.mark.parametrize("G,M,N,K", SHAPES)
@@ -43,14 +45,18 @@ def test_gemm_small_integers_bit_exact(layout, G, M, N, K):
 # few token rows: one, around 16-row tiles, past 64 and up to the streaming kernel's limit; short and ragged contractions;
 # shards whose widths leave a remainder in every tile width; the last two have so many weight rows that more than 16
 # token rows take the tile kernel
-@pytest.mark.parametrize("G,N,K", [(2, 8, 8), (8, 1376, 512), (3, 520, 72), (2, 1288, 2048), (1, 40, 4104), (4, 8192, 136),
-                                   (16, 2056, 200)])
+FEW_ROWS = [(2, 8, 8), (8, 1376, 512), (3, 520, 72), (2, 1288, 2048), (1, 40, 4104), (4, 8192, 136), (16, 2056, 200),
+            (2, 4104, 1160), (2, 6152, 1160)]
+FEW_ROWS_M = (1, 2, 15, 16, 17, 32, 33, 48, 63, 64, 65, 80, 97, 128, 129)
+
+
+@pytest.mark.parametrize("G,N,K", FEW_ROWS)
 def test_gemm_few_rows_small_integers_bit_exact(G, N, K):
     import torch
     rng = np.random.default_rng(N + K)
     b = rng.integers(-2, 3, size=(G, N, K)).astype(np.float32)
     db = B.to_device(I.f32_to_bf16_bits(b))
-    for M in (1, 2, 15, 16, 17, 32, 33, 48, 63, 64, 65, 80, 97, 128, 129):
+    for M in FEW_ROWS_M:
         a = rng.integers(-2, 3, size=(G, M, K)).astype(np.float32)
         want = I.f32_to_bf16_bits(np.matmul(a, b.transpose(0, 2, 1)))
         da = B.to_device(I.f32_to_bf16_bits(a))
