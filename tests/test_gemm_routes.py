@@ -65,6 +65,19 @@ def _reachable():
                         yield B.GEMM_NT, SHARED, 1, M, N, K, G
 
 
+def test_exact_gemm_tests_walk_over_several_large_tiles():
+    """The persistent tiles (0 to 2) with more tiles than compute units, 1, 2 and 3 stages of k or 2 and 3, in every layout."""
+    from tests import test_gpu_gemm_exact as exact
+    size = {0: (256, 256), 1: (192, 256), 2: (256, 192)}
+    walks = set()
+    for layout in (B.GEMM_NT, B.GEMM_NN, B.GEMM_TN):
+        for G, M, N, K in exact.SHAPES:
+            r = B.gemm_route(layout, PLAIN, G, M, N, K)
+            if r in size and G * -(-M // size[r][0]) * -(-N // size[r][1]) > 256:
+                walks.add((layout, r, -(-K // 64)))
+        assert {(layout, 0, s) for s in (1, 2, 3)} | {(layout, r, s) for r in (1, 2) for s in (2, 3)} <= walks
+
+
 def test_gpu_tests_reach_every_gemm_kernel():
     from tests import test_gpu_gemm_exact as exact
     from tests import test_gpu_gemm_kernels as blocks

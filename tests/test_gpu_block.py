@@ -118,10 +118,11 @@ def test_mlp_block_fwd_bwd(swi, T, n, h, ffn, p, scale):
 
 
 @pytest.mark.parametrize("swi,T,n,h,p", [
+    # most of a block's launches, the token rows being M: (which kernel takes which epilogue: test_gpu_gemm_kernels.py)
     (False, 8, 570, 1544, 0.5), (True, 8, 777, 1160, 0.301),       # 192 x 256 tiles
     (False, 8, 1000, 1160, 0.301), (True, 8, 1000, 1160, 0.5),     # 256 x 192 tiles
-    (False, 8, 200, 1160, 0.5), (True, 8, 200, 1160, 0.301),       # 128 x 128 tiles, two groups of waves (gradients)
-    (False, 2, 250, 776, 0.301), (True, 2, 250, 776, 0.5),         # 64 x 64 tiles, two groups of waves (gradients)
+    (False, 8, 200, 1160, 0.5), (True, 8, 200, 1160, 0.301),       # 64 x 128; gradients 128 x 128 by two groups of waves
+    (False, 2, 250, 776, 0.301), (True, 2, 250, 776, 0.5),         # 64 x 64; gradients by two groups of waves
 ])
 def test_mlp_block_on_every_tile_shape(swi, T, n, h, p):
     """Every fused epilogue on the tile shapes of ragged and small launches, edges in both directions, hs inside a tile."""

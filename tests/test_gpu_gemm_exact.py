@@ -10,7 +10,8 @@ from paper_2506_19645_amd import inputs as I
 pytestmark = pytest.mark.gpu
 
 # (G, M, N, K): below / at / past one tile in each dimension; 1, 2 and 3 stages of k with and without a remainder;
-# more tiles than compute units with stage counts 1, 2, 3 (the stream of copies runs on from tile to tile)
+# more tiles than compute units with stage counts 1, 2, 3 (the stream of copies runs on from tile to tile).  The tiles named
+# below are those of the layouts' choice on 256 compute units; tests/test_gemm_routes.py checks that none is left out
 SHAPES = [(1, 8, 8, 8), (2, 256, 256, 64), (1, 264, 248, 72), (1, 520, 776, 200), (3, 296, 520, 136), (1, 24, 136, 320),
           (5, 2048, 2048, 64), (5, 2040, 1928, 128), (5, 2008, 2056, 184),
           # 192 x 256 and 256 x 192 tiles: one round with a remainder in both directions, several tiles per workgroup with
@@ -20,8 +21,8 @@ SHAPES = [(1, 8, 8, 8), (2, 256, 256, 64), (1, 264, 248, 72), (1, 520, 776, 200)
           # two groups of waves on one contraction, 64 x 64 and 128 x 128 tiles: last stages that one group has to itself
           # and that both share
           (4, 296, 520, 2056), (4, 200, 520, 1096), (8, 456, 776, 1096), (8, 456, 776, 3080),
-          # 256 x 256 tiles of 200 rows
-          (8, 200, 6152, 72)]
+          # 256 x 256 tiles: one round, and several tiles per workgroup with 1, 2 and 3 stages
+          (8, 200, 6152, 72), (5, 1016, 5112, 64), (5, 1016, 5112, 72), (5, 1016, 5112, 136)]
 
 
 @pytest.mark.parametrize("G,M,N,K", SHAPES)
