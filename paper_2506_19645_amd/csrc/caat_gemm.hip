@@ -165,10 +165,14 @@ hipError_t launch_gemm(const GemmParams& p, int layout, int epilogue, hipStream_
 // The shared channels of all ranks as one product with a contraction kcat times as long: few tiles, each a long chain.
 // A prompt of some hundred tokens leaves most of the chip idle, so the ranks are cut into groups that are summed in
 // parallel into fp32 buffers, and a second kernel adds the groups up in ascending order.  The number of groups is the one
-// with the least modelled time, the model of the tile choice (on the 256 compute units of the chip, so that the workspace
-// does not depend on the device that is current) times 1.4 for weights that come from HBM and not, as where the model was
-// fitted, from the memory-side cache, plus the merge: a launch and the fp32 sums at 7 TB/s.  Measured for 777 tokens, 2048
-// shared channels, 8 ranks (us, 1 / 2 / 4 / 8 groups): 512 k per rank 39 / 37 / 36 / 40, 1376 k 121 / 94 / 69 / 66.
+// with the least modelled time, the model of the tile choice (on the 256 compute units of the chip, so that
+// the bits do not depend on the device that is current) times 1.4 for weights that come from HBM and not, as where the model was
+// fitted, from the memory-side cache, plus the merge: 5 us and the fp32 sums at 7 TB/s.  Both constants are checked on 20
+// products (2 to 8 ranks, h = 2048 to 8192, 512 to 5504 k per rank, hs = h / 2 and h / 4) of 65 to 2048 tokens: 0.4 % off the
+// best number of groups on average, 11 % at worst.  Examples (us, 1 / 2 / 4 / 8 groups; tokens x hs x k per rank x ranks):
+//   777 x 2048 x 512 x 8    40 / 41 / 40 / 45      777 x 2048 x 1376 x 8    117 / 91 / 66 / 67
+//   65 x 2048 x 512 x 8     29 / 22 / 17 / 17     1024 x 2048 x 1376 x 8    112 / 93 / 80 / 72
+//   777 x 1024 x 512 x 4    18 / 19 / 22           777 x 2048 x 3584 x 4    116 / 92 / 70
 // `scratch_bytes`: what there is for the groups' sums.
 static int gemm_shared_groups(int M, int N, int K, int kcat, size_t scratch_bytes) {
   GemmParams q = {};
@@ -184,7 +188,7 @@ static int gemm_shared_groups(int M, int N, int K, int kcat, size_t scratch_byte
     double us = 0.0;
     choose_tile(q, 0, EPI_PARTIAL, 256, &us);
     us *= 1.4;
-    if (g > 1) us += 3.4 + (double)g * M * N * 4.0 / 7e6;
+    if (g > 1) us += 5.0 + (double)g * M * N * 4.0 / 7e6;
     if (g == 1 || us < cost) {
       cost = us;
       best = g;

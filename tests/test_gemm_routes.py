@@ -28,8 +28,17 @@ def test_private_columns_alone_take_the_kernel_of_the_whole_shard():
                 assert (B.gemm_route(B.GEMM_NT, ROWPAR, G, M, part, K, 1, h) >= 16) == whole
 
 
+SHARED = 6
+
+
+@pytest.mark.parametrize("M,N,K,T,best", [(777, 2048, 1376, 8, (4, 8)), (65, 2048, 512, 8, (4, 8)), (777, 2048, 3584, 4, (4,)),
+                                          (777, 1024, 512, 4, (1,)), (1024, 1024, 512, 4, (1,)), (2048, 512, 512, 4, (1,))])
+def test_shared_channels_are_cut_into_groups_of_ranks_where_that_is_faster(M, N, K, T, best):
+    assert max(B.gemm_route(B.GEMM_NT, SHARED, 1, M, N, K, T) // 256, 1) in best
+
+
 # ---------------------------------------------------------------- what the GPU tests reach
-GELU_BWD, SWIGLU_BWD, SHARED = 4, 5, 6
+GELU_BWD, SWIGLU_BWD = 4, 5
 
 
 def _route(layout, epilogue, *sizes):
