@@ -758,12 +758,17 @@ __global__ __launch_bounds__(256) void sync_norm_rank_kernel(const bf16_t* __res
   }
 }
 
-// up to four workgroups per compute unit, which all run at once; beyond that the T reads of the partial sums cost more than
-// the spreading gains
+// Up to four workgroups per compute unit, which all run at once, and up to 48 MB for what they read and write in all: beyond,
+// the T reads of the partial sums, which no cache of one XCD holds any more, cost more than the spreading gains.  Workgroup
+// per token / per (token, rank), us behind a copy of the partial sums (T x tokens x h, hs; MB):
+//   8 x 64 x 4096, 2048 (29) 5.8 / 4.5    8 x 32 x 8192, 8192 (46) 10.4 / 7.9    8 x 64 x 4096, 4096 (46) 6.7 / 7.1
+//   8 x 128 x 4096, 2048 (59) 7.2 / 9.4   4 x 256 x 4096, 4096 (59) 7.0 / 11.5   8 x 128 x 8192, 8192 (185) 19.4 / 35.8
 static constexpr long long SYNC_NORM_RANK_MAX = 1024;
+static constexpr long long SYNC_NORM_RANK_TRAFFIC = 48000000;
 static bool sync_norm_rank_ever(int T, int h) { return (T == 2 || T == 4 || T == 8) && h > 1024; }
 bool sync_norm_rank_takes(int T, long long tokens, int h, int hs) {
-  return sync_norm_takes(T, tokens, h, hs) && sync_norm_rank_ever(T, h) && tokens * T <= SYNC_NORM_RANK_MAX;
+  return sync_norm_takes(T, tokens, h, hs) && sync_norm_rank_ever(T, h) && tokens * T <= SYNC_NORM_RANK_MAX &&
+         tokens * T * ((long long)T * hs + 3LL * h) * 2 <= SYNC_NORM_RANK_TRAFFIC;
 }
 size_t sync_norm_rank_bytes(int T, long long tokens, int h) {
   return sync_norm_rank_ever(T, h) ? (size_t)std::min(tokens * T, SYNC_NORM_RANK_MAX) * (size_t)h * 2 : 0;
