@@ -24,9 +24,10 @@
 // drain under the next tile.  Decode-sized tiles (STREAM_B) may cover fewer output columns than the MFMA tile is wide
 // (bn_out).
 //
-// What bounds the block-sized tiles: on N(0,1) operands the chip's power, then the operand copies and the epilogue.  A
-// loop of MFMAs on registers alone sustains 1.55 - 1.79 PFLOP/s with 32x32x16 and 1.98 - 2.03 with 16x16x32 (2.49 / 2.45
-// on zeros, where both run at full clock), hence the shape.  h = 2048, T = 4, ffn 8192, 8192 tokens, forward GELU /
+// What bounds the block-sized tiles: the matrix pipes are busy for 49 - 66 % of a launch (waits and barriers of the main loop,
+// epilogues that both waves of a SIMD run at the same time), at 1.8 - 1.95 GHz on N(0,1) operands.  A loop of MFMAs on
+// registers alone sustains 1.77 PFLOP/s with 32x32x16 and 2.02 with 16x16x32 on such operands, the chip's power limit (2.48 /
+// 2.39 on zeros, where both run at full clock), hence the shape.  h = 2048, T = 4, ffn 8192, 8192 tokens, forward GELU /
 // row-parallel / GELU' / dX / dA: 263 / 247 / 281 / 243 / 213 us with 32x32x16, an epilogue through LDS and a barrier
 // between tiles, 250 / 235 / 271 / 227 / 204 us as it is; 7B SwiGLU (T = 8, 4096 tokens) 670 / 403 / 414 / 608 / 621
 // to 626 / 379 / 391 / 557 / 603 us.  Without any epilogue (results dropped) the same launches take 194 / 205 / 220 /
