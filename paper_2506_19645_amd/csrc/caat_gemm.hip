@@ -100,12 +100,21 @@ static int choose_tile(const GemmParams& p, int layout, int epilogue, int n_cu, 
 
 // Few token rows (NT): the weights are what has to be read.  The streaming kernel reads them best, except where many token
 // rows meet many weight rows: every workgroup reads all of its token rows, so there a tile kernel takes over (the 64 x 128
-// one up to 64 token rows).  Streaming / tile kernel, us, weights from HBM:
-//   17 - 48   below 128 weight rows per compute unit.  32 token rows: 24576 of 2048 k 20.4 / 23.3, 28672 of 8192 79 / 91, 32768
-//             of 1376 23.3 / 23.1, of 512 12.2 / 10.0; 48 token rows: 24576 of 2048 23.4 / 23.8, 28672 of 8192 90 / 93, 32768 of
-//             1376 29.5 / 23.9; above the line at best 8 % faster (49152 of 2048), below it at worst 22 % slower (27648 of 5120)
-//   49 - 64   below 96.  64 token rows: 16384 of 3072 22.7 / 23.9, 22016 of 4096 38.0 / 38.6, 20480 of 1728 19.4 / 16.6, 24576 of
-//             2048 25.0 / 23.9, 27648 of 5120 68 / 54, 32768 of 1376 29.5 / 24.5
+// one up to 64 token rows).  Weight rows whose stride is a multiple of 4 KB start on the same memory channels; the tiles, which
+// read a piece of 128 rows at a time, lose 5 to 30 % by that, and the line lies higher.  Streaming / tile kernel, us, weights from
+// HBM; the lines from 17 to 64 rows are chosen on 2810 products with 24 to 64 token rows each (512 to 8192 k, 30 to 128 weight rows
+// per compute unit, 2 to 8 ranks): 0.3 % off the fastest kernel on average, 23 % at worst.
+//   1 - 16    always, but for SwiGLU with 65 to 80 and 97 to 112 weight rows per compute unit (stride of 4 KB: always): tiles of
+//             16 gate and 16 up rows take three and four rounds, 64 x 128 tiles one.  1 / 16 token rows: 28672 of 5120 52.7 / 59.1
+//             against 45.2 / 45.9, 28672 of 512 12.2 / 12.3 against 8.4 / 8.6; at 81 to 96 and 113 to 128 the tiles gain 5 % at best
+//   17 - 32   below 80 weight rows per compute unit (stride of 4 KB: 128).  32 token rows: 20480 of 1728 16.2 / 15.9, 27648 of 5120
+//             55 / 49, 28672 of 8192 79 / 91, of 4096 45.0 / 47.5
+//   33 - 64   below 65 (stride of 4 KB: 96).  48 token rows: 20480 of 1728 17.4 / 16.4, 27648 of 5120 61 / 50, 22016 of 4096
+//             36.6 / 38.8, 28672 of 4096 48.0 / 47.0 (in a layer 48.6 / 45.8); 64 token rows: 20480 of 1728 19.4 / 16.6, 24576 of
+//             2048 25.0 / 23.9, 22016 of 4096 38.0 / 38.6
+//   33 - 48   leave the streaming kernel no good tile for 49 to 64 weight rows per compute unit, which is one 64 x 64 tile for
+//             each: 48 token rows, streaming / 64 x 64: 13824 of 5120 39.2 / 33.1, 15360 of 5120 39.3 / 33.2, 16384 of 1376
+//             15.8 / 14.2; stride of 4 KB: 16384 of 6144 47.0 / 46.3, no gain on average; 56 rows 13824 of 5120 32.2 / 33.4
 //   65 - 128  while one round of workgroups covers the launch, or two of the widest a long contraction.  96 token rows, one
 //             round: 6144 of 4096 17.1 / 24.2, 12288 of 4096 28.4 / 36.8; two of the widest: 20480 of 1728 28.9 / 27.7, 24576 of
 //             2048 33.9 / 33.2, 22016 of 4096 56.8 / 57.8 (in a layer 61.0 / 63.2); other: 8192 of 5504 35.7 / 33.6, 16384 of
@@ -119,11 +128,16 @@ static int choose_route(const GemmParams& p, int layout, int epilogue, int n_cu)
     if (p.n_route > 0) q.N = p.n_route;
     const long long wrows = (long long)q.G * q.N * (epilogue == EPI_SWIGLU_FWD ? 2 : 1);
     const StreamTile t = choose_stream_tile(q, epilogue, n_cu);
+    const bool pages = p.K % 2048 == 0;   // rows of whole 4 KB
     bool stream = true;
     if (p.M > 64) stream = t.tiles <= n_cu || (t.tiles <= 2LL * n_cu && t.rt == 6 && p.K >= 4096);
-    else if (p.M > 16) stream = wrows < (p.M <= 48 ? 128LL : 96LL) * n_cu;
-    if (stream) return ROUTE_STREAM;
-    if (p.M <= 64) return ROUTE_FEW_ROWS;
+    else if (p.M <= 16) stream = !(epilogue == EPI_SWIGLU_FWD && !pages && ((wrows > 64LL * n_cu && wrows <= 80LL * n_cu) ||
+                                                                           (wrows > 96LL * n_cu && wrows <= 112LL * n_cu)));
+    else stream = wrows < (p.M <= 32 ? (pages ? 128LL : 80LL) : (pages ? 96LL : 65LL)) * n_cu;
+    const bool one_tile_each = p.M > 32 && p.M <= 48 && !pages && wrows > 48LL * n_cu && wrows <= 64LL * n_cu &&
+                               epilogue != EPI_SWIGLU_FWD;
+    if (stream && !one_tile_each) return ROUTE_STREAM;
+    if (p.M <= 64 && !one_tile_each) return ROUTE_FEW_ROWS;
   }
   return choose_tile(p, layout, epilogue, n_cu);
 }

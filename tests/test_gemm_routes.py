@@ -12,7 +12,12 @@ PLAIN, GELU, SWIGLU, ROWPAR = 0, 1, 2, 3
     (ROWPAR, 8, 1024, 5504, 65, False), (ROWPAR, 8, 2048, 1376, 96, False), (GELU, 8, 1728, 5120, 96, False),
     (SWIGLU, 4, 3584, 4096, 96, False), (ROWPAR, 8, 3072, 2048, 128, False), (SWIGLU, 8, 1728, 5120, 128, False),
     (SWIGLU, 8, 1376, 4096, 64, True), (ROWPAR, 8, 3072, 2048, 64, False), (SWIGLU, 8, 1728, 5120, 64, False),
-    (SWIGLU, 4, 3584, 4096, 48, True), (ROWPAR, 8, 4096, 1376, 48, False), (ROWPAR, 8, 4096, 1376, 16, True),
+    (SWIGLU, 4, 3584, 4096, 32, True), (SWIGLU, 4, 3584, 4096, 48, False), (SWIGLU, 8, 1376, 4096, 48, True),
+    (SWIGLU, 8, 1728, 5120, 32, False), (SWIGLU, 8, 1728, 5120, 48, False), (ROWPAR, 8, 4096, 1376, 48, False), (ROWPAR, 8, 4096, 1376, 16, True),
+    (PLAIN, 8, 1920, 5120, 48, False), (GELU, 8, 1728, 5120, 33, False), (ROWPAR, 8, 2048, 1376, 48, False),   # 64 x 64 tiles
+    (GELU, 8, 1728, 5120, 32, True), (GELU, 8, 1728, 5120, 49, True), (PLAIN, 8, 1536, 4096, 48, True), (SWIGLU, 4, 2048, 3072, 48, True),
+    (SWIGLU, 8, 1728, 5120, 1, False), (SWIGLU, 8, 1728, 5120, 16, False), (SWIGLU, 4, 3584, 512, 8, False), (GELU, 8, 3456, 5120, 1, True),
+    (SWIGLU, 8, 1792, 4096, 1, True), (SWIGLU, 8, 1376, 4104, 1, True),
     (PLAIN, 1, 8, 8, 129, False)])
 def test_few_token_rows_stream_the_weights_where_that_is_faster(epilogue, G, N, K, M, streams):
     assert (B.gemm_route(B.GEMM_NT, epilogue, G, M, N, K) >= 16) == streams
