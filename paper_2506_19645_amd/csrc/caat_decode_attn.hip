@@ -6,9 +6,10 @@
 // grouped-query heads share one pass over the rows and a small batch still fills the chip.  Its waves take 16-key blocks
 // in turn; every wave copies its blocks global -> LDS (whole rows) into two slots that only it reads, waits for its own
 // copies alone, and computes S = K q^T and O^T += V^T P with MFMAs (columns = query heads; most are idle for multi-head
-// attention, but the matrix unit has nothing else to do).  P goes in as the sum of two bf16 values (16 significant
-// bits), so the result is that of fp32 probabilities.  The waves' partial results meet in LDS in a fixed order, the
-// ranges' in a second small kernel.
+// attention, but the matrix unit has nothing else to do).  P goes in as an exact sum of three bf16 values, so the result is
+// that of fp32 probabilities; a wave whose sums are not finite (infinity less infinity inside such a sum) repeats its keys
+// with fp32 MFMAs, which as the only path cost a decode layer 2 to 4 %.  The waves' partial results meet in
+// LDS in a fixed order, the ranges' in a second small kernel.
 // Against one workgroup per query head that streamed its rows through registers (us, before -> now): batch 64, 32 heads,
 // 2048 keys 317 -> 312 (6.9 TB/s); batch 1, 3001 keys 51.5 -> 18; batch 16, 64 query / 8 key heads, 1999 keys 160 -> 31;
 // batch 32, 32 / 8 heads, 4000 keys 314 -> 85; batch 100, 16 heads, 300 keys 47 -> 47.  Two waves, or blocks of 32 keys,
