@@ -11,6 +11,8 @@ pytestmark = pytest.mark.gpu
 # (SwiGLU, T, tokens, h, ffn / T, hs, reduce in the GEMM); tests/test_gemm_routes.py checks on the host that they reach
 # every kernel that sizes like these can reach
 BLOCKS = [
+    (True, 8, 1, 72, 1736, 32, False), (True, 8, 16, 136, 1200, 64, False), (False, 8, 40, 72, 2040, 32, False),
+    (False, 8, 33, 2040, 72, 1000, False),
     (True, 1, 1, 200, 72, 60, False), (False, 1, 1, 72, 1160, 16, False), (False, 4, 1, 3080, 72, 1536, True),
     (False, 6, 1, 72, 2056, 16, False), (False, 8, 5, 1160, 1160, 576, True), (False, 8, 5, 1544, 1544, 0, False),
     (True, 8, 17, 1032, 72, 1032, True), (True, 2, 17, 72, 2056, 32, True), (False, 8, 17, 72, 1032, 16, False),
