@@ -47,7 +47,7 @@ EXPORTS = ["caat_shared_channels", "caat_status_string", "caat_workspace_bytes",
            "caat_partial_sync", "caat_norm_fwd", "caat_partial_sync_norm_fwd", "caat_norm_bwd_workspace_bytes",
            "caat_norm_bwd", "caat_norm_bwd_static", "caat_gemm_bf16", "caat_block_fwd", "caat_block_bwd"]
 TOOL_EXPORTS = ["caat_profile_enable", "caat_profile_reset", "caat_profile_count", "caat_profile_get", "caat_hbm_probe",
-                "caat_gemm_route"]
+                "caat_gemm_route", "caat_gemm_pair_route"]
 
 _lib = None
 
@@ -99,6 +99,8 @@ def lib() -> C.CDLL:
         L.caat_hbm_probe.restype = i
         L.caat_gemm_route.argtypes = [i, i, i, ll, ll, ll, i, ll]
         L.caat_gemm_route.restype = i
+        L.caat_gemm_pair_route.argtypes = [i, ll, ll, ll]
+        L.caat_gemm_pair_route.restype = i
         _lib = L
     return _lib
 
@@ -271,6 +273,10 @@ def hbm_probe(src, dst, nbytes: int, mode: int, stream=None) -> None:
 
 def gemm_route(layout: int, epilogue: int, G: int, M: int, N: int, K: int, ranks: int = 1, shard_cols: int = 0) -> int:
     return lib().caat_gemm_route(layout, epilogue, G, M, N, K, ranks, shard_cols)
+
+
+def gemm_pair_route(G: int, M: int, N: int, K: int) -> int:
+    return lib().caat_gemm_pair_route(G, M, N, K)
 
 
 def profile_enable(on: bool) -> None:

@@ -11,7 +11,8 @@ CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libcaat.so")
 SOURCES = ["caat_api.hip", "caat_gemm.hip", "caat_gemm_tiles_256x256.hip", "caat_gemm_tiles_192x256.hip",
            "caat_gemm_tiles_256x192.hip", "caat_gemm_tiles_128x128.hip", "caat_gemm_tiles_small.hip",
-           "caat_gemm_tiles_split.hip", "caat_gemm_stream.hip",
+           "caat_gemm_tiles_split.hip", "caat_gemm_pair_256x256.hip", "caat_gemm_pair_192x256.hip",
+           "caat_gemm_pair_128x128.hip", "caat_gemm_pair_small.hip", "caat_gemm_stream.hip",
            "caat_stream.hip", "caat_attn.hip", "caat_decode_attn.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",

@@ -315,6 +315,26 @@ int attn_block_fwd(const caat_desc* d, const caat_ws_layout& L, const void* cons
   return hip_status(e);
 }
 
+// A data gradient and the weight gradient that waits for the same tensor, in one launch (with the sums of the norm's parameter
+// gradients, if any are given) or one after the other.  While launches are timed every GEMM is one of its own, with a time
+// of its own.
+GemmPair grad_pair(const GemmParams& nn, const GemmParams& tn) {
+  GemmPair p = {-1, false, false, 0.0};
+  return g_prof_on ? p : gemm_pair(nn, tn);
+}
+hipError_t grad_gemms(const GemmPair& p, const GemmParams& nn, int epilogue, const char* name, const GemmParams& tn,
+                      const NormSums& sums, hipStream_t s) {
+  if (p.tile >= 0) return launch_gemm_pair(p, nn, epilogue, tn, sums, s);
+  hipError_t e;
+  {
+    ProfScope ps(s, name);
+    e = launch_gemm(nn, 1, epilogue, s);
+  }
+  if (e != hipSuccess) return e;
+  ProfScope ps(s, "gemm_tn_wgrad");
+  return launch_gemm(tn, 2, EPI_PLAIN, s);
+}
+
 // Attention sub-block backward (Fig. 2b applied to Eq. A5): norm backward per rank first, dr_m = g_m un-reduced, the
 // partial channel-reduce on g, then per rank dH = dZt Wo, dWo = dZt^T H, the attention-core gradient w.r.t. the rotated
 // q, k and v, the inverse rotation of dq and dk, dX = dqkv Wqkv (never reduced over ranks) and dWqkv = dqkv^T X.
@@ -345,55 +365,53 @@ int attn_block_bwd(const caat_desc* d, const caat_ws_layout& L, const void* cons
   bf16_t* dH = (bf16_t*)(ws + L.off_dH);
   bf16_t* dQKV = (bf16_t*)(ws + L.off_dP);
   hipError_t e;
-  GemmParams q;
+  GemmParams H1, O, X, W;
+  std::memset(&H1, 0, sizeof(H1));   // dH_m = dZt_m Wo_m (NN): [n,h] x [h,hd]
+  H1.a = dZt; H1.lda = h; H1.stride_a = n * h;
+  H1.b = (const bf16_t*)wo; H1.ldb = hd; H1.stride_b = h * hd;
+  H1.c = dH; H1.ldc = hd; H1.stride_c = n * hd;
+  H1.G = (int)T; H1.M = (int)n; H1.N = (int)hd; H1.K = (int)h;
+  std::memset(&O, 0, sizeof(O));   // dWo_m [h,hd] = dZt_m^T H_m (TN, reduction over tokens)
+  O.a = dZt; O.lda = h; O.stride_a = n * h;
+  O.b = H; O.ldb = hd; O.stride_b = n * hd;
+  O.c = (bf16_t*)dwo; O.ldc = hd; O.stride_c = h * hd; O.late_c = 1;   // gradients leave the block: not read again here
+  O.G = (int)T; O.M = (int)h; O.N = (int)hd; O.K = (int)n;
+  std::memset(&X, 0, sizeof(X));   // dX_m = dqkv_m Wqkv_m (NN): [n,qw] x [qw,h]; not reduced over ranks
+  X.a = dQKV; X.lda = qw; X.stride_a = n * qw;
+  X.b = (const bf16_t*)wqkv; X.ldb = h; X.stride_b = qw * h;
+  X.c = (bf16_t*)dx; X.ldc = h; X.stride_c = n * h; X.late_c = 1;
+  X.G = (int)T; X.M = (int)n; X.N = (int)h; X.K = (int)qw;
+  std::memset(&W, 0, sizeof(W));   // dWqkv_m [qw,h] = dqkv_m^T X_m (TN)
+  W.a = dQKV; W.lda = qw; W.stride_a = n * qw;
+  W.b = (const bf16_t*)x; W.ldb = h; W.stride_b = n * h;
+  W.c = (bf16_t*)dwqkv; W.ldc = h; W.stride_c = qw * h; W.late_c = 1;
+  W.G = (int)T; W.M = (int)qw; W.N = (int)h; W.K = (int)n;
+  NormSums sums = {};   // where the first two GEMMs run as one launch, the sums of dgamma / dbeta ride on it
+  const GemmPair first = grad_pair(H1, O);
+  NormSums* later = first.tile >= 0 ? &sums : nullptr;
 #define CAAT_STEP(name, call) { ProfScope ps(s, name); e = (call); } if (e != hipSuccess) return CAAT_EHIP;
   if (fuse_norm_bwd_reduce(d)) {
     // norm backward and the reduce on its result in one launch (the shared channels are not read back from memory)
     CAAT_STEP("norm_bwd_sync", launch_norm_bwd_sync((const bf16_t*)dx_out, (const bf16_t*)dr_out, (const bf16_t*)r_out,
                                                     (const bf16_t*)gamma, mean, rstd, (bf16_t*)dr, dZt, dgamma, dbeta, d->norm,
-                                                    (int)T, n, (int)h, d->hs, d->private_scale, ws + L.off_scratch, s))
+                                                    (int)T, n, (int)h, d->hs, d->private_scale, ws + L.off_scratch, s, later))
   } else {
     CAAT_STEP("norm_bwd", launch_norm_bwd((const bf16_t*)dx_out, (const bf16_t*)dr_out, (const bf16_t*)r_out, (const bf16_t*)gamma,
                                           mean, rstd, (bf16_t*)dr, dZt, dgamma, dbeta, d->norm, (int)T, n, (int)h, d->hs,
-                                          d->private_scale, ws + L.off_scratch, s, true))
+                                          d->private_scale, ws + L.off_scratch, s, true, later))
     // when no 8-channel vector straddles hs, the norm backward leaves the shared channels of dZt to the reduce, which
     // reads them from dr (the same values) instead of reading them back from dZt: one write of T*n*hs values less
     CAAT_STEP("partial_sync_bwd", d->hs % 8 == 0
                                       ? launch_partial_sync_shared_from((const bf16_t*)dr, dZt, (int)T, n, (int)h, d->hs, s)
                                       : launch_partial_sync(dZt, nullptr, dZt, (int)T, n, (int)h, d->hs, 1.0f, s))
   }
-  // dH_m = dZt_m Wo_m (NN): [n,h] x [h,hd]
-  std::memset(&q, 0, sizeof(q));
-  q.a = dZt; q.lda = h; q.stride_a = n * h;
-  q.b = (const bf16_t*)wo; q.ldb = hd; q.stride_b = h * hd;
-  q.c = dH; q.ldc = hd; q.stride_c = n * hd;
-  q.G = (int)T; q.M = (int)n; q.N = (int)hd; q.K = (int)h;
-  CAAT_STEP("gemm_nn_dgrad", launch_gemm(q, 1, EPI_PLAIN, s))
-  // dWo_m [h,hd] = dZt_m^T H_m (TN, reduction over tokens)
-  std::memset(&q, 0, sizeof(q));
-  q.a = dZt; q.lda = h; q.stride_a = n * h;
-  q.b = H; q.ldb = hd; q.stride_b = n * hd;
-  q.c = (bf16_t*)dwo; q.ldc = hd; q.stride_c = h * hd; q.late_c = 1;   // gradients leave the block: not read again here
-  q.G = (int)T; q.M = (int)h; q.N = (int)hd; q.K = (int)n;
-  CAAT_STEP("gemm_tn_wgrad", launch_gemm(q, 2, EPI_PLAIN, s))
+  e = grad_gemms(first, H1, EPI_PLAIN, "gemm_nn_dgrad", O, sums, s);
+  if (e != hipSuccess) return CAAT_EHIP;
   CAAT_STEP("flash_attn_bwd", launch_flash_bwd(QKV, H, dH, stats, dQKV, T * d->batch, d->seq, hpr, kvpr, d->head_dim, s))
   CAAT_STEP("rope_bwd", launch_rope(dQKV, T * n, d->seq, (int)qw, hpr + kvpr, d->head_dim, d->rope_base, 0, true, s))
-  // dX_m = dqkv_m Wqkv_m (NN): [n,qw] x [qw,h]; not reduced over ranks
-  std::memset(&q, 0, sizeof(q));
-  q.a = dQKV; q.lda = qw; q.stride_a = n * qw;
-  q.b = (const bf16_t*)wqkv; q.ldb = h; q.stride_b = qw * h;
-  q.c = (bf16_t*)dx; q.ldc = h; q.stride_c = n * h; q.late_c = 1;
-  q.G = (int)T; q.M = (int)n; q.N = (int)h; q.K = (int)qw;
-  CAAT_STEP("gemm_nn_dgrad", launch_gemm(q, 1, EPI_PLAIN, s))
-  // dWqkv_m [qw,h] = dqkv_m^T X_m (TN)
-  std::memset(&q, 0, sizeof(q));
-  q.a = dQKV; q.lda = qw; q.stride_a = n * qw;
-  q.b = (const bf16_t*)x; q.ldb = h; q.stride_b = n * h;
-  q.c = (bf16_t*)dwqkv; q.ldc = h; q.stride_c = qw * h; q.late_c = 1;
-  q.G = (int)T; q.M = (int)qw; q.N = (int)h; q.K = (int)n;
-  CAAT_STEP("gemm_tn_wgrad", launch_gemm(q, 2, EPI_PLAIN, s))
+  e = grad_gemms(grad_pair(X, W), X, EPI_PLAIN, "gemm_nn_dgrad", W, NormSums{}, s);
 #undef CAAT_STEP
-  return CAAT_OK;
+  return hip_status(e);
 }
 
 // One Llama-style decoder layer at inference (which uses the partial channel-reduce too, Sec. 3.2), either for one
@@ -544,6 +562,18 @@ int caat_gemm_route(int layout, int epilogue, int G, long long M, long long N, l
   std::memset(&p, 0, sizeof(p));
   p.G = G; p.M = (int)M; p.N = (int)N; p.K = (int)K; p.kcat = ranks; p.n_route = (int)shard_cols;
   return gemm_route(p, layout, epilogue);
+}
+
+int caat_gemm_pair_route(int G, long long M, long long N, long long K) {
+  constexpr long long MAX = 0x7FFFFFFFLL;
+  if (G < 1 || M < 1 || N < 1 || K < 1 || M > MAX || N > MAX || K > MAX) return -2;
+  GemmParams nn, tn;
+  std::memset(&nn, 0, sizeof(nn));
+  std::memset(&tn, 0, sizeof(tn));
+  nn.G = G; nn.M = (int)M; nn.N = (int)N; nn.K = (int)K;
+  tn.G = G; tn.M = (int)K; tn.N = (int)N; tn.K = (int)M;
+  const GemmPair p = gemm_pair(nn, tn);
+  return p.tile < 0 ? -1 : p.tile + (p.tn_first ? 16 : 0) + (p.one_each ? 32 : 0);
 }
 
 int caat_profile_enable(int on) {
@@ -773,20 +803,47 @@ int caat_block_bwd(const caat_desc* d, const void* const* weights, const void* x
   // a6/a7: norm backward per rank FIRST (Fig. 2b): g_m = dr_out_m + NormBwd(dx_out_m); dr_m = g_m un-reduced;
   // a copy with scaled private channels goes to dZt; dgamma/dbeta summed over tokens and ranks
   hipError_t e;
+  // The four GEMMs of the backward pass: G (dY with the activation derivative), B (dB), X (dX), A (dA).
+  GemmParams G, X, Bw, A;
+  std::memset(&G, 0, sizeof(G));   // a9 + a10: dY_m = dZt_m B_m (NN), fused with the activation derivative -> dP_m
+  G.a = dZt; G.lda = h; G.stride_a = n * h;
+  G.b = (const bf16_t*)w1; G.ldb = fr; G.stride_b = h * fr;
+  G.c = dP; G.ldc = pw; G.stride_c = n * pw;
+  G.aux = P; G.ldaux = pw; G.stride_aux = n * pw;
+  G.G = (int)T; G.M = (int)n; G.N = (int)fr; G.K = (int)h; G.half = (int)fr;
+  std::memset(&Bw, 0, sizeof(Bw));   // a9: dB_m [h, f/T] = dZt_m^T Y_m (TN, reduction over tokens)
+  Bw.a = dZt; Bw.lda = h; Bw.stride_a = n * h;
+  Bw.b = Y; Bw.ldb = fr; Bw.stride_b = n * fr;
+  Bw.c = (bf16_t*)dw1; Bw.ldc = fr; Bw.stride_c = h * fr; Bw.late_c = 1;
+  Bw.G = (int)T; Bw.M = (int)h; Bw.N = (int)fr; Bw.K = (int)n;
+  std::memset(&X, 0, sizeof(X));   // a11: dX_m = dP_m A_m (NN); NOT reduced over ranks (Sec. 4: the only reduce sits at the row-parallel output)
+  X.a = dP; X.lda = pw; X.stride_a = n * pw;
+  X.b = (const bf16_t*)w0; X.ldb = h; X.stride_b = pw * h;
+  X.c = (bf16_t*)dx; X.ldc = h; X.stride_c = n * h; X.late_c = 1;
+  X.G = (int)T; X.M = (int)n; X.N = (int)h; X.K = (int)pw;
+  std::memset(&A, 0, sizeof(A));   // a11: dA_m [pw, h] = dP_m^T X_m (TN)
+  A.a = dP; A.lda = pw; A.stride_a = n * pw;
+  A.b = (const bf16_t*)x; A.ldb = h; A.stride_b = n * h;
+  A.c = (bf16_t*)dw0; A.ldc = h; A.stride_c = pw * h; A.late_c = 1;
+  A.G = (int)T; A.M = (int)pw; A.N = (int)h; A.K = (int)n;
+  // where G and B run as one launch, the sums of dgamma / dbeta ride on it
+  NormSums sums = {};
+  const GemmPair first = grad_pair(G, Bw);
+  NormSums* later = first.tile >= 0 ? &sums : nullptr;
   if (fuse_norm_bwd_reduce(d)) {
     // ... as one launch where the shape allows: the reduce sums the rounded residual gradients straight from the
     // registers of the norm backward instead of reading them back
     ProfScope ps(s, "norm_bwd_sync");
     e = launch_norm_bwd_sync((const bf16_t*)dx_out, (const bf16_t*)dr_out, (const bf16_t*)r_out, (const bf16_t*)gamma, mean,
                              rstd, (bf16_t*)dr, dZt, dgamma, dbeta, d->norm, (int)T, n, (int)h, d->hs, d->private_scale,
-                             ws + L.off_scratch, s);
+                             ws + L.off_scratch, s, later);
     if (e != hipSuccess) return CAAT_EHIP;
   } else {
     {
       ProfScope ps(s, "norm_bwd");
       e = launch_norm_bwd((const bf16_t*)dx_out, (const bf16_t*)dr_out, (const bf16_t*)r_out, (const bf16_t*)gamma,
                           mean, rstd, (bf16_t*)dr, dZt, dgamma, dbeta, d->norm, (int)T, n, (int)h, d->hs,
-                          d->private_scale, ws + L.off_scratch, s, true);
+                          d->private_scale, ws + L.off_scratch, s, true, later);
     }
     if (e != hipSuccess) return CAAT_EHIP;
     // a8: the same partial channel-reduce on the gradients, shared channels only, fp32 accumulation.  When no 8-channel
@@ -800,56 +857,14 @@ int caat_block_bwd(const caat_desc* d, const void* const* weights, const void* x
     if (e != hipSuccess) return CAAT_EHIP;
   }
 
-  // The four GEMMs of the backward pass, in the order G (activation-derivative GEMM), B (dB), X (dX), A (dA).
+  // One at a time they run in the order G, B, X, A.
   // Whichever GEMM runs right behind the streaming norm-backward kernel measured about 20 us slower than elsewhere in
   // the sequence (that kernel's fresh writes are still draining).  The six admissible orders (h = 2048, T = 4, 8192
   // tokens): B G X A 1.637 ms per step, G B X A 1.645, the rest 1.645 - 1.679; B first only moves the slow slot from G
   // to the weight-gradient GEMM (213 -> 221 us averaged over its two launches), so the plain order stays.
-  GemmParams q;
-  auto run_B = [&]() {
-    std::memset(&q, 0, sizeof(q));
-    q.a = dZt; q.lda = h; q.stride_a = n * h;
-    q.b = Y; q.ldb = fr; q.stride_b = n * fr;
-    q.c = (bf16_t*)dw1; q.ldc = fr; q.stride_c = h * fr; q.late_c = 1;
-    q.G = (int)T; q.M = (int)h; q.N = (int)fr; q.K = (int)n;
-    ProfScope ps(s, "gemm_tn_wgrad");
-    return launch_gemm(q, 2, EPI_PLAIN, s);
-  };
-  auto run_G = [&]() {
-    std::memset(&q, 0, sizeof(q));
-    q.a = dZt; q.lda = h; q.stride_a = n * h;
-    q.b = (const bf16_t*)w1; q.ldb = fr; q.stride_b = h * fr;
-    q.c = dP; q.ldc = pw; q.stride_c = n * pw;
-    q.aux = P; q.ldaux = pw; q.stride_aux = n * pw;
-    q.G = (int)T; q.M = (int)n; q.N = (int)fr; q.K = (int)h; q.half = (int)fr;
-    ProfScope ps(s, swi ? "gemm_nn_swiglu_bwd" : "gemm_nn_gelu_bwd");
-    return launch_gemm(q, 1, swi ? EPI_SWIGLU_BWD : EPI_GELU_BWD, s);
-  };
-  auto run_X = [&]() {
-    std::memset(&q, 0, sizeof(q));
-    q.a = dP; q.lda = pw; q.stride_a = n * pw;
-    q.b = (const bf16_t*)w0; q.ldb = h; q.stride_b = pw * h;
-    q.c = (bf16_t*)dx; q.ldc = h; q.stride_c = n * h; q.late_c = 1;
-    q.G = (int)T; q.M = (int)n; q.N = (int)h; q.K = (int)pw;
-    ProfScope ps(s, "gemm_nn_dgrad");
-    return launch_gemm(q, 1, EPI_PLAIN, s);
-  };
-  auto run_A = [&]() {
-    std::memset(&q, 0, sizeof(q));
-    q.a = dP; q.lda = pw; q.stride_a = n * pw;
-    q.b = (const bf16_t*)x; q.ldb = h; q.stride_b = n * h;
-    q.c = (bf16_t*)dw0; q.ldc = h; q.stride_c = pw * h; q.late_c = 1;
-    q.G = (int)T; q.M = (int)pw; q.N = (int)h; q.K = (int)n;
-    ProfScope ps(s, "gemm_tn_wgrad");
-    return launch_gemm(q, 2, EPI_PLAIN, s);
-  };
-  e = run_G();   // a9 + a10: dY_m = dZt_m B_m (NN), fused with the activation derivative -> dP_m
+  e = grad_gemms(first, G, swi ? EPI_SWIGLU_BWD : EPI_GELU_BWD, swi ? "gemm_nn_swiglu_bwd" : "gemm_nn_gelu_bwd", Bw, sums, s);
   if (e != hipSuccess) return CAAT_EHIP;
-  e = run_B();   // a9: dB_m [h, f/T] = dZt_m^T Y_m (TN, reduction over tokens)
-  if (e != hipSuccess) return CAAT_EHIP;
-  e = run_X();   // a11: dX_m = dP_m A_m (NN); NOT reduced over ranks (Sec. 4: the only reduce sits at the row-parallel output)
-  if (e != hipSuccess) return CAAT_EHIP;
-  e = run_A();   // a11: dA_m [pw, h] = dP_m^T X_m (TN)
+  e = grad_gemms(grad_pair(X, A), X, EPI_PLAIN, "gemm_nn_dgrad", A, NormSums{}, s);
   return hip_status(e);
 }
 

@@ -16,6 +16,10 @@ template <> hipError_t launch_block_sized<Cfg64x64>(const GemmParams&, int, int,
 template <> hipError_t launch_block_sized<Cfg128x128k>(const GemmParams&, int, int, hipStream_t);
 template <> hipError_t launch_block_sized<Cfg64x64k>(const GemmParams&, int, int, hipStream_t);
 
+#define CAAT_PAIR(CFG) template <> hipError_t launch_pair<CFG>(const GemmParams&, int, const GemmParams&, const NormSums&, bool, bool, hipStream_t);
+CAAT_PAIR(Cfg256x256) CAAT_PAIR(Cfg192x256) CAAT_PAIR(Cfg128x128) CAAT_PAIR(Cfg64x128) CAAT_PAIR(Cfg64x64)
+#undef CAAT_PAIR
+
 static int compute_units() {
   static int n_cu = 0;
   if (n_cu == 0) {
@@ -74,10 +78,12 @@ struct TileShape {
   int bm, bn, per_cu;   // per_cu: workgroups a compute unit holds
   int k;                // depth of a stage
   double stage, tile;   // us
+  bool persist;
 };
-static constexpr TileShape TILES[] = {{256, 256, 1, 64, 1.64, 8.1}, {192, 256, 1, 64, 1.35, 6.3}, {256, 192, 1, 64, 1.35, 6.7},
-                                      {128, 128, 2, 64, 0.98, 4.2}, {64, 128, 2, 64, 0.69, 2.6}, {64, 64, 2, 64, 0.446, 1.8},
-                                      {128, 128, 1, 128, 1.15, 3.8}, {64, 64, 1, 128, 0.473, 2.5}};
+static constexpr TileShape TILES[] = {{256, 256, 1, 64, 1.64, 8.1, true}, {192, 256, 1, 64, 1.35, 6.3, true},
+                                      {256, 192, 1, 64, 1.35, 6.7, true}, {128, 128, 2, 64, 0.98, 4.2, false},
+                                      {64, 128, 2, 64, 0.69, 2.6, false}, {64, 64, 2, 64, 0.446, 1.8, false},
+                                      {128, 128, 1, 128, 1.15, 3.8, false}, {64, 64, 1, 128, 0.473, 2.5, false}};
 static int choose_tile(const GemmParams& p, int layout, int epilogue, int n_cu, double* us = nullptr) {
   const bool swi = epilogue == EPI_SWIGLU_FWD;
   int best = 0;
@@ -145,15 +151,19 @@ static int choose_route(const GemmParams& p, int layout, int epilogue, int n_cu)
   return choose_tile(p, layout, epilogue, n_cu);
 }
 
-hipError_t launch_gemm(const GemmParams& p, int layout, int epilogue, hipStream_t s) {
+static bool in_range(const GemmParams& p, int epilogue) {
   // buffer-load offsets are 32-bit and relative to the tile origin: the farthest row a tile touches times the
   // row stride must stay below 2 GiB
   const long long far_rows = (epilogue == EPI_SWIGLU_FWD ? (long long)p.half : 0) + 256 + 64;  // rows or k-rows
-  if (far_rows * p.lda * 2 >= 0x7FFFF000LL || far_rows * p.ldb * 2 >= 0x7FFFF000LL) return hipErrorInvalidValue;
+  if (far_rows * p.lda * 2 >= 0x7FFFF000LL || far_rows * p.ldb * 2 >= 0x7FFFF000LL) return false;
   // the epilogue's buffer offsets are relative to a wave's first row: up to 256 rows of any output / second operand
   const long long ldmax = std::max(std::max(p.ldc, p.ldc2), p.ldaux);
   const long long elem = epilogue == EPI_PARTIAL ? 4 : 2;
-  if ((256 * ldmax + 2 * (long long)p.half + (long long)p.N) * elem >= 0x7FFFFFFFLL) return hipErrorInvalidValue;
+  return (256 * ldmax + 2 * (long long)p.half + (long long)p.N) * elem < 0x7FFFFFFFLL;
+}
+
+hipError_t launch_gemm(const GemmParams& p, int layout, int epilogue, hipStream_t s) {
+  if (!in_range(p, epilogue)) return hipErrorInvalidValue;
   const int n_cu = compute_units();
   GemmParams q = p;
   q.bn_out = 0;  // block-sized tiles always cover their full width
@@ -175,6 +185,77 @@ hipError_t launch_gemm(const GemmParams& p, int layout, int epilogue, hipStream_
     case EPI_GELU_FWD: return launch_one<CfgSkinny, false, false, EPI_GELU_FWD>(q, s);
     case EPI_SWIGLU_FWD: return launch_one<CfgSkinny, false, false, EPI_SWIGLU_FWD>(q, s);
     case EPI_ROWPAR: return launch_one<CfgSkinny, false, false, EPI_ROWPAR>(q, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+// Both gradient GEMMs in one launch (gemm_pair_kernel): the one with the longer tiles first, on as many workgroups as fit on the
+// chip; the other one's workgroups start wherever a slot is or comes free, each with one tile or, persistent tiles with an even
+// share of several, which saves 1.5 us a tile.  Time by the model of the tile choice: the end of the last tile.  The tiles that
+// only win alone (256 x 192 and those that share a contraction) are left out.
+// Measured on 44 training steps of 135 to 8192 tokens, T = 2 to 8, h = 512 to 4096 (backward pass, us; one after the
+// other / paired): 4 x 360 tokens of 512, ffn 1792 36.4 / 25.7, 8 x 147 of 1536, ffn 6144 57.8 / 41.2, 4 x 731 of 2048,
+// ffn 5504 155 / 132, 4 x 1111 of 2048, ffn 5632 204 / 188, 4 x 8192 of 2048, ffn 8192 1027 / 1000.
+static GemmPair plan_pair(const TileShape& t, int index, const GemmParams& nn, const GemmParams& tn, int n_cu) {
+  auto tiles = [&](const GemmParams& p) { return (((long long)p.M + t.bm - 1) / t.bm) * (((long long)p.N + t.bn - 1) / t.bn) * p.G; };
+  auto us = [&](const GemmParams& p) { return (double)(((long long)p.K + t.k - 1) / t.k) * t.stage + t.tile; };
+  const double un = us(nn), ut = us(tn);
+  const bool tf = ut > un;
+  const long long slots = (long long)t.per_cu * n_cu, na = tiles(tf ? tn : nn), nb = tiles(tf ? nn : tn);
+  const double ua = tf ? ut : un, ub = tf ? un : ut;
+  // behind the first GEMM n_hi slots are free at hi, n_lo at lo
+  const long long n_hi = na % slots, n_lo = slots - n_hi;
+  const double lo = (double)(na / slots) * ua, hi = n_hi ? lo + ua : lo;
+  // one tile at a time to whichever slot is free first; whole rounds of all slots beforehand
+  struct { double at; long long n; } cls[3] = {{lo, n_lo}, {hi, n_hi}, {0.0, 0}};
+  const double ub1 = ub + (t.persist ? 1.5 : 0.0);
+  long long left = nb;
+  const long long rounds = left > 3 * slots ? left / slots - 2 : 0;
+  left -= rounds * slots;
+  cls[0].at += rounds * ub1;
+  if (n_hi) cls[1].at += rounds * ub1;
+  double each = hi;
+  while (left > 0) {
+    const int c = cls[1].n && cls[1].at < cls[0].at ? 1 : 0;
+    cls[c].at += ub1;
+    each = std::max(each, cls[c].at);
+    left -= cls[c].n;
+  }
+  double end = each;
+  bool one_each = true;
+  if (t.persist) {   // even shares: the first nb % g workgroups have one tile more
+    const long long g = std::min(slots, nb), more = nb % g;
+    const double share = (double)(nb / g) * ub;
+    const double even = std::max({hi, lo + share + (more ? ub : 0.0), g > n_lo ? hi + share + (more > n_lo ? ub : 0.0) : 0.0});
+    one_each = each < even;
+    end = std::min(each, even);
+  }
+  const double fill = (na * ua + nb * ub) / (slots * end);
+  return {index, tf, one_each, end * (0.55 + 0.45 * std::min(fill, 1.0))};
+}
+GemmPair gemm_pair(const GemmParams& nn, const GemmParams& tn) {
+  const int n_cu = compute_units();
+  GemmPair best = {-1, false, false, 0.0};
+  for (int i : {0, 1, 3, 4, 5}) {
+    const GemmPair p = plan_pair(TILES[i], i, nn, tn, n_cu);
+    if (best.tile < 0 || p.us < best.us) best = p;
+  }
+  double a = 0.0, b = 0.0;
+  choose_tile(nn, 1, EPI_PLAIN, n_cu, &a);
+  choose_tile(tn, 2, EPI_PLAIN, n_cu, &b);
+  if (best.us >= a + b + 2.0) best.tile = -1;   // (a launch less is worth some 5 us, but the model is no better than that)
+  return best;
+}
+
+hipError_t launch_gemm_pair(const GemmPair& p, const GemmParams& nn, int epilogue, const GemmParams& tn, const NormSums& sums,
+                            hipStream_t s) {
+  if (!in_range(nn, epilogue) || !in_range(tn, EPI_PLAIN)) return hipErrorInvalidValue;
+  switch (p.tile) {
+    case 0: return launch_pair<Cfg256x256>(nn, epilogue, tn, sums, p.tn_first, p.one_each, s);
+    case 1: return launch_pair<Cfg192x256>(nn, epilogue, tn, sums, p.tn_first, p.one_each, s);
+    case 3: return launch_pair<Cfg128x128>(nn, epilogue, tn, sums, p.tn_first, p.one_each, s);
+    case 4: return launch_pair<Cfg64x128>(nn, epilogue, tn, sums, p.tn_first, p.one_each, s);
+    case 5: return launch_pair<Cfg64x64>(nn, epilogue, tn, sums, p.tn_first, p.one_each, s);
     default: return hipErrorInvalidValue;
   }
 }

@@ -277,15 +277,14 @@ __device__ __forceinline__ long long b_tile_row(int rr, int n0, int bn_out, int 
   }
 }
 
+// The tiles of workgroup `bid` of `nb` that share a launch (nb a multiple of 8, or bid is blockIdx.x: bid % 8 names the XCD).
 template <class CFG, bool AT, bool BT, int EPI>
-__global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kernel(const GemmParams p) {
+__device__ __forceinline__ void gemm_tiles(const GemmParams& p, uint4* smem, int bid, int nb) {
   constexpr int BM = CFG::BM, BN = CFG::BN, NSTAGE = CFG::NSTAGE;
   constexpr int TM = CFG::TM, TN = CFG::TN, WTM = CFG::WTM, WTN = CFG::WTN;
   constexpr bool SWI = (EPI == EPI_SWIGLU_FWD);
   constexpr int BN_OUT = SWI ? BN / 2 : BN;  // output columns covered by one tile
   static_assert(!SWI || WTN % 64 == 0, "SwiGLU pairing needs 32 gate and 32 up columns per wave");
-
-  __shared__ uint4 smem[CFG::SMEM_CHUNKS];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -309,7 +308,6 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
   const int total = tiles * p.G;
   int pid, pid_end, pid_step;
   {
-    const int bid = blockIdx.x, nb = gridDim.x;
     const int q = total >> 3, rem = total & 7, x = bid & 7;
     const int start = x * q + (x < rem ? x : rem);
     pid_end = start + q + (x < rem ? 1 : 0);
@@ -773,26 +771,77 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
 }
 
 template <class CFG, bool AT, bool BT, int EPI>
+__global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kernel(const GemmParams p) {
+  __shared__ uint4 smem[CFG::SMEM_CHUNKS];
+  gemm_tiles<CFG, AT, BT, EPI>(p, smem, blockIdx.x, gridDim.x);
+}
+
+// The two gradient GEMMs that wait for the same tensor, the data gradient (NN) and the weight gradient (TN), in one launch, and
+// in front of them the sums of the norm's parameter gradients (n_sums workgroups, see norm_sums).  They do not depend on
+// each other: workgroups of the second one (the one with the shorter tiles) start wherever the first leaves a slot idle, and
+// there are one or two launches less, each with a start, an end and a last round of its own.  n_sums and n_first are
+// multiples of 8, so that a workgroup's number within its GEMM names its XCD.  256 tokens of h = 768, T = 2, ffn 3072:
+// 6 launches of 39.4 us become 3 of 30.1; 1111 tokens of 2048, T = 4, SwiGLU, ffn 5632: 204 -> 188 us; see choose_pair.
+template <class CFG, int EPI>
+__global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_pair_kernel(const GemmParams nn, const GemmParams tn,
+                                                                                      const NormSums sums, int n_sums, int n_first,
+                                                                                      int tn_first) {
+  __shared__ uint4 smem[CFG::SMEM_CHUNKS];
+  int b = blockIdx.x;
+  if (b < n_sums) {
+    norm_sums(sums, b, reinterpret_cast<float4*>(smem));
+    return;
+  }
+  b -= n_sums;
+  const bool first = b < n_first;
+  const int nb = first ? n_first : (int)gridDim.x - n_sums - n_first;
+  if (!first) b -= n_first;
+  if (first == (tn_first != 0)) gemm_tiles<CFG, true, true, EPI_PLAIN>(tn, smem, b, nb);
+  else gemm_tiles<CFG, false, true, EPI>(nn, smem, b, nb);
+}
+
+// workgroups for `total` tiles, 0 if there are too many or the device cannot be asked
+template <class CFG>
+static long long tile_blocks(long long total) {
+  if (total <= 0 || total > 0x7FFFFFFFLL) return 0;
+  if (!CFG::PERSIST) return total;
+  static int n_cu = 0;  // as many workgroups as the compute units hold at once
+  if (n_cu == 0) {
+    int dev = 0, v = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+      return 0;
+    n_cu = v > 0 ? v : 256;
+  }
+  return total < (long long)n_cu * CFG::WGS_PER_CU ? total : (long long)n_cu * CFG::WGS_PER_CU;
+}
+
+template <class CFG, bool AT, bool BT, int EPI>
 static hipError_t launch_one(const GemmParams& p, hipStream_t s) {
   constexpr int BN_OUT = (EPI == EPI_SWIGLU_FWD) ? CFG::BN / 2 : CFG::BN;
   if (p.bn_out < 0 || p.bn_out > BN_OUT || (p.bn_out & 7)) return hipErrorInvalidValue;
   const long long bn_out = (CFG::STREAM_B && p.bn_out > 0) ? p.bn_out : BN_OUT;  // as in the kernel
   const long long tiles_m = (p.M + CFG::BM - 1) / CFG::BM;
   const long long tiles_n = (p.N + bn_out - 1) / bn_out;
-  const long long total = tiles_m * tiles_n * p.G;
-  if (total <= 0 || total > 0x7FFFFFFFLL) return hipErrorInvalidValue;
-  long long blocks = total;
-  if (CFG::PERSIST) {
-    static int n_cu = 0;  // as many workgroups as the compute units hold at once
-    if (n_cu == 0) {
-      int dev = 0, v = 0;
-      if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        return hipErrorInvalidValue;
-      n_cu = v > 0 ? v : 256;
-    }
-    if (blocks > (long long)n_cu * CFG::WGS_PER_CU) blocks = (long long)n_cu * CFG::WGS_PER_CU;
-  }
+  const long long blocks = tile_blocks<CFG>(tiles_m * tiles_n * p.G);
+  if (blocks <= 0) return hipErrorInvalidValue;
   hipLaunchKernelGGL((gemm_kernel<CFG, AT, BT, EPI>), dim3((unsigned)blocks), dim3(CFG::THREADS), 0, s, p);
+  return hipGetLastError();
+}
+
+template <class CFG, int EPI>
+static hipError_t launch_pair_one(const GemmParams& nn, const GemmParams& tn, const NormSums& sums, bool tn_first, bool one_each,
+                                  hipStream_t s) {
+  auto tiles = [](const GemmParams& p) {
+    return ((long long)p.M + CFG::BM - 1) / CFG::BM * ((p.N + CFG::BN - 1) / CFG::BN) * p.G;
+  };
+  const long long t1 = tiles(tn_first ? tn : nn), t2 = tiles(tn_first ? nn : tn);
+  const long long b1 = tile_blocks<CFG>(t1), b2 = one_each ? t2 : tile_blocks<CFG>(t2);
+  if (b1 <= 0 || b2 <= 0 || b1 + b2 > 0x7FFF0000LL) return hipErrorInvalidValue;
+  auto eights = [](long long v) { return ((unsigned)v + 7u) & ~7u; };
+  const unsigned n_sums = eights(norm_sums_blocks(sums)), n_first = eights(b1), n_second = eights(b2);
+  const unsigned grid = n_sums + n_first + n_second;
+  hipLaunchKernelGGL((gemm_pair_kernel<CFG, EPI>), dim3(grid), dim3(CFG::THREADS), 0, s, nn, tn, sums, (int)n_sums, (int)n_first,
+                     tn_first ? 1 : 0);
   return hipGetLastError();
 }
 

@@ -20,6 +20,23 @@ typedef TileCfg<64, 64, 2, 2, 4, false, false, 2> Cfg64x64k;
 template <class CFG>
 hipError_t launch_block_sized(const GemmParams& p, int layout, int epilogue, hipStream_t s);
 
+// data gradient (NN, `epilogue`) and weight gradient (TN) in one launch
+template <class CFG>
+hipError_t launch_pair(const GemmParams& nn, int epilogue, const GemmParams& tn, const NormSums& sums, bool tn_first, bool one_each,
+                       hipStream_t s);
+
+#define CAAT_INSTANTIATE_PAIR(CFG)                                                                                             \
+  template <>                                                                                                                  \
+  hipError_t launch_pair<CFG>(const GemmParams& nn, int epilogue, const GemmParams& tn, const NormSums& sums, bool tn_first,   \
+                              bool one_each, hipStream_t s) {                                                                                 \
+    switch (epilogue) {                                                                                                        \
+      case EPI_PLAIN: return launch_pair_one<CFG, EPI_PLAIN>(nn, tn, sums, tn_first, one_each, s);                                       \
+      case EPI_GELU_BWD: return launch_pair_one<CFG, EPI_GELU_BWD>(nn, tn, sums, tn_first, one_each, s);                                 \
+      case EPI_SWIGLU_BWD: return launch_pair_one<CFG, EPI_SWIGLU_BWD>(nn, tn, sums, tn_first, one_each, s);                             \
+      default: return hipErrorInvalidValue;                                                                                    \
+    }                                                                                                                          \
+  }
+
 #define CAAT_INSTANTIATE_TILES(CFG)                                                                                            \
   template <>                                                                                                                  \
   hipError_t launch_block_sized<CFG>(const GemmParams& p, int layout, int epilogue, hipStream_t s) {                           \

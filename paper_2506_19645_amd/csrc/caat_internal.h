@@ -200,8 +200,71 @@ struct GemmParams {
   int n_route;         // EPI_ROWPAR on a part of a shard's columns: the columns of the whole shard (0 = N); see gemm_route
 };
 
+// Sums of the partial rows of dgamma / dbeta that the norm backward leaves: partial [nb][2][h] over nb in a fixed order.  Only
+// the first `ncols` columns of a partial row are read: 2h for LayerNorm (dgamma | dbeta), h for RMSNorm, whose backward never
+// writes the dbeta half.  A workgroup (its first 256 threads) owns 64 columns, a thread 4 of them, one 16-byte load per partial
+// row; its 16 row groups each add every 16th partial row (4 independent chains), and the 16 group sums are combined in
+// ascending order through LDS (red: 256 float4).  h % 8 == 0, so 2h is a multiple of 4.
+struct NormSums {
+  const float* partial;   // null: nothing to add up
+  int nb, h, ncols;
+  float* dgamma;
+  float* dbeta;
+};
+inline int norm_sums_blocks(const NormSums& f) { return f.partial ? (f.ncols + 63) / 64 : 0; }
+__device__ __forceinline__ void norm_sums(const NormSums& f, int block, float4* red) {
+  const int cl = threadIdx.x & 15, rg = threadIdx.x >> 4;
+  const int c = (block * 16 + cl) * 4;
+  const long long w = 2LL * f.h;
+  auto add = [](float4& a, const float4& b) { a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w; };
+  if (rg < 16) {
+    float4 s[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) s[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (c < f.ncols) {
+      int b = rg;
+      for (; b + 48 < f.nb; b += 64) {
+        float4 v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = *reinterpret_cast<const float4*>(f.partial + (long long)(b + 16 * k) * w + c);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) add(s[k], v[k]);
+      }
+      for (; b < f.nb; b += 16) add(s[0], *reinterpret_cast<const float4*>(f.partial + (long long)b * w + c));
+    }
+    add(s[0], s[1]);
+    add(s[2], s[3]);
+    add(s[0], s[2]);
+    red[rg * 16 + cl] = s[0];
+  }
+  __syncthreads();
+  if (rg == 0 && c < f.ncols) {
+    float4 t = red[cl];
+#pragma unroll
+    for (int k = 1; k < 16; ++k) add(t, red[k * 16 + cl]);
+    const float o[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (c + e < f.h) f.dgamma[c + e] = o[e];
+      else if (f.dbeta) f.dbeta[c + e - f.h] = o[e];
+    }
+  }
+}
+hipError_t launch_norm_sums(const NormSums& f, hipStream_t s);
+
 // layout: 0 NT, 1 NN, 2 TN (see caat_gemm_layout).  Returns hipError_t of the launch.
 hipError_t launch_gemm(const GemmParams& p, int layout, int epilogue, hipStream_t s);
+// Data gradient nn (NN, epilogue EPI_PLAIN / EPI_GELU_BWD / EPI_SWIGLU_BWD), weight gradient tn (TN, plain) and, if there are
+// any, the sums of the norm's parameter gradients in one launch
+struct GemmPair {
+  int tile;          // shape 0, 1, 3, 4 or 5 of launch_gemm's; -1: one launch after the other is as fast
+  bool tn_first;     // the weight gradient's tiles take longer and go first
+  bool one_each;     // a workgroup of the second GEMM takes one tile
+  double us;         // modelled time
+};
+GemmPair gemm_pair(const GemmParams& nn, const GemmParams& tn);
+hipError_t launch_gemm_pair(const GemmPair& p, const GemmParams& nn, int epilogue, const GemmParams& tn, const NormSums& sums,
+                            hipStream_t s);
 // EPI_SHARED_BCAST (NT, kcat ranks in the contraction), directly or as fp32 sums over groups of ranks that a second kernel
 // adds up.  scratch: gemm_shared_scratch_bytes() bytes; with less, or none, there are fewer groups
 size_t gemm_shared_scratch_bytes(int M, int N, int kcat);
@@ -242,18 +305,19 @@ bool sync_norm_rank_takes(int T, long long tokens, int h, int hs);
 size_t sync_norm_rank_bytes(int T, long long tokens, int h);   // that buffer: never less for more tokens, for any hs
 hipError_t launch_sync_norm_rank(const bf16_t* part, const bf16_t* resid, const bf16_t* gamma, bf16_t* out, bf16_t* xout,
                                  float* rstd, int T, long long tokens, int h, int hs, float eps, hipStream_t s);
+// `later` (both norm backward calls): the sums of dgamma / dbeta are left to the caller and described there
 size_t norm_bwd_workspace_bytes(int T, long long tokens, int h);
 hipError_t launch_norm_bwd(const bf16_t* dy, const bf16_t* dres, const bf16_t* x, const bf16_t* gamma,
                            const float* mean, const float* rstd, bf16_t* g_out, bf16_t* g_scaled, float* dgamma,
                            float* dbeta, int norm, int T, long long tokens, int h, int hs, float private_scale,
-                           void* workspace, hipStream_t s, bool skip_shared_scaled = false);
+                           void* workspace, hipStream_t s, bool skip_shared_scaled = false, NormSums* later = nullptr);
 // norm backward + the backward partial channel-reduce in one launch (hs % 8 == 0; T = 4 up to h = 2048, T = 2 up to
 // h = 4096: norm_bwd_sync_takes); hipErrorInvalidValue if the shape is not taken.  Same workspace as launch_norm_bwd.
 bool norm_bwd_sync_takes(int T, long long tokens, int h, int hs);
 hipError_t launch_norm_bwd_sync(const bf16_t* dy, const bf16_t* dres, const bf16_t* x, const bf16_t* gamma,
                                 const float* mean, const float* rstd, bf16_t* g_out, bf16_t* g_red, float* dgamma,
                                 float* dbeta, int norm, int T, long long tokens, int h, int hs, float private_scale,
-                                void* workspace, hipStream_t s);
+                                void* workspace, hipStream_t s, NormSums* later = nullptr);
 // shared channels of dst = sum over ranks of src's; dst's other channels are not touched (hs % 8 == 0)
 hipError_t launch_partial_sync_shared_from(const bf16_t* src, bf16_t* dst, int T, long long tokens, int h, int hs,
                                            hipStream_t s);

@@ -1209,49 +1209,13 @@ __global__ __launch_bounds__(NT) void norm_bwd_sync_kernel(const bf16_t* __restr
   }
 }
 
-// sums partial[nb][2][h] over nb in a fixed order: a workgroup owns 64 columns (a thread 4 of them, one 16-byte
-// load per partial row), its 16 row groups each add every 16th partial row (4 independent chains), and the 16 group
-// sums are combined in ascending order through LDS.  h % 8 == 0, so 2h is a multiple of 4.  Only the first `ncols`
-// columns of a partial row are read and reduced: 2h for LayerNorm (dgamma | dbeta), h for RMSNorm, whose backward
-// kernels never write the dbeta half of a partial row (and whose dbeta is never stored).
-__global__ __launch_bounds__(256) void norm_bwd_finalize_kernel(const float* __restrict__ partial, int nb, int h,
-                                                                int ncols, float* __restrict__ dgamma,
-                                                                float* __restrict__ dbeta) {
-  __shared__ float4 red[16][16];
-  const int cl = threadIdx.x & 15, rg = threadIdx.x >> 4;
-  const int c = (blockIdx.x * 16 + cl) * 4;
-  const long long w = 2LL * h;
-  float4 s[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) s[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-  auto add = [](float4& a, const float4& b) { a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w; };
-  if (c < ncols) {
-    int b = rg;
-    for (; b + 48 < nb; b += 64) {
-      float4 v[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) v[k] = *reinterpret_cast<const float4*>(partial + (long long)(b + 16 * k) * w + c);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) add(s[k], v[k]);
-    }
-    for (; b < nb; b += 16) add(s[0], *reinterpret_cast<const float4*>(partial + (long long)b * w + c));
-  }
-  add(s[0], s[1]);
-  add(s[2], s[3]);
-  add(s[0], s[2]);
-  red[rg][cl] = s[0];
-  __syncthreads();
-  if (rg == 0 && c < ncols) {
-    float4 t = red[0][cl];
-#pragma unroll
-    for (int k = 1; k < 16; ++k) add(t, red[k][cl]);
-    const float o[4] = {t.x, t.y, t.z, t.w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      if (c + e < h) dgamma[c + e] = o[e];
-      else if (dbeta) dbeta[c + e - h] = o[e];
-    }
-  }
+__global__ __launch_bounds__(256) void norm_bwd_finalize_kernel(const NormSums f) {
+  __shared__ float4 red[256];
+  norm_sums(f, blockIdx.x, red);
+}
+hipError_t launch_norm_sums(const NormSums& f, hipStream_t s) {
+  hipLaunchKernelGGL(norm_bwd_finalize_kernel, dim3((unsigned)norm_sums_blocks(f)), dim3(256), 0, s, f);
+  return hipGetLastError();
 }
 
 static constexpr int NORM_BWD_WIDE_H = 4096;          // rows wider than this take the workgroup-per-row kernel
@@ -1304,7 +1268,7 @@ static hipError_t norm_bwd_dispatch(const bf16_t* dy, const bf16_t* dres, const 
 hipError_t launch_norm_bwd(const bf16_t* dy, const bf16_t* dres, const bf16_t* x, const bf16_t* gamma,
                            const float* mean, const float* rstd, bf16_t* g_out, bf16_t* g_scaled, float* dgamma,
                            float* dbeta, int norm, int T, long long tokens, int h, int hs, float private_scale,
-                           void* workspace, hipStream_t s, bool skip_shared_scaled) {
+                           void* workspace, hipStream_t s, bool skip_shared_scaled, NormSums* later) {
   const long long rows = (long long)T * tokens;
   const int skip_shared = (skip_shared_scaled && g_scaled != nullptr && hs % 8 == 0) ? 1 : 0;
   if (rows == 0) return hipSuccess;
@@ -1326,9 +1290,12 @@ hipError_t launch_norm_bwd(const bf16_t* dy, const bf16_t* dres, const bf16_t* x
   else return hipErrorInvalidValue;
   if (e != hipSuccess) return e;
   const int ncols = norm == 0 ? 2 * h : h;           // RMSNorm has no dbeta: that half of a partial row is never written
-  hipLaunchKernelGGL(norm_bwd_finalize_kernel, dim3((unsigned)((ncols + 63) / 64)), dim3(256), 0, s, partial, (int)nb,
-                     h, ncols, dgamma, norm == 0 ? dbeta : nullptr);
-  return hipGetLastError();
+  const NormSums sums = {partial, (int)nb, h, ncols, dgamma, norm == 0 ? dbeta : nullptr};
+  if (later) {
+    *later = sums;
+    return hipSuccess;
+  }
+  return launch_norm_sums(sums, s);
 }
 
 // Shapes the fused norm backward + reduce takes: a thread (of 256) holds x, dy and dres of its column groups for all T
@@ -1365,7 +1332,7 @@ static hipError_t norm_bwd_sync_dispatch(const bf16_t* dy, const bf16_t* dres, c
 hipError_t launch_norm_bwd_sync(const bf16_t* dy, const bf16_t* dres, const bf16_t* x, const bf16_t* gamma,
                                 const float* mean, const float* rstd, bf16_t* g_out, bf16_t* g_red, float* dgamma,
                                 float* dbeta, int norm, int T, long long tokens, int h, int hs, float private_scale,
-                                void* workspace, hipStream_t s) {
+                                void* workspace, hipStream_t s, NormSums* later) {
   if (!norm_bwd_sync_takes(T, tokens, h, hs)) return hipErrorInvalidValue;
   // as many partial rows as the row-wise kernels would use for this shape at most, so that the same workspace serves
   long long nb = norm_bwd_blocks((long long)T * tokens, h);
@@ -1383,9 +1350,12 @@ hipError_t launch_norm_bwd_sync(const bf16_t* dy, const bf16_t* dres, const bf16
 #undef CAAT_NBS
   if (e != hipSuccess) return e;
   const int ncols = norm == 0 ? 2 * h : h;
-  hipLaunchKernelGGL(norm_bwd_finalize_kernel, dim3((unsigned)((ncols + 63) / 64)), dim3(256), 0, s, partial, (int)nb,
-                     h, ncols, dgamma, norm == 0 ? dbeta : nullptr);
-  return hipGetLastError();
+  const NormSums sums = {partial, (int)nb, h, ncols, dgamma, norm == 0 ? dbeta : nullptr};
+  if (later) {
+    *later = sums;
+    return hipSuccess;
+  }
+  return launch_norm_sums(sums, s);
 }
 
 // ---------------------------------------------------------------------------------------------------------

@@ -16,7 +16,9 @@ extern "C" {
  * caat_block_fwd / caat_block_bwd bracket every kernel they enqueue with a pair of HIP events on the caller's
  * stream.  caat_profile_get waits for record `index` (in launch order since the last reset) and returns a
  * static kernel-family name (host pointer to a NUL-terminated string) and the elapsed milliseconds.  Events
- * are created on first use and reused after a reset.  Not thread-safe; off by default.
+ * are created on first use and reused after a reset.  Not thread-safe; off by default.  While it is on, the backward's
+ * GEMMs are enqueued one by one, also where they otherwise share a launch (caat_gemm_pair_route), so that each has a time of
+ * its own.
  */
 int caat_profile_enable(int on);
 int caat_profile_reset(void);
@@ -50,6 +52,14 @@ int caat_hbm_probe(const void* src, void* dst, size_t bytes, int mode, void* hip
  * or -1 for arguments out of range.
  */
 int caat_gemm_route(int layout, int epilogue, int G, long long M, long long N, long long K, int ranks, long long shard_cols);
+
+/*
+ * How the backward enqueues a data gradient [M, N] of contraction K and the weight gradient [K, N] of contraction M that goes
+ * with it, for G ranks (host only): -1 one after the other (caat_gemm_route names the kernels), else in one launch: tile 0, 1,
+ * 3, 4 or 5 of caat_gemm_route, + 16 where the weight gradient's tiles come first, + 32 where a workgroup of the second of
+ * them takes one tile and not a share of several.  -2 for arguments out of range.
+ */
+int caat_gemm_pair_route(int G, long long M, long long N, long long K);
 
 #ifdef __cplusplus
 }

@@ -1,0 +1,23 @@
+"""Which gradient GEMMs share a launch, asked on the host."""
+from paper_2506_19645_amd import binding as B
+from tests import test_gpu_gemm_pairs as pairs
+
+
+def test_gpu_tests_reach_every_pair_kernel_and_every_order():
+    seen = set()
+    for swi, T, n, h, fr, hs in pairs.PAIRS:
+        for first, (N, K) in ((True, (fr, h)), (False, (h, 2 * fr if swi else fr))):
+            r = B.gemm_pair_route(T, n, N, K)
+            if r >= 0:
+                seen |= {(r % 16, ("gelu", "swiglu")[swi] if first else "plain"), r}
+    missing = {(tile, e) for tile in (0, 1, 3, 4, 5) for e in ("gelu", "swiglu", "plain")} - seen
+    # persistent tiles: either GEMM first, the second by the tile and in shares; others: either first, always by the tile
+    missing |= ({0, 16, 32, 48, 17, 33, 35, 51, 36, 52, 37, 53} | {1, 49}) - seen
+    assert not missing, sorted(map(str, missing))
+
+
+def test_training_steps_pair_their_gradient_gemms_unless_one_is_a_long_chain():
+    for T, n, h, fr in ((2, 256, 768, 1536), (4, 1111, 2048, 1408), (4, 8192, 2048, 2048), (8, 147, 1536, 768)):
+        assert B.gemm_pair_route(T, n, fr, h) >= 0
+    assert B.gemm_pair_route(2, 7476, 512, 1024) == -1        # 8 x 512 columns from 7476 rows: tiles that share a contraction
+    assert B.gemm_pair_route(0, 1, 8, 8) == B.gemm_pair_route(1, 1 << 31, 8, 8) == -2

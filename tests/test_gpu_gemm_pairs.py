@@ -1,0 +1,50 @@
+"""The backward's GEMMs two to a launch: every tile shape with every fused epilogue that a pair has, and the same launches one
+after the other, which the library takes while launches are timed."""
+import pytest
+
+from paper_2506_19645_amd import binding as B
+from tests.test_gpu_block import check_mlp_block, oracle_mlp_block, run_mlp_block
+from tests.test_gpu_gemm_kernels import BLOCKS, block_config
+from tests.util import make_inputs
+
+pytestmark = pytest.mark.gpu
+
+# (SwiGLU, T, tokens, h, ffn / T, hs); contractions with a remainder, ragged edges, more tiles than the chip holds at once and
+# fewer; tests/test_gemm_pair_routes.py checks on the host which launches they reach
+PAIRS = [
+    (False, 8, 1000, 1032, 520, 512), (True, 8, 1000, 1032, 520, 21), (False, 4, 1300, 1160, 1032, 0), (True, 4, 1300, 1160, 1032, 1160),
+    (False, 8, 136, 264, 2056, 64), (True, 8, 136, 264, 2056, 79), (True, 8, 1160, 264, 1032, 264), (False, 2, 1300, 1032, 1544, 512),
+    (True, 2, 1300, 1032, 1544, 0), (False, 16, 1300, 1032, 136, 512), (True, 4, 200, 1160, 4104, 256), (False, 8, 136, 1160, 2056, 576),
+    (False, 8, 1, 72, 3080, 40), (True, 16, 1, 72, 1544, 72), (False, 8, 100, 8, 3080, 8), (True, 16, 100, 72, 1544, 0),
+    (False, 4, 65, 8, 3080, 0), (True, 8, 65, 136, 1544, 100), (False, 4, 1, 136, 2056, 136), (True, 8, 17, 72, 1032, 21),
+    (False, 1, 1, 8, 8, 4), (True, 2, 65, 72, 136, 33), (False, 2, 100, 136, 200, 64), (True, 2, 33, 200, 72, 128),
+    (False, 2, 256, 768, 1536, 384), (False, 2, 2048, 1032, 3080, 0), (True, 4, 1300, 264, 2056, 128),
+    (False, 4, 1300, 264, 4104, 128), (True, 1, 65, 8, 72, 5), (True, 4, 100, 72, 1544, 32), (True, 8, 65, 72, 1032, 72), (True, 8, 100, 8, 2056, 8),
+]
+
+
+def check(swi, T, n, h, fr, hs):
+    cfg = block_config(swi, T, n, h, fr, hs)
+    d = make_inputs(cfg, seed=31, weight_std=0.05)
+    got = run_mlp_block(cfg, d)
+    w, fwd, g = oracle_mlp_block(cfg, d)
+    check_mlp_block(cfg, d, got, w, fwd, g)
+
+
+@pytest.mark.parametrize("swi,T,n,h,fr,hs", PAIRS)
+def test_mlp_block_with_paired_gemms(swi, T, n, h, fr, hs):
+    check(swi, T, n, h, fr, hs)
+
+
+@pytest.mark.parametrize("swi,T,n,h,fr,hs", [b[:6] for b in BLOCKS])
+def test_mlp_block_with_every_gemm_a_launch_of_its_own(swi, T, n, h, fr, hs):
+    if B.gemm_pair_route(T, n, fr, h) < 0:
+        return   # tests/test_gpu_gemm_kernels.py runs them so
+    B.profile_reset()
+    B.profile_enable(True)
+    try:
+        check(swi, T, n, h, fr, hs)
+    finally:
+        B.profile_enable(False)
+    assert sum(name.startswith("gemm") for name, _ in B.profile_records()) == 6
+    B.profile_reset()
