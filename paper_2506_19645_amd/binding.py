@@ -47,7 +47,8 @@ EXPORTS = ["caat_shared_channels", "caat_status_string", "caat_workspace_bytes",
            "caat_partial_sync", "caat_norm_fwd", "caat_partial_sync_norm_fwd", "caat_norm_bwd_workspace_bytes",
            "caat_norm_bwd", "caat_norm_bwd_static", "caat_gemm_bf16", "caat_block_fwd", "caat_block_bwd"]
 TOOL_EXPORTS = ["caat_profile_enable", "caat_profile_reset", "caat_profile_count", "caat_profile_get", "caat_hbm_probe",
-                "caat_gemm_route", "caat_gemm_pair_route"]
+                "caat_gemm_route", "caat_gemm_pair_route",
+                "caat_gemm_shared_pair_route"]
 
 _lib = None
 
@@ -101,6 +102,8 @@ def lib() -> C.CDLL:
         L.caat_gemm_route.restype = i
         L.caat_gemm_pair_route.argtypes = [i, ll, ll, ll]
         L.caat_gemm_pair_route.restype = i
+        L.caat_gemm_shared_pair_route.argtypes = [i, ll, ll, ll, ll]
+        L.caat_gemm_shared_pair_route.restype = i
         _lib = L
     return _lib
 
@@ -277,6 +280,10 @@ def gemm_route(layout: int, epilogue: int, G: int, M: int, N: int, K: int, ranks
 
 def gemm_pair_route(G: int, M: int, N: int, K: int) -> int:
     return lib().caat_gemm_pair_route(G, M, N, K)
+
+
+def gemm_shared_pair_route(T: int, M: int, h: int, hs: int, K: int) -> int:
+    return lib().caat_gemm_shared_pair_route(T, M, h, hs, K)
 
 
 def profile_enable(on: bool) -> None:

@@ -203,32 +203,34 @@ int rowpar_pcr(const caat_desc* d, const bf16_t* a, long long kdim, const bf16_t
     const long long ldp = dd ? h - hs : h, ldsh = dd ? hs : h;
     const bf16_t* resid_p = dd ? resid + n * hs : resid + hs;
     bf16_t* out_p = dd ? out + n * hs : out + hs;
-    if (hs < h) {
-      std::memset(&q, 0, sizeof(q));
-      q.a = a; q.lda = kdim; q.stride_a = n * kdim;
-      q.b = w + (long long)hs * kdim; q.ldb = kdim; q.stride_b = h * kdim;
-      q.c = out_p; q.ldc = ldp; q.stride_c = n * ldp;
-      q.aux = resid_p; q.ldaux = ldp; q.stride_aux = n * ldp;
-      q.G = (int)T; q.M = (int)n; q.N = (int)(h - hs); q.K = (int)kdim;
-      q.hs = 0; q.scale = d->private_scale;
-      q.n_route = (int)h;   // the kernel, and so the order of the sums, as without reduce_in_gemm
-      {
-        ProfScope ps(s, "gemm_nt_rowpar_private");
-        e = launch_gemm(q, 0, EPI_ROWPAR, s);
-      }
+    GemmParams priv;
+    std::memset(&priv, 0, sizeof(priv));
+    priv.a = a; priv.lda = kdim; priv.stride_a = n * kdim;
+    priv.b = w + (long long)hs * kdim; priv.ldb = kdim; priv.stride_b = h * kdim;
+    priv.c = out_p; priv.ldc = ldp; priv.stride_c = n * ldp;
+    priv.aux = resid_p; priv.ldaux = ldp; priv.stride_aux = n * ldp;
+    priv.G = (int)T; priv.M = (int)n; priv.N = (int)(h - hs); priv.K = (int)kdim;
+    priv.hs = 0; priv.scale = d->private_scale;
+    priv.n_route = (int)h;   // the kernel, and so the order of the sums, as without reduce_in_gemm
+    std::memset(&q, 0, sizeof(q));
+    q.a = a; q.lda = kdim; q.kstride_a = n * kdim;
+    q.b = w; q.ldb = kdim; q.kstride_b = h * kdim;
+    q.c = out; q.ldc = ldsh; q.stride_c = n * h;
+    q.aux = resid; q.ldaux = ldsh; q.stride_aux = n * h;
+    q.G = 1; q.M = (int)n; q.N = hs; q.K = (int)kdim; q.kcat = (int)T; q.bcast = dd ? 1 : (int)T;
+    bool done = false;
+    if (hs > 0 && hs < h && !g_prof_on) {   // (timed launches: each of its own, see grad_pair)
+      e = launch_gemm_shared_private(q, priv, scratch, scratch_bytes, &done, s);
       if (e != hipSuccess) return CAAT_EHIP;
     }
-    if (hs > 0) {
-      std::memset(&q, 0, sizeof(q));
-      q.a = a; q.lda = kdim; q.kstride_a = n * kdim;
-      q.b = w; q.ldb = kdim; q.kstride_b = h * kdim;
-      q.c = out; q.ldc = ldsh; q.stride_c = n * h;
-      q.aux = resid; q.ldaux = ldsh; q.stride_aux = n * h;
-      q.G = 1; q.M = (int)n; q.N = hs; q.K = (int)kdim; q.kcat = (int)T; q.bcast = dd ? 1 : (int)T;
-      {
-        ProfScope ps(s, "gemm_nt_shared_kcat");
-        e = launch_gemm_shared(q, scratch, scratch_bytes, s);
-      }
+    if (hs < h && !done) {
+      ProfScope ps(s, "gemm_nt_rowpar_private");
+      e = launch_gemm(priv, 0, EPI_ROWPAR, s);
+      if (e != hipSuccess) return CAAT_EHIP;
+    }
+    if (hs > 0 && !done) {
+      ProfScope ps(s, "gemm_nt_shared_kcat");
+      e = launch_gemm_shared(q, scratch, scratch_bytes, s);
       if (e != hipSuccess) return CAAT_EHIP;
     }
     return CAAT_OK;
@@ -573,7 +575,20 @@ int caat_gemm_pair_route(int G, long long M, long long N, long long K) {
   nn.G = G; nn.M = (int)M; nn.N = (int)N; nn.K = (int)K;
   tn.G = G; tn.M = (int)K; tn.N = (int)N; tn.K = (int)M;
   const GemmPair p = gemm_pair(nn, tn);
-  return p.tile < 0 ? -1 : p.tile + (p.tn_first ? 16 : 0) + (p.one_each ? 32 : 0);
+  return p.tile < 0 ? -1 : p.tile + (p.second_first ? 16 : 0) + (p.one_each ? 32 : 0);
+}
+
+int caat_gemm_shared_pair_route(int T, long long M, long long h, long long hs, long long K) {
+  constexpr long long MAX = 0x7FFFFFFFLL;
+  if (T < 1 || M < 1 || hs < 1 || h <= hs || K < 1 || M > MAX || h > MAX || K > MAX) return -2;
+  GemmParams p, priv;
+  std::memset(&p, 0, sizeof(p));
+  std::memset(&priv, 0, sizeof(priv));
+  p.G = 1; p.M = (int)M; p.N = (int)hs; p.K = (int)K; p.kcat = T;
+  priv.G = T; priv.M = (int)M; priv.N = (int)(h - hs); priv.K = (int)K; priv.n_route = (int)h;
+  int groups = 1;
+  const GemmPair pair = gemm_shared_pair(p, priv, gemm_shared_scratch_bytes((int)M, (int)hs, T), &groups);
+  return pair.tile < 0 ? -1 : pair.tile + (pair.second_first ? 16 : 0) + (pair.one_each ? 32 : 0) + 256 * groups;
 }
 
 int caat_profile_enable(int on) {

@@ -16,7 +16,8 @@ template <> hipError_t launch_block_sized<Cfg64x64>(const GemmParams&, int, int,
 template <> hipError_t launch_block_sized<Cfg128x128k>(const GemmParams&, int, int, hipStream_t);
 template <> hipError_t launch_block_sized<Cfg64x64k>(const GemmParams&, int, int, hipStream_t);
 
-#define CAAT_PAIR(CFG) template <> hipError_t launch_pair<CFG>(const GemmParams&, int, const GemmParams&, const NormSums&, bool, bool, hipStream_t);
+#define CAAT_PAIR(CFG) \
+  template <> hipError_t launch_pair<CFG>(const GemmPair&, const GemmParams&, int, const GemmParams&, int, const NormSums&, hipStream_t);
 CAAT_PAIR(Cfg256x256) CAAT_PAIR(Cfg192x256) CAAT_PAIR(Cfg128x128) CAAT_PAIR(Cfg64x128) CAAT_PAIR(Cfg64x64)
 #undef CAAT_PAIR
 
@@ -196,13 +197,13 @@ hipError_t launch_gemm(const GemmParams& p, int layout, int epilogue, hipStream_
 // Measured on 44 training steps of 135 to 8192 tokens, T = 2 to 8, h = 512 to 4096 (backward pass, us; one after the
 // other / paired): 4 x 360 tokens of 512, ffn 1792 36.4 / 25.7, 8 x 147 of 1536, ffn 6144 57.8 / 41.2, 4 x 731 of 2048,
 // ffn 5504 155 / 132, 4 x 1111 of 2048, ffn 5632 204 / 188, 4 x 8192 of 2048, ffn 8192 1027 / 1000.
-static GemmPair plan_pair(const TileShape& t, int index, const GemmParams& nn, const GemmParams& tn, int n_cu) {
+static GemmPair plan_pair(const TileShape& t, int index, const GemmParams& p1, const GemmParams& p2, int n_cu) {
   auto tiles = [&](const GemmParams& p) { return (((long long)p.M + t.bm - 1) / t.bm) * (((long long)p.N + t.bn - 1) / t.bn) * p.G; };
-  auto us = [&](const GemmParams& p) { return (double)(((long long)p.K + t.k - 1) / t.k) * t.stage + t.tile; };
-  const double un = us(nn), ut = us(tn);
-  const bool tf = ut > un;
-  const long long slots = (long long)t.per_cu * n_cu, na = tiles(tf ? tn : nn), nb = tiles(tf ? nn : tn);
-  const double ua = tf ? ut : un, ub = tf ? un : ut;
+  auto us = [&](const GemmParams& p) { return (double)(((long long)p.K + t.k - 1) / t.k) * (p.kcat > 1 ? p.kcat : 1) * t.stage + t.tile; };
+  const double u1 = us(p1), u2 = us(p2);
+  const bool sf = u2 > u1;
+  const long long slots = (long long)t.per_cu * n_cu, na = tiles(sf ? p2 : p1), nb = tiles(sf ? p1 : p2);
+  const double ua = sf ? u2 : u1, ub = sf ? u1 : u2;
   // behind the first GEMM n_hi slots are free at hi, n_lo at lo
   const long long n_hi = na % slots, n_lo = slots - n_hi;
   const double lo = (double)(na / slots) * ua, hi = n_hi ? lo + ua : lo;
@@ -231,15 +232,19 @@ static GemmPair plan_pair(const TileShape& t, int index, const GemmParams& nn, c
     end = std::min(each, even);
   }
   const double fill = (na * ua + nb * ub) / (slots * end);
-  return {index, tf, one_each, end * (0.55 + 0.45 * std::min(fill, 1.0))};
+  return {index, sf, one_each, end * (0.55 + 0.45 * std::min(fill, 1.0))};
+}
+static GemmPair best_pair(const GemmParams& p1, const GemmParams& p2, int n_cu) {
+  GemmPair best = {-1, false, false, 0.0};
+  for (int i : {0, 1, 3, 4, 5}) {
+    const GemmPair p = plan_pair(TILES[i], i, p1, p2, n_cu);
+    if (best.tile < 0 || p.us < best.us) best = p;
+  }
+  return best;
 }
 GemmPair gemm_pair(const GemmParams& nn, const GemmParams& tn) {
   const int n_cu = compute_units();
-  GemmPair best = {-1, false, false, 0.0};
-  for (int i : {0, 1, 3, 4, 5}) {
-    const GemmPair p = plan_pair(TILES[i], i, nn, tn, n_cu);
-    if (best.tile < 0 || p.us < best.us) best = p;
-  }
+  GemmPair best = best_pair(nn, tn, n_cu);
   double a = 0.0, b = 0.0;
   choose_tile(nn, 1, EPI_PLAIN, n_cu, &a);
   choose_tile(tn, 2, EPI_PLAIN, n_cu, &b);
@@ -247,17 +252,21 @@ GemmPair gemm_pair(const GemmParams& nn, const GemmParams& tn) {
   return best;
 }
 
-hipError_t launch_gemm_pair(const GemmPair& p, const GemmParams& nn, int epilogue, const GemmParams& tn, const NormSums& sums,
-                            hipStream_t s) {
-  if (!in_range(nn, epilogue) || !in_range(tn, EPI_PLAIN)) return hipErrorInvalidValue;
+static hipError_t launch_any_pair(const GemmPair& p, const GemmParams& p1, int epilogue1, const GemmParams& p2, int epilogue2,
+                                  const NormSums& sums, hipStream_t s) {
+  if (!in_range(p1, epilogue1) || !in_range(p2, epilogue2)) return hipErrorInvalidValue;
   switch (p.tile) {
-    case 0: return launch_pair<Cfg256x256>(nn, epilogue, tn, sums, p.tn_first, p.one_each, s);
-    case 1: return launch_pair<Cfg192x256>(nn, epilogue, tn, sums, p.tn_first, p.one_each, s);
-    case 3: return launch_pair<Cfg128x128>(nn, epilogue, tn, sums, p.tn_first, p.one_each, s);
-    case 4: return launch_pair<Cfg64x128>(nn, epilogue, tn, sums, p.tn_first, p.one_each, s);
-    case 5: return launch_pair<Cfg64x64>(nn, epilogue, tn, sums, p.tn_first, p.one_each, s);
+    case 0: return launch_pair<Cfg256x256>(p, p1, epilogue1, p2, epilogue2, sums, s);
+    case 1: return launch_pair<Cfg192x256>(p, p1, epilogue1, p2, epilogue2, sums, s);
+    case 3: return launch_pair<Cfg128x128>(p, p1, epilogue1, p2, epilogue2, sums, s);
+    case 4: return launch_pair<Cfg64x128>(p, p1, epilogue1, p2, epilogue2, sums, s);
+    case 5: return launch_pair<Cfg64x64>(p, p1, epilogue1, p2, epilogue2, sums, s);
     default: return hipErrorInvalidValue;
   }
+}
+hipError_t launch_gemm_pair(const GemmPair& p, const GemmParams& nn, int epilogue, const GemmParams& tn, const NormSums& sums,
+                            hipStream_t s) {
+  return launch_any_pair(p, nn, epilogue, tn, EPI_PLAIN, sums, s);
 }
 
 // The shared channels of all ranks as one product with a contraction kcat times as long: few tiles, each a long chain.
@@ -272,26 +281,36 @@ hipError_t launch_gemm_pair(const GemmPair& p, const GemmParams& nn, int epilogu
 //   65 x 2048 x 512 x 8     29 / 22 / 17 / 17     1024 x 2048 x 1376 x 8    112 / 93 / 80 / 72
 //   777 x 1024 x 512 x 4    18 / 19 / 22           777 x 2048 x 3584 x 4    116 / 92 / 70
 // `scratch_bytes`: what there is for the groups' sums.
-static int gemm_shared_groups(int M, int N, int K, int kcat, size_t scratch_bytes) {
+static int gemm_shared_groups(int M, int N, int K, int kcat, size_t scratch_bytes, const GemmParams* priv = nullptr,
+                              GemmPair* pair = nullptr, double* us_out = nullptr) {
   GemmParams q = {};
   q.M = M;
   q.N = N;
   q.K = K;
   int best = 1;
   double cost = 0.0;
+  if (pair) pair->tile = -1;
   for (int g = 1; g <= kcat; g *= 2) {
     if (kcat % g != 0 || (g > 1 && (size_t)g * M * N * sizeof(float) > scratch_bytes)) break;
     q.G = g;
     q.kcat = kcat / g;
     double us = 0.0;
-    choose_tile(q, 0, EPI_PARTIAL, 256, &us);
+    GemmPair p = {-1, false, false, 0.0};
+    if (priv) {
+      p = best_pair(*priv, q, 256);
+      us = p.us;
+    } else {
+      choose_tile(q, 0, EPI_PARTIAL, 256, &us);
+    }
     us *= 1.4;
     if (g > 1) us += 5.0 + (double)g * M * N * 4.0 / 7e6;
     if (g == 1 || us < cost) {
       cost = us;
       best = g;
+      if (pair) *pair = p;
     }
   }
+  if (us_out) *us_out = cost;
   return best;
 }
 
@@ -301,9 +320,8 @@ size_t gemm_shared_scratch_bytes(int M, int N, int kcat) {
   return kcat > 1 ? std::min((size_t)kcat * M * N * sizeof(float), (size_t)128 << 20) : 0;
 }
 
-hipError_t launch_gemm_shared(const GemmParams& p, void* scratch, size_t scratch_bytes, hipStream_t s) {
-  const int groups = gemm_shared_groups(p.M, p.N, p.K, p.kcat, scratch ? scratch_bytes : 0);
-  if (groups == 1) return launch_gemm(p, 0, EPI_SHARED_BCAST, s);
+// p cut into groups of ranks whose fp32 sums go to scratch
+static GemmParams shared_groups(const GemmParams& p, int groups, void* scratch) {
   GemmParams q = p;
   q.G = groups;
   q.kcat = p.kcat / groups;
@@ -314,10 +332,44 @@ hipError_t launch_gemm_shared(const GemmParams& p, void* scratch, size_t scratch
   q.stride_c = (long long)p.M * p.N;
   q.aux = nullptr;
   q.ldaux = 0;
-  const hipError_t e = launch_gemm(q, 0, EPI_PARTIAL, s);
-  if (e != hipSuccess) return e;
+  return q;
+}
+static hipError_t merge_groups(const GemmParams& p, int groups, const void* scratch, hipStream_t s) {
   return launch_shared_merge(reinterpret_cast<const float*>(scratch), groups, p.aux, p.c, p.M, p.N, p.ldaux, p.ldc, p.stride_aux,
                              p.stride_c, p.bcast, s);
+}
+hipError_t launch_gemm_shared(const GemmParams& p, void* scratch, size_t scratch_bytes, hipStream_t s) {
+  const int groups = gemm_shared_groups(p.M, p.N, p.K, p.kcat, scratch ? scratch_bytes : 0);
+  if (groups == 1) return launch_gemm(p, 0, EPI_SHARED_BCAST, s);
+  const hipError_t e = launch_gemm(shared_groups(p, groups, scratch), 0, EPI_PARTIAL, s);
+  return e != hipSuccess ? e : merge_groups(p, groups, scratch, s);
+}
+
+// With the private columns in the same launch the groups are chosen anew: the private tiles fill what the shared ones leave idle.
+// Not where the private columns stream their weights (65 to 128 token rows, see choose_route).  Prefill layers of the 7B shape,
+// us, two launches / one: T = 8, hs = h / 2, 777 tokens 479 / 469, 200 tokens 242 / 222, 100 tokens 173 / 161; hs = h / 4, 1500
+// tokens 801 / 765; 3 x 500 tokens of 2048, T = 2, hs = h / 4 247 / 216.
+GemmPair gemm_shared_pair(const GemmParams& p, const GemmParams& priv, size_t scratch_bytes, int* groups) {
+  GemmPair pair = {-1, false, false, 0.0};
+  const int n_cu = compute_units();
+  *groups = 1;
+  if (choose_route(priv, 0, EPI_ROWPAR, n_cu) >= ROUTE_FEW_ROWS) return pair;
+  double alone = 0.0, both = 0.0, us = 0.0;
+  gemm_shared_groups(p.M, p.N, p.K, p.kcat, scratch_bytes, nullptr, nullptr, &alone);
+  choose_tile(priv, 0, EPI_ROWPAR, n_cu, &us);
+  *groups = gemm_shared_groups(p.M, p.N, p.K, p.kcat, scratch_bytes, &priv, &pair, &both);
+  if (both >= alone + 1.4 * us + 2.0) pair.tile = -1;
+  return pair;
+}
+hipError_t launch_gemm_shared_private(const GemmParams& p, const GemmParams& priv, void* scratch, size_t scratch_bytes, bool* taken,
+                                      hipStream_t s) {
+  int groups = 1;
+  const GemmPair pair = gemm_shared_pair(p, priv, scratch ? scratch_bytes : 0, &groups);
+  *taken = pair.tile >= 0;
+  if (!*taken) return hipSuccess;
+  const hipError_t e = groups == 1 ? launch_any_pair(pair, priv, EPI_ROWPAR, p, EPI_SHARED_BCAST, NormSums{}, s)
+                                   : launch_any_pair(pair, priv, EPI_ROWPAR, shared_groups(p, groups, scratch), EPI_PARTIAL, NormSums{}, s);
+  return e != hipSuccess || groups == 1 ? e : merge_groups(p, groups, scratch, s);
 }
 
 int gemm_route(const GemmParams& p, int layout, int epilogue) {

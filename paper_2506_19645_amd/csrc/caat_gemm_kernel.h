@@ -776,29 +776,37 @@ __global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_kern
   gemm_tiles<CFG, AT, BT, EPI>(p, smem, blockIdx.x, gridDim.x);
 }
 
-// The two gradient GEMMs that wait for the same tensor, the data gradient (NN) and the weight gradient (TN), in one launch, and
-// in front of them the sums of the norm's parameter gradients (n_sums workgroups, see norm_sums).  They do not depend on
-// each other: workgroups of the second one (the one with the shorter tiles) start wherever the first leaves a slot idle, and
-// there are one or two launches less, each with a start, an end and a last round of its own.  n_sums and n_first are
-// multiples of 8, so that a workgroup's number within its GEMM names its XCD.  256 tokens of h = 768, T = 2, ffn 3072:
-// 6 launches of 39.4 us become 3 of 30.1; 1111 tokens of 2048, T = 4, SwiGLU, ffn 5632: 204 -> 188 us; see choose_pair.
-template <class CFG, int EPI>
-__global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_pair_kernel(const GemmParams nn, const GemmParams tn,
+// Two GEMMs that do not depend on each other in one launch: the data gradient (NN) and the weight gradient (TN) that wait for
+// the same tensor, with the sums of the norm's parameter gradients in front of them (n_sums workgroups, see norm_sums), or the
+// private and the shared columns of a row-parallel product with the reduce inside (both NT).  Workgroups of the second one
+// (the one with the shorter tiles) start wherever the first leaves a slot idle, and there are one or two launches less, each
+// with a start, an end and a last round of its own.  n_sums and n_first are multiples of 8, so that a workgroup's number
+// within its GEMM names its XCD.  256 tokens of h = 768, T = 2, ffn 3072: 6 launches of 39.4 us become 3 of 30.1; 1111
+// tokens of 2048, T = 4, SwiGLU, ffn 5632: 204 -> 188 us; see gemm_pair.
+template <class CFG, class P1, class P2>
+__global__ __launch_bounds__(CFG::THREADS, CFG::MIN_WAVES_PER_EU) void gemm_pair_kernel(const GemmParams p1, const GemmParams p2,
                                                                                       const NormSums sums, int n_sums, int n_first,
-                                                                                      int tn_first) {
+                                                                                      int second_first) {
   __shared__ uint4 smem[CFG::SMEM_CHUNKS];
   int b = blockIdx.x;
-  if (b < n_sums) {
-    norm_sums(sums, b, reinterpret_cast<float4*>(smem));
-    return;
+  if constexpr (P1::BT) {
+    if (b < n_sums) {
+      norm_sums(sums, b, reinterpret_cast<float4*>(smem));
+      return;
+    }
+    b -= n_sums;
   }
-  b -= n_sums;
   const bool first = b < n_first;
   const int nb = first ? n_first : (int)gridDim.x - n_sums - n_first;
   if (!first) b -= n_first;
-  if (first == (tn_first != 0)) gemm_tiles<CFG, true, true, EPI_PLAIN>(tn, smem, b, nb);
-  else gemm_tiles<CFG, false, true, EPI>(nn, smem, b, nb);
+  if (first == (second_first != 0)) gemm_tiles<CFG, P2::AT, P2::BT, P2::EPI>(p2, smem, b, nb);
+  else gemm_tiles<CFG, P1::AT, P1::BT, P1::EPI>(p1, smem, b, nb);
 }
+template <bool AT_, bool BT_, int EPI_>
+struct GemmKind {   // operand layouts and epilogue
+  static constexpr bool AT = AT_, BT = BT_;
+  static constexpr int EPI = EPI_;
+};
 
 // workgroups for `total` tiles, 0 if there are too many or the device cannot be asked
 template <class CFG>
@@ -828,20 +836,20 @@ static hipError_t launch_one(const GemmParams& p, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <class CFG, int EPI>
-static hipError_t launch_pair_one(const GemmParams& nn, const GemmParams& tn, const NormSums& sums, bool tn_first, bool one_each,
+template <class CFG, class P1, class P2>
+static hipError_t launch_pair_one(const GemmPair& pair, const GemmParams& p1, const GemmParams& p2, const NormSums& sums,
                                   hipStream_t s) {
   auto tiles = [](const GemmParams& p) {
     return ((long long)p.M + CFG::BM - 1) / CFG::BM * ((p.N + CFG::BN - 1) / CFG::BN) * p.G;
   };
-  const long long t1 = tiles(tn_first ? tn : nn), t2 = tiles(tn_first ? nn : tn);
-  const long long b1 = tile_blocks<CFG>(t1), b2 = one_each ? t2 : tile_blocks<CFG>(t2);
+  const bool sf = pair.second_first;
+  const long long t1 = tiles(sf ? p2 : p1), t2 = tiles(sf ? p1 : p2);
+  const long long b1 = tile_blocks<CFG>(t1), b2 = pair.one_each ? t2 : tile_blocks<CFG>(t2);
   if (b1 <= 0 || b2 <= 0 || b1 + b2 > 0x7FFF0000LL) return hipErrorInvalidValue;
   auto eights = [](long long v) { return ((unsigned)v + 7u) & ~7u; };
-  const unsigned n_sums = eights(norm_sums_blocks(sums)), n_first = eights(b1), n_second = eights(b2);
-  const unsigned grid = n_sums + n_first + n_second;
-  hipLaunchKernelGGL((gemm_pair_kernel<CFG, EPI>), dim3(grid), dim3(CFG::THREADS), 0, s, nn, tn, sums, (int)n_sums, (int)n_first,
-                     tn_first ? 1 : 0);
+  const unsigned n_sums = P1::BT ? eights(norm_sums_blocks(sums)) : 0u, n_first = eights(b1), n_second = eights(b2);
+  hipLaunchKernelGGL((gemm_pair_kernel<CFG, P1, P2>), dim3(n_sums + n_first + n_second), dim3(CFG::THREADS), 0, s, p1, p2, sums,
+                     (int)n_sums, (int)n_first, sf ? 1 : 0);
   return hipGetLastError();
 }
 

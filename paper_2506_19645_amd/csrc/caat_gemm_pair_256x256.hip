@@ -1,4 +1,4 @@
-// Pairs of gradient GEMMs in one launch, 256 x 256 tiles.
+// Pairs of GEMMs in one launch, 256 x 256 tiles.
 #include "caat_gemm_tiles.h"
 
 namespace caat {

@@ -1,4 +1,4 @@
-// Pairs of gradient GEMMs in one launch, 64 x 128 and 64 x 64 tiles.
+// Pairs of GEMMs in one launch, 64 x 128 and 64 x 64 tiles.
 #include "caat_gemm_tiles.h"
 
 namespace caat {

@@ -20,21 +20,36 @@ typedef TileCfg<64, 64, 2, 2, 4, false, false, 2> Cfg64x64k;
 template <class CFG>
 hipError_t launch_block_sized(const GemmParams& p, int layout, int epilogue, hipStream_t s);
 
-// data gradient (NN, `epilogue`) and weight gradient (TN) in one launch
+// two GEMMs in one launch: epilogue1 EPI_PLAIN, EPI_GELU_BWD or EPI_SWIGLU_BWD: p1 NN, p2 TN and plain; EPI_ROWPAR: both NT, p2
+// with EPI_PARTIAL or EPI_SHARED_BCAST
 template <class CFG>
-hipError_t launch_pair(const GemmParams& nn, int epilogue, const GemmParams& tn, const NormSums& sums, bool tn_first, bool one_each,
-                       hipStream_t s);
+hipError_t launch_pair(const GemmPair& pair, const GemmParams& p1, int epilogue1, const GemmParams& p2, int epilogue2,
+                       const NormSums& sums, hipStream_t s);
+
+template <class CFG>
+static hipError_t launch_pair_impl(const GemmPair& pair, const GemmParams& p1, int epilogue1, const GemmParams& p2, int epilogue2,
+                                   const NormSums& sums, hipStream_t s) {
+  typedef GemmKind<true, true, EPI_PLAIN> Wgrad;
+  typedef GemmKind<false, false, EPI_ROWPAR> Private;
+  if (epilogue1 == EPI_ROWPAR) {
+    if (epilogue2 == EPI_PARTIAL) return launch_pair_one<CFG, Private, GemmKind<false, false, EPI_PARTIAL>>(pair, p1, p2, sums, s);
+    if (epilogue2 == EPI_SHARED_BCAST) return launch_pair_one<CFG, Private, GemmKind<false, false, EPI_SHARED_BCAST>>(pair, p1, p2, sums, s);
+    return hipErrorInvalidValue;
+  }
+  if (epilogue2 != EPI_PLAIN) return hipErrorInvalidValue;
+  switch (epilogue1) {
+    case EPI_PLAIN: return launch_pair_one<CFG, GemmKind<false, true, EPI_PLAIN>, Wgrad>(pair, p1, p2, sums, s);
+    case EPI_GELU_BWD: return launch_pair_one<CFG, GemmKind<false, true, EPI_GELU_BWD>, Wgrad>(pair, p1, p2, sums, s);
+    case EPI_SWIGLU_BWD: return launch_pair_one<CFG, GemmKind<false, true, EPI_SWIGLU_BWD>, Wgrad>(pair, p1, p2, sums, s);
+    default: return hipErrorInvalidValue;
+  }
+}
 
 #define CAAT_INSTANTIATE_PAIR(CFG)                                                                                             \
   template <>                                                                                                                  \
-  hipError_t launch_pair<CFG>(const GemmParams& nn, int epilogue, const GemmParams& tn, const NormSums& sums, bool tn_first,   \
-                              bool one_each, hipStream_t s) {                                                                                 \
-    switch (epilogue) {                                                                                                        \
-      case EPI_PLAIN: return launch_pair_one<CFG, EPI_PLAIN>(nn, tn, sums, tn_first, one_each, s);                                       \
-      case EPI_GELU_BWD: return launch_pair_one<CFG, EPI_GELU_BWD>(nn, tn, sums, tn_first, one_each, s);                                 \
-      case EPI_SWIGLU_BWD: return launch_pair_one<CFG, EPI_SWIGLU_BWD>(nn, tn, sums, tn_first, one_each, s);                             \
-      default: return hipErrorInvalidValue;                                                                                    \
-    }                                                                                                                          \
+  hipError_t launch_pair<CFG>(const GemmPair& pair, const GemmParams& p1, int epilogue1, const GemmParams& p2, int epilogue2,  \
+                              const NormSums& sums, hipStream_t s) {                                                           \
+    return launch_pair_impl<CFG>(pair, p1, epilogue1, p2, epilogue2, sums, s);                                                 \
   }
 
 #define CAAT_INSTANTIATE_TILES(CFG)                                                                                            \

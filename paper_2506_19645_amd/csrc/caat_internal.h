@@ -254,14 +254,15 @@ hipError_t launch_norm_sums(const NormSums& f, hipStream_t s);
 
 // layout: 0 NT, 1 NN, 2 TN (see caat_gemm_layout).  Returns hipError_t of the launch.
 hipError_t launch_gemm(const GemmParams& p, int layout, int epilogue, hipStream_t s);
-// Data gradient nn (NN, epilogue EPI_PLAIN / EPI_GELU_BWD / EPI_SWIGLU_BWD), weight gradient tn (TN, plain) and, if there are
-// any, the sums of the norm's parameter gradients in one launch
+// Two GEMMs that do not depend on each other in one launch (gemm_pair_kernel)
 struct GemmPair {
-  int tile;          // shape 0, 1, 3, 4 or 5 of launch_gemm's; -1: one launch after the other is as fast
-  bool tn_first;     // the weight gradient's tiles take longer and go first
-  bool one_each;     // a workgroup of the second GEMM takes one tile
-  double us;         // modelled time
+  int tile;           // shape 0, 1, 3, 4 or 5 of launch_gemm's; -1: one launch after the other is as fast
+  bool second_first;  // the second one's tiles take longer and go first
+  bool one_each;      // a workgroup of the GEMM that goes last takes one tile
+  double us;          // modelled time
 };
+// Data gradient nn (NN, epilogue EPI_PLAIN / EPI_GELU_BWD / EPI_SWIGLU_BWD), weight gradient tn (TN, plain) and, if there are
+// any, the sums of the norm's parameter gradients
 GemmPair gemm_pair(const GemmParams& nn, const GemmParams& tn);
 hipError_t launch_gemm_pair(const GemmPair& p, const GemmParams& nn, int epilogue, const GemmParams& tn, const NormSums& sums,
                             hipStream_t s);
@@ -269,6 +270,10 @@ hipError_t launch_gemm_pair(const GemmPair& p, const GemmParams& nn, int epilogu
 // adds up.  scratch: gemm_shared_scratch_bytes() bytes; with less, or none, there are fewer groups
 size_t gemm_shared_scratch_bytes(int M, int N, int kcat);
 hipError_t launch_gemm_shared(const GemmParams& p, void* scratch, size_t scratch_bytes, hipStream_t s);
+// the same with the private columns (EPI_ROWPAR, NT) in one launch; *taken = false and nothing launched where that is not faster
+GemmPair gemm_shared_pair(const GemmParams& p, const GemmParams& priv, size_t scratch_bytes, int* groups);
+hipError_t launch_gemm_shared_private(const GemmParams& p, const GemmParams& priv, void* scratch, size_t scratch_bytes, bool* taken,
+                                      hipStream_t s);
 // the second kernel: for m in [0, bcast): out[m] = round_bf16(sum over groups of part) + resid[m]; part [groups][M][N] fp32
 hipError_t launch_shared_merge(const float* part, int groups, const bf16_t* resid, bf16_t* out, long long M, int N, long long ldr,
                                long long ldo, long long stride_r, long long stride_o, int bcast, hipStream_t s);

@@ -16,9 +16,9 @@ extern "C" {
  * caat_block_fwd / caat_block_bwd bracket every kernel they enqueue with a pair of HIP events on the caller's
  * stream.  caat_profile_get waits for record `index` (in launch order since the last reset) and returns a
  * static kernel-family name (host pointer to a NUL-terminated string) and the elapsed milliseconds.  Events
- * are created on first use and reused after a reset.  Not thread-safe; off by default.  While it is on, the backward's
- * GEMMs are enqueued one by one, also where they otherwise share a launch (caat_gemm_pair_route), so that each has a time of
- * its own.
+ * are created on first use and reused after a reset.  Not thread-safe; off by default.  While it is on, GEMMs are
+ * enqueued one by one, also where they otherwise share a launch (caat_gemm_pair_route, caat_gemm_shared_pair_route), so that
+ * each has a time of its own.
  */
 int caat_profile_enable(int on);
 int caat_profile_reset(void);
@@ -60,6 +60,13 @@ int caat_gemm_route(int layout, int epilogue, int G, long long M, long long N, l
  * them takes one tile and not a share of several.  -2 for arguments out of range.
  */
 int caat_gemm_pair_route(int G, long long M, long long N, long long K);
+
+/*
+ * The same for the row-parallel product of reduce_in_gemm, M tokens of contraction K per rank (host only): -1 the private and
+ * the shared columns one after the other, else caat_gemm_pair_route's numbers (the shared columns in place of the weight
+ * gradient) + 256 times the groups of ranks that the shared columns are summed in, with all the scratch that helps.
+ */
+int caat_gemm_shared_pair_route(int T, long long M, long long h, long long hs, long long K);
 
 #ifdef __cplusplus
 }

@@ -21,3 +21,15 @@ def test_training_steps_pair_their_gradient_gemms_unless_one_is_a_long_chain():
         assert B.gemm_pair_route(T, n, fr, h) >= 0
     assert B.gemm_pair_route(2, 7476, 512, 1024) == -1        # 8 x 512 columns from 7476 rows: tiles that share a contraction
     assert B.gemm_pair_route(0, 1, 8, 8) == B.gemm_pair_route(1, 1 << 31, 8, 8) == -2
+
+
+def test_gpu_tests_reach_every_pair_of_private_and_shared_columns():
+    """Every tile with the shared sums in groups and directly (1 group)."""
+    seen = set()
+    for T, n, h, fr, hs in pairs.SHARED:
+        r = B.gemm_shared_pair_route(T, n, h, hs, fr)
+        assert r >= 0
+        seen.add((r % 16, r // 256 > 1))
+    assert seen == {(tile, groups) for tile in (0, 1, 3, 4, 5) for groups in (False, True)}
+    assert B.gemm_shared_pair_route(8, 128, 1536, 768, 2048) == -1   # the private columns stream their weights
+    assert B.gemm_shared_pair_route(8, 96, 4096, 4096, 512) == -2

@@ -1,5 +1,6 @@
 """The backward's GEMMs two to a launch: every tile shape with every fused epilogue that a pair has, and the same launches one
 after the other, which the library takes while launches are timed."""
+import numpy as np
 import pytest
 
 from paper_2506_19645_amd import binding as B
@@ -20,6 +21,15 @@ PAIRS = [
     (False, 1, 1, 8, 8, 4), (True, 2, 65, 72, 136, 33), (False, 2, 100, 136, 200, 64), (True, 2, 33, 200, 72, 128),
     (False, 2, 256, 768, 1536, 384), (False, 2, 2048, 1032, 3080, 0), (True, 4, 1300, 264, 2056, 128),
     (False, 4, 1300, 264, 4104, 128), (True, 1, 65, 8, 72, 5), (True, 4, 100, 72, 1544, 32), (True, 8, 65, 72, 1032, 72), (True, 8, 100, 8, 2056, 8),
+]
+
+# (T, tokens, h, ffn / T, hs): private and shared columns of a product with the reduce inside in one launch, summed in groups of
+# ranks and directly
+SHARED = [
+    (8, 456, 3080, 72, 8), (8, 136, 4096, 264, 8), (2, 1300, 3080, 72, 8), (8, 200, 3080, 72, 8), (8, 777, 1032, 72, 8), (8, 65, 2056, 264, 8),
+    (4, 136, 72, 264, 32), (8, 2048, 4096, 72, 2048), (8, 1300, 3080, 72, 8), (4, 1300, 2056, 1032, 1024), (2, 456, 4096, 8, 8),
+    (2, 1000, 2056, 72, 1024), (8, 456, 2056, 264, 1024), (2, 200, 4096, 8, 8), (8, 65, 4096, 264, 4088), (2, 136, 72, 8, 32),
+    (8, 65, 2056, 264, 2048),
 ]
 
 
@@ -48,3 +58,14 @@ def test_mlp_block_with_every_gemm_a_launch_of_its_own(swi, T, n, h, fr, hs):
         B.profile_enable(False)
     assert sum(name.startswith("gemm") for name, _ in B.profile_records()) == 6
     B.profile_reset()
+
+
+@pytest.mark.parametrize("T,n,h,fr,hs", SHARED)
+def test_reduce_in_gemm_with_both_parts_in_one_launch(T, n, h, fr, hs):
+    cfg = block_config(False, T, n, h, fr, hs)
+    d = make_inputs(cfg, seed=37, weight_std=0.05)
+    got = run_mlp_block(cfg, d, reduce_in_gemm=True)
+    w, fwd, g = oracle_mlp_block(cfg, d)
+    check_mlp_block(cfg, d, got, w, fwd, g)
+    other = run_mlp_block(cfg, d, backward=False)
+    assert np.array_equal(got["Rp_bits"][:, :, hs:], other["Rp_bits"][:, :, hs:])   # private channels: the same bits
