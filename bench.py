@@ -326,7 +326,7 @@ def cpu_baseline_other_kinds(name, cfg, bwd):
 
 class AttnBench(MlpBench):
     """Attention sub-block (C4): forward = QKV GEMM, RoPE, causal attention, o_proj + partial sync, norm; backward =
-    norm backward, partial sync, o_proj gradients, attention-core gradient, inverse RoPE, QKV gradients."""
+    norm backward, partial sync, o_proj gradients, attention-core gradient (rotated back on its way out), QKV gradients."""
 
     def __init__(self, cfg, seed=0, backward=True):
         import torch
@@ -423,7 +423,7 @@ def bench_attention_kinds(args, cfg, base):
             # (o_proj: 2nh^2, qkv: 6nh^2) share a kernel family, so the per-launch figure is their mean
             fl.update({"flash_attn_bwd": 5.0 * cfg.batch * s * s * h, "gemm_nn_dgrad": 4.0 * n * h * h,
                        "gemm_tn_wgrad": 4.0 * n * h * h})
-            by.update({"rope_bwd": 2.0 * T * n * 2 * hd * 2, "partial_sync_bwd": 2.0 * T * n * hs_of(cfg) * 2,
+            by.update({"partial_sync_bwd": 2.0 * T * n * hs_of(cfg) * 2,
                        "norm_bwd_sync": 5.0 * T * n * h * 2,
                        "norm_bwd": 5.0 * T * n * h * 2 - (T * n * hs_of(cfg) * 2 if hs_of(cfg) % 8 == 0 else 0)})
             work += 5.0 * cfg.batch * s * s * h + 16.0 * n * h * h

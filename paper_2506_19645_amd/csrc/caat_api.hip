@@ -291,7 +291,7 @@ int attn_block_fwd(const caat_desc* d, const caat_ws_layout& L, const void* cons
   if (e != hipSuccess) return CAAT_EHIP;
   {
     ProfScope ps(s, "rope");
-    e = launch_rope(QKV, T * n, d->seq, (int)qw, hpr + kvpr, d->head_dim, d->rope_base, 0, false, s);
+    e = launch_rope(QKV, T * n, d->seq, (int)qw, hpr + kvpr, d->head_dim, d->rope_base, 0, s);
   }
   if (e != hipSuccess) return CAAT_EHIP;
   {
@@ -339,7 +339,7 @@ hipError_t grad_gemms(const GemmPair& p, const GemmParams& nn, int epilogue, con
 
 // Attention sub-block backward (Fig. 2b applied to Eq. A5): norm backward per rank first, dr_m = g_m un-reduced, the
 // partial channel-reduce on g, then per rank dH = dZt Wo, dWo = dZt^T H, the attention-core gradient w.r.t. the rotated
-// q, k and v, the inverse rotation of dq and dk, dX = dqkv Wqkv (never reduced over ranks) and dWqkv = dqkv^T X.
+// q, k and v with dq and dk rotated back on their way out, dX = dqkv Wqkv (never reduced over ranks) and dWqkv = dqkv^T X.
 int attn_block_bwd(const caat_desc* d, const caat_ws_layout& L, const void* const* weights, const void* x, const void* r_out,
                    void* workspace, size_t ws_bytes, const void* dx_out, const void* dr_out, void* dx, void* dr,
                    void* const* dweights, float* dgamma, float* dbeta, void* hip_stream) {
@@ -409,8 +409,8 @@ int attn_block_bwd(const caat_desc* d, const caat_ws_layout& L, const void* cons
   }
   e = grad_gemms(first, H1, EPI_PLAIN, "gemm_nn_dgrad", O, sums, s);
   if (e != hipSuccess) return CAAT_EHIP;
-  CAAT_STEP("flash_attn_bwd", launch_flash_bwd(QKV, H, dH, stats, dQKV, T * d->batch, d->seq, hpr, kvpr, d->head_dim, s))
-  CAAT_STEP("rope_bwd", launch_rope(dQKV, T * n, d->seq, (int)qw, hpr + kvpr, d->head_dim, d->rope_base, 0, true, s))
+  CAAT_STEP("flash_attn_bwd", launch_flash_bwd(QKV, H, dH, stats, dQKV, T * d->batch, d->seq, hpr, kvpr, d->head_dim,
+                                               d->rope_base, s))
   e = grad_gemms(grad_pair(X, W), X, EPI_PLAIN, "gemm_nn_dgrad", W, NormSums{}, s);
 #undef CAAT_STEP
   return hip_status(e);

@@ -333,14 +333,15 @@ hipError_t launch_hbm_probe(const void* src, void* dst, size_t bytes, int mode, 
 // Projections of one rank-row: [heads*128 q | kv_heads*128 k | kv_heads*128 v] (grouped-query attention when
 // kv_heads < heads; heads, kv_heads are per rank); ld = (heads + 2*kv_heads)*128.
 hipError_t launch_rope(bf16_t* qkv, long long rows, int seq, int ld, int n_rot, int d, float base, long long pos0,
-                       bool inverse, hipStream_t s);
+                       hipStream_t s);
 hipError_t launch_rope_append(bf16_t* qkv, bf16_t* kc, bf16_t* vc, long long n_seq, int seq, int hpr, int kvpr, int d,
                               float base, long long cap, long long pos0, hipStream_t s);   // RoPE + KV cache store in one pass
 size_t attn_stats_bytes(long long n_seq, int heads, int seq);   // fp32 [n_seq*heads][2][seq rounded up to 64]: lse, D
 hipError_t launch_flash_fwd(const bf16_t* qkv, bf16_t* out, float* stats, long long n_seq, int seq, int heads, int kv_heads,
                             int d, hipStream_t s);
+// dqkv: gradients of the un-rotated projections
 hipError_t launch_flash_bwd(const bf16_t* qkv, const bf16_t* out, const bf16_t* dout, float* stats, bf16_t* dqkv,
-                            long long n_seq, int seq, int heads, int kv_heads, int d, hipStream_t s);
+                            long long n_seq, int seq, int heads, int kv_heads, int d, float rope_base, hipStream_t s);
 // scratch: decode_attn_scratch_bytes() bytes; with less, or none, the keys are taken in fewer ranges
 size_t decode_attn_scratch_bytes(long long n_seq, int hpr, int kvpr);
 hipError_t launch_decode_attn(const bf16_t* qkv, bf16_t* kc, bf16_t* vc, bf16_t* out, long long n_seq, int hpr, int kvpr,
