@@ -641,7 +641,7 @@ int caat_partial_sync_norm_fwd(void* io, const void* resid, const void* gamma, c
   if (misaligned(io) || misaligned(resid) || misaligned(gamma) || misaligned(x_out) || (beta && misaligned(beta)))
     return CAAT_EALIGN;
   if (tokens == 0) return CAAT_OK;
-  if (!sync_norm_takes(T, tokens, h, hs)) return CAAT_EUNSUPPORTED;
+  if (hs % 8 != 0 || !sync_norm_takes(T, tokens, h, hs)) return CAAT_EUNSUPPORTED;
   return hip_status(launch_sync_norm((bf16_t*)io, (const bf16_t*)resid, (const bf16_t*)gamma, (const bf16_t*)beta, (bf16_t*)x_out,
                                      mean, rstd, norm, T, tokens, h, hs, eps, (hipStream_t)hip_stream));
 }

@@ -299,7 +299,7 @@ hipError_t launch_partial_sync_shared(bf16_t* io, const bf16_t* resid, int T, lo
 hipError_t launch_norm_fwd(const bf16_t* x, const bf16_t* gamma, const bf16_t* beta, bf16_t* y, float* mean,
                            float* rstd, int norm, int T, long long tokens, int h, float eps, hipStream_t s,
                            int dedup_hs = 0);
-// reduce on the shared channels + residual + norm in one launch (hs % 8 == 0; T in {2,4,8} with h <= 8192, T = 16 with
+// reduce on the shared channels + residual + norm in one launch (T in {2,4,8} with h <= 8192, T = 16 with
 // h <= 4096: sync_norm_takes); hipErrorInvalidValue if the shape is not taken
 bool sync_norm_takes(int T, long long tokens, int h, int hs);
 hipError_t launch_sync_norm(bf16_t* io, const bf16_t* resid, const bf16_t* gamma, const bf16_t* beta, bf16_t* xout,
@@ -316,7 +316,7 @@ hipError_t launch_norm_bwd(const bf16_t* dy, const bf16_t* dres, const bf16_t* x
                            const float* mean, const float* rstd, bf16_t* g_out, bf16_t* g_scaled, float* dgamma,
                            float* dbeta, int norm, int T, long long tokens, int h, int hs, float private_scale,
                            void* workspace, hipStream_t s, bool skip_shared_scaled = false, NormSums* later = nullptr);
-// norm backward + the backward partial channel-reduce in one launch (hs % 8 == 0; T = 4 up to h = 2048, T = 2 up to
+// norm backward + the backward partial channel-reduce in one launch (T = 4 up to h = 2048, T = 2 up to
 // h = 4096: norm_bwd_sync_takes); hipErrorInvalidValue if the shape is not taken.  Same workspace as launch_norm_bwd.
 bool norm_bwd_sync_takes(int T, long long tokens, int h, int hs);
 hipError_t launch_norm_bwd_sync(const bf16_t* dy, const bf16_t* dres, const bf16_t* x, const bf16_t* gamma,

@@ -455,7 +455,7 @@ hipError_t launch_norm_fwd(const bf16_t* x, const bf16_t* gamma, const bf16_t* b
 // ALL ranks: it sums the T partial vectors of the shared channels in ascending rank order, adds each rank's residual,
 // rounds once and stores R' (exactly what partial_sync_kernel does), keeps every rank's row (rounded values, packed)
 // in registers, and then normalises each rank's row with its own statistics (what norm_fwd_kernel does on R':
-// RMSNorm, or LayerNorm with the two-pass variance).  hs % 8 == 0; a thread holds NG 16-byte column groups of every
+// RMSNorm, or LayerNorm with the two-pass variance).  A thread holds NG 16-byte column groups of every
 // rank's row (h <= 8 NT NG), so the register budget is NG*TT*4: T = 16 is taken up to h = 4096.  NT threads: 256, or for a
 // few tokens as many as there are column groups (NG = 1), so that a token is one trip to memory and not one per group
 // (a group's stores may alias the next one's loads, so the compiler keeps them apart): T = 8, 16 tokens of 8192 12.8 ->
@@ -487,10 +487,10 @@ __global__ __launch_bounds__(NT) void sync_norm_kernel(bf16_t* io, const bf16_t*
     if (vi < nvec) {
       const int col = vi * 8;
       const long long off = i * h + col;
-      if (col < hs) {                                     // shared channels (hs is a multiple of 8)
+      if (col < hs) {                                     // shared channels
         float sum[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        uint4 pv[TT];     // the T partials and the T residual vectors are requested together
         {
-          uint4 pv[TT];   // the T partials and the T residual vectors are requested together
 #pragma unroll
           for (int m = 0; m < TT; ++m) {
             pv[m] = big ? ld_stream(io + m * plane + off) : *reinterpret_cast<const uint4*>(io + m * plane + off);
@@ -510,6 +510,12 @@ __global__ __launch_bounds__(NT) void sync_norm_kernel(bf16_t* io, const bf16_t*
           unpack8(val[g][m], r);
 #pragma unroll
           for (int e = 0; e < 8; ++e) o[e] = sum[e] + r[e];
+          if (col + 8 > hs) {                             // the vector that hs ends in: its private channels are final
+            float f[8];
+            unpack8(pv[m], f);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[e] = col + e < hs ? o[e] : f[e];
+          }
           val[g][m] = pack8(o);
           if (big) st_stream(io + m * plane + off, val[g][m]);
           else *reinterpret_cast<uint4*>(io + m * plane + off) = val[g][m];
@@ -639,10 +645,11 @@ static hipError_t sync_norm_dispatch(bf16_t* io, const bf16_t* resid, const bf16
   return hipGetLastError();
 }
 
-// shapes the fused reduce + norm kernel takes: whole 16-byte groups of shared channels, T in {2, 4, 8} up to h = 8192 and
-// T = 16 up to h = 4096 (a thread keeps its columns of all T rows in registers)
+// shapes the fused reduce + norm kernel takes: T in {2, 4, 8} up to h = 8192 and T = 16 up to h = 4096 (a thread keeps its
+// columns of all T rows in registers).  hs may end inside a vector: with the four kernels that ran for such an hs before
+// (reduce, norm; norm backward, reduce) a SwiGLU step of T = 4, 1111 tokens, h = 2048, hs = 1433 took 307 us, with these two 294
 bool sync_norm_takes(int T, long long tokens, int h, int hs) {
-  if (hs <= 0 || hs % 8 != 0 || hs > h || h % 8 != 0 || h > 8192 || tokens <= 0 || tokens > 0x7FFFFFFFLL) return false;
+  if (hs <= 0 || hs > h || h % 8 != 0 || h > 8192 || tokens <= 0 || tokens > 0x7FFFFFFFLL) return false;
   if (T == 2 || T == 4 || T == 8) return true;
   return T == 16 && h <= 4096;
 }
@@ -696,6 +703,7 @@ __global__ __launch_bounds__(256) void sync_norm_rank_kernel(const bf16_t* __res
   const long long plane = n * (long long)h;
   const int nvec = h >> 3;
   uint4 pv[NG][TT], rv[NG], gw[NG];
+  uint4 own = make_uint4(0u, 0u, 0u, 0u);                // the vector that hs ends in: its private channels are final
 #pragma unroll
   for (int g = 0; g < NG; ++g) {
     const int vi = g * 256 + tid;
@@ -709,6 +717,7 @@ __global__ __launch_bounds__(256) void sync_norm_rank_kernel(const bf16_t* __res
 #pragma unroll
         for (int k = 0; k < TT; ++k) pv[g][k] = *reinterpret_cast<const uint4*>(part + k * plane + off);
         rv[g] = *reinterpret_cast<const uint4*>(resid + m * plane + off);
+        if (vi * 8 + 8 > hs) own = *reinterpret_cast<const uint4*>(part + m * plane + off);
       } else {
         rv[g] = *reinterpret_cast<const uint4*>(part + m * plane + off);   // private: final since the GEMM epilogue
       }
@@ -718,7 +727,7 @@ __global__ __launch_bounds__(256) void sync_norm_rank_kernel(const bf16_t* __res
 #pragma unroll
   for (int g = 0; g < NG; ++g) {
     const int vi = g * 256 + tid;
-    if (vi * 8 < hs) {                                   // hs is a multiple of 8 and at most h
+    if (vi * 8 < hs) {                                   // hs is at most h
       float sum[8] = {0, 0, 0, 0, 0, 0, 0, 0}, r[8];
 #pragma unroll
       for (int k = 0; k < TT; ++k) {
@@ -730,6 +739,11 @@ __global__ __launch_bounds__(256) void sync_norm_rank_kernel(const bf16_t* __res
       unpack8(rv[g], r);
 #pragma unroll
       for (int e = 0; e < 8; ++e) sum[e] += r[e];
+      if (vi * 8 + 8 > hs) {
+        unpack8(own, r);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) sum[e] = vi * 8 + e < hs ? sum[e] : r[e];
+      }
       rv[g] = pack8(sum);
     }
     float f[8];
@@ -1053,7 +1067,7 @@ __global__ __launch_bounds__(256) void norm_bwd_wide_kernel(const bf16_t* __rest
 // g_out -- rounds once and stores the result to every rank's row of g_red; private channels of g_red get scale * g_m.
 // A workgroup walks a contiguous range of tokens and keeps its threads' columns of dgamma / dbeta in registers over
 // all of them (summed over tokens AND ranks), one partial row per workgroup; norm_bwd_finalize_kernel adds them up.
-// hs % 8 == 0.  Saves, against the two kernels, the read-back of the shared channels and one launch.
+// Saves, against the two kernels, the read-back of the shared channels and one launch.
 template <int TT, int NG, bool LN, int NT>
 __global__ __launch_bounds__(NT) void norm_bwd_sync_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ dres,
                                                             const bf16_t* __restrict__ x, const bf16_t* __restrict__ gamma,
@@ -1160,9 +1174,8 @@ __global__ __launch_bounds__(NT) void norm_bwd_sync_kernel(const bf16_t* __restr
         float gm[8];
         unpack8(gam[g], gm);
         float sum[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-        for (int m = 0; m < TT; ++m) {
-          float fx[8], fd[8], r[8], o[8];
+        auto grad = [&](int m, float* o) {   // rank m's residual gradient
+          float fx[8], fd[8], r[8];
           unpack8(wx[g][m], fx);
           unpack8(wd[g][m], fd);
           unpack8(wr[g][m], r);
@@ -1172,6 +1185,11 @@ __global__ __launch_bounds__(NT) void norm_bwd_sync_kernel(const bf16_t* __restr
             const float dxh = fd[e] * gm[e];
             o[e] = r[e] + rs[m] * (LN ? (dxh - c1[m] - xh * c2[m]) : (dxh - xh * c2[m]));
           }
+        };
+#pragma unroll
+        for (int m = 0; m < TT; ++m) {
+          float o[8];
+          grad(m, o);
           const long long off = m * plane + i * h + col;
           const uint4 gb = pack8(o);
           if (col < hs) {                 // shared channels: the reduce runs on the ROUNDED residual gradient
@@ -1187,10 +1205,19 @@ __global__ __launch_bounds__(NT) void norm_bwd_sync_kernel(const bf16_t* __restr
             *reinterpret_cast<uint4*>(g_red + off) = pack8(o);
           }
         }
-        if (col < hs) {
+        if (col + 8 <= hs) {
           const uint4 sb = pack8(sum);    // one rounding, the same bits on every rank
 #pragma unroll
           for (int m = 0; m < TT; ++m) *reinterpret_cast<uint4*>(g_red + m * plane + i * h + col) = sb;
+        } else if (col < hs) {            // the vector that hs ends in: its private channels scaled
+#pragma unroll
+          for (int m = 0; m < TT; ++m) {
+            float o[8];
+            grad(m, o);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[e] = col + e < hs ? sum[e] : o[e] * scale;
+            *reinterpret_cast<uint4*>(g_red + m * plane + i * h + col) = pack8(o);
+          }
         }
       }
     }
@@ -1308,7 +1335,7 @@ static int norm_bwd_sync_groups(int T, int h) {
   return ((T == 2 || T == 4) && T * ng <= 4) ? ng : 0;
 }
 bool norm_bwd_sync_takes(int T, long long tokens, int h, int hs) {
-  if (hs <= 0 || hs % 8 != 0 || hs > h || h % 8 != 0 || h > 8192 || tokens <= 0) return false;
+  if (hs <= 0 || hs > h || h % 8 != 0 || h > 8192 || tokens <= 0) return false;
   return norm_bwd_sync_groups(T, h) != 0;
 }
 
