@@ -255,6 +255,10 @@ int rowpar_pcr(const caat_desc* d, const bf16_t* a, long long kdim, const bf16_t
   return CAAT_OK;
 }
 
+// q and k are rotated (and k and v go to the caches) in the epilogue of the product that makes them.  Where its tile cannot,
+// that is a pass of its own, and so it is while launches are timed.
+bool rope_in_gemm(const GemmParams& p) { return !g_prof_on && gemm_takes_rope(p); }
+
 // Attention sub-block forward (Eq. A5 + Sec. 4): per rank q,k,v = X_m Wqkv_m^T; RoPE(q,k); causal attention per head;
 // Zt_m = H_m Wo_m^T with the private half of the partial channel-reduce in the epilogue; shared half; norm.
 int attn_block_fwd(const caat_desc* d, const caat_ws_layout& L, const void* const* weights, const void* x, const void* r,
@@ -284,12 +288,14 @@ int attn_block_fwd(const caat_desc* d, const caat_ws_layout& L, const void* cons
   g1.b = (const bf16_t*)wqkv; g1.ldb = h; g1.stride_b = qw * h;
   g1.c = QKV; g1.ldc = qw; g1.stride_c = n * qw;
   g1.G = (int)T; g1.M = (int)n; g1.N = (int)qw; g1.K = (int)h;
+  g1.rope = {(int)d->seq, hpr * 128, kvpr * 128, (int)d->batch, log2f(d->rope_base), nullptr, nullptr, 0};
+  const bool rotate = rope_in_gemm(g1);
   {
     ProfScope ps(s, "gemm_nt_qkv");
-    e = launch_gemm(g1, 0, EPI_PLAIN, s);
+    e = launch_gemm(g1, 0, rotate ? EPI_ROPE : EPI_PLAIN, s);
   }
   if (e != hipSuccess) return CAAT_EHIP;
-  {
+  if (!rotate) {
     ProfScope ps(s, "rope");
     e = launch_rope(QKV, T * n, d->seq, (int)qw, hpr + kvpr, d->head_dim, d->rope_base, 0, s);
   }
@@ -465,10 +471,14 @@ int layer_fwd(const caat_desc* d, const caat_ws_layout& L, const void* const* we
   q.b = (const bf16_t*)wqkv; q.ldb = h; q.stride_b = qw * h;
   q.c = QKV; q.ldc = qw; q.stride_c = n * qw;
   q.G = (int)T; q.M = (int)n; q.N = (int)qw; q.K = (int)h;
-  CAAT_STEP("gemm_nt_qkv", launch_gemm(q, 0, EPI_PLAIN, s))
+  q.rope = {(int)d->seq, (int)hpr * 128, (int)kvpr * 128, (int)d->batch, log2f(d->rope_base), (bf16_t*)kv_k, (bf16_t*)kv_v, d->kv_cap};
+  const bool rotate = prefill && rope_in_gemm(q);
+  CAAT_STEP("gemm_nt_qkv", launch_gemm(q, 0, rotate ? EPI_ROPE : EPI_PLAIN, s))
   if (prefill) {
-    CAAT_STEP("rope_kv_append", launch_rope_append(QKV, (bf16_t*)kv_k, (bf16_t*)kv_v, T * d->batch, d->seq, (int)hpr, (int)kvpr,
-                                                   d->head_dim, d->rope_base, d->kv_cap, d->kv_len, s))
+    if (!rotate) {
+      CAAT_STEP("rope_kv_append", launch_rope_append(QKV, (bf16_t*)kv_k, (bf16_t*)kv_v, T * d->batch, d->seq, (int)hpr, (int)kvpr,
+                                                     d->head_dim, d->rope_base, d->kv_cap, d->kv_len, s))
+    }
     CAAT_STEP("flash_attn_fwd", launch_flash_fwd(QKV, H, nullptr, T * d->batch, d->seq, (int)hpr, (int)kvpr, d->head_dim, s))
   } else {
     // decode: the attention kernel rotates q and the new k itself, appends k, v to the caches and attends to

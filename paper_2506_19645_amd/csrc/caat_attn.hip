@@ -31,22 +31,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t attn_rsrc(const void* p) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)0x80000000, 0x00020000);
 }
 
-// Rotary frequency j < d/2, base^(-2j/d) as an fp32 number, over 2 pi: revolutions per position, in two floats.
-__device__ __forceinline__ float2 rope_freq(int j, int d, float log2_base) {
-  constexpr float REV = 0.159154937f, REV_LO = 6.42063833e-9f;   // 1/(2 pi) = REV + REV_LO
-  const float inv = exp2f(-2.0f * (float)j / (float)d * log2_base), hi = inv * REV;
-  return make_float2(hi, __builtin_fmaf(inv, REV_LO, __builtin_fmaf(inv, REV, -hi)));
-}
-// Sine and cosine at position pos.  The hardware's take revolutions; the product is carried in two floats, so that what is left
-// of it behind the point is good to 1e-7 at any position, where pos times the frequency rounded to fp32 is off by 2e-4 rad at
-// 4000: largest error of 4096 positions, base 10000, against 64 bits 1.2e-4 (that of the fp32 frequency), 2.4e-4 that way.
-__device__ __forceinline__ void rope_sincos(float pos, float2 freq, float& sn, float& cs) {
-  const float r = pos * freq.x;
-  const float f = __builtin_amdgcn_fractf(r) + __builtin_fmaf(pos, freq.y, __builtin_fmaf(pos, freq.x, -r));
-  sn = __builtin_amdgcn_sinf(f);
-  cs = __builtin_amdgcn_cosf(f);
-}
-
 // ---------------------------------------------------------------------------------------------------------
 // RoPE in place on the q and k column blocks of qkv [rows, ld] (row = rank*tokens + batch*seq + pos; the first
 // n_rot heads of a row, i.e. the q heads then the k heads, are rotated, the v heads after them are not):

@@ -163,12 +163,23 @@ static bool in_range(const GemmParams& p, int epilogue) {
   return (256 * ldmax + 2 * (long long)p.half + (long long)p.N) * elem < 0x7FFFFFFFLL;
 }
 
+// Only where the plain product's own tile has waves of 64 columns, 32 channels of a head and the 32 that they are rotated with
+// (256 x 256, 192 x 256, 128 x 128, 64 x 128); 256 x 192 and 64 x 64 tiles and the kernels for few rows leave the rotation to a
+// pass of its own, whose time the choice of another tile would cost.  With the pass / in the epilogue, forward and backward of an
+// attention block of h = 4096, T = 8, 4096 tokens 2455 / 2418 us, 3 x 1003 tokens of 2048, T = 4, 8 key heads 454 / 446; a
+// prefill layer of 16 x 2048 tokens of 4096 15.37 / 15.21 ms, of 777 464.7 / 460.8 us.
+bool gemm_takes_rope(const GemmParams& p) {
+  const int r = choose_route(p, 0, EPI_PLAIN, compute_units());
+  return (r == 0 || r == 1 || r == 3 || r == 4) && in_range(p, EPI_PLAIN);
+}
+
 hipError_t launch_gemm(const GemmParams& p, int layout, int epilogue, hipStream_t s) {
   if (!in_range(p, epilogue)) return hipErrorInvalidValue;
+  if (epilogue == EPI_ROPE && (layout != 0 || !gemm_takes_rope(p))) return hipErrorInvalidValue;
   const int n_cu = compute_units();
   GemmParams q = p;
   q.bn_out = 0;  // block-sized tiles always cover their full width
-  switch (choose_route(p, layout, epilogue, n_cu)) {
+  switch (choose_route(p, layout, epilogue == EPI_ROPE ? (int)EPI_PLAIN : epilogue, n_cu)) {
     case 0: return launch_block_sized<Cfg256x256>(q, layout, epilogue, s);
     case 1: return launch_block_sized<Cfg192x256>(q, layout, epilogue, s);
     case 2: return launch_block_sized<Cfg256x192>(q, layout, epilogue, s);

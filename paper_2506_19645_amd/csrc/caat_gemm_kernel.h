@@ -262,8 +262,9 @@ struct OperandSel<true, ROWS, NWAVES, BKS_, GROUPED> { typedef RowContigOperand<
 // Which weight row (relative to the tile's first row n0) lies in row rr of the B tile in LDS, or -1 for none.  Plain
 // epilogues: rows in order, as many as the tile covers (bn_out) and the matrix has.  SwiGLU: each wave's WTN tile rows
 // are 32 gate rows, then the 32 up rows of the same output columns (`half` rows further down), and so on, so that an
-// accumulator pair of a wave holds gate and up of the same 32 outputs.
-template <class CFG, bool SWI>
+// accumulator pair of a wave holds gate and up of the same 32 outputs.  RoPE: a wave's 64 tile rows are channels j .. j + 31 of a
+// head of 128 and the 32 that they are rotated with, 64 further on.
+template <class CFG, bool SWI, bool ROPE>
 __device__ __forceinline__ long long b_tile_row(int rr, int n0, int bn_out, int N, int half) {
   if constexpr (SWI) {
     const int w = rr / CFG::WTN, rw = rr - w * CFG::WTN;
@@ -271,6 +272,9 @@ __device__ __forceinline__ long long b_tile_row(int rr, int n0, int bn_out, int 
     const int col = (w * (CFG::WTN / 64) + (j >> 1)) * 32 + c;  // output column relative to n0
     if (col >= bn_out || n0 + col >= half) return -1;
     return (long long)col + ((j & 1) ? half : 0);
+  } else if constexpr (ROPE) {
+    const int w = rr >> 6, col = (w >> 1) * 128 + (w & 1) * 32 + (rr & 32) * 2 + (rr & 31);
+    return n0 + col < N ? (long long)col : -1;
   } else {
     const int nrem = (N - n0) < bn_out ? (N - n0) : bn_out;
     return rr < nrem ? (long long)rr : -1;
@@ -285,6 +289,8 @@ __device__ __forceinline__ void gemm_tiles(const GemmParams& p, uint4* smem, int
   constexpr bool SWI = (EPI == EPI_SWIGLU_FWD);
   constexpr int BN_OUT = SWI ? BN / 2 : BN;  // output columns covered by one tile
   static_assert(!SWI || WTN % 64 == 0, "SwiGLU pairing needs 32 gate and 32 up columns per wave");
+  constexpr bool ROPE = (EPI == EPI_ROPE);
+  static_assert(!ROPE || (WTN == 64 && BN % 128 == 0), "a wave rotates 32 channels of a head with the 32 that lie 64 further on");
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -353,7 +359,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmParams& p, uint4* smem, int
             [=](int rr) -> long long { return (rr < mrem) ? (long long)rr : -1; });
     if constexpr (!BT) {
       const int n0c = n0, bnc = bn_out, Nc = p.N, halfc = p.half;
-      auto rowmap = [=](int rr) -> long long { return b_tile_row<CFG, SWI>(rr, n0c, bnc, Nc, halfc); };
+      auto rowmap = [=](int rr) -> long long { return b_tile_row<CFG, SWI, ROPE>(rr, n0c, bnc, Nc, halfc); };
       lb.init(bg + (long long)n0 * p.ldb, p.ldb, rowmap);
     } else {
       const int nrem = p.N - n0 < BN ? p.N - n0 : BN;
@@ -415,7 +421,8 @@ __device__ __forceinline__ void gemm_tiles(const GemmParams& p, uint4* smem, int
   rb.init(smem + A_CHUNKS, wn * WTN, kw * NSUB, lane);
 
   constexpr int NS = WTN / 32;                   // 32-column groups of a wave's sub-tile
-  // epilogue stores per wave and tile (known at compile time except for the broadcast epilogue's loop over ranks)
+  // epilogue stores per wave and tile (known at compile time except for the broadcast epilogue's loop over ranks; RoPE's
+  // stores to the caches are not counted: the wait that counts on this number waits for some of them too)
   constexpr int EPI_STORES =
       (EPI == EPI_SHARED_BCAST)
           ? 1000
@@ -755,6 +762,65 @@ __device__ __forceinline__ void gemm_tiles(const GemmParams& p, uint4* smem, int
           const bool ok = row < p.M - wrow0 && col < ncols && col - en0 < bn_out;
           const uint4 w = __builtin_bit_cast(uint4, acc[i][j]);
           put(rf, w, ok, (unsigned)((row * p.ldc + col) * 4), 0);
+        }
+      }
+    } else if constexpr (ROPE) {
+      // q and k are rotated as they were rounded, 8 pairs (j, j + 64) of a row per lane.  A sine and a cosine for each pair and
+      // row would cost more than the pass over q and k that this saves: 16 rows on the angle has grown by the same amount for
+      // every lane, so the pair is turned by that (fp32; 8 steps at most, 1e-6 against the 1e-4 of an fp32 frequency), and it
+      // is only taken anew where the sequence ended in between.
+      const int head = en0 + (wn >> 1) * 128;          // first column of the wave's head
+      const int j0 = (wn & 1) * 32 + ecol0;            // the lane's first pair
+      const bool rot = head < p.rope.q + p.rope.k;
+      const unsigned seq = (unsigned)p.rope.seq;
+      const unsigned vo = head < p.N ? (unsigned)(((elane & 15) * p.ldc + head + j0) * 2) : OOB;
+      bf16_t* cache = nullptr;
+      if (p.rope.kc && head >= p.rope.q && head < p.N) cache = rot ? p.rope.kc : p.rope.vc;
+      const int kv = (head - p.rope.q) / 128 - (rot ? 0 : p.rope.k / 128);
+      float sn[8] = {}, cs[8] = {}, sn16[8] = {}, cs16[8] = {};
+      int until = 0;                                   // rows from wrow0 on that lie in the sequence of the row before
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        const int row = i * 16 + (elane & 15);
+        const bool rowok = row < p.M - wrow0;
+        uint4 lo = rounded(i, 0), hi = rounded(i, 1);
+        if (rot) {
+          if (16 * i + 15 < until) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              const float c = cs[e] * cs16[e] - sn[e] * sn16[e];
+              sn[e] = sn[e] * cs16[e] + cs[e] * sn16[e];
+              cs[e] = c;
+            }
+          } else {
+            until = 16 * i + (int)(seq - (unsigned)(wrow0 + 16 * i) % seq);
+            const float pos = (float)((unsigned)(wrow0 + row) % seq);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              const float2 f = rope_freq(j0 + e, 128, p.rope.log2_base);
+              rope_sincos(pos, f, sn[e], cs[e]);
+              rope_sincos(16.0f, f, sn16[e], cs16[e]);
+            }
+          }
+          auto turn = [&](unsigned& a, unsigned& b, int e) {
+            const float x0 = lo_bf(a), x1 = hi_bf(a), y0 = lo_bf(b), y1 = hi_bf(b);
+            a = pack2bf(x0 * cs[e] - y0 * sn[e], x1 * cs[e + 1] - y1 * sn[e + 1]);
+            b = pack2bf(y0 * cs[e] + x0 * sn[e], y1 * cs[e + 1] + x1 * sn[e + 1]);
+          };
+          turn(lo.x, hi.x, 0);
+          turn(lo.y, hi.y, 2);
+          turn(lo.z, hi.z, 4);
+          turn(lo.w, hi.w, 6);
+        }
+        const int so = i * 16 * (int)p.ldc * 2;
+        put(rc, lo, rowok, vo, so);
+        put(rc, hi, rowok && vo != OOB, vo + 128, so);
+        if (cache && rowok) {
+          // the caches are read by later decode steps, not by this layer's attention: non-temporal stores
+          const unsigned r = (unsigned)(wrow0 + row), sq = r / seq;
+          bf16_t* dst = cache + ((((long long)eg * p.rope.batch + sq) * (p.rope.k / 128) + kv) * p.rope.cap + (r - sq * seq)) * 128 + j0;
+          st_stream(dst, lo);
+          st_stream(dst + 64, hi);
         }
       }
     } else if constexpr (EPI == EPI_ROWPAR) {

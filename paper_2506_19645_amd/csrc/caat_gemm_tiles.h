@@ -72,6 +72,9 @@ static hipError_t launch_block_sized_impl(const GemmParams& p, int layout, int e
         case EPI_ROWPAR: return launch_one<CFG, false, false, EPI_ROWPAR>(p, s);
         case EPI_SHARED_BCAST: return launch_one<CFG, false, false, EPI_SHARED_BCAST>(p, s);
         case EPI_PARTIAL: return launch_one<CFG, false, false, EPI_PARTIAL>(p, s);
+        case EPI_ROPE:         // see gemm_takes_rope
+          if constexpr (CFG::WTN == 64) return launch_one<CFG, false, false, EPI_ROPE>(p, s);
+          else return hipErrorInvalidValue;
         default: return hipErrorInvalidValue;
       }
     case 1:  // NN

@@ -167,6 +167,22 @@ __device__ __forceinline__ void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
+// Rotary frequency j < d/2, base^(-2j/d) as an fp32 number, over 2 pi: revolutions per position, in two floats.
+__device__ __forceinline__ float2 rope_freq(int j, int d, float log2_base) {
+  constexpr float REV = 0.159154937f, REV_LO = 6.42063833e-9f;   // 1/(2 pi) = REV + REV_LO
+  const float inv = exp2f(-2.0f * (float)j / (float)d * log2_base), hi = inv * REV;
+  return make_float2(hi, __builtin_fmaf(inv, REV_LO, __builtin_fmaf(inv, REV, -hi)));
+}
+// Sine and cosine at position pos.  The hardware's take revolutions; the product is carried in two floats, so that what is left
+// of it behind the point is good to 1e-7 at any position, where pos times the frequency rounded to fp32 is off by 2e-4 rad at
+// 4000: largest error of 4096 positions, base 10000, against 64 bits 1.2e-4 (that of the fp32 frequency), 2.4e-4 that way.
+__device__ __forceinline__ void rope_sincos(float pos, float2 freq, float& sn, float& cs) {
+  const float r = pos * freq.x;
+  const float f = __builtin_amdgcn_fractf(r) + __builtin_fmaf(pos, freq.y, __builtin_fmaf(pos, freq.x, -r));
+  sn = __builtin_amdgcn_sinf(f);
+  cs = __builtin_amdgcn_cosf(f);
+}
+
 // ---------------------------------------------------------------- GEMM
 enum GemmEpilogue {
   EPI_PLAIN = 0,       // c = acc
@@ -176,7 +192,8 @@ enum GemmEpilogue {
   EPI_GELU_BWD = 4,    // c = acc * gelu'(aux)
   EPI_SWIGLU_BWD = 5,  // c[:, col] = acc*up*silu'(gate), c[:, half+col] = acc*silu(gate); aux = [gate|up]
   EPI_SHARED_BCAST = 6, // for m in [0, bcast): c[m] = round_bf16(acc) + aux[m]   (c, aux advance by stride_c / stride_aux)
-  EPI_PARTIAL = 7      // c as fp32 = acc: partial sums over a part of the contraction (launch_gemm_shared)
+  EPI_PARTIAL = 7,     // c as fp32 = acc: partial sums over a part of the contraction (launch_gemm_shared)
+  EPI_ROPE = 8         // c = [q | k | v] heads of 128, q and k rotated; with caches, k and v stored there as well
 };
 
 struct GemmParams {
@@ -198,6 +215,14 @@ struct GemmParams {
   int late_c;          // EPI_PLAIN: c is not read again soon (weight / input gradients): store it with the non-temporal hint
   int bn_out;          // decode-sized tiles: output columns one tile covers (0 = the tile's full width); set by launch_gemm
   int n_route;         // EPI_ROWPAR on a part of a shard's columns: the columns of the whole shard (0 = N); see gemm_route
+  struct Rope {        // EPI_ROPE; positions are row % seq
+    int seq, q, k;     // q columns, then k columns, then as many v columns
+    int batch;         // sequences of a rank
+    float log2_base;
+    bf16_t* kc;        // caches [G * batch][k / 128][cap][128], or null
+    bf16_t* vc;
+    long long cap;
+  } rope;
 };
 
 // Sums of the partial rows of dgamma / dbeta that the norm backward leaves: partial [nb][2][h] over nb in a fixed order.  Only
@@ -254,6 +279,8 @@ hipError_t launch_norm_sums(const NormSums& f, hipStream_t s);
 
 // layout: 0 NT, 1 NN, 2 TN (see caat_gemm_layout).  Returns hipError_t of the launch.
 hipError_t launch_gemm(const GemmParams& p, int layout, int epilogue, hipStream_t s);
+// whether the tile that an NT product gets can rotate q and k on their way out (EPI_ROPE)
+bool gemm_takes_rope(const GemmParams& p);
 // Two GEMMs that do not depend on each other in one launch (gemm_pair_kernel)
 struct GemmPair {
   int tile;           // shape 0, 1, 3, 4 or 5 of launch_gemm's; -1: one launch after the other is as fast

@@ -1,0 +1,68 @@
+"""q and k rotated in the epilogue of the product that makes them, and k and v stored to the caches there: every tile that can,
+sequences that end in and between a wave's 16-row steps, against the pass of its own and the oracle."""
+import numpy as np
+import pytest
+
+from paper_2506_19645_amd import binding as B
+from paper_2506_19645_amd import inputs as I
+from tests.test_gpu_attn import _cfg as attn_cfg, check_attn, oracle_attn_block, run_attn_block
+from tests.test_gpu_prefill import _cfg as prefill_cfg, check_prefill, oracle_prefill, run_prefill
+from tests.util import assert_close, bits_to_f64, make_inputs
+
+pytestmark = pytest.mark.gpu
+
+# T, heads, key heads, sequences, tokens, base; the tile of the product
+CASES = [(2, 4, 4, 400, 7, 1e4, 3), (2, 4, 2, 130, 16, 1e4, 4), (2, 2, 2, 3, 1003, 1e4, 4), (1, 8, 2, 5, 333, 5e5, 4),
+         (2, 8, 8, 9, 257, 1e4, 3), (4, 8, 4, 31, 65, 0.5, 4), (2, 8, 2, 300, 17, 1e4, 3), (1, 4, 4, 1, 2049, 1e4, 4),
+         (4, 8, 8, 200, 33, 1e4, 1), (4, 8, 8, 310, 32, 1e4, 0), (4, 8, 8, 23, 431, 1.5, 0)]
+
+
+def timed(run):
+    """The same with every launch timed, where the rotation is a pass of its own."""
+    B.profile_reset()
+    B.profile_enable(True)
+    try:
+        return run(), {name for name, _ in B.profile_records()}
+    finally:
+        B.profile_enable(False)
+        B.profile_reset()
+
+
+def check_rotated(a, b, dh=128):
+    """Heads [..., 128] rotated on the two routes: each rounds to bf16 (to half a step, at most 2^-8 of the value: one step apart), and the angles differ
+    by no more than those of the fp32 product position times frequency may (2^-24 of 2049 positions: 1.3e-4, allowed 2.6e-4)."""
+    a, b = (x.reshape(x.shape[:-1] + (-1, 2, dh // 2)) for x in (a, b))
+    size = np.sqrt((b ** 2).sum(axis=-2, keepdims=True))
+    assert (np.abs(a - b) <= 2.0 ** -7 * np.maximum(np.abs(a), np.abs(b)) + 2.6e-4 * size).all()
+
+
+@pytest.mark.parametrize("T,heads,kv,batch,seq,base,tile", CASES)
+def test_attention_block(T, heads, kv, batch, seq, base, tile):
+    cfg = attn_cfg(T, batch, seq, heads, 0.5, kv_heads=kv).with_(rope_base=base)
+    assert B.gemm_route(B.GEMM_NT, 0, T, cfg.tokens, cfg.qkv_r, cfg.h) == tile
+    d = make_inputs(cfg, seed=47, with_grads=False, weight_std=0.05 if cfg.h < 1024 else 0.02)
+    got = run_attn_block(cfg, d)
+    two, names = timed(lambda: run_attn_block(cfg, d))
+    assert "rope" in names
+    rot = cfg.hd_r + cfg.kvd_r
+    check_rotated(got["QKV"][..., :rot], two["QKV"][..., :rot])
+    assert np.array_equal(got["QKV"][..., rot:], two["QKV"][..., rot:])
+    check_attn(cfg, d, got, oracle_attn_block(cfg, d)[1])
+
+
+@pytest.mark.parametrize("T,heads,kv,batch,seq,base,tile", CASES)
+def test_prefill_layer(T, heads, kv, batch, seq, base, tile):
+    cfg = prefill_cfg(T, batch, seq, heads, T * 136, 0.5, kv_heads=kv).with_(rope_base=base)
+    assert B.gemm_route(B.GEMM_NT, 0, T, cfg.tokens, cfg.qkv_r, cfg.h) == tile
+    d = make_inputs(cfg, seed=48, weight_std=0.05 if cfg.h < 1024 else 0.02)
+    got = run_prefill(cfg, d, kv_cap=seq + 5)
+    two, names = timed(lambda: run_prefill(cfg, d, kv_cap=seq + 5))
+    assert "rope_kv_append" in names
+    k, v = got["Kc_bits"], got["Vc_bits"]
+    assert not k[:, :, :, seq:].any() and not v[:, :, :, seq:].any()
+    check_rotated(bits_to_f64(k[:, :, :, :seq]), bits_to_f64(two["Kc_bits"][:, :, :, :seq]))
+    assert np.array_equal(v, two["Vc_bits"])
+    w, ref = oracle_prefill(cfg, d)
+    check_prefill(cfg, d, got, ref)
+    assert_close(bits_to_f64(k[:, :, :, :seq]), ref["K"], "K cache")
+    assert_close(bits_to_f64(v[:, :, :, :seq]), ref["V"], "V cache")
