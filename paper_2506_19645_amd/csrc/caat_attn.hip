@@ -1,5 +1,5 @@
 // Attention core of the partial-sync attention sub-block (Eq. A5, first line) for gfx950: rotary embedding of
-// q and k in place, and causal softmax(q k^T / sqrt(d)) v per head with an online softmax (one pass over the keys,
+// q and k in place (where the product that makes them has not done it), and causal softmax(q k^T / sqrt(d)) v per head with an online softmax (one pass over the keys,
 // MFMA 32x32x16 bf16 for both contractions, fp32 scores / statistics / accumulators).  head_dim = 128.
 //
 // Work split: a workgroup of 4 waves owns 128 consecutive queries of one (rank, sequence, head); each wave owns
@@ -617,26 +617,52 @@ __device__ __forceinline__ void rotate_back(f32x16_t* x, const float2* freq, flo
     }
 }
 
+// D rows of the statistics as a pass of its own, for dQ and dK / dV in one launch: D[query] = sum_d dO * O, fp32; 16 lanes per
+// (row, head).
+__global__ __launch_bounds__(256) void attn_bwd_prep_kernel(const bf16_t* __restrict__ dout, const bf16_t* __restrict__ out,
+                                                            float* __restrict__ stats, long long n_seq, int seq, int seq_pad,
+                                                            int hd, int heads) {
+  const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
+  const int c = (int)(idx & 15);
+  const long long item = idx >> 4;                         // (sequence * heads + head) * seq_pad + pos
+  if (item >= n_seq * heads * seq_pad) return;
+  const int pos = (int)(item % seq_pad);
+  const long long sh = item / seq_pad;
+  const int head = (int)(sh % heads);
+  const long long sq = sh / heads;
+  float acc = 0.0f;
+  if (pos < seq) {
+    const long long o = (sq * seq + pos) * (long long)hd + (long long)head * HD + c * 8;
+    const uint4 a = *reinterpret_cast<const uint4*>(dout + o);
+    const uint4 b = *reinterpret_cast<const uint4*>(out + o);
+    acc = lo_bf(a.x) * lo_bf(b.x) + hi_bf(a.x) * hi_bf(b.x) + lo_bf(a.y) * lo_bf(b.y) + hi_bf(a.y) * hi_bf(b.y) +
+          lo_bf(a.z) * lo_bf(b.z) + hi_bf(a.z) * hi_bf(b.z) + lo_bf(a.w) * lo_bf(b.w) + hi_bf(a.w) * hi_bf(b.w);
+  }
+  acc += __shfl_xor(acc, 1, 64);
+  acc += __shfl_xor(acc, 2, 64);
+  acc += __shfl_xor(acc, 4, 64);
+  acc += __shfl_xor(acc, 8, 64);
+  if (c == 0) stats[(sh * 2 + 1) * seq_pad + pos] = acc;
+}
+
 // ---- dQ: a workgroup owns 128 queries of one (sequence, head), a wave 32 of them (lane = query), keys in blocks of 64.
 //   S^T = K q^T and dP^T = V dO^T (A operand = K / V row fragments from LDS, B operand = q / dO registers);
 //   dS^T registers, rounded to bf16, are the B operand of dQ^T += K^T dS^T (A operand = transpose reads of K).
 //   D[query] = sum_d dO * O, fp32, is taken here, where dO is in registers, and left for the dK / dV kernel that runs behind; a
 //   pass of its own read dO and O for it: 14.6 of the 2510 us of an attention block of 4096 tokens, h = 4096, T = 8 (now 2500),
 //   6.7 of the 465 us of 3 x 1003 tokens of 2048, T = 4 (now 460).
-__global__ __launch_bounds__(256, 2) void flash_bwd_dq_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ out,
-                                                           const bf16_t* __restrict__ dout, float* __restrict__ stats,
-                                                           bf16_t* __restrict__ dqkv, int seq, int seq_pad, int hd, int heads,
-                                                           int kv_heads, int n_qblk, float scale_log2, float scale, int chunk,
-                                                           float log2_base) {
-  __shared__ uint4 smem[4 * BKV * KCH];  // K slot 0, K slot 1, V slot 0, V slot 1: 64 rows x 16 chunks each = 64 KB
-  __shared__ float2 freq[HD / 2];
+//   MAKE_D false: D is there already.
+template <bool MAKE_D>
+__device__ __forceinline__ void bwd_dq(uint4* smem, float2* freq, int bid, int n_bh, const bf16_t* __restrict__ qkv,
+                                       const bf16_t* __restrict__ out, const bf16_t* __restrict__ dout, float* __restrict__ stats,
+                                       bf16_t* __restrict__ dqkv, int seq, int seq_pad, int hd, int heads, int kv_heads, int n_qblk,
+                                       float scale_log2, float scale, int chunk, float log2_base) {
   const int tid = threadIdx.x, lane = tid & 63;
   if (tid < HD / 2) freq[tid] = rope_freq(tid, HD, log2_base);   // (first read behind the walk's barriers)
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int frow = lane & 31, hf = lane >> 5;
-  const int n_bh = gridDim.x / n_qblk;
   int lpt_rank;
-  const int bh = attn_block_order(blockIdx.x, n_bh, n_qblk, chunk, lpt_rank);
+  const int bh = attn_block_order(bid, n_bh, n_qblk, chunk, lpt_rank);
   const int qb = n_qblk - 1 - lpt_rank;                      // heaviest (last) query blocks first
   const int head = bh % heads;
   const long long seq_row0 = (long long)(bh / heads) * seq;
@@ -649,23 +675,31 @@ __global__ __launch_bounds__(256, 2) void flash_bwd_dq_kernel(const bf16_t* __re
   const int qrow = q0 + wave * 32 + frow;
   const bool qvalid = qrow < seq;
 
-  bf16x8_t qf[HD / 16], dof[HD / 16], of[HD / 16];
+  bf16x8_t qf[HD / 16], dof[HD / 16];
   load_row_frags(qbase, ld, qrow, qvalid, hf, qf);
   load_row_frags(dobase, hd, qrow, qvalid, hf, dof);
-  load_row_frags(out + seq_row0 * (long long)hd + (long long)head * HD, hd, qrow, qvalid, hf, of);
   float my_lse = qvalid ? stats[(long long)bh * 2 * seq_pad + qrow] : 0.0f;
-  settle_row_frags(qf);
-  settle_row_frags(dof);
-  settle_row_frags(of);
-  float my_d = 0.0f;                                       // lanes 32 apart hold the two halves of a query
+  float* const d_row = stats + ((long long)bh * 2 + 1) * seq_pad + qrow;
+  float my_d = 0.0f;
+  if constexpr (MAKE_D) {
+    bf16x8_t of[HD / 16];
+    load_row_frags(out + seq_row0 * (long long)hd + (long long)head * HD, hd, qrow, qvalid, hf, of);
+    settle_row_frags(qf);
+    settle_row_frags(dof);
+    settle_row_frags(of);
 #pragma unroll
-  for (int ks = 0; ks < HD / 16; ++ks) {
-    const uint4 a = __builtin_bit_cast(uint4, dof[ks]), b = __builtin_bit_cast(uint4, of[ks]);
-    my_d += lo_bf(a.x) * lo_bf(b.x) + hi_bf(a.x) * hi_bf(b.x) + lo_bf(a.y) * lo_bf(b.y) + hi_bf(a.y) * hi_bf(b.y) +
-            lo_bf(a.z) * lo_bf(b.z) + hi_bf(a.z) * hi_bf(b.z) + lo_bf(a.w) * lo_bf(b.w) + hi_bf(a.w) * hi_bf(b.w);
+    for (int ks = 0; ks < HD / 16; ++ks) {                 // lanes 32 apart hold the two halves of a query
+      const uint4 a = __builtin_bit_cast(uint4, dof[ks]), b = __builtin_bit_cast(uint4, of[ks]);
+      my_d += lo_bf(a.x) * lo_bf(b.x) + hi_bf(a.x) * hi_bf(b.x) + lo_bf(a.y) * lo_bf(b.y) + hi_bf(a.y) * hi_bf(b.y) +
+              lo_bf(a.z) * lo_bf(b.z) + hi_bf(a.z) * hi_bf(b.z) + lo_bf(a.w) * lo_bf(b.w) + hi_bf(a.w) * hi_bf(b.w);
+    }
+    my_d += __shfl_xor(my_d, 32, 64);
+    if (hf == 0 && qrow < seq_pad) *d_row = my_d;          // zero behind the sequence's end
+  } else {
+    if (qvalid) my_d = *d_row;
+    settle_row_frags(qf);
+    settle_row_frags(dof);
   }
-  my_d += __shfl_xor(my_d, 32, 64);
-  if (hf == 0 && qrow < seq_pad) stats[((long long)bh * 2 + 1) * seq_pad + qrow] = my_d;   // zero behind the sequence's end
   asm volatile("" : "+v"(my_lse), "+v"(my_d));
 
   f32x16_t acc[HD / 32];
@@ -750,6 +784,17 @@ __global__ __launch_bounds__(256, 2) void flash_bwd_dq_kernel(const bf16_t* __re
   }
 }
 
+__global__ __launch_bounds__(256, 2) void flash_bwd_dq_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ out,
+                                                           const bf16_t* __restrict__ dout, float* __restrict__ stats,
+                                                           bf16_t* __restrict__ dqkv, int seq, int seq_pad, int hd, int heads,
+                                                           int kv_heads, int n_qblk, float scale_log2, float scale, int chunk,
+                                                           float log2_base) {
+  __shared__ uint4 smem[4 * BKV * KCH];  // K slot 0, K slot 1, V slot 0, V slot 1: 64 rows x 16 chunks each = 64 KB
+  __shared__ float2 freq[HD / 2];
+  bwd_dq<true>(smem, freq, blockIdx.x, gridDim.x / n_qblk, qkv, out, dout, stats, dqkv, seq, seq_pad, hd, heads, kv_heads, n_qblk,
+               scale_log2, scale, chunk, log2_base);
+}
+
 // ---- dK, dV: a workgroup owns 128 keys of one (sequence, head), a wave 32 of them (lane = key), queries in blocks of 64
 // from the diagonal to the end of the sequence.  S = Q k^T and dP = dO v^T (A operand = Q / dO row fragments from LDS,
 // B operand = k / v registers); the P and dS registers, rounded to bf16, are the B operands of dV^T += dO^T P and
@@ -758,19 +803,16 @@ __global__ __launch_bounds__(256, 2) void flash_bwd_dq_kernel(const bf16_t* __re
 static constexpr int BQB = 64;                              // queries per step of the dK/dV kernel
 static constexpr int DKV_STAGE = 2 * BQB * KCH + 64;        // uint4 per stage: Q tile, dO tile, 1 KB of statistics
 
-__global__ __launch_bounds__(256) void flash_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dout,
-                                                            const float* __restrict__ stats, bf16_t* __restrict__ dqkv, int seq,
-                                                            int seq_pad, int hd, int heads, int kv_heads, int n_kblk,
-                                                            float scale_log2, float scale, int chunk, float log2_base) {
-  __shared__ uint4 smem[2 * DKV_STAGE];
-  __shared__ float2 freq[HD / 2];
+__device__ __forceinline__ void bwd_dkv(uint4* smem, float2* freq, int bid, int n_bh, const bf16_t* __restrict__ qkv,
+                                        const bf16_t* __restrict__ dout, const float* __restrict__ stats,
+                                        bf16_t* __restrict__ dqkv, int seq, int seq_pad, int hd, int heads, int kv_heads, int n_kblk,
+                                        float scale_log2, float scale, int chunk, float log2_base) {
   const int tid = threadIdx.x, lane = tid & 63;
   if (tid < HD / 2) freq[tid] = rope_freq(tid, HD, log2_base);   // (first read behind the walk's barriers)
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int frow = lane & 31, hf = lane >> 5;
-  const int n_bh = gridDim.x / n_kblk;                        // sequences x key/value heads
   int kb;                                                     // heaviest (first) key blocks first
-  const int bh = attn_block_order(blockIdx.x, n_bh, n_kblk, chunk, kb);
+  const int bh = attn_block_order(bid, n_bh, n_kblk, chunk, kb);
   const int kvh = bh % kv_heads;
   const int grp = heads / kv_heads;                           // query heads that read this key / value head
   const long long sq = bh / kv_heads;
@@ -1036,9 +1078,44 @@ __global__ __launch_bounds__(256) void flash_bwd_dkv_kernel(const bf16_t* __rest
   }
 }
 
+__global__ __launch_bounds__(256) void flash_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dout,
+                                                            const float* __restrict__ stats, bf16_t* __restrict__ dqkv, int seq,
+                                                            int seq_pad, int hd, int heads, int kv_heads, int n_kblk,
+                                                            float scale_log2, float scale, int chunk, float log2_base) {
+  __shared__ uint4 smem[2 * DKV_STAGE];
+  __shared__ float2 freq[HD / 2];
+  bwd_dkv(smem, freq, blockIdx.x, gridDim.x / n_kblk, qkv, dout, stats, dqkv, seq, seq_pad, hd, heads, kv_heads, n_kblk, scale_log2,
+          scale, chunk, log2_base);
+}
+
+// Both in one launch, for few workgroups (bwd_in_one): n_dkv of dK / dV, then those of dQ, which take the compute units that are idle.
+__global__ __launch_bounds__(256) void flash_bwd_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dout,
+                                                        float* __restrict__ stats, bf16_t* __restrict__ dqkv, int seq, int seq_pad,
+                                                        int hd, int heads, int kv_heads, int n_blk, float scale_log2, float scale,
+                                                        int chunk, float log2_base, int n_dkv) {
+  __shared__ uint4 smem[2 * DKV_STAGE];
+  __shared__ float2 freq[HD / 2];
+  static_assert(2 * DKV_STAGE >= 4 * BKV * KCH, "room for dQ's tiles");
+  if ((int)blockIdx.x < n_dkv)
+    bwd_dkv(smem, freq, blockIdx.x, n_dkv / n_blk, qkv, dout, stats, dqkv, seq, seq_pad, hd, heads, kv_heads, n_blk, scale_log2, scale,
+            chunk, log2_base);
+  else
+    bwd_dq<false>(smem, freq, blockIdx.x - n_dkv, (gridDim.x - n_dkv) / n_blk, qkv, nullptr, dout, stats, dqkv, seq, seq_pad, hd, heads,
+                  kv_heads, n_blk, scale_log2, scale, chunk, log2_base);
+}
+
+// dQ and dK / dV in one launch, D by the pass in front: while the workgroups of dK / dV, which a compute unit holds one at a time,
+// fit on the chip at once, that launch is as long as its longest walk and leaves the rest idle, and dQ finds room there.  With more
+// of them the units are busy and dQ, two workgroups to a unit in a launch of its own, loses by being alone on one.  Attention
+// blocks, forward and backward (T, h, key heads, sequences x tokens: workgroups of dK / dV, us apart / in one launch):
+//   4, 2048, 8, 3 x 1003: 192, 437 / 413     8, 4096, 8, 1 x 2048: 128, 1062 / 1003     2, 768, 6, 4 x 256: 48, 98 / 86
+//   4, 2048, 16, 1 x 1003: 128, 259 / 227    8, 4096, 8, 1 x 4096: 256, 2138 / 2052     8, 4096, 8, 4 x 1024: 256, 1585 / 1583
+//   8, 4096, 32, 1 x 1500: 384, 881 / 872    4, 2048, 8, 6 x 1003: 384, 774 / 785       8, 4096, 32, 1 x 3000: 768, 1783 / 1809
+static bool bwd_in_one(long long n_dkv) { return n_dkv <= compute_units(); }
+
 // Backward of the attention core for every (sequence, head): qkv (rotated q | k | v), out = forward output, dout its
-// gradient, stats with the forward's lse rows -> dqkv (gradients w.r.t. the ROTATED q, k and w.r.t. v, same layout
-// as qkv).  The D rows of stats are filled here.
+// gradient, stats with the forward's lse rows -> dqkv (gradients w.r.t. q and k before their rotation and w.r.t. v, same
+// layout as qkv).  The D rows of stats that dK / dV reads are filled here, by the dQ kernel or by a pass of their own.
 hipError_t launch_flash_bwd(const bf16_t* qkv, const bf16_t* out, const bf16_t* dout, float* stats, bf16_t* dqkv,
                             long long n_seq, int seq, int heads, int kv_heads, int d, float rope_base, hipStream_t s) {
   if (d != HD || kv_heads < 1 || heads % kv_heads != 0) return hipErrorInvalidValue;
@@ -1051,11 +1128,22 @@ hipError_t launch_flash_bwd(const bf16_t* qkv, const bf16_t* out, const bf16_t* 
     return hipErrorInvalidValue;
   const float inv_sqrt_d = 1.0f / sqrtf((float)d);
   const float scale_log2 = 1.4426950408889634f * inv_sqrt_d;
+  const long long n_dkv = n_seq * kv_heads * n_qblk;
+  if (bwd_in_one(n_dkv)) {
+    const long long prep_threads = n_bh * seq_pad * 16;
+    hipLaunchKernelGGL(attn_bwd_prep_kernel, dim3((unsigned)((prep_threads + 255) / 256)), dim3(256), 0, s, dout, out, stats, n_seq,
+                       seq, seq_pad, hd, heads);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(flash_bwd_kernel, dim3((unsigned)(n_dkv + n_bh * n_qblk)), dim3(256), 0, s, qkv, dout, stats, dqkv, seq,
+                       seq_pad, hd, heads, kv_heads, n_qblk, scale_log2, inv_sqrt_d, attn_chunk_heads(seq), log2f(rope_base), (int)n_dkv);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(flash_bwd_dq_kernel, dim3((unsigned)(n_bh * n_qblk)), dim3(256), 0, s, qkv, out, dout, stats, dqkv, seq,
                      seq_pad, hd, heads, kv_heads, n_qblk, scale_log2, inv_sqrt_d, attn_chunk_heads(seq), log2f(rope_base));
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(flash_bwd_dkv_kernel, dim3((unsigned)(n_seq * kv_heads * n_qblk)), dim3(256), 0, s, qkv, dout, stats, dqkv,
+  hipLaunchKernelGGL(flash_bwd_dkv_kernel, dim3((unsigned)n_dkv), dim3(256), 0, s, qkv, dout, stats, dqkv,
                      seq, seq_pad, hd, heads, kv_heads, n_qblk, scale_log2, inv_sqrt_d, attn_chunk_heads(seq), log2f(rope_base));
   return hipGetLastError();
 }

@@ -21,7 +21,7 @@ template <> hipError_t launch_block_sized<Cfg64x64k>(const GemmParams&, int, int
 CAAT_PAIR(Cfg256x256) CAAT_PAIR(Cfg192x256) CAAT_PAIR(Cfg128x128) CAAT_PAIR(Cfg64x128) CAAT_PAIR(Cfg64x64)
 #undef CAAT_PAIR
 
-static int compute_units() {
+int compute_units() {
   static int n_cu = 0;
   if (n_cu == 0) {
     int dev = 0, v = 0;

@@ -278,6 +278,7 @@ __device__ __forceinline__ void norm_sums(const NormSums& f, int block, float4* 
 hipError_t launch_norm_sums(const NormSums& f, hipStream_t s);
 
 // layout: 0 NT, 1 NN, 2 TN (see caat_gemm_layout).  Returns hipError_t of the launch.
+int compute_units();   // of the current device; 256 where it cannot be asked
 hipError_t launch_gemm(const GemmParams& p, int layout, int epilogue, hipStream_t s);
 // whether the tile that an NT product gets can rotate q and k on their way out (EPI_ROPE)
 bool gemm_takes_rope(const GemmParams& p);

@@ -1,5 +1,6 @@
-"""The sums dO * O of the attention backward, made by the dQ kernel for the dK / dV kernel: sequences that end inside a block of
-queries on a workspace full of NaN give the bits they give on a cleared one, and the oracle's gradients."""
+"""The sums dO * O of the attention backward, made by the dQ kernel for the dK / dV kernel or, up to 256 workgroups of dK / dV, in
+front of both in one launch: sequences that end inside a block of queries on a workspace full of NaN give the bits they give on a
+cleared one, and the oracle's gradients."""
 import numpy as np
 import pytest
 
@@ -10,7 +11,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("T,heads,kv,batch,seq", [(2, 4, 4, 1, 1), (2, 4, 2, 3, 63), (1, 4, 1, 2, 65), (2, 4, 4, 1, 128), (2, 8, 4, 2, 129),
-                                                  (1, 8, 1, 1, 190), (4, 8, 8, 1, 257)])
+                                                  (1, 8, 1, 1, 190), (4, 8, 8, 1, 257),
+                                                  (2, 4, 4, 64, 127), (2, 4, 4, 65, 100), (2, 4, 4, 35, 191), (1, 8, 2, 129, 65),
+                                                  (1, 4, 1, 260, 1), (2, 8, 4, 22, 257)])
 def test_row_sums_on_a_workspace_of_nan(T, heads, kv, batch, seq, monkeypatch):
     import torch
     cfg = _cfg(T, batch, seq, heads, 0.5, kv_heads=kv)
