@@ -1067,17 +1067,19 @@ __global__ __launch_bounds__(256) void norm_bwd_wide_kernel(const bf16_t* __rest
 // g_out -- rounds once and stores the result to every rank's row of g_red; private channels of g_red get scale * g_m.
 // A workgroup walks a contiguous range of tokens and keeps its threads' columns of dgamma / dbeta in registers over
 // all of them (summed over tokens AND ranks), one partial row per workgroup; norm_bwd_finalize_kernel adds them up.
-// Saves, against the two kernels, the read-back of the shared channels and one launch.
-template <int TT, int NG, bool LN, int NT>
-__global__ __launch_bounds__(NT) void norm_bwd_sync_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ dres,
+// Saves, against the two kernels, the read-back of the shared channels and one launch.  GP = 2: two groups of NT threads take a
+// token each at a time and add their columns up at the end.
+template <int TT, int NG, bool LN, int NT, int GP>
+__global__ __launch_bounds__(NT * GP) void norm_bwd_sync_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ dres,
                                                             const bf16_t* __restrict__ x, const bf16_t* __restrict__ gamma,
                                                             const float* __restrict__ mean, const float* __restrict__ rstd,
                                                             bf16_t* __restrict__ g_out, bf16_t* __restrict__ g_red,
                                                             float* __restrict__ partial, long long n, int h, int hs,
                                                             float scale, long long tokens_per_block) {
   constexpr int NW = NT / 64;
-  __shared__ float red[2][2][NW][TT];   // [token parity][c1 | c2][wave][rank]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  static_assert(GP == 1 || (GP == 2 && NG == 1), "two groups of threads meet in one exchange");
+  __shared__ float red[2][2][NW * GP][TT];   // [token parity][c1 | c2][wave][rank]
+  const int grp = GP == 1 ? 0 : threadIdx.x / NT, tid = threadIdx.x - grp * NT, lane = tid & 63, wave = threadIdx.x >> 6;
   const int nvec = h >> 3;
   const float inv_h = 1.0f / (float)h;
   const long long plane = n * (long long)h;
@@ -1097,8 +1099,10 @@ __global__ __launch_bounds__(NT) void norm_bwd_sync_kernel(const bf16_t* __restr
   const long long t0 = (long long)blockIdx.x * tokens_per_block;
   long long t1 = t0 + tokens_per_block;
   if (t1 > n) t1 = n;
-  for (long long i = t0; i < t1; ++i) {
-    const int par = (int)((i - t0) & 1);
+  for (long long i0 = t0; i0 < t1; i0 += GP) {
+    const long long i = i0 + grp;
+    const bool live = GP == 1 || i < t1;
+    const int par = (int)((i0 - t0) / GP & 1);
     // the three inputs of all T rows of the token are requested together (read once: non-temporal)
     uint4 wx[NG][TT], wd[NG][TT], wr[NG][TT];
 #pragma unroll
@@ -1109,7 +1113,7 @@ __global__ __launch_bounds__(NT) void norm_bwd_sync_kernel(const bf16_t* __restr
         wx[g][m] = make_uint4(0u, 0u, 0u, 0u);
         wd[g][m] = wx[g][m];
         wr[g][m] = wx[g][m];
-        if (vi < nvec) {
+        if (vi < nvec && live) {
           const long long off = m * plane + i * h + vi * 8;
           wx[g][m] = ld_stream(x + off);
           wd[g][m] = ld_stream(dy + off);
@@ -1120,8 +1124,8 @@ __global__ __launch_bounds__(NT) void norm_bwd_sync_kernel(const bf16_t* __restr
     float mu[TT], rs[TT], c1[TT], c2[TT];
 #pragma unroll
     for (int m = 0; m < TT; ++m) {
-      mu[m] = LN ? mean[m * n + i] : 0.0f;
-      rs[m] = rstd[m * n + i];
+      mu[m] = LN && live ? mean[m * n + i] : 0.0f;
+      rs[m] = live ? rstd[m * n + i] : 0.0f;
       c1[m] = 0.0f;
       c2[m] = 0.0f;
     }
@@ -1160,8 +1164,8 @@ __global__ __launch_bounds__(NT) void norm_bwd_sync_kernel(const bf16_t* __restr
       float s1 = 0.0f, s2 = 0.0f;
 #pragma unroll
       for (int w = 0; w < NW; ++w) {     // the waves' sums in ascending order
-        if constexpr (LN) s1 += red[par][0][w][m];
-        s2 += red[par][1][w][m];
+        if constexpr (LN) s1 += red[par][0][grp * NW + w][m];
+        s2 += red[par][1][grp * NW + w][m];
       }
       if constexpr (LN) c1[m] = s1 * inv_h;
       c2[m] = s2 * inv_h;
@@ -1169,7 +1173,7 @@ __global__ __launch_bounds__(NT) void norm_bwd_sync_kernel(const bf16_t* __restr
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
       const int vi = g * NT + tid;
-      if (vi < nvec) {
+      if (vi < nvec && live) {
         const int col = vi * 8;
         float gm[8];
         unpack8(gam[g], gm);
@@ -1220,6 +1224,27 @@ __global__ __launch_bounds__(NT) void norm_bwd_sync_kernel(const bf16_t* __restr
           }
         }
       }
+    }
+  }
+  if constexpr (GP == 2) {               // the second group's columns are added to the first's
+    __shared__ float4 part[(LN ? 4 : 2) * NT];
+    if (grp == 1) {
+#pragma unroll
+      for (int q = 0; q < (LN ? 4 : 2); ++q) {
+        const float* v = (q < 2 ? dgam[0] : dbet[0]) + (q & 1) * 4;
+        part[q * NT + tid] = make_float4(v[0], v[1], v[2], v[3]);
+      }
+    }
+    __syncthreads();
+    if (grp == 1) return;
+#pragma unroll
+    for (int q = 0; q < (LN ? 4 : 2); ++q) {
+      float* v = (q < 2 ? dgam[0] : dbet[0]) + (q & 1) * 4;
+      const float4 w = part[q * NT + tid];
+      v[0] += w.x;
+      v[1] += w.y;
+      v[2] += w.z;
+      v[3] += w.w;
     }
   }
   float* prow = partial + (long long)blockIdx.x * 2 * h;
@@ -1339,16 +1364,16 @@ bool norm_bwd_sync_takes(int T, long long tokens, int h, int hs) {
   return norm_bwd_sync_groups(T, h) != 0;
 }
 
-template <int TT, int NG, int NT>
+template <int TT, int NG, int NT, int GP>
 static hipError_t norm_bwd_sync_dispatch(const bf16_t* dy, const bf16_t* dres, const bf16_t* x, const bf16_t* gamma,
                                          const float* mean, const float* rstd, bf16_t* g_out, bf16_t* g_red, float* partial,
                                          int norm, long long tokens, int h, int hs, float scale, long long nb, long long tpb,
                                          hipStream_t s) {
   if (norm == 0)
-    hipLaunchKernelGGL((norm_bwd_sync_kernel<TT, NG, true, NT>), dim3((unsigned)nb), dim3(NT), 0, s, dy, dres, x, gamma, mean,
+    hipLaunchKernelGGL((norm_bwd_sync_kernel<TT, NG, true, NT, GP>), dim3((unsigned)nb), dim3(NT * GP), 0, s, dy, dres, x, gamma, mean,
                        rstd, g_out, g_red, partial, tokens, h, hs, scale, tpb);
   else
-    hipLaunchKernelGGL((norm_bwd_sync_kernel<TT, NG, false, NT>), dim3((unsigned)nb), dim3(NT), 0, s, dy, dres, x, gamma, mean,
+    hipLaunchKernelGGL((norm_bwd_sync_kernel<TT, NG, false, NT, GP>), dim3((unsigned)nb), dim3(NT * GP), 0, s, dy, dres, x, gamma, mean,
                        rstd, g_out, g_red, partial, tokens, h, hs, scale, tpb);
   return hipGetLastError();
 }
@@ -1370,10 +1395,16 @@ hipError_t launch_norm_bwd_sync(const bf16_t* dy, const bf16_t* dres, const bf16
   float* partial = reinterpret_cast<float*>(workspace);
   const int ng = norm_bwd_sync_groups(T, h);
   hipError_t e = hipErrorInvalidValue;
-#define CAAT_NBS(TT_, NG_) e = norm_bwd_sync_dispatch<TT_, NG_, 256>(dy, dres, x, gamma, mean, rstd, g_out, g_red, partial, norm, tokens, h, hs, private_scale, nb, tpb, s)
-  if (T == 2 && ng == 1) CAAT_NBS(2, 1);
-  else if (T == 2 && ng == 2) CAAT_NBS(2, 2);
-  else if (T == 4 && ng == 1) CAAT_NBS(4, 1);
+#define CAAT_NBS(TT_, NG_, NT_, GP_) e = norm_bwd_sync_dispatch<TT_, NG_, NT_, GP_>(dy, dres, x, gamma, mean, rstd, g_out, g_red, partial, norm, tokens, h, hs, private_scale, nb, tpb, s)
+  // Half of 256 threads cover a row of up to 1024 channels: two tokens at a time, or half of the bytes are in flight.  MLP steps
+  // with one / two tokens: T = 4, 8192 tokens of 1024 575 / 563 us, 16384 of 768 850 / 814, 1000 of 512 63.0 / 60.0; T = 2, 4096
+  // of 768 187 / 180, 256 of 768 52.6 / 50.8.
+  const bool two = h <= 1024 && tpb > 1;
+  if (T == 2 && two) CAAT_NBS(2, 1, 128, 2);
+  else if (T == 4 && two) CAAT_NBS(4, 1, 128, 2);
+  else if (T == 2 && ng == 1) CAAT_NBS(2, 1, 256, 1);
+  else if (T == 2 && ng == 2) CAAT_NBS(2, 2, 256, 1);
+  else if (T == 4 && ng == 1) CAAT_NBS(4, 1, 256, 1);
 #undef CAAT_NBS
   if (e != hipSuccess) return e;
   const int ncols = norm == 0 ? 2 * h : h;
