@@ -489,8 +489,8 @@ __global__ __launch_bounds__(NT) void sync_norm_kernel(bf16_t* io, const bf16_t*
       const long long off = i * h + col;
       if (col < hs) {                                     // shared channels
         float sum[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        uint4 pv[TT];     // the T partials and the T residual vectors are requested together
         {
+          uint4 pv[TT];   // the T partials and the T residual vectors are requested together
 #pragma unroll
           for (int m = 0; m < TT; ++m) {
             pv[m] = big ? ld_stream(io + m * plane + off) : *reinterpret_cast<const uint4*>(io + m * plane + off);
@@ -511,8 +511,8 @@ __global__ __launch_bounds__(NT) void sync_norm_kernel(bf16_t* io, const bf16_t*
 #pragma unroll
           for (int e = 0; e < 8; ++e) o[e] = sum[e] + r[e];
           if (col + 8 > hs) {                             // the vector that hs ends in: its private channels are final
-            float f[8];
-            unpack8(pv[m], f);
+            float f[8];                                   // (read again, by one thread: kept, they cost all shapes 4 T registers)
+            unpack8(*reinterpret_cast<const uint4*>(io + m * plane + off), f);
 #pragma unroll
             for (int e = 0; e < 8; ++e) o[e] = col + e < hs ? o[e] : f[e];
           }
