@@ -218,21 +218,24 @@ static GemmPair plan_pair(const TileShape& t, int index, const GemmParams& p1, c
   // behind the first GEMM n_hi slots are free at hi, n_lo at lo
   const long long n_hi = na % slots, n_lo = slots - n_hi;
   const double lo = (double)(na / slots) * ua, hi = n_hi ? lo + ua : lo;
-  // one tile at a time to whichever slot is free first; whole rounds of all slots beforehand
-  struct { double at; long long n; } cls[3] = {{lo, n_lo}, {hi, n_hi}, {0.0, 0}};
+  // one tile at a time to whichever slot is free first: those free at lo catch up with the others, then whole rounds of all
+  // slots, then the last tiles
+  struct { double at; long long n; } cls[2] = {{lo, n_lo}, {hi, n_hi}};
   const double ub1 = ub + (t.persist ? 1.5 : 0.0);
   long long left = nb;
+  const long long ahead = std::min(left / n_lo, (long long)((hi - lo) / ub1));
+  cls[0].at += ahead * ub1;
+  left -= ahead * n_lo;
   const long long rounds = left > 3 * slots ? left / slots - 2 : 0;
   left -= rounds * slots;
   cls[0].at += rounds * ub1;
-  if (n_hi) cls[1].at += rounds * ub1;
-  double each = hi;
+  cls[1].at += rounds * ub1;
   while (left > 0) {
     const int c = cls[1].n && cls[1].at < cls[0].at ? 1 : 0;
     cls[c].at += ub1;
-    each = std::max(each, cls[c].at);
     left -= cls[c].n;
   }
+  const double each = std::max(cls[0].at, n_hi ? cls[1].at : lo);
   double end = each;
   bool one_each = true;
   if (t.persist) {   // even shares: the first nb % g workgroups have one tile more
