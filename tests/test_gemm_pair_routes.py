@@ -3,16 +3,38 @@ from paper_2506_19645_amd import binding as B
 from tests import test_gpu_gemm_pairs as pairs
 
 
+TILES = {0: (256, 256), 1: (192, 256), 3: (128, 128), 4: (64, 128), 5: (64, 64)}
+SLOTS = 256   # workgroups of persistent tiles that run at once
+
+
+def tiles(M, N, G, tile):
+    bm, bn = TILES[tile]
+    return -(-M // bm) * -(-N // bn) * G
+
+
 def test_gpu_tests_reach_every_pair_kernel_and_every_order():
     seen = set()
     for swi, T, n, h, fr, hs in pairs.PAIRS:
         for first, (N, K) in ((True, (fr, h)), (False, (h, 2 * fr if swi else fr))):
             r = B.gemm_pair_route(T, n, N, K)
-            if r >= 0:
-                seen |= {(r % 16, ("gelu", "swiglu")[swi] if first else "plain"), r}
-    missing = {(tile, e) for tile in (0, 1, 3, 4, 5) for e in ("gelu", "swiglu", "plain")} - seen
+            if r < 0:
+                continue
+            tile, wgrad_first, one_each, epi = r % 16, bool(r & 16), bool(r & 32), ("gelu", "swiglu")[swi] if first else "plain"
+            seen |= {(tile, epi), r}
+            if tile > 1 or n % TILES[tile][0] == 0 or N % TILES[tile][1] == 0:
+                continue
+            dgrad, wgrad = tiles(n, N, T, tile), tiles(K, N, T, tile)
+            if (wgrad if wgrad_first else dgrad) > SLOTS:
+                seen.add(("first walks", tile, wgrad_first))
+            if (dgrad if wgrad_first else wgrad) > SLOTS and not one_each:
+                seen.add(("second walks a share", tile, wgrad_first))
+            if dgrad > SLOTS and not (wgrad_first and one_each):
+                seen.add(("data gradient walks", epi))
+    missing = {(tile, e) for tile in TILES for e in ("gelu", "swiglu", "plain")} - seen
     # persistent tiles: either GEMM first, the second by the tile and in shares; others: either first, always by the tile
     missing |= ({0, 16, 32, 48, 17, 33, 35, 51, 36, 52, 37, 53} | {1, 49}) - seen
+    missing |= {(walk, tile, wf) for walk in ("first walks", "second walks a share") for tile in (0, 1) for wf in (False, True)} - seen
+    missing |= {("data gradient walks", e) for e in ("gelu", "swiglu")} - seen
     assert not missing, sorted(map(str, missing))
 
 

@@ -21,6 +21,11 @@ PAIRS = [
     (False, 1, 1, 8, 8, 4), (True, 2, 65, 72, 136, 33), (False, 2, 100, 136, 200, 64), (True, 2, 33, 200, 72, 128),
     (False, 2, 256, 768, 1536, 384), (False, 2, 2048, 1032, 3080, 0), (True, 4, 1300, 264, 2056, 128),
     (False, 4, 1300, 264, 4104, 128), (True, 1, 65, 8, 72, 5), (True, 4, 100, 72, 1544, 32), (True, 8, 65, 72, 1032, 72), (True, 8, 100, 8, 2056, 8),
+    # persistent tiles walked several to a workgroup: by the first GEMM and, in shares, by the second, either one the data
+    # gradient, with ragged edges; the GELU and the SwiGLU derivative among those that walk
+    (True, 8, 264, 1672, 488, 837), (True, 16, 136, 1288, 72, 640), (True, 16, 264, 136, 2056, 72), (False, 16, 264, 136, 2056, 21),
+    (True, 16, 456, 2192, 200, 1096), (True, 16, 390, 2056, 72, 513), (True, 16, 777, 1288, 264, 0), (True, 16, 264, 2072, 72, 2072),
+    (True, 16, 390, 2184, 200, 546), (True, 16, 390, 1288, 264, 648), (True, 16, 264, 2056, 264, 100), (True, 16, 136, 1800, 264, 904),
 ]
 
 # (T, tokens, h, ffn / T, hs): private and shared columns of a product with the reduce inside in one launch, summed in groups of
