@@ -594,7 +594,7 @@ int caat_gemm_shared_pair_route(int T, long long M, long long h, long long hs, l
   GemmParams p, priv;
   std::memset(&p, 0, sizeof(p));
   std::memset(&priv, 0, sizeof(priv));
-  p.G = 1; p.M = (int)M; p.N = (int)hs; p.K = (int)K; p.kcat = T;
+  p.G = 1; p.M = (int)M; p.N = (int)hs; p.K = (int)K; p.kcat = p.bcast = T;
   priv.G = T; priv.M = (int)M; priv.N = (int)(h - hs); priv.K = (int)K; priv.n_route = (int)h;
   int groups = 1;
   const GemmPair pair = gemm_shared_pair(p, priv, gemm_shared_scratch_bytes((int)M, (int)hs, T), &groups);

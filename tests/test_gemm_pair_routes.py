@@ -52,13 +52,30 @@ def test_a_pair_is_as_long_as_its_last_tile():
         assert B.gemm_pair_route(T, n, N, K) == -1
 
 
+def test_the_stores_to_all_ranks_count_in_a_pair():
+    """Few large tiles that store to 16 or 8 ranks each: forward passes took 194 us for 154, 206 for 165, 119 for 102 in a pair of
+    128 x 128 tiles."""
+    for T, n, h, hs, K in ((16, 4979, 512, 328, 112), (16, 6745, 512, 128, 128), (8, 7723, 512, 128, 256)):
+        r = B.gemm_shared_pair_route(T, n, h, hs, K)
+        assert r == -1 or r % 16 > 3 or r // 256 > 1
+
+
 def test_gpu_tests_reach_every_pair_of_private_and_shared_columns():
-    """Every tile with the shared sums in groups and directly (1 group)."""
-    seen = set()
+    """Every tile with the shared sums in groups and directly (1 group); persistent tiles of which a workgroup walks several, by
+    whichever part is first and by the private columns in shares (short shared sums of more tiles than that are not paired)."""
+    seen, walks = set(), set()
     for T, n, h, fr, hs in pairs.SHARED:
         r = B.gemm_shared_pair_route(T, n, h, hs, fr)
         assert r >= 0
-        seen.add((r % 16, r // 256 > 1))
-    assert seen == {(tile, groups) for tile in (0, 1, 3, 4, 5) for groups in (False, True)}
+        tile, groups, shared_first, one_each = r % 16, r // 256, bool(r & 16), bool(r & 32)
+        seen.add((tile, groups > 1))
+        if tile < 2:
+            private, shared = tiles(n, h - hs, T, tile), tiles(n, hs, groups, tile)
+            if (shared if shared_first else private) > SLOTS:
+                walks.add("shared first" if shared_first else "private first")
+            if shared_first and private > SLOTS and not one_each:
+                walks.add("private shares")
+    assert seen == {(tile, groups) for tile in TILES for groups in (False, True)}
+    assert walks == {"shared first", "private first", "private shares"}
     assert B.gemm_shared_pair_route(8, 128, 1536, 768, 2048) == -1   # the private columns stream their weights
     assert B.gemm_shared_pair_route(8, 96, 4096, 4096, 512) == -2
