@@ -1,5 +1,6 @@
 // Instantiations and launch dispatch of the grouped bf16 shard GEMM (kernel template in caat_gemm_kernel.h).
 #include <algorithm>
+#include <cmath>
 #include "caat_gemm_tiles.h"
 
 namespace caat {
@@ -204,7 +205,7 @@ hipError_t launch_gemm(const GemmParams& p, int layout, int epilogue, hipStream_
 // What a tile's stores to all ranks, and the loads of what is added to them, take at a compute unit's share of the copy rate: a
 // launch of few large tiles ends with that (T = 16, 4979 tokens, h = 512, hs = 328, K = 112: 194 us with 117 tiles of 128 x 128 in
 // the pair, 154 apart on 468 of 64 x 64).
-static double bcast_us(const TileShape& t, int ranks) { return (double)ranks * t.bm * t.bn * 4.0 / 21e3; }
+static double bcast_us(const TileShape& t, double copies) { return copies * t.bm * t.bn * 4.0 / 21e3; }
 
 // Both gradient GEMMs in one launch (gemm_pair_kernel): the one with the longer tiles first, on as many workgroups as fit on the
 // chip; the other one's workgroups start wherever a slot is or comes free, each with one tile or, persistent tiles with an even
@@ -216,12 +217,12 @@ static double bcast_us(const TileShape& t, int ranks) { return (double)ranks * t
 // Two things the constants of single launches don't hold: 64 x 64 tiles beside another GEMM's take 10 % longer (3779 random pairs,
 // each tile timed), and a GEMM of one row of persistent tiles pulls every byte of its weights from memory with one stage on its
 // way, 1.4 times the time a stage takes from the caches (133 tokens of 4096, ffn 16384, T = 4: 230 us on 192 x 256 tiles, 205 apart).
-static GemmPair plan_pair(const TileShape& t, int index, const GemmParams& p1, const GemmParams& p2, int n_cu) {
+static GemmPair plan_pair(const TileShape& t, int index, const GemmParams& p1, const GemmParams& p2, int n_cu, double copies) {
   auto tiles = [&](const GemmParams& p) { return (((long long)p.M + t.bm - 1) / t.bm) * (((long long)p.N + t.bn - 1) / t.bn) * p.G; };
   auto us = [&](const GemmParams& p) {
     const bool cold = t.persist && p.M <= t.bm && (&p == &p1 || p.kcat > 0);   // the weight gradient reads no weights
     const double stages = (double)(((long long)p.K + t.k - 1) / t.k) * (p.kcat > 1 ? p.kcat : 1);
-    return stages * t.stage * (cold ? 1.4 : 1.0) + t.tile + bcast_us(t, p.bcast);
+    return stages * t.stage * (cold ? 1.4 : 1.0) + t.tile + (&p == &p2 ? bcast_us(t, copies) : 0.0);
   };
   const double u1 = us(p1), u2 = us(p2);
   const bool sf = u2 > u1;
@@ -260,10 +261,10 @@ static GemmPair plan_pair(const TileShape& t, int index, const GemmParams& p1, c
   const double fill = (na * ua + nb * ub) / (slots * end);
   return {index, sf, one_each, end * (0.55 + 0.45 * std::min(fill, 1.0)) * (t.bm == 64 && t.bn == 64 ? 1.1 : 1.0)};
 }
-static GemmPair best_pair(const GemmParams& p1, const GemmParams& p2, int n_cu) {
+static GemmPair best_pair(const GemmParams& p1, const GemmParams& p2, int n_cu, double copies = 0.0) {   // that p2 stores
   GemmPair best = {-1, false, false, 0.0};
   for (int i : {0, 1, 3, 4, 5}) {
-    const GemmPair p = plan_pair(TILES[i], i, p1, p2, n_cu);
+    const GemmPair p = plan_pair(TILES[i], i, p1, p2, n_cu, copies);
     if (best.tile < 0 || p.us < best.us) best = p;
   }
   return best;
@@ -312,38 +313,27 @@ hipError_t launch_gemm_pair(const GemmPair& p, const GemmParams& nn, int epilogu
 //   65 x 2048 x 512 x 8     29 / 22 / 17 / 17     1024 x 2048 x 1376 x 8    112 / 93 / 80 / 72
 //   777 x 1024 x 512 x 4    18 / 19 / 22           777 x 2048 x 3584 x 4    116 / 92 / 70
 // `scratch_bytes`: what there is for the groups' sums.
-static int gemm_shared_groups(int M, int N, int K, int kcat, size_t scratch_bytes, const GemmParams* priv = nullptr, int bcast = 0,
-                              GemmPair* pair = nullptr, double* us_out = nullptr) {
-  const int n_cu = compute_units();
+static int gemm_shared_groups(int M, int N, int K, int kcat, size_t scratch_bytes, double* gemm_us = nullptr) {
   GemmParams q = {};
   q.M = M;
   q.N = N;
   q.K = K;
   int best = 1;
   double cost = 0.0;
-  if (pair) pair->tile = -1;
   for (int g = 1; g <= kcat; g *= 2) {
     if (kcat % g != 0 || (g > 1 && (size_t)g * M * N * sizeof(float) > scratch_bytes)) break;
     q.G = g;
     q.kcat = kcat / g;
-    q.bcast = g == 1 ? bcast : 0;
     double us = 0.0;
-    GemmPair p = {-1, false, false, 0.0};
-    if (priv) {
-      p = best_pair(*priv, q, n_cu);
-      us = p.us;
-    } else {
-      choose_tile(q, 0, EPI_PARTIAL, n_cu, &us);
-    }
+    choose_tile(q, 0, EPI_PARTIAL, compute_units(), &us);
     us *= 1.4;
-    if (g > 1) us += 5.0 + (double)g * M * N * (priv ? 8.0 : 4.0) / 7e6;
-    if (g == 1 || us < cost) {
-      cost = us;
+    const double all = g > 1 ? us + 5.0 + (double)g * M * N * 4.0 / 7e6 : us;
+    if (g == 1 || all < cost) {
+      cost = all;
       best = g;
-      if (pair) *pair = p;
+      if (gemm_us) *gemm_us = us;
     }
   }
-  if (us_out) *us_out = cost;
   return best;
 }
 
@@ -378,29 +368,24 @@ hipError_t launch_gemm_shared(const GemmParams& p, void* scratch, size_t scratch
   return e != hipSuccess ? e : merge_groups(p, groups, scratch, s);
 }
 
-// With the private columns in the same launch the groups are chosen anew: the private tiles fill what the shared ones leave idle.
-// Not where the private columns stream their weights (65 to 128 token rows, see choose_route).  Prefill layers of the 7B shape,
-// us, two launches / one: T = 8, hs = h / 2, 777 tokens 479 / 469, 200 tokens 242 / 222, 100 tokens 173 / 161; hs = h / 4, 1500
-// tokens 801 / 765; 3 x 500 tokens of 2048, T = 2, hs = h / 4 247 / 216.  The groups' sums are priced at the bytes written and read
-// here; on 3660 random products (every tile and number of groups timed) the launches taken then take 0.799 of the time apart, 1 %
-// lose more than 2 %; without the broadcast's time and with half of the sums' bytes 0.807 and 4 %.
+// The private columns in the same launch: their tiles fill what the shared ones leave idle.  Not where they stream their weights
+// (65 to 128 token rows, see choose_route).  The groups are those of the two launches, so the bits are the same either way.
 GemmPair gemm_shared_pair(const GemmParams& p, const GemmParams& priv, size_t scratch_bytes, int* groups) {
   GemmPair pair = {-1, false, false, 0.0};
   const int n_cu = compute_units();
-  *groups = 1;
+  double shared = 0.0, us = 0.0;
+  *groups = gemm_shared_groups(p.M, p.N, p.K, p.kcat, scratch_bytes, &shared);
   if (choose_route(priv, 0, EPI_ROWPAR, n_cu) >= ROUTE_FEW_ROWS) return pair;
-  double alone = 0.0, both = 0.0, us = 0.0;
-  if (gemm_shared_groups(p.M, p.N, p.K, p.kcat, scratch_bytes, nullptr, 0, nullptr, &alone) == 1) {
-    GemmParams q = p;
-    q.G = 1;
-    const TileShape& t = TILES[choose_tile(q, 0, EPI_SHARED_BCAST, n_cu)];
-    const long long tiles = (((long long)p.M + t.bm - 1) / t.bm) * (((long long)p.N + t.bn - 1) / t.bn), slots = (long long)t.per_cu * n_cu;
-    alone += (double)((tiles + slots - 1) / slots) * bcast_us(t, p.bcast);
-  }
+  const double copies = *groups == 1 ? (double)p.bcast : 0.0;
+  GemmParams q = p;
+  q.G = *groups;
+  q.kcat = p.kcat / *groups;
+  const TileShape& t = TILES[choose_tile(q, 0, EPI_PARTIAL, n_cu)];
+  const long long tiles = (((long long)p.M + t.bm - 1) / t.bm) * (((long long)p.N + t.bn - 1) / t.bn), slots = (long long)t.per_cu * n_cu;
+  shared += (double)((tiles + slots - 1) / slots) * bcast_us(t, copies);
   choose_tile(priv, 0, EPI_ROWPAR, n_cu, &us);
-  *groups = gemm_shared_groups(p.M, p.N, p.K, p.kcat, scratch_bytes, &priv, p.bcast, &pair, &both);
-  if (!pays(both, alone + 1.4 * us)) pair.tile = -1;
-  return pair;
+  const GemmPair best = best_pair(priv, q, n_cu, copies);
+  return pays(1.4 * best.us, shared + 1.4 * us) ? best : pair;
 }
 hipError_t launch_gemm_shared_private(const GemmParams& p, const GemmParams& priv, void* scratch, size_t scratch_bytes, bool* taken,
                                       hipStream_t s) {

@@ -35,8 +35,9 @@ SHARED = [
     (4, 136, 72, 264, 32), (8, 2048, 4096, 72, 2048), (8, 1300, 3080, 72, 8), (4, 1300, 2056, 1032, 1024), (2, 456, 4096, 8, 8),
     (2, 1000, 2056, 72, 1024), (8, 456, 2056, 264, 1024), (2, 200, 4096, 8, 8), (8, 65, 4096, 264, 4088), (2, 136, 72, 8, 32),
     (8, 65, 2056, 264, 2048),
-    # stored to all ranks from the pair itself; several persistent tiles to a workgroup: the shared columns first, the private ones in shares
-    (2, 3500, 3352, 1072, 2448), (2, 2056, 4056, 416, 3984), (2, 1160, 3440, 8, 3408), (4, 2300, 3680, 136, 3592), (8, 2824, 1104, 8, 192),
+    # stored to all ranks from the pair itself; several persistent tiles to a workgroup: private columns first, either part second in shares
+    (2, 3500, 3352, 1072, 2448), (2, 2056, 4056, 416, 3984), (2, 1160, 3440, 8, 3408), (16, 264, 3248, 72, 8), (16, 390, 1088, 88, 16),
+    (16, 264, 4136, 72, 400), (8, 2056, 944, 656, 544),
 ]
 
 
@@ -76,3 +77,11 @@ def test_reduce_in_gemm_with_both_parts_in_one_launch(T, n, h, fr, hs):
     check_mlp_block(cfg, d, got, w, fwd, g)
     other = run_mlp_block(cfg, d, backward=False)
     assert np.array_equal(got["Rp_bits"][:, :, hs:], other["Rp_bits"][:, :, hs:])   # private channels: the same bits
+    B.profile_reset()
+    B.profile_enable(True)
+    try:
+        two = run_mlp_block(cfg, d, backward=False, reduce_in_gemm=True)            # the two parts one after the other
+    finally:
+        B.profile_enable(False)
+        B.profile_reset()
+    assert np.array_equal(got["Rp_bits"], two["Rp_bits"])                           # all channels: the same bits
