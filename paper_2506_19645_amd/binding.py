@@ -286,8 +286,9 @@ def gemm_shared_pair_route(T: int, M: int, h: int, hs: int, K: int) -> int:
     return lib().caat_gemm_shared_pair_route(T, M, h, hs, K)
 
 
-def profile_enable(on: bool) -> None:
-    _check(lib().caat_profile_enable(1 if on else 0), "caat_profile_enable")
+def profile_enable(on: bool, as_run: bool = False) -> None:
+    """Times every launch; as_run: the launches of an untimed call, otherwise every GEMM in one of its own."""
+    _check(lib().caat_profile_enable((2 if as_run else 1) if on else 0), "caat_profile_enable")
 
 
 def profile_reset() -> None:

@@ -32,22 +32,23 @@ struct ProfRec {
   const char* name;
   hipEvent_t e0, e1;
 };
-bool g_prof_on = false;
-std::vector<ProfRec> g_prof;   // event pool, reused after caat_profile_reset
+int g_prof = 0;                // 1: every GEMM and rotation a launch of its own, 2: the launches that an untimed call makes
+std::vector<ProfRec> g_prof_recs;   // event pool, reused after caat_profile_reset
 size_t g_prof_used = 0;
+bool one_by_one() { return g_prof == 1; }
 
 struct ProfScope {
   hipStream_t s;
   ProfRec* rec;
   ProfScope(hipStream_t stream, const char* name) : s(stream), rec(nullptr) {
-    if (!g_prof_on) return;
-    if (g_prof_used == g_prof.size()) {
+    if (!g_prof) return;
+    if (g_prof_used == g_prof_recs.size()) {
       ProfRec r;
       r.name = name;
       if (hipEventCreate(&r.e0) != hipSuccess || hipEventCreate(&r.e1) != hipSuccess) return;
-      g_prof.push_back(r);
+      g_prof_recs.push_back(r);
     }
-    rec = &g_prof[g_prof_used++];
+    rec = &g_prof_recs[g_prof_used++];
     rec->name = name;
     (void)hipEventRecord(rec->e0, s);
   }
@@ -218,17 +219,20 @@ int rowpar_pcr(const caat_desc* d, const bf16_t* a, long long kdim, const bf16_t
     q.c = out; q.ldc = ldsh; q.stride_c = n * h;
     q.aux = resid; q.ldaux = ldsh; q.stride_aux = n * h;
     q.G = 1; q.M = (int)n; q.N = hs; q.K = (int)kdim; q.kcat = (int)T; q.bcast = dd ? 1 : (int)T;
-    bool done = false;
-    if (hs > 0 && hs < h && !g_prof_on) {   // (timed launches: each of its own, see grad_pair)
-      e = launch_gemm_shared_private(q, priv, scratch, scratch_bytes, &done, s);
-      if (e != hipSuccess) return CAAT_EHIP;
+    if (hs > 0 && hs < h && !one_by_one()) {
+      int groups = 1;
+      const GemmPair pair = gemm_shared_pair(q, priv, scratch ? scratch_bytes : 0, &groups);
+      if (pair.tile >= 0) {
+        ProfScope ps(s, "gemm_nt_rowpar_private+gemm_nt_shared_kcat");
+        return hip_status(launch_gemm_shared_private(pair, groups, q, priv, scratch, s));
+      }
     }
-    if (hs < h && !done) {
+    if (hs < h) {
       ProfScope ps(s, "gemm_nt_rowpar_private");
       e = launch_gemm(priv, 0, EPI_ROWPAR, s);
       if (e != hipSuccess) return CAAT_EHIP;
     }
-    if (hs > 0 && !done) {
+    if (hs > 0) {
       ProfScope ps(s, "gemm_nt_shared_kcat");
       e = launch_gemm_shared(q, scratch, scratch_bytes, s);
       if (e != hipSuccess) return CAAT_EHIP;
@@ -256,8 +260,8 @@ int rowpar_pcr(const caat_desc* d, const bf16_t* a, long long kdim, const bf16_t
 }
 
 // q and k are rotated (and k and v go to the caches) in the epilogue of the product that makes them.  Where its tile cannot,
-// that is a pass of its own, and so it is while launches are timed.
-bool rope_in_gemm(const GemmParams& p) { return !g_prof_on && gemm_takes_rope(p); }
+// that is a pass of its own, and so it is while launches are timed one by one.
+bool rope_in_gemm(const GemmParams& p) { return !one_by_one() && gemm_takes_rope(p); }
 
 // Attention sub-block forward (Eq. A5 + Sec. 4): per rank q,k,v = X_m Wqkv_m^T; RoPE(q,k); causal attention per head;
 // Zt_m = H_m Wo_m^T with the private half of the partial channel-reduce in the epilogue; shared half; norm.
@@ -324,18 +328,23 @@ int attn_block_fwd(const caat_desc* d, const caat_ws_layout& L, const void* cons
 }
 
 // A data gradient and the weight gradient that waits for the same tensor, in one launch (with the sums of the norm's parameter
-// gradients, if any are given) or one after the other.  While launches are timed every GEMM is one of its own, with a time
-// of its own.
+// gradients, if any are given) or one after the other, as they are while launches are timed one by one.
 GemmPair grad_pair(const GemmParams& nn, const GemmParams& tn) {
   GemmPair p = {-1, false, false, 0.0};
-  return g_prof_on ? p : gemm_pair(nn, tn);
+  return one_by_one() ? p : gemm_pair(nn, tn);
 }
-hipError_t grad_gemms(const GemmPair& p, const GemmParams& nn, int epilogue, const char* name, const GemmParams& tn,
-                      const NormSums& sums, hipStream_t s) {
-  if (p.tile >= 0) return launch_gemm_pair(p, nn, epilogue, tn, sums, s);
+hipError_t grad_gemms(const GemmPair& p, const GemmParams& nn, int epilogue, const GemmParams& tn, const NormSums& sums,
+                      hipStream_t s) {
+  const int k = epilogue == EPI_GELU_BWD ? 1 : epilogue == EPI_SWIGLU_BWD ? 2 : 0;
+  if (p.tile >= 0) {
+    static const char* const names[] = {"gemm_nn_dgrad+gemm_tn_wgrad", "gemm_nn_gelu_bwd+gemm_tn_wgrad", "gemm_nn_swiglu_bwd+gemm_tn_wgrad"};
+    ProfScope ps(s, names[k]);
+    return launch_gemm_pair(p, nn, epilogue, tn, sums, s);
+  }
   hipError_t e;
   {
-    ProfScope ps(s, name);
+    static const char* const names[] = {"gemm_nn_dgrad", "gemm_nn_gelu_bwd", "gemm_nn_swiglu_bwd"};
+    ProfScope ps(s, names[k]);
     e = launch_gemm(nn, 1, epilogue, s);
   }
   if (e != hipSuccess) return e;
@@ -413,11 +422,11 @@ int attn_block_bwd(const caat_desc* d, const caat_ws_layout& L, const void* cons
                                       ? launch_partial_sync_shared_from((const bf16_t*)dr, dZt, (int)T, n, (int)h, d->hs, s)
                                       : launch_partial_sync(dZt, nullptr, dZt, (int)T, n, (int)h, d->hs, 1.0f, s))
   }
-  e = grad_gemms(first, H1, EPI_PLAIN, "gemm_nn_dgrad", O, sums, s);
+  e = grad_gemms(first, H1, EPI_PLAIN, O, sums, s);
   if (e != hipSuccess) return CAAT_EHIP;
   CAAT_STEP("flash_attn_bwd", launch_flash_bwd(QKV, H, dH, stats, dQKV, T * d->batch, d->seq, hpr, kvpr, d->head_dim,
                                                d->rope_base, s))
-  e = grad_gemms(grad_pair(X, W), X, EPI_PLAIN, "gemm_nn_dgrad", W, NormSums{}, s);
+  e = grad_gemms(grad_pair(X, W), X, EPI_PLAIN, W, NormSums{}, s);
 #undef CAAT_STEP
   return hip_status(e);
 }
@@ -602,7 +611,7 @@ int caat_gemm_shared_pair_route(int T, long long M, long long h, long long hs, l
 }
 
 int caat_profile_enable(int on) {
-  g_prof_on = on != 0;
+  g_prof = on == 2 ? 2 : on != 0;
   return CAAT_OK;
 }
 
@@ -615,7 +624,7 @@ int caat_profile_count(void) { return (int)g_prof_used; }
 
 int caat_profile_get(int index, const char** name, float* ms) {
   if (index < 0 || (size_t)index >= g_prof_used || !name || !ms) return CAAT_EINVAL;
-  ProfRec& r = g_prof[(size_t)index];
+  ProfRec& r = g_prof_recs[(size_t)index];
   if (hipEventSynchronize(r.e1) != hipSuccess) return CAAT_EHIP;
   if (hipEventElapsedTime(ms, r.e0, r.e1) != hipSuccess) return CAAT_EHIP;
   *name = r.name;
@@ -887,9 +896,9 @@ int caat_block_bwd(const caat_desc* d, const void* const* weights, const void* x
   // the sequence (that kernel's fresh writes are still draining).  The six admissible orders (h = 2048, T = 4, 8192
   // tokens): B G X A 1.637 ms per step, G B X A 1.645, the rest 1.645 - 1.679; B first only moves the slow slot from G
   // to the weight-gradient GEMM (213 -> 221 us averaged over its two launches), so the plain order stays.
-  e = grad_gemms(first, G, swi ? EPI_SWIGLU_BWD : EPI_GELU_BWD, swi ? "gemm_nn_swiglu_bwd" : "gemm_nn_gelu_bwd", Bw, sums, s);
+  e = grad_gemms(first, G, swi ? EPI_SWIGLU_BWD : EPI_GELU_BWD, Bw, sums, s);
   if (e != hipSuccess) return CAAT_EHIP;
-  e = grad_gemms(grad_pair(X, A), X, EPI_PLAIN, "gemm_nn_dgrad", A, NormSums{}, s);
+  e = grad_gemms(grad_pair(X, A), X, EPI_PLAIN, A, NormSums{}, s);
   return hip_status(e);
 }
 

@@ -387,12 +387,8 @@ GemmPair gemm_shared_pair(const GemmParams& p, const GemmParams& priv, size_t sc
   const GemmPair best = best_pair(priv, q, n_cu, copies);
   return pays(1.4 * best.us, shared + 1.4 * us) ? best : pair;
 }
-hipError_t launch_gemm_shared_private(const GemmParams& p, const GemmParams& priv, void* scratch, size_t scratch_bytes, bool* taken,
+hipError_t launch_gemm_shared_private(const GemmPair& pair, int groups, const GemmParams& p, const GemmParams& priv, void* scratch,
                                       hipStream_t s) {
-  int groups = 1;
-  const GemmPair pair = gemm_shared_pair(p, priv, scratch ? scratch_bytes : 0, &groups);
-  *taken = pair.tile >= 0;
-  if (!*taken) return hipSuccess;
   const hipError_t e = groups == 1 ? launch_any_pair(pair, priv, EPI_ROWPAR, p, EPI_SHARED_BCAST, NormSums{}, s)
                                    : launch_any_pair(pair, priv, EPI_ROWPAR, shared_groups(p, groups, scratch), EPI_PARTIAL, NormSums{}, s);
   return e != hipSuccess || groups == 1 ? e : merge_groups(p, groups, scratch, s);

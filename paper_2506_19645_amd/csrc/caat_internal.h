@@ -298,9 +298,9 @@ hipError_t launch_gemm_pair(const GemmPair& p, const GemmParams& nn, int epilogu
 // adds up.  scratch: gemm_shared_scratch_bytes() bytes; with less, or none, there are fewer groups
 size_t gemm_shared_scratch_bytes(int M, int N, int kcat);
 hipError_t launch_gemm_shared(const GemmParams& p, void* scratch, size_t scratch_bytes, hipStream_t s);
-// the same with the private columns (EPI_ROWPAR, NT) in one launch; *taken = false and nothing launched where that is not faster
+// The same with the private columns (EPI_ROWPAR, NT) in one launch, tile -1 where that is not faster.  scratch_bytes: 0 without scratch
 GemmPair gemm_shared_pair(const GemmParams& p, const GemmParams& priv, size_t scratch_bytes, int* groups);
-hipError_t launch_gemm_shared_private(const GemmParams& p, const GemmParams& priv, void* scratch, size_t scratch_bytes, bool* taken,
+hipError_t launch_gemm_shared_private(const GemmPair& pair, int groups, const GemmParams& p, const GemmParams& priv, void* scratch,
                                       hipStream_t s);
 // the second kernel: for m in [0, bcast): out[m] = round_bf16(sum over groups of part) + resid[m]; part [groups][M][N] fp32
 hipError_t launch_shared_merge(const float* part, int groups, const bf16_t* resid, bf16_t* out, long long M, int N, long long ldr,

@@ -16,9 +16,13 @@ extern "C" {
  * caat_block_fwd / caat_block_bwd bracket every kernel they enqueue with a pair of HIP events on the caller's
  * stream.  caat_profile_get waits for record `index` (in launch order since the last reset) and returns a
  * static kernel-family name (host pointer to a NUL-terminated string) and the elapsed milliseconds.  Events
- * are created on first use and reused after a reset.  Not thread-safe; off by default.  While it is on, GEMMs are
- * enqueued one by one, also where they otherwise share a launch (caat_gemm_pair_route, caat_gemm_shared_pair_route), so that
- * each has a time of its own.
+ * are created on first use and reused after a reset.  Not thread-safe; off by default.
+ * on = 2: the kernels of an untimed call, so the same results; two GEMMs in one launch (caat_gemm_pair_route,
+ * caat_gemm_shared_pair_route) are one record named after both, "a+b".
+ * on = 1: every GEMM a launch of its own, so that each has a time, and the rotation of q and k a pass of its own.  Other kernels
+ * run then, and low-order bits may differ from an untimed call's: a gradient's contraction may be split between two groups of
+ * waves, and the rotation takes every angle's sine and cosine itself (in the product's epilogue most are turned on from 16 rows
+ * before), so the gradients, the projections, the caches and what follows from them.
  */
 int caat_profile_enable(int on);
 int caat_profile_reset(void);

@@ -140,6 +140,37 @@ def test_profile_records_every_launch(separate):
     assert B.profile_records() == []
 
 
+def _timed_as_run(run):
+    B.profile_reset()
+    B.profile_enable(True, as_run=True)
+    try:
+        return run(), [n for n, ms in B.profile_records() if ms > 0.0]
+    finally:
+        B.profile_enable(False)
+        B.profile_reset()
+
+
+@pytest.mark.parametrize("reduce_in_gemm", [False, True])
+def test_timing_the_launches_as_they_run_changes_nothing(reduce_in_gemm):
+    """Every output of a timed call has the bits of an untimed one, and a pair of GEMMs is one record."""
+    cfg = mlp_cfg(False, 4, 360, 512, 1792, 0.5)
+    d = make_inputs(cfg, seed=68)
+    want = run_mlp_block(cfg, d, reduce_in_gemm=reduce_in_gemm)
+    got, names = _timed_as_run(lambda: run_mlp_block(cfg, d, reduce_in_gemm=reduce_in_gemm))
+    rowpar = ["gemm_nt_rowpar_private+gemm_nt_shared_kcat", "norm_fwd"] if reduce_in_gemm else ["gemm_nt_rowpar", "partial_sync_norm_fwd"]
+    assert names == ["gemm_nt_gelu_fwd"] + rowpar + ["norm_bwd_sync", "gemm_nn_gelu_bwd+gemm_tn_wgrad", "gemm_nn_dgrad+gemm_tn_wgrad"]
+    for name in want:
+        assert np.array_equal(got[name], want[name]), name
+
+    cfg = attn_cfg(2, 3, 1003, 2, 0.5)
+    d = make_inputs(cfg, seed=69, with_grads=True, weight_std=0.05)
+    want = run_attn_block(cfg, d, backward=True, reduce_in_gemm=reduce_in_gemm)
+    got, names = _timed_as_run(lambda: run_attn_block(cfg, d, backward=True, reduce_in_gemm=reduce_in_gemm))
+    assert names[:2] == ["gemm_nt_qkv", "flash_attn_fwd"] and "rope" not in names
+    for name in want:
+        assert np.array_equal(got[name], want[name]), name
+
+
 def test_hbm_probe_modes():
     """The measuring tool: every mode runs, the copy modes copy, bad arguments are refused before any launch."""
     import torch
