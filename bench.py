@@ -61,6 +61,8 @@ def flops_per_launch(name: str, cfg, which: int = 0) -> float:
         "gemm_nn_gelu_bwd": 2.0 * n * h * f, "gemm_nn_swiglu_bwd": 2.0 * n * h * f,
         "gemm_nn_dgrad": 2.0 * n * f * h * k1,
         "gemm_tn_wgrad": (2.0 * n * f * h + 2.0 * n * f * h * k1) / 2.0,   # two launches per step: dB and dA
+        "gemm_nn_gelu_bwd+gemm_tn_wgrad": 4.0 * n * h * f, "gemm_nn_swiglu_bwd+gemm_tn_wgrad": 4.0 * n * h * f,   # with dB
+        "gemm_nn_dgrad+gemm_tn_wgrad": 4.0 * n * h * f * k1,               # with dA
     }
     return table.get(name, 0.0)
 
@@ -171,11 +173,36 @@ class MlpBench:
         wall_ms = (time.perf_counter() - t0) * 1e3
         return e0.elapsed_time(e1) / steps, wall_ms / steps
 
+    def time_turns(self, descs, steps, warmup):
+        """ms per step of each descriptor, a few steps of one after a few of the other, in turns: what a step takes drifts by
+        more over a run than these differ."""
+        torch = self.torch
+        for d in descs:
+            for _ in range(warmup):
+                self.step(d)
+        rounds = min(steps, 6)
+        per = -(-steps // rounds)
+        marks = []
+        for i in range(rounds):
+            for k in range(len(descs)) if i % 2 == 0 else reversed(range(len(descs))):
+                e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                e0.record()
+                for _ in range(per):
+                    self.step(descs[k])
+                e1.record()
+                marks.append((k, e0, e1))
+        torch.cuda.synchronize()
+        ms = [0.0] * len(descs)
+        for k, e0, e1 in marks:
+            ms[k] += e0.elapsed_time(e1) / (rounds * per)
+        return ms
+
     def profile_steps(self, desc, steps):
-        """Per-launch durations (HIP events on the launch stream around every kernel) averaged per kernel family."""
+        """Per-launch durations (HIP events on the launch stream around every kernel, the kernels of the untimed step) averaged per
+        kernel family; two GEMMs in one launch are a family named after both, "a+b"."""
         B = self.B
         B.profile_reset()
-        B.profile_enable(True)
+        B.profile_enable(True, as_run=True)
         for _ in range(steps):
             self.step(desc)
         self.torch.cuda.synchronize()
@@ -422,7 +449,7 @@ def bench_attention_kinds(args, cfg, base):
             # five contractions instead of two in the attention core; the two NN and the two TN launches of a step
             # (o_proj: 2nh^2, qkv: 6nh^2) share a kernel family, so the per-launch figure is their mean
             fl.update({"flash_attn_bwd": 5.0 * cfg.batch * s * s * h, "gemm_nn_dgrad": 4.0 * n * h * h,
-                       "gemm_tn_wgrad": 4.0 * n * h * h})
+                       "gemm_tn_wgrad": 4.0 * n * h * h, "gemm_nn_dgrad+gemm_tn_wgrad": 8.0 * n * h * h})
             by.update({"partial_sync_bwd": 2.0 * T * n * hs_of(cfg) * 2,
                        "norm_bwd_sync": 5.0 * T * n * h * 2,
                        "norm_bwd": 5.0 * T * n * h * 2 - (T * n * hs_of(cfg) * 2 if hs_of(cfg) % 8 == 0 else 0)})
@@ -700,10 +727,9 @@ def bench_mlp(args, cfg, base):
         for p in (1.0, 0.5, 0.25, 0.0):
             c = base.with_(p=p)
             dsc = B.make_desc(c, reduce_in_gemm=args.reduce_in_gemm)
-            ms_p, _ = bench.time_steps(dsc, args.steps, args.warmup)   # same warm-up as the headline: the clocks ramp
             # the reduce as a kernel of its own (the in-HBM stand-in for the collective): its time in the step against p
             dsep = B.make_desc(c, reduce_in_gemm=args.reduce_in_gemm, separate_reduce=True)
-            ms_sep, _ = bench.time_steps(dsep, max(5, args.steps // 2), max(3, args.warmup // 2))
+            ms_p, ms_sep = bench.time_turns([dsc, dsep], args.steps, args.warmup)   # same warm-up as the headline: the clocks ramp
             pr = bench.profile_steps(dsep, 5)
             sa_ms, sa_gbs = standalone_sync(torch, B, c, hs_of(c))
             sc_ms, sc_gbs = standalone_sync(torch, B, c, hs_of(c), compact=True)
