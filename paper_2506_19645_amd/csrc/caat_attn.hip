@@ -49,9 +49,7 @@ __global__ __launch_bounds__(256) void rope_kernel(bf16_t* qkv, long long rows, 
   float sn[8], cs[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    const int j = grp * 8 + e;
-    const float inv = exp2f(-2.0f * (float)j / (float)d * log2_base);
-    sincosf(pos * inv, &sn[e], &cs[e]);
+    rope_sincos(pos, rope_freq(grp * 8 + e, d, log2_base), sn[e], cs[e]);
   }
   bf16_t* p = qkv + row * (long long)ld + grp * 8;  // q heads first, k heads right after them
   for (int head = 0; head < n_rot; ++head, p += d) {
@@ -124,10 +122,8 @@ __global__ __launch_bounds__(256) void rope_append_kernel(bf16_t* qkv, bf16_t* _
     float x1[2] = {lo_bf(lw[w]), hi_bf(lw[w])}, x2[2] = {lo_bf(hw[w]), hi_bf(hw[w])}, y1[2], y2[2];
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
-      const int j = grp * 8 + w * 2 + e;
-      const float inv = exp2f(-2.0f * (float)j / (float)d * log2_base);
       float sn, cs;
-      sincosf(pos * inv, &sn, &cs);
+      rope_sincos(pos, rope_freq(grp * 8 + w * 2 + e, d, log2_base), sn, cs);
       y1[e] = x1[e] * cs - x2[e] * sn;
       y2[e] = x2[e] * cs + x1[e] * sn;
     }

@@ -97,10 +97,9 @@ __global__ __launch_bounds__(64 * DNW) void decode_attn_kernel(const bf16_t* __r
 #pragma unroll
   for (int i = 0; i < DNS; ++i) copy(b0 + wave + i * DNW, i);
   if (tid < 64) {
-    // angle j of the position, j = 0 .. 63, once per workgroup (the same expressions as the RoPE kernels)
-    const float inv = exp2f(-2.0f * (float)tid / 128.0f * log2_base);
+    // angle j of the position, j = 0 .. 63, once per workgroup (the RoPE kernels' sine and cosine)
     float sn, cs;
-    sincosf((float)(nkeys - 1) * inv, &sn, &cs);
+    rope_sincos((float)(nkeys - 1), rope_freq(tid, 128, log2_base), sn, cs);
     s_cs[tid] = cs;
     s_sn[tid] = sn;
   }

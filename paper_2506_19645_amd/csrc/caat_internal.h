@@ -167,6 +167,8 @@ __device__ __forceinline__ void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
+// Every kernel that rotates takes its angles from these two, so that prefill and decode put the same key into the cache and the
+// backward pass undoes the rotation that the forward pass made.
 // Rotary frequency j < d/2, base^(-2j/d) as an fp32 number, over 2 pi: revolutions per position, in two floats.
 __device__ __forceinline__ float2 rope_freq(int j, int d, float log2_base) {
   constexpr float REV = 0.159154937f, REV_LO = 6.42063833e-9f;   // 1/(2 pi) = REV + REV_LO
