@@ -169,8 +169,14 @@ static bool in_range(const GemmParams& p, int epilogue) {
 // pass of its own, whose time the choice of another tile would cost.  With the pass / in the epilogue, forward and backward of an
 // attention block of h = 4096, T = 8, 4096 tokens 2455 / 2418 us, 3 x 1003 tokens of 2048, T = 4, 8 key heads 454 / 446; a
 // prefill layer of 16 x 2048 tokens of 4096 15.37 / 15.21 ms, of 777 464.7 / 460.8 us.
+// Nor 256 x 256 tiles with sequences of fewer than 8 tokens: every sine and cosine is then taken anew in each of a wave's eight
+// steps of 16 rows, which a full chip of large tiles does not hide.  Forward passes on such tiles, time with the pass over time in
+// the epilogue, 1335 random blocks and layers: 1 token 0.987 (worst 0.942), 2 0.991, 3 0.998, 4 and 5 1.003 (worst 0.971), 6 and 7
+// 1.001, 8 to 11 1.010, 12 to 31 1.010, 128 and more 1.023; on 192 x 256 tiles 1.001 at 1 token, 1.01 to 1.08 from 2 tokens on
+// the others.
 bool gemm_takes_rope(const GemmParams& p) {
   const int r = choose_route(p, 0, EPI_PLAIN, compute_units());
+  if (r == 0 && p.rope.seq < 8) return false;
   return (r == 0 || r == 1 || r == 3 || r == 4) && in_range(p, EPI_PLAIN);
 }
 

@@ -70,6 +70,27 @@ def test_prefill_layer(T, heads, kv, batch, seq, base, tile):
     assert_close(bits_to_f64(v[:, :, :, :seq]), ref["V"], "V cache")
 
 
+@pytest.mark.parametrize("batch,seq", [(9921, 1), (1417, 7), (1240, 8)])
+def test_short_sequences_on_large_tiles(batch, seq):
+    """From 8 tokens on in the epilogue of a 256 x 256 tile; the pass and the epilogue agree."""
+    cfg = attn_cfg(4, batch, seq, 8, 0.5)
+    assert B.gemm_route(B.GEMM_NT, 0, 4, cfg.tokens, cfg.qkv_r, cfg.h) == 0
+    d = make_inputs(cfg, seed=52, with_grads=False)
+    B.profile_reset()
+    B.profile_enable(True, as_run=True)
+    try:
+        got = run_attn_block(cfg, d)
+        names = {name for name, _ in B.profile_records()}
+    finally:
+        B.profile_enable(False)
+        B.profile_reset()
+    assert ("rope" in names) == (seq < 8)
+    two, _ = timed(lambda: run_attn_block(cfg, d))
+    rot = cfg.hd_r + cfg.kvd_r
+    check_rotated(got["QKV"][..., :rot], two["QKV"][..., :rot])
+    assert np.array_equal(got["QKV"][..., rot:], two["QKV"][..., rot:])
+
+
 # far out in a sequence, where an angle of a position times an fp32 frequency that is rounded once is off by 1e-3
 FAR = 20000
 
