@@ -101,7 +101,8 @@ typedef struct caat_desc {
                            kinds' internal residual) store the shared channels ONCE instead of T identical copies:
                            [tokens, hs] followed by the private channels [T, tokens, h - hs], one contiguous buffer of
                            tokens*hs + T*tokens*(h-hs) elements.  x / x_out keep the [T, tokens, h] layout. */
-  int separate_reduce;  /* 0: where the shape allows (see caat_partial_sync_norm_fwd) the reduce over ranks, the residual
+  int separate_reduce;  /* 0: where the shape allows (hs > 0, T and h as in caat_partial_sync_norm_fwd; hs may end inside a
+                           16-byte group here, which that call refuses) the reduce over ranks, the residual
                            add and the norm that follows run as ONE kernel, which does not read the reduced channels
                            back from memory.  1: the reduce stays a kernel of its own (caat_partial_sync's kernel, the
                            in-HBM stand-in for the tensor-parallel collective, whose time against p is what the

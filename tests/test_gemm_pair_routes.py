@@ -38,6 +38,11 @@ def test_gpu_tests_reach_every_pair_kernel_and_every_order():
     assert not missing, sorted(map(str, missing))
 
 
+def test_most_blocks_that_run_one_by_one_would_pair():
+    runs = [pairs.paired(*b[:5]) for b in pairs.BLOCKS]
+    assert sum(runs) >= 40, (sum(runs), len(runs))
+
+
 def test_training_steps_pair_their_gradient_gemms_unless_one_is_a_long_chain():
     for T, n, h, fr in ((2, 256, 768, 1536), (4, 1111, 2048, 1408), (4, 8192, 2048, 2048), (8, 147, 1536, 768)):
         assert B.gemm_pair_route(T, n, fr, h) >= 0

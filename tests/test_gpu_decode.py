@@ -54,7 +54,7 @@ def oracle_decode(cfg, d):
     (1, 2, 2, 256, 129, 0.0, 0, 1.0),
     (2, 5, 8, 2 * 256, 200, 0.5, 2, 1.0),     # grouped-query attention: 4 query heads per key / value head
     (2, 3, 8, 2 * 256, 70, 0.5, 4, 1.0),      # two groups per rank
-    (2, 4, 4, 2 * 256, 50, 0.3, 0, 1.0),      # hs = 153: not a multiple of 8, so the reduce and the norm stay two kernels
+    (2, 4, 4, 2 * 256, 50, 0.3, 0, 1.0),      # hs = 153 ends inside a 16-byte group, in the one-launch reduce + norm
     (8, 6, 8, 8 * 128, 90, 0.5, 0, 1.0),      # tensor-parallel degree 8 through the one-launch reduce + norm
     (4, 7, 4, 4 * 128, 61, 0.5, 0, 2.0),      # private channel scaling sqrt(T) (Sec. 4) in both halves of the layer
     (2, 5, 4, 2 * 256, 40, 0.0, 0, 2.0 ** 0.5),   # the same at p = 0: every channel private and scaled
@@ -62,7 +62,7 @@ def oracle_decode(cfg, d):
     (4, 3, 12, 4 * 128, 40, 0.5, 0, 1.0),     # reduce + norm per token and rank: one column group per thread (h = 1536), ...
     (2, 5, 20, 2 * 256, 30, 0.25, 0, 1.0),    # ... two (2560, the second one ragged), ...
     (8, 2, 40, 8 * 128, 20, 0.4, 8, 1.0),     # ... and four (5120), hs = 2048
-    (16, 2, 32, 16 * 136, 20, 0.3, 0, 4.0),   # T = 16, hs not a multiple of 8 (two-kernel route), scaling sqrt(T)
+    (16, 2, 32, 16 * 136, 20, 0.3, 0, 4.0),   # T = 16, hs not a multiple of 8 (one launch, in place), scaling sqrt(T)
 ])
 def test_decode_layer(T, b, heads, ffn, L, p, kv_heads, scale):
     cfg = _cfg(T, b, heads, ffn, L, p, kv_heads, scale)
@@ -84,6 +84,26 @@ def test_decode_layer(T, b, heads, ffn, L, p, kv_heads, scale):
         for m in range(1, T):
             assert np.array_equal(got["R2_bits"][m, :, :hs], got["R2_bits"][0, :, :hs])
             assert np.array_equal(got["R1_bits"][m, :, :hs], got["R1_bits"][0, :, :hs])
+
+
+@pytest.mark.parametrize("T,b,heads,ffn,L,p,scale", [
+    (2, 4, 4, 2 * 256, 50, 0.3, 1.0), (16, 2, 32, 16 * 136, 20, 0.3, 4.0), (8, 5, 16, 8 * 72, 33, 0.777, 1.0), (4, 1, 20, 4 * 128, 17, 1.0, 1.0)])
+def test_decode_layer_with_the_reduce_and_the_norm_as_two_kernels(T, b, heads, ffn, L, p, scale):
+    """The same against the oracle where the caller asks for the reduce as a kernel of its own; hs a multiple of 8 and not."""
+    cfg = _cfg(T, b, heads, ffn, L, p, 0, scale)
+    d = make_inputs(cfg, seed=34, weight_std=0.05 if cfg.h < 4096 else 0.02)
+    B.profile_reset()
+    B.profile_enable(True, as_run=True)
+    try:
+        got = run_decode(cfg, d, separate_reduce=True)
+        names = [name for name, _ in B.profile_records()]
+    finally:
+        B.profile_enable(False)
+        B.profile_reset()
+    assert names.count("partial_sync_fwd") == 2 and "partial_sync_norm_fwd" not in names
+    ref = oracle_decode(cfg, d)
+    for name in ("X1", "H", "R1", "X2", "R2"):
+        assert_close(got[name], ref[name], name)
 
 
 @pytest.mark.parametrize("separate", [False, True])

@@ -41,6 +41,11 @@ SHARED = [
 ]
 
 
+def paired(swi, T, n, h, fr):
+    """Whether any of a backward pass's pairs of GEMMs shares a launch."""
+    return B.gemm_pair_route(T, n, fr, h) >= 0 or B.gemm_pair_route(T, n, h, 2 * fr if swi else fr) >= 0
+
+
 def check(swi, T, n, h, fr, hs):
     cfg = block_config(swi, T, n, h, fr, hs)
     d = make_inputs(cfg, seed=31, weight_std=0.05)
@@ -56,8 +61,8 @@ def test_mlp_block_with_paired_gemms(swi, T, n, h, fr, hs):
 
 @pytest.mark.parametrize("swi,T,n,h,fr,hs", [b[:6] for b in BLOCKS])
 def test_mlp_block_with_every_gemm_a_launch_of_its_own(swi, T, n, h, fr, hs):
-    if B.gemm_pair_route(T, n, fr, h) < 0:
-        return   # tests/test_gpu_gemm_kernels.py runs them so
+    if not paired(swi, T, n, h, fr):
+        pytest.skip("two launches anyway, as tests/test_gpu_gemm_kernels.py runs them")
     B.profile_reset()
     B.profile_enable(True)
     try:
