@@ -347,7 +347,7 @@ hipError_t launch_norm_bwd(const bf16_t* dy, const bf16_t* dres, const bf16_t* x
                            float* dbeta, int norm, int T, long long tokens, int h, int hs, float private_scale,
                            void* workspace, hipStream_t s, bool skip_shared_scaled = false, NormSums* later = nullptr);
 // norm backward + the backward partial channel-reduce in one launch (T = 4 up to h = 2048, T = 2 up to
-// h = 4096: norm_bwd_sync_takes); hipErrorInvalidValue if the shape is not taken.  Same workspace as launch_norm_bwd.
+// h = 4096, see norm_bwd_sync_takes); hipErrorInvalidValue if the shape is not taken.  Same workspace as launch_norm_bwd.
 bool norm_bwd_sync_takes(int T, long long tokens, int h, int hs);
 hipError_t launch_norm_bwd_sync(const bf16_t* dy, const bf16_t* dres, const bf16_t* x, const bf16_t* gamma,
                                 const float* mean, const float* rstd, bf16_t* g_out, bf16_t* g_red, float* dgamma,

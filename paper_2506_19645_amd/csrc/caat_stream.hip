@@ -1354,13 +1354,17 @@ hipError_t launch_norm_bwd(const bf16_t* dy, const bf16_t* dres, const bf16_t* x
 // rows of a token, and the kernel only beats the two separate kernels while that is at most 4 (rank, column group)
 // pairs per input (T = 4 up to h = 2048, T = 2 up to h = 4096).  Measured beyond that budget, T = 8 and h = 4096 with
 // 256, 512 or 1024 threads: 327 - 354 us against 279 us for the two kernels (every register of a one-wave-per-SIMD
-// budget, or spills), so those shapes keep the two kernels.
+// budget, or spills), so those shapes keep the two kernels.  So do many tokens of few channels, where at most 64 of a group's 128
+// threads have a column: h = 512, backward of an MLP of 64 columns per rank, two kernels over one, T = 4 4000 tokens 0.95, 8192
+// 0.95, 16384 0.97, 2000 1.00; T = 2 0.99 / 0.97 / 0.96, 2000 1.02 (with hs inside a 16-byte group 0.98 to 1.00, 2000 1.03 to 1.07);
+// h = 768 and 1024, T = 2 and 4, 4000 to 16384 tokens 0.99 to 1.07, from 130 to 2000 tokens every width 1.00 to 1.27.
 static int norm_bwd_sync_groups(int T, int h) {
   const int ng = (h / 8 + 255) / 256;
   return ((T == 2 || T == 4) && T * ng <= 4) ? ng : 0;
 }
 bool norm_bwd_sync_takes(int T, long long tokens, int h, int hs) {
   if (hs <= 0 || hs > h || h % 8 != 0 || h > 8192 || tokens <= 0) return false;
+  if (h <= 512 && tokens >= 3000) return false;
   return norm_bwd_sync_groups(T, h) != 0;
 }
 
