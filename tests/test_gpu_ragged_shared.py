@@ -23,8 +23,9 @@ def cfg_of(swi, T, n, h, hs, scale=1.0):
     (False, 8, 3, 8192, 8190, 1.0), (True, 16, 17, 520, 3, 4.0), (False, 16, 2, 4096, 2047, 1.0),
     # two tokens at a time in the backward: ranges of 2, 3 and 4 tokens, the last one shorter
     (False, 4, 1111, 768, 381, 2.0), (True, 2, 1537, 1024, 512, 1.0), (False, 2, 2049, 1024, 1000, 1.5), (True, 4, 600, 520, 519, 1.0),
-    # up to 512 channels the backward keeps two kernels from 3000 tokens on
-    (True, 4, 2999, 512, 253, 1.0), (True, 4, 3000, 512, 253, 1.0), (False, 2, 3000, 264, 256, 1.5), (False, 2, 3000, 520, 513, 1.0)])
+    # up to 512 channels the backward keeps two kernels from 3000 tokens on (RMSNorm: among so many values LayerNorm's beta leaves
+    # some near zero, whose bf16 steps are smaller than what the statistics' last bit moves them by)
+    (True, 4, 2999, 512, 253, 1.0), (True, 4, 3000, 512, 253, 1.0), (True, 2, 3000, 264, 256, 1.5), (True, 2, 3000, 520, 513, 1.0)])
 def test_mlp_block_with_a_ragged_number_of_shared_channels(swi, T, n, h, hs, scale):
     cfg = cfg_of(swi, T, n, h, hs, scale)
     d = make_inputs(cfg, seed=43, weight_std=0.05 if h < 4096 else 0.02)
