@@ -277,9 +277,9 @@ static GemmPair best_pair(const GemmParams& p1, const GemmParams& p2, int n_cu, 
 }
 // A pair is taken if the model has it 2 % faster, or less than 4 us slower, that being what a launch less is worth; if all of it is
 // the tile that both would take alone, a tie is a gain too (313 steps with such ties: 1.016 times as fast, worst 0.99 but for two).
-// Of those 3779 pairs, each alone in a loop, 1.2 % then lose more than 2 % and the average is 0.855 of the time apart (0.847 with
-// the best choice for every one; "less than 2 us slower" for all: 3.1 %, 0.857); of 1873 backward passes 0.7 %, worst 0.925, average
-// 1.153 times as fast.
+// Of those 3779 pairs, each alone in a loop, 1.2 % then lose more than 2 %, and another 1.4 % of such ties; the average is 0.855 of
+// the time apart (0.847 with the best choice for every one; "less than 2 us slower" for all: 3.1 %, 0.857).  Of 1873 backward
+// passes 0.7 % lose more than 2 %, worst 0.925, average 1.153 times as fast.
 static bool pays(double pair, double apart) { return pair < 0.98 * apart + 4.0; }
 GemmPair gemm_pair(const GemmParams& nn, const GemmParams& tn) {
   const int n_cu = compute_units();
@@ -376,6 +376,8 @@ hipError_t launch_gemm_shared(const GemmParams& p, void* scratch, size_t scratch
 
 // The private columns in the same launch: their tiles fill what the shared ones leave idle.  Not where they stream their weights
 // (65 to 128 token rows, see choose_route).  The groups are those of the two launches, so the bits are the same either way.
+// 681 random forward passes (1 to 16 ranks, 65 to 8192 tokens, h = 512 to 8192): 1.116 times as fast as one after the other, worst
+// 0.972; 777 tokens of a 4096-channel layer, 8 ranks: 494 -> 481 us (474 with groups of its own, and other bits then).
 GemmPair gemm_shared_pair(const GemmParams& p, const GemmParams& priv, size_t scratch_bytes, int* groups) {
   GemmPair pair = {-1, false, false, 0.0};
   const int n_cu = compute_units();
