@@ -319,7 +319,7 @@ hipError_t launch_gemm_pair(const GemmPair& p, const GemmParams& nn, int epilogu
 //   65 x 2048 x 512 x 8     29 / 22 / 17 / 17     1024 x 2048 x 1376 x 8    112 / 93 / 80 / 72
 //   777 x 1024 x 512 x 4    18 / 19 / 22           777 x 2048 x 3584 x 4    116 / 92 / 70
 // `scratch_bytes`: what there is for the groups' sums.
-static int gemm_shared_groups(int M, int N, int K, int kcat, size_t scratch_bytes, double* gemm_us = nullptr) {
+static int gemm_shared_groups(int M, int N, int K, int kcat, size_t scratch_bytes) {
   GemmParams q = {};
   q.M = M;
   q.N = N;
@@ -331,13 +331,12 @@ static int gemm_shared_groups(int M, int N, int K, int kcat, size_t scratch_byte
     q.G = g;
     q.kcat = kcat / g;
     double us = 0.0;
-    choose_tile(q, 0, EPI_PARTIAL, compute_units(), &us);
+    choose_tile(q, 0, EPI_PARTIAL, 256, &us);
     us *= 1.4;
-    const double all = g > 1 ? us + 5.0 + (double)g * M * N * 4.0 / 7e6 : us;
-    if (g == 1 || all < cost) {
-      cost = all;
+    if (g > 1) us += 5.0 + (double)g * M * N * 4.0 / 7e6;
+    if (g == 1 || us < cost) {
+      cost = us;
       best = g;
-      if (gemm_us) *gemm_us = us;
     }
   }
   return best;
@@ -382,15 +381,15 @@ GemmPair gemm_shared_pair(const GemmParams& p, const GemmParams& priv, size_t sc
   GemmPair pair = {-1, false, false, 0.0};
   const int n_cu = compute_units();
   double shared = 0.0, us = 0.0;
-  *groups = gemm_shared_groups(p.M, p.N, p.K, p.kcat, scratch_bytes, &shared);
+  *groups = gemm_shared_groups(p.M, p.N, p.K, p.kcat, scratch_bytes);
   if (choose_route(priv, 0, EPI_ROWPAR, n_cu) >= ROUTE_FEW_ROWS) return pair;
   const double copies = *groups == 1 ? (double)p.bcast : 0.0;
   GemmParams q = p;
   q.G = *groups;
   q.kcat = p.kcat / *groups;
-  const TileShape& t = TILES[choose_tile(q, 0, EPI_PARTIAL, n_cu)];
+  const TileShape& t = TILES[choose_tile(q, 0, EPI_PARTIAL, n_cu, &shared)];
   const long long tiles = (((long long)p.M + t.bm - 1) / t.bm) * (((long long)p.N + t.bn - 1) / t.bn), slots = (long long)t.per_cu * n_cu;
-  shared += (double)((tiles + slots - 1) / slots) * bcast_us(t, copies);
+  shared = 1.4 * shared + (double)((tiles + slots - 1) / slots) * bcast_us(t, copies);
   choose_tile(priv, 0, EPI_ROWPAR, n_cu, &us);
   const GemmPair best = best_pair(priv, q, n_cu, copies);
   return pays(1.4 * best.us, shared + 1.4 * us) ? best : pair;
